@@ -195,27 +195,32 @@ int build_impl(apss_index* ix, const int64_t* row_ptr, const int32_t* col, const
   if ((rc = reset_err(ws))) return rc;
   uint32_t* err = ws.err.p;
   unsigned long long* bad = ws.bad.p;
-  CHK(launch_check_rowptr(in.prp, n, nnz, err, bad, s), "check row_ptr");
-  if ((rc = check_err(s, err, bad, "build_index"))) return rc;
-  CHK(launch_validate_rows(in.prp, in.pcol, in.pval, n, m, 1e-5, err, bad, s), "validate");
+  DBuf<unsigned long long> longest_dev;
+  CHK(longest_dev.alloc(1), "alloc");
+  CHK(fill_u64((uint64_t*)longest_dev.p, 0ull, 1, s), "fill");
+  unsigned long long longest = 0;
+  CHK(launch_check_rowptr(in.prp, n, nnz, err, bad, longest_dev.p, s), "check row_ptr");
+  CHK(hipMemcpyAsync(&longest, longest_dev.p, sizeof(longest), hipMemcpyDeviceToHost, s), "longest row");
   if ((rc = check_err(s, err, bad, "build_index"))) return rc;
 
-  // density order and maxweight_d(V)
+  // the remaining checks, density order and maxweight_d(V)
   DBuf<uint32_t> cnt, mwbits, cnt_r;
   CHK(cnt.alloc(m), "alloc");
   CHK(mwbits.alloc(m), "alloc");
   CHK(cnt_r.alloc(m), "alloc");
   CHK(fill_u32(cnt.p, 0u, m, s), "fill");
   CHK(fill_u32(mwbits.p, 0u, m, s), "fill");
-  CHK(launch_count_dims(in.pcol, in.pval, nnz, cnt.p, mwbits.p, s), "count dims");
+  CHK(launch_validate_count(in.prp, in.pcol, in.pval, n, m, 1e-5, cnt.p, mwbits.p, err, bad, s), "validate");
+  if ((rc = check_err(s, err, bad, "build_index"))) return rc;
   const int dbits = ceil_log2((uint64_t)m);
   const int cbits = ceil_log2((uint64_t)n + 1);
   SortScratch& ss = ws.ss;
+  // sized for the list sort too (at most nnz postings), so that it grows once
   const int64_t big = std::max<int64_t>(nnz, m);
   CHK(ss.k1.reserve(big), "alloc sort");
-  CHK(ss.v64a.reserve(m), "alloc sort");
+  CHK(ss.v64a.reserve(big), "alloc sort");
   CHK(ss.k2.reserve(big), "alloc sort");
-  CHK(ss.v64b.reserve(m), "alloc sort");
+  CHK(ss.v64b.reserve(big), "alloc sort");
   CHK(ss.hist.reserve(radix_hist_elems(big)), "alloc sort");
   CHK(ss.scan.reserve(radix_scan_tmp_elems(big)), "alloc sort");
   CHK(launch_dim_keys(cnt.p, m, n, dbits, ss.k1.p, ss.v64a.p, s), "dim keys");
@@ -229,8 +234,6 @@ int build_impl(apss_index* ix, const int64_t* row_ptr, const int32_t* col, const
   // rows in rank space, densest dimension first
   const int rbits = dbits;
   const int nbits = ceil_log2((uint64_t)std::max<int64_t>(n, 1));
-  CHK(ss.v32a.reserve(nnz), "alloc");
-  CHK(launch_row_keys(in.prp, in.pcol, in.pval, ix->rank.p, n, rbits, ss.k1.p, ss.v32a.p, s), "row keys");
   ix->rows.n = n;
   ix->rows.nnz = nnz;
   CHK(ix->rows.rp.alloc(n + 1), "alloc");
@@ -238,8 +241,24 @@ int build_impl(apss_index* ix, const int64_t* row_ptr, const int32_t* col, const
   ix->rows.rp_host.resize((size_t)n + 1);
   CHK(hipMemcpyAsync(ix->rows.rp_host.data(), in.prp, sizeof(int64_t) * (n + 1), hipMemcpyDeviceToHost, s), "copy");
   CHK(ix->rows.rc.alloc(nnz), "alloc");
-  if ((rc = sort_rows(ws, ss.k1.p, ss.v32a.p, nnz, nbits + rbits, rbits, ix->rows.rc.p, err))) return rc;
-  if ((rc = check_err(s, err, nullptr, "build_index"))) return rc;
+  if (longest <= (unsigned long long)kLongRow) {
+    DBuf<unsigned int> nlong;
+    DBuf<uint32_t> longs;
+    CHK(nlong.alloc(1), "alloc");
+    CHK(longs.alloc(nnz / kWaveRow + 1), "alloc");
+    CHK(fill_u32(nlong.p, 0u, 1, s), "fill");
+    CHK(launch_sort_rows(in.prp, in.pcol, in.pval, ix->rank.p, n, (int64_t)longest, ix->rows.rc.p, err, nlong.p,
+                         longs.p, s),
+        "row sort");
+    if ((rc = check_err(s, err, nullptr, "build_index"))) return rc;
+  } else {
+    // a row past one workgroup's LDS: radix passes over (row, rank) keys
+    CHK(ss.k1.reserve(nnz), "alloc sort");
+    CHK(ss.v32a.reserve(nnz), "alloc");
+    CHK(launch_row_keys(in.prp, in.pcol, in.pval, ix->rank.p, n, rbits, ss.k1.p, ss.v32a.p, s), "row keys");
+    if ((rc = sort_rows(ws, ss.k1.p, ss.v32a.p, nnz, nbits + rbits, rbits, ix->rows.rc.p, err))) return rc;
+    if ((rc = check_err(s, err, nullptr, "build_index"))) return rc;
+  }
   return build_lists(ix);
 }
 
@@ -264,17 +283,16 @@ int build_lists(apss_index* ix) {
   // below head (the screened join's head cut, or nothing at all for the
   // all-pairs-0-array index); -1: the paper's cutoff
   const int32_t head = ix->opts.index_all ? 0 : (ix->head_cut > 0 ? ix->head_cut : -1);
-  CHK(launch_cutoff(ix->rows.rp.p, ix->rows.rc.p, ix->mw_r.p, n, ix->t_build, ix->opts.query_safe ? 1 : 0, head,
-                    ix->rs.p, ix->rows.mw.p, nidx.p, s),
-      "cutoff");
-  CHK(exclusive_scan_i64(nidx.p, n, scan_tmp.p, total.p, s), "scan");
-  // the largest unindexed-part norm and each row's as a byte: the hashed
-  // filter's tests before it reads a row's statistics
+  // (with the largest unindexed-part norm and each row's as a byte: the
+  // hashed filter's tests before it reads a row's statistics)
   DBuf<uint32_t> pmax;
   CHK(pmax.alloc(1), "alloc");
   CHK(ix->pn8.alloc(std::max<int64_t>(n, 1)), "alloc");
   CHK(fill_u32(pmax.p, 0u, 1, s), "fill");
-  CHK(launch_max_pnrm(ix->rs.p, n, pmax.p, ix->pn8.p, s), "max norm");
+  CHK(launch_cutoff(ix->rows.rp.p, ix->rows.rc.p, ix->mw_r.p, n, ix->t_build, ix->opts.query_safe ? 1 : 0, head,
+                    ix->rs.p, ix->rows.mw.p, nidx.p, pmax.p, ix->pn8.p, s),
+      "cutoff");
+  CHK(exclusive_scan_i64(nidx.p, n, scan_tmp.p, total.p, s), "scan");
   int64_t P = 0;
   uint32_t pmax_bits = 0u;
   CHK(hipMemcpyAsync(&P, total.p, sizeof(int64_t), hipMemcpyDeviceToHost, s), "read P");
@@ -297,11 +315,7 @@ int build_lists(apss_index* ix) {
   CHK(launch_emit_indexed(ix->rows.rp.p, ix->rows.rc.p, ix->rs.p, nidx.p, n, ss.k1.p, ss.v64a.p, s), "emit");
   CHK(radix_sort_u64(ss.k1.p, ss.v64a.p, ss.k2.p, ss.v64b.p, P, rbits, ss.hist.p, ss.scan.p, s), "list sort");
   CHK(ix->off.alloc(m + 1), "alloc");
-  CHK(fill_u64((uint64_t*)ix->off.p, 0ull, m + 1, s), "fill");
-  CHK(launch_count_ranks(ss.k1.p, P, ix->off.p, s), "count");
-  DBuf<int64_t> scan2;
-  CHK(scan2.alloc(scan_tmp_elems(m + 1)), "alloc");
-  CHK(exclusive_scan_i64(ix->off.p, m + 1, scan2.p, nullptr, s), "scan");
+  CHK(launch_list_offsets(ss.k1.p, P, m, ix->off.p, s), "list offsets");
   // two padding entries after the last list let the join read positions p
   // and p + 1 for any p <= P (p = 0 too when there are no lists)
   CHK(ix->post.alloc(P + 2), "alloc");
@@ -1081,7 +1095,7 @@ int stage_queries(apss_index* ix, Workspace& ws, int64_t nq, const int64_t* q_ro
   rows.n = nq;
   if (on_device) {
     if ((rc = stage_csr(s, nq, q_row_ptr, q_col, q_val, on_device, &nnz, in))) return rc;
-    CHK(launch_check_rowptr(in.prp, nq, nnz, err, bad, s), "check row_ptr");
+    CHK(launch_check_rowptr(in.prp, nq, nnz, err, bad, nullptr, s), "check row_ptr");
     if ((rc = check_err(s, err, bad, "query"))) return rc;
     CHK(rows.rp.reserve(nq + 1), "alloc");
     CHK(hipMemcpyAsync(rows.rp.p, in.prp, sizeof(int64_t) * (nq + 1), hipMemcpyDeviceToDevice, s), "copy");

@@ -13,12 +13,21 @@ enum ErrBits : uint32_t {
   ERR_DUP = 16u,     // repeated dimension inside a row
 };
 
+// longest (may be NULL): *longest = max(*longest, longest row)
 hipError_t launch_check_rowptr(const int64_t* rp, int64_t n, int64_t nnz, uint32_t* err, unsigned long long* bad,
-                               hipStream_t s);
-hipError_t launch_validate_rows(const int64_t* rp, const int32_t* col, const float* val, int64_t n, int64_t m,
-                                double tol, uint32_t* err, unsigned long long* bad, hipStream_t s);
-hipError_t launch_count_dims(const int32_t* col, const float* val, int64_t nnz, uint32_t* cnt, uint32_t* mwbits,
-                             hipStream_t s);
+                               unsigned long long* longest, hipStream_t s);
+// also counts every dimension's components and takes its largest weight (cnt and mwbits zeroed before)
+hipError_t launch_validate_count(const int64_t* rp, const int32_t* col, const float* val, int64_t n, int64_t m,
+                                 double tol, uint32_t* cnt, uint32_t* mwbits, uint32_t* err, unsigned long long* bad,
+                                 hipStream_t s);
+// Rows in rank space for rows of at most kLongRow components (longest: the
+// longest one).  nlong: one zeroed counter; longs: room for the rows longer
+// than kWaveRow, at most nnz / kWaveRow.
+constexpr int kWaveRow = 512;
+constexpr int kLongRow = 8192;
+hipError_t launch_sort_rows(const int64_t* rp, const int32_t* col, const float* val, const int32_t* rank, int64_t n,
+                            int64_t longest, RComp* rc, uint32_t* err, unsigned int* nlong, uint32_t* longs,
+                            hipStream_t s);
 hipError_t launch_dim_keys(const uint32_t* cnt, int64_t m, int64_t n, int dbits, uint64_t* keys, uint64_t* vals,
                            hipStream_t s);
 hipError_t launch_rank_from_sorted(const uint64_t* vals, int64_t m, const uint32_t* cnt, const uint32_t* mwbits,
@@ -28,15 +37,16 @@ hipError_t launch_row_keys(const int64_t* rp, const int32_t* col, const float* v
 hipError_t launch_unpack_rows(const uint64_t* keys, const uint32_t* vals, int64_t nnz, int rbits, RComp* rc,
                               uint32_t* err, hipStream_t s);
 // head >= 0: the unindexed part of every row is its components of rank < head (t and l2 unused;
-// head = 0 indexes every component); head < 0: the running-bound cutoff at t
+// head = 0 indexes every component); head < 0: the running-bound cutoff at t.
+// *pmax = max over rows of rs[r].pnrm as float bits (atomicMax; zeroed before); pn8[r]: its byte code
 hipError_t launch_cutoff(const int64_t* rp, const RComp* rc, const float* mw_r, int64_t n, float t, int l2,
-                         int32_t head, RowStat* rs, float* xmw, int64_t* nidx, hipStream_t s);
+                         int32_t head, RowStat* rs, float* xmw, int64_t* nidx, uint32_t* pmax, uint8_t* pn8,
+                         hipStream_t s);
 hipError_t launch_emit_indexed(const int64_t* rp, const RComp* rc, const RowStat* rs, const int64_t* ibase, int64_t n,
                                uint64_t* keys, uint64_t* vals, hipStream_t s);
-hipError_t launch_count_ranks(const uint64_t* keys, int64_t P, int64_t* cnt, hipStream_t s);
+// off[r] = first position of the sorted keys[0, P) that is >= r, r = 0..m
+hipError_t launch_list_offsets(const uint64_t* keys, int64_t P, int64_t m, int64_t* off, hipStream_t s);
 hipError_t launch_unpack_post(const uint64_t* vals, int64_t P, Post* post, hipStream_t s);
-// *out = max over rows of rs[r].pnrm as float bits (atomicMax; *out zeroed before)
-hipError_t launch_max_pnrm(const RowStat* rs, int64_t n, uint32_t* out, uint8_t* pn8, hipStream_t s);
 hipError_t launch_pack_post4(const Post* post, int64_t P, uint32_t* post4, hipStream_t s);
 hipError_t launch_block_offsets(const int64_t* off, const Post* post, int32_t H, int64_t nb, int32_t CB,
                                 uint32_t* hoff, hipStream_t s);
