@@ -180,7 +180,7 @@ int stage_csr(hipStream_t s, int64_t n, const int64_t* row_ptr, const int32_t* c
 
 int hoff_slot(int cb) { return cb == 1024 ? 0 : 1; }
 
-int build_lists(apss_index* ix);
+int build_lists(apss_index* ix, const uint32_t* cnt_r = nullptr);
 
 int build_impl(apss_index* ix, const int64_t* row_ptr, const int32_t* col, const float* val, int on_device) {
   Workspace& ws = ix->ws;
@@ -259,12 +259,145 @@ int build_impl(apss_index* ix, const int64_t* row_ptr, const int32_t* col, const
     if ((rc = sort_rows(ws, ss.k1.p, ss.v32a.p, nnz, nbits + rbits, rbits, ix->rows.rc.p, err))) return rc;
     if ((rc = check_err(s, err, nullptr, "build_index"))) return rc;
   }
-  return build_lists(ix);
+  return build_lists(ix, cnt_r.p);
+}
+
+// An index whose self-joins may take the list-pair kernels: the default
+// algorithm with no geometry asked for (a tile variant, range width or group
+// given by the caller names the accumulating kernel).
+bool pairs_eligible(const apss_index* ix) {
+  const apss_opts& o = ix->opts;
+  return ix->head_cut == 0 && !o.index_all && o.local_parts <= 1 && !o.remscore && !o.screen_dims && o.variant < 0 &&
+         o.range_rows == 0 && o.range_group == 0 && !getenv("APSS_VARIANT") && !getenv("APSS_RANGE_ROWS") &&
+         !getenv("APSS_RANGE_GROUP") && ix->n > 1 && ix->n <= (1 << 25);  // (a list's units are counted in 32 bits)
+}
+
+// Sketches, deep lists and work units, from the sorted list values in the
+// sort scratch (with the lists of every index).
+int build_pair_lists(apss_index* ix, const uint32_t* cnt_r) {
+  Workspace& ws = ix->ws;
+  hipStream_t s = ws.stream;
+  SortScratch& ss = ws.ss;
+  const int64_t n = ix->n, m = ix->m, P = ix->P;
+  const int64_t nt = list_tiles(P);
+  const int64_t longest = std::max(nt, m + 1);
+  DBuf<int64_t> tiles, scan, total;
+  CHK(tiles.alloc(longest), "alloc");
+  CHK(scan.alloc(scan_tmp_elems(longest)), "alloc");
+  CHK(total.alloc(1), "alloc");
+  int64_t deep = 0;
+  CHK(launch_count_deep(ss.v64a.p, P, tiles.p, s), "deep lists");
+  CHK(exclusive_scan_i64(tiles.p, nt, scan.p, total.p, s), "scan");
+  CHK(hipMemcpyAsync(&deep, total.p, sizeof(int64_t), hipMemcpyDeviceToHost, s), "deep lists");
+  CHK(hipStreamSynchronize(s), "deep lists");
+  CHK(ix->dl.alloc(deep), "alloc");
+  CHK(ix->doff.alloc(m + 1), "alloc");
+  uint32_t* pos = (uint32_t*)ss.k2.p;  // the sort's second keys are free
+  CHK(launch_lists(ss.v64a.p, P, ix->post.p, ix->post4.p, tiles.p, pos, ix->dl.p, s), "lists");
+  CHK(launch_deep_offsets(ix->off.p, pos, P, m, deep, ix->doff.p, s), "deep lists");
+  // groups of ranks of about equal component counts, and the sketches
+  CHK(ix->gid.alloc(m), "alloc");
+  CHK(ix->sk.alloc(n * kSkGroups), "alloc");
+  CHK(launch_widen(cnt_r, m, tiles.p, s), "groups");
+  CHK(exclusive_scan_i64(tiles.p, m, scan.p, nullptr, s), "scan");
+  CHK(launch_groups(tiles.p, cnt_r, m, ix->nnz, ix->gid.p, s), "groups");
+  int64_t longs = 0;
+  for (int64_t r = 0; r < n; ++r) longs += ix->rows.rp_host[(size_t)r + 1] - ix->rows.rp_host[(size_t)r] > kFineRow;
+  CHK(ix->fidx.alloc(n), "alloc");
+  CHK(ix->fsk.alloc(longs * kFineGroups), "alloc");
+  DBuf<unsigned int> nfine;
+  CHK(nfine.alloc(1), "alloc");
+  CHK(fill_u32(nfine.p, 0u, 1, s), "fill");
+  CHK(launch_sketch(ix->rows.rp.p, ix->rows.rc.p, ix->gid.p, n, ix->sk.p, nfine.p, ix->fidx.p, ix->fsk.p, s), "sketches");
+  // work units by rank
+  DBuf<int64_t> stiles;
+  CHK(stiles.alloc(m + 1), "alloc");
+  CHK(launch_unit_counts(ix->doff.p, m, true, tiles.p, s), "units");
+  CHK(launch_unit_counts(ix->doff.p, m, false, stiles.p, s), "units");
+  CHK(exclusive_scan_i64(tiles.p, m, scan.p, total.p, s), "scan");
+  CHK(hipMemcpyAsync(&ix->nwide, total.p, sizeof(int64_t), hipMemcpyDeviceToHost, s), "units");
+  CHK(exclusive_scan_i64(stiles.p, m, scan.p, total.p, s), "scan");
+  CHK(hipMemcpyAsync(&ix->nshort, total.p, sizeof(int64_t), hipMemcpyDeviceToHost, s), "units");
+  CHK(hipStreamSynchronize(s), "units");
+  CHK(ix->wide.alloc(ix->nwide), "alloc");
+  CHK(ix->shorts.alloc(ix->nshort), "alloc");
+  CHK(launch_unit_fill(ix->doff.p, tiles.p, m, true, ix->wide.p, s), "units");
+  CHK(launch_unit_fill(ix->doff.p, stiles.p, m, false, ix->shorts.p, s), "units");
+  ix->pair_groups = pairs_resident_groups();
+  // The list-pair kernels or the accumulating one, whichever should take
+  // less, by their measured rates (MI355X): the accumulating kernel visits
+  // 8e11-1e12 list entries a second (1.0e12 on 100,000 rows of mean 80 at
+  // t = 0.5, 8e11 on 500,000 of mean 120 at 0.7); the list-pair kernels test
+  // 1.5e12 pairs a second, take 1.6 ns per short unit (a wave's), decide a
+  // survivor in 0.45 ns, and count the candidates of a query in a block of
+  // 4,096 rows in 2 ns (mean 120; in proportion to the components).  Those
+  // two workloads took 30 and 490 ms with the one, 13 and 77 ms with the
+  // other.  The survivors are estimated from every k-th unit, and doubled:
+  // on rows that the sketches do not tell apart (flat weights over few
+  // dimensions) they are most pairs, and the accumulating kernel is ahead.
+  // A join at a higher threshold than the index's has fewer.
+  DBuf<unsigned long long> cnt;
+  CHK(cnt.alloc(C_NUM), "alloc");
+  CHK(ws.qctr.reserve(kQueueCounters), "alloc queues");
+  CHK(fill_u64((uint64_t*)cnt.p, 0ull, C_NUM, s), "fill");
+  CHK(fill_u32(ws.qctr.p, 0u, kQueueCounters, s), "fill");
+  JoinPlan plan;
+  bind_pairs(ix, ix->t_build, ws.qctr.p, nullptr, 0, plan);
+  plan.pa.counters = cnt.p;
+  const int64_t units = ix->nwide + ix->nshort / kShortUnits;
+  plan.pa.sample = std::max<int64_t>(1, units / 4096);
+  CHK(launch_pairs(plan.pa, plan.pg, s), "sample");
+  CHK(launch_visits(cnt_r, ix->off.p, m, cnt.p + C_TAILVISITS, s), "sample");
+  unsigned long long c[C_NUM];
+  CHK(hipMemcpyAsync(c, cnt.p, sizeof(c), hipMemcpyDeviceToHost, s), "sample");
+  CHK(hipStreamSynchronize(s), "sample");
+  const double k = (double)plan.pa.sample;
+  const double blocks = (double)((n + kCountRows - 1) / kCountRows);
+  const double pairs_ms = 1e3 * (k * (double)c[C_VISITS] / 1.5e12 + 2.0 * k * (double)c[C_SURVIVORS] * 0.45e-9 +
+                                 (double)ix->nshort * 1.6e-9 + 0.5 * blocks * (double)ix->nnz * (2e-9 / 120.0));
+  const double lists_ms = 1e3 * (double)c[C_TAILVISITS] / 1e12;
+  // (up to one block of rows launches and waits are most of either: 0.24 ms
+  // against 0.27 ms for 2,000 rows, so there only many survivors decide)
+  const bool few = k * (double)c[C_SURVIVORS] <= 64.0 * (double)n;
+  ix->pairs_ready = n <= kCountRows ? few : pairs_ms < lists_ms;
+  if (ix->opts.reserved[0] == kProbePairs) ix->pairs_ready = true;
+  if (!ix->pairs_ready) {
+    ix->sk.release();
+    ix->fsk.release();
+    ix->gid.release();
+    ix->fidx.release();
+    ix->dl.release();
+    ix->doff.release();
+    ix->wide.release();
+    ix->shorts.release();
+  }
+  return APSS_OK;
+}
+
+// Bitmaps of the densest ranks for the candidate count (after prepare()).
+int build_bitmaps(apss_index* ix) {
+  const int slot = ix->hoff[0].p ? 0 : 1;
+  const int cb = slot == 0 ? 1024 : 2048;
+  ix->count_ranks = std::min<int32_t>(kCountRanks, ix->H);
+  ix->count_blocks = (ix->n + kCountRows - 1) / kCountRows;
+  CHK(ix->bm.alloc(ix->count_blocks * ix->count_ranks * kCountWords), "alloc");
+  CHK(ix->seg.alloc(ix->count_blocks * ix->H), "alloc");
+  CHK(launch_segments(ix->hoff[slot].p, ix->H, cb, ix->hoff_nb[slot], ix->count_blocks, ix->seg.p, ix->ws.stream),
+      "bitmaps");
+  ix->present_words = std::max<int64_t>(1, (ix->m - ix->H + 31) / 32);
+  const int64_t nw = ix->count_blocks * ix->present_words;
+  CHK(ix->present.alloc(nw), "alloc");
+  CHK(fill_u32(ix->present.p, 0u, nw, ix->ws.stream), "fill");
+  CHK(launch_present(ix->off.p, ix->post.p, ix->H, ix->m, ix->present_words, ix->present.p, ix->ws.stream), "bitmaps");
+  CHK(launch_bitmaps(ix->post.p, ix->hoff[slot].p, ix->H, cb, ix->hoff_nb[slot], ix->count_ranks, ix->count_blocks,
+                     ix->bm.p, ix->ws.stream),
+      "bitmaps");
+  return APSS_OK;
 }
 
 // From the rank-space rows on: cutoff of every row, the inverted lists of
 // the indexed parts and the lookup tables of the join.
-int build_lists(apss_index* ix) {
+int build_lists(apss_index* ix, const uint32_t* cnt_r) {
   Workspace& ws = ix->ws;
   hipStream_t s = ws.stream;
   SortScratch& ss = ws.ss;
@@ -312,7 +445,10 @@ int build_lists(apss_index* ix) {
   CHK(ss.v64b.reserve(P), "alloc");
   CHK(ss.hist.reserve(radix_hist_elems(P)), "alloc");
   CHK(ss.scan.reserve(radix_scan_tmp_elems(P)), "alloc");
-  CHK(launch_emit_indexed(ix->rows.rp.p, ix->rows.rc.p, ix->rs.p, nidx.p, n, ss.k1.p, ss.v64a.p, s), "emit");
+  const bool pairs = cnt_r && pairs_eligible(ix) && P > 0;
+  // rows may exceed norm 1 by 1e-5, and the scan rounds: 1e-4 covers both
+  const double lim = pairs ? (double)ix->t_build * (double)ix->t_build * (1.0 - 1e-4) : -1.0;
+  CHK(launch_emit_indexed(ix->rows.rp.p, ix->rows.rc.p, ix->rs.p, nidx.p, n, lim, ss.k1.p, ss.v64a.p, s), "emit");
   CHK(radix_sort_u64(ss.k1.p, ss.v64a.p, ss.k2.p, ss.v64b.p, P, rbits, ss.hist.p, ss.scan.p, s), "list sort");
   CHK(ix->off.alloc(m + 1), "alloc");
   CHK(launch_list_offsets(ss.k1.p, P, m, ix->off.p, s), "list offsets");
@@ -320,13 +456,16 @@ int build_lists(apss_index* ix) {
   // and p + 1 for any p <= P (p = 0 too when there are no lists)
   CHK(ix->post.alloc(P + 2), "alloc");
   CHK(fill_u64((uint64_t*)ix->post.p + P, ~0ull, 2, s), "fill");
-  CHK(launch_unpack_post(ss.v64a.p, P, ix->post.p, s), "post");
   // the join's list loads put a chunk's base in the scalar offset, which the
   // hardware range check does not cover: 64 zero entries after the last list
   // keep a chunk's lanes past its end inside the allocation
   CHK(ix->post4.alloc(P + kPost4Pad), "alloc");
   CHK(fill_u32(ix->post4.p + P, 0u, kPost4Pad, s), "fill");
-  CHK(launch_pack_post4(ix->post.p, P, ix->post4.p, s), "post4");
+  if (pairs) {
+    if ((rc = build_pair_lists(ix, cnt_r))) return rc;
+  } else {
+    CHK(launch_lists(ss.v64a.p, P, ix->post.p, ix->post4.p, nullptr, nullptr, nullptr, s), "lists");
+  }
 
   // local pruning: split the indexed ranks into parts of about equal
   // postings; ranks are in decreasing density, so the first parts hold the
@@ -354,6 +493,7 @@ int build_lists(apss_index* ix) {
   if (H > m) H = (int32_t)m;
   ix->H = H;
   if ((rc = prepare(ix, s, ix->variant, ix->range_rows))) return rc;
+  if (ix->pairs_ready && (rc = build_bitmaps(ix))) return rc;
   CHK(hipStreamSynchronize(s), "build_index");
   // sort scratch is re-grown on demand by the joins
   ss.k1.release();
@@ -570,6 +710,13 @@ int plan_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, fl
   hipStream_t s = ws.stream;
   int rc0 = prepare(ix, s, ix->variant, ix->range_rows);
   if (rc0) return rc0;
+  if (triangle && use_pairs(ix)) {
+    CHK(ws.qctr.reserve(kQueueCounters), "alloc queues");
+    CHK(ws.counters.reserve(C_NUM), "alloc counters");
+    CHK(ws.pq.reserve(3 * pair_queue_entries(ix)), "alloc queues");
+    bind_pairs(ix, t, ws.qctr.p, ws.pq.p, ws.pq.n / 3, P);
+    return APSS_OK;
+  }
   JoinLayout L;
   if ((rc0 = plan_layout(ix, Q, triangle, L))) return rc0;
   CHK(ws.tstart.reserve(L.ntiles + 1), "alloc tiles");
@@ -577,28 +724,100 @@ int plan_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, fl
       "tiles");
   CHK(ws.qcum.reserve((int64_t)L.cum.size()), "alloc queues");
   CHK(hipMemcpyAsync(ws.qcum.p, L.cum.data(), sizeof(int64_t) * L.cum.size(), hipMemcpyHostToDevice, s), "queues");
-  CHK(ws.qctr.reserve(8), "alloc queues");
+  CHK(ws.qctr.reserve(kQueueCounters), "alloc queues");
   CHK(ws.counters.reserve(C_NUM), "alloc counters");
   CHK(ws.wg_cur.reserve((int64_t)L.G * L.wg_stride), "alloc cursors");
   bind_plan(ix, Q, triangle, t, qt_dev, qrs, L, ws.tstart.p, ws.qcum.p, ws.qctr.p, ws.wg_cur.p, P);
   return APSS_OK;
 }
 
-// Launch a planned join writing pairs into ws.raw_key / raw_sim through ws.counters.
-int launch_planned(Workspace& ws, JoinPlan& P) {
+bool use_pairs(const apss_index* ix) { return ix->pairs_ready && !ix->pairs_off; }
+
+// 256 per row covers the survivors of the million-vector workloads many times
+// over; between 1M and 64M entries of 12 bytes.
+int64_t pair_queue_entries(const apss_index* ix) {
+  return std::max<int64_t>(1 << 20, std::min<int64_t>(256 * ix->n, 64ll << 20));
+}
+
+void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue_dev, int64_t qcap, JoinPlan& P) {
+  P = JoinPlan{};
+  P.pairs = true;
+  P.bj = ceil_log2((uint64_t)ix->n);
+  P.bi = P.bj;
+  P.pg = ix->pair_groups;
+  PairArgs& a = P.pa;
+  a.rp = ix->rows.rp.p;
+  a.rc = ix->rows.rc.p;
+  a.sk = ix->sk.p;
+  a.gid = ix->gid.p;
+  a.fidx = ix->fidx.p;
+  a.fsk = ix->fsk.p;
+  a.dl = ix->dl.p;
+  a.doff = ix->doff.p;
+  a.wide = ix->wide.p;
+  a.shorts = ix->shorts.p;
+  a.nwide = ix->nwide;
+  a.nshort = ix->nshort;
+  a.uctr = uctr_dev;
+  a.queue = queue_dev;
+  a.qcap = qcap;
+  a.t = t;
+  a.thr = pair_threshold(t);
+  a.bj = P.bj;
+  CountArgs& c = P.ca;
+  c.rp = ix->rows.rp.p;
+  c.rc = ix->rows.rc.p;
+  c.nq = ix->n;
+  c.triangle = 1;
+  c.bm = ix->bm.p;
+  c.HB = ix->count_ranks;
+  c.n = ix->n;
+  c.nblk = ix->count_blocks;
+  c.post = ix->post.p;
+  c.post4 = ix->post4.p;
+  c.seg = ix->seg.p;
+  c.H = ix->H;
+  c.toff = ix->toff.p;
+  c.m_tail = (int32_t)(ix->m - ix->H);
+  c.rr = ix->toff_rows;
+  c.nR = ix->toff_nR;
+  c.present = ix->present.p;
+  c.present_words = ix->present_words;
+  // about eight work items per compute unit, of at least a few queries per wave
+  const int64_t want = ix->n * ix->count_blocks / 2 / 2048;
+  c.chunk = std::max<int64_t>(64, std::min<int64_t>(4096, (want + 63) / 64 * 64));
+}
+
+int launch_plan(JoinPlan& P, uint64_t* out_key, float* out_sim, int64_t cap, unsigned long long* counters,
+                unsigned int* qctr, hipStream_t s) {
+  CHK(fill_u32(qctr, 0u, kQueueCounters, s), "fill");
+  if (P.pairs) {
+    P.pa.out_key = out_key;
+    P.pa.out_sim = out_sim;
+    P.pa.cap = cap;
+    P.pa.counters = counters;
+    P.ca.counters = counters;
+    CHK(launch_count(P.ca, s), "count kernel");
+    CHK(launch_pairs(P.pa, P.pg, s), "pair kernel");
+    return APSS_OK;
+  }
   JoinArgs& a = P.a;
-  a.out_key = ws.raw_key.p;
-  a.out_sim = ws.raw_sim.p;
-  a.cap = ws.raw_key.n;
-  a.counters = ws.counters.p;
-  a.qctr = ws.qctr.p;
-  CHK(fill_u32(ws.qctr.p, 0u, 8, ws.stream), "fill");
+  a.out_key = out_key;
+  a.out_sim = out_sim;
+  a.cap = cap;
+  a.counters = counters;
+  a.qctr = qctr;
   if (!join_args_complete(a)) {
     set_error("internal: join launched with a missing device buffer");
     return APSS_EDEVICE;
   }
-  CHK(launch_join(a, P.variant, P.G, ws.stream), "join kernel");
+  CHK(launch_join(a, P.variant, P.G, s), "join kernel");
   return APSS_OK;
+}
+
+// Launch a planned join writing pairs into ws.raw_key / raw_sim through ws.counters.
+int launch_planned(Workspace& ws, JoinPlan& P) {
+  return launch_plan(P, ws.raw_key.p, ws.raw_sim.p, ws.raw_key.n, ws.counters.p, ws.qctr.p, ws.stream);
 }
 
 int ensure_pair_capacity(Workspace& ws, int64_t cap) {
@@ -881,7 +1100,7 @@ namespace {
 int64_t join_cap_hint(const apss_index* ix) { return std::max<int64_t>(1 << 20, 32 * ix->n); }
 
 std::vector<const void*> graph_buffers(const apss_index* ix, const Workspace& ws) {
-  return {ws.tstart.p, ws.qcum.p, ws.qctr.p, ws.counters.p, ws.wg_cur.p, ws.raw_key.p, ws.raw_sim.p, ws.ss.k2.p,
+  return {ws.tstart.p, ws.qcum.p, ws.qctr.p, ws.counters.p, ws.wg_cur.p, ws.pq.p, ws.raw_key.p, ws.raw_sim.p, ws.ss.k2.p,
           ws.ss.v32b.p, ws.ss.hist.p, ws.ss.scan.p, ix->toff.p, ix->hoff[0].p, ix->hoff[1].p,
           (const void*)(intptr_t)ix->variant, (const void*)(intptr_t)ix->range_rows,
           (const void*)(intptr_t)ix->range_group};

@@ -42,12 +42,20 @@ hipError_t launch_unpack_rows(const uint64_t* keys, const uint32_t* vals, int64_
 hipError_t launch_cutoff(const int64_t* rp, const RComp* rc, const float* mw_r, int64_t n, float t, int l2,
                          int32_t head, RowStat* rs, float* xmw, int64_t* nidx, uint32_t* pmax, uint8_t* pn8,
                          hipStream_t s);
+// lim >= 0: mark (sign bit of the weight) the components up to which the row's squared norm is at least lim
 hipError_t launch_emit_indexed(const int64_t* rp, const RComp* rc, const RowStat* rs, const int64_t* ibase, int64_t n,
-                               uint64_t* keys, uint64_t* vals, hipStream_t s);
+                               double lim, uint64_t* keys, uint64_t* vals, hipStream_t s);
 // off[r] = first position of the sorted keys[0, P) that is >= r, r = 0..m
 hipError_t launch_list_offsets(const uint64_t* keys, int64_t P, int64_t m, int64_t* off, hipStream_t s);
-hipError_t launch_unpack_post(const uint64_t* vals, int64_t P, Post* post, hipStream_t s);
-hipError_t launch_pack_post4(const Post* post, int64_t P, uint32_t* post4, hipStream_t s);
+// Lists from the sorted values: entries and their packed copy; with dl, the
+// marked entries' ids (tiles: exclusive scan of launch_count_deep's
+// list_tiles(P) counts) and the marked entries before each position
+int64_t list_tiles(int64_t P);
+hipError_t launch_count_deep(const uint64_t* vals, int64_t P, int64_t* tiles, hipStream_t s);
+hipError_t launch_lists(const uint64_t* vals, int64_t P, Post* post, uint32_t* post4, const int64_t* tiles,
+                        uint32_t* pos, uint32_t* dl, hipStream_t s);
+hipError_t launch_deep_offsets(const int64_t* off, const uint32_t* pos, int64_t P, int64_t m, int64_t deep,
+                               int64_t* doff, hipStream_t s);
 hipError_t launch_block_offsets(const int64_t* off, const Post* post, int32_t H, int64_t nb, int32_t CB,
                                 uint32_t* hoff, hipStream_t s);
 hipError_t launch_query_keys(const int64_t* rp, const int32_t* col, const float* val, const int32_t* rank, int64_t nq,

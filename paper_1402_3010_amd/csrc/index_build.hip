@@ -363,19 +363,40 @@ __global__ __launch_bounds__(256) void k_cutoff(const int64_t* __restrict__ rp, 
 }
 
 // Indexed components in row-major order -> (key = rank, value = y << 32 | weight bits),
-// one wave per row.
+// one wave per row.  DEEP: the weight's sign bit marks the components whose
+// row's norm over the ranks up to them reaches the build threshold (squared
+// norm at least lim; lim is a little low, so that rounding here and norms a
+// little over 1 lose none).
+template <bool DEEP>
 __global__ __launch_bounds__(256) void k_emit_indexed(const int64_t* __restrict__ rp, const RComp* __restrict__ rc,
                                                       const RowStat* __restrict__ rs, const int64_t* __restrict__ ibase,
-                                                      int64_t n, uint64_t* __restrict__ keys,
+                                                      int64_t n, double lim, uint64_t* __restrict__ keys,
                                                       uint64_t* __restrict__ vals) {
   const int lane = (int)(threadIdx.x & 63u);
   for (int64_t r = (int64_t)blockIdx.x * 4 + (int64_t)(threadIdx.x >> 6); r < n; r += (int64_t)gridDim.x * 4) {
-    const int64_t a = rp[r] + rs[r].cut, b = rp[r + 1];
-    const int64_t o = ibase[r] - a;
-    for (int64_t k = a + lane; k < b; k += 64) {
-      const RComp c = rc[k];
-      keys[o + k] = (uint64_t)(uint32_t)c.r;
-      vals[o + k] = ((uint64_t)(uint32_t)r << 32) | (uint64_t)__float_as_uint(c.w);
+    const int64_t first = rp[r] + rs[r].cut, b = rp[r + 1];
+    const int64_t o = ibase[r] - first;
+    double before = 0.0;  // squared norm of the components before this chunk
+    for (int64_t k0 = DEEP ? rp[r] : first; k0 < b; k0 += 64) {
+      const int64_t k = k0 + lane;
+      RComp c{0, 0.0f};
+      if (k < b) c = rc[k];
+      uint32_t deep = 0u;
+      if constexpr (DEEP) {
+        double sq = (double)c.w * (double)c.w;
+#pragma unroll
+        for (int s = 1; s < 64; s <<= 1) {
+          const double u = __shfl_up(sq, s, 64);
+          if (lane >= s) sq += u;
+        }
+        sq += before;
+        deep = sq >= lim ? 0x80000000u : 0u;
+        before = lane_value(sq, 63);
+      }
+      if (k >= first && k < b) {
+        keys[o + k] = (uint64_t)(uint32_t)c.r;
+        vals[o + k] = ((uint64_t)(uint32_t)r << 32) | (uint64_t)(__float_as_uint(c.w) | deep);
+      }
     }
   }
 }
@@ -397,27 +418,85 @@ __global__ void k_list_offsets(const uint64_t* __restrict__ keys, int64_t P, int
   }
 }
 
-__global__ void k_unpack_post(const uint64_t* __restrict__ vals, int64_t P, Post* __restrict__ post) {
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < P; k += (int64_t)gridDim.x * blockDim.x) {
-    const uint64_t v = vals[k];
-    Post p;
-    p.y = (uint32_t)(v >> 32);
-    p.w = __uint_as_float((uint32_t)v);
-    post[k] = p;
+// The sorted list entries, in tiles of kListTile: marked (deep) entries per
+// tile, and after a scan of those counts the lists themselves.
+constexpr int kListTile = 2048;
+
+__global__ __launch_bounds__(256) void k_count_deep(const uint64_t* __restrict__ vals, int64_t P,
+                                                    int64_t* __restrict__ tiles) {
+  __shared__ uint32_t total;
+  if (threadIdx.x == 0) total = 0u;
+  __syncthreads();
+  const int64_t base = (int64_t)blockIdx.x * kListTile;
+  uint32_t c = 0;
+#pragma unroll
+  for (int it = 0; it < kListTile / 256; ++it) {
+    const int64_t k = base + it * 256 + (int64_t)threadIdx.x;
+    c += (uint32_t)__popcll(__ballot(k < P && ((uint32_t)vals[k < P ? k : 0] >> 31)));
+  }
+  if ((threadIdx.x & 63u) == 0) atomicAdd(&total, c);
+  __syncthreads();
+  if (threadIdx.x == 0) tiles[blockIdx.x] = (int64_t)total;
+}
+
+// List entries {id, weight} and their packed copy for streaming: low 16 bits
+// = vector id mod 2^16 (its offset inside any power-of-two block), high 16
+// bits = the weight in units of 2^-15 rounded up (w * 2^15 is exact in float,
+// so the ceiling is the smallest such unit count not below w).  DEEP: the
+// marked entries' ids close up into dl, and pos[k] counts those before k.
+template <bool DEEP>
+__global__ __launch_bounds__(256) void k_lists(const uint64_t* __restrict__ vals, int64_t P, Post* __restrict__ post,
+                                               uint32_t* __restrict__ post4, const int64_t* __restrict__ tiles,
+                                               uint32_t* __restrict__ pos, uint32_t* __restrict__ dl) {
+  __shared__ uint32_t wtot[4];
+  const int lane = (int)(threadIdx.x & 63u), wave = (int)(threadIdx.x >> 6);
+  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  // each wave takes consecutive entries, so that its marked ones close up in order
+  constexpr int kPer = kListTile / 256;
+  const int64_t base = (int64_t)blockIdx.x * kListTile + wave * (64 * kPer) + lane;
+  uint64_t m[kPer];
+  uint32_t y[kPer], mine = 0u;
+#pragma unroll
+  for (int it = 0; it < kPer; ++it) {
+    const int64_t k = base + it * 64;
+    bool deep = false;
+    y[it] = 0u;
+    if (k < P) {
+      const uint64_t v = vals[k];
+      Post p;
+      p.y = (uint32_t)(v >> 32);
+      p.w = __uint_as_float((uint32_t)v & 0x7FFFFFFFu);
+      post[k] = p;
+      uint32_t w15 = (uint32_t)ceilf(p.w * 32768.0f);
+      if (w15 > 0xFFFFu) w15 = 0xFFFFu;
+      post4[k] = (p.y & 0xFFFFu) | (w15 << 16);
+      deep = ((uint32_t)v >> 31) != 0u;
+      y[it] = p.y;
+    }
+    m[it] = __ballot(deep);
+    mine += (uint32_t)__popcll(m[it]);
+  }
+  if constexpr (DEEP) {
+    if (lane == 0) wtot[wave] = mine;
+    __syncthreads();
+    uint32_t at = (uint32_t)tiles[blockIdx.x];
+    for (int w = 0; w < wave; ++w) at += wtot[w];
+#pragma unroll
+    for (int it = 0; it < kPer; ++it) {
+      const int64_t k = base + it * 64;
+      const uint32_t here = at + (uint32_t)__popcll(m[it] & lt);
+      if (k < P) pos[k] = here;
+      if ((m[it] >> lane) & 1ull) dl[here] = y[it];
+      at += (uint32_t)__popcll(m[it]);
+    }
   }
 }
 
-// Packed copy of the list entries for streaming: low 16 bits = vector id mod
-// 2^16 (its offset inside any power-of-two block), high 16 bits = the weight
-// in units of 2^-15 rounded up (w * 2^15 is exact in float, so the ceiling is
-// the smallest such unit count not below w).
-__global__ void k_pack_post4(const Post* __restrict__ post, int64_t P, uint32_t* __restrict__ post4) {
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < P; k += (int64_t)gridDim.x * blockDim.x) {
-    const Post p = post[k];
-    uint32_t w15 = (uint32_t)ceilf(p.w * 32768.0f);
-    if (w15 > 0xFFFFu) w15 = 0xFFFFu;
-    post4[k] = (p.y & 0xFFFFu) | (w15 << 16);
-  }
+// doff[r] = marked entries before list r
+__global__ void k_deep_offsets(const int64_t* __restrict__ off, const uint32_t* __restrict__ pos, int64_t P, int64_t m,
+                               int64_t deep, int64_t* __restrict__ doff) {
+  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r <= m; r += (int64_t)gridDim.x * blockDim.x)
+    doff[r] = off[r] < P ? (int64_t)pos[off[r]] : deep;
 }
 
 // hoff[b * H + r] = first position in list r whose vector id is >= b * CB.
@@ -573,9 +652,12 @@ hipError_t launch_cutoff(const int64_t* rp, const RComp* rc, const float* mw_r, 
 }
 
 hipError_t launch_emit_indexed(const int64_t* rp, const RComp* rc, const RowStat* rs, const int64_t* ibase, int64_t n,
-                               uint64_t* keys, uint64_t* vals, hipStream_t s) {
+                               double lim, uint64_t* keys, uint64_t* vals, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_emit_indexed, dim3(row_grid(n)), dim3(256), 0, s, rp, rc, rs, ibase, n, keys, vals);
+  if (lim >= 0.0)
+    hipLaunchKernelGGL(k_emit_indexed<true>, dim3(row_grid(n)), dim3(256), 0, s, rp, rc, rs, ibase, n, lim, keys, vals);
+  else
+    hipLaunchKernelGGL(k_emit_indexed<false>, dim3(row_grid(n)), dim3(256), 0, s, rp, rc, rs, ibase, n, lim, keys, vals);
   return hipGetLastError();
 }
 
@@ -584,13 +666,28 @@ hipError_t launch_list_offsets(const uint64_t* keys, int64_t P, int64_t m, int64
   return hipSuccess;
 }
 
-hipError_t launch_unpack_post(const uint64_t* vals, int64_t P, Post* post, hipStream_t s) {
-  LAUNCH(k_unpack_post, P, vals, P, post);
-  return hipSuccess;
+int64_t list_tiles(int64_t P) { return (P + kListTile - 1) / kListTile; }
+
+hipError_t launch_count_deep(const uint64_t* vals, int64_t P, int64_t* tiles, hipStream_t s) {
+  if (P <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_count_deep, dim3((unsigned)list_tiles(P)), dim3(256), 0, s, vals, P, tiles);
+  return hipGetLastError();
 }
 
-hipError_t launch_pack_post4(const Post* post, int64_t P, uint32_t* post4, hipStream_t s) {
-  LAUNCH(k_pack_post4, P, post, P, post4);
+hipError_t launch_lists(const uint64_t* vals, int64_t P, Post* post, uint32_t* post4, const int64_t* tiles,
+                        uint32_t* pos, uint32_t* dl, hipStream_t s) {
+  if (P <= 0) return hipSuccess;
+  const unsigned g = (unsigned)list_tiles(P);
+  if (dl)
+    hipLaunchKernelGGL(k_lists<true>, dim3(g), dim3(256), 0, s, vals, P, post, post4, tiles, pos, dl);
+  else
+    hipLaunchKernelGGL(k_lists<false>, dim3(g), dim3(256), 0, s, vals, P, post, post4, tiles, pos, dl);
+  return hipGetLastError();
+}
+
+hipError_t launch_deep_offsets(const int64_t* off, const uint32_t* pos, int64_t P, int64_t m, int64_t deep,
+                               int64_t* doff, hipStream_t s) {
+  LAUNCH(k_deep_offsets, m + 1, off, pos, P, m, deep, doff);
   return hipSuccess;
 }
 

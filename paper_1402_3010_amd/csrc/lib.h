@@ -11,6 +11,7 @@
 #include "../../include/apss.h"
 #include "apss_internal.h"
 #include "join.h"
+#include "pairs.h"
 
 namespace apss {
 
@@ -122,6 +123,7 @@ struct Workspace {
   SortScratch ss;
   DBuf<int64_t> tstart, qcum;
   DBuf<unsigned int> qctr;
+  DBuf<uint32_t> pq;         // survivor queue of the list-pair join
   DBuf<uint32_t> wg_cur;
   DBuf<unsigned long long> counters;
   DBuf<int64_t> uniq_total;  // distinct pairs after a join with local pruning
@@ -151,7 +153,7 @@ struct Workspace {
   }
   int64_t bytes() const {
     return ss.bytes() + tstart.bytes() + qcum.bytes() + qctr.bytes() + wg_cur.bytes() + counters.bytes() +
-           raw_key.bytes() + raw_sim.bytes() + qt.bytes() + uniq_total.bytes() + qadm.bytes() + q_col.bytes() + q_val.bytes() + s_keys.bytes() + s_cand.bytes() + s_sid.bytes() +
+           raw_key.bytes() + raw_sim.bytes() + pq.bytes() + qt.bytes() + uniq_total.bytes() + qadm.bytes() + q_col.bytes() + q_val.bytes() + s_keys.bytes() + s_cand.bytes() + s_sid.bytes() +
            s_tiles.bytes() + s_nh.bytes() + s_X.bytes();
   }
 };
@@ -182,6 +184,18 @@ struct apss_index {
   int32_t parts = 1;
   apss::DBuf<int32_t> part_lo;
   std::vector<int32_t> part_lo_host;
+  // the list-pair self-join (pairs.hip): sketches, deep lists, work units and
+  // the candidate count's bitmaps; empty unless pairs_ready
+  bool pairs_ready = false;
+  bool pairs_off = false;  // joins take the accumulating kernel all the same (while it is tuned)
+  apss::DBuf<uint8_t> sk, fsk;
+  apss::DBuf<uint16_t> gid;
+  apss::DBuf<uint32_t> dl, bm, present, fidx;
+  apss::DBuf<int64_t> doff;
+  apss::DBuf<uint2> wide, shorts, seg;
+  int64_t nwide = 0, nshort = 0, count_blocks = 0, present_words = 0;
+  int32_t count_ranks = 0;
+  apss::PairGroups pair_groups;
   // lazily built tables (guarded by prep_mu)
   std::mutex prep_mu;
   apss::DBuf<uint32_t> hoff[2];  // per-block offsets of the dense lists (block width 1024, 2048)
@@ -220,9 +234,13 @@ struct JoinLayout {
 
 // A join kernel launch with every argument but its outputs and counters.
 struct JoinPlan {
+  bool pairs = false;  // the list-pair join: pa and ca in place of a
+  PairArgs pa{};
+  CountArgs ca{};
   JoinArgs a{};
   int variant = 0;
   int G = 0;
+  PairGroups pg;
   int bi = 0, bj = 0;
 };
 
@@ -235,6 +253,23 @@ int plan_layout(apss_index* ix, const QuerySet& Q, int triangle, JoinLayout& L);
 void bind_plan(apss_index* ix, const QuerySet& Q, int triangle, float t, const float* qt_dev, const RowStat* qrs,
                const JoinLayout& L, const int64_t* tstart_dev, const int64_t* qcum_dev, unsigned int* qctr_dev,
                uint32_t* wg_cur_dev, JoinPlan& P);
+
+// Work queue counters of a launch: 8 queues of the accumulating join, or the
+// list-pair join's units and survivors (3).
+constexpr int kQueueCounters = 8;
+// Test hook outside the ABI: apss_opts.reserved[0] of an index whose self-joins
+// take the list-pair kernels whatever the cost rule says.
+constexpr int32_t kProbePairs = 0x50414952;
+// True when a self-join of the index takes the list-pair kernels.
+bool use_pairs(const apss_index* ix);
+// The list-pair self-join's kernel arguments, with 2 unit counters.
+void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue_dev, int64_t qcap, JoinPlan& P);
+// Survivor queue entries (3 words each) of a self-join by list pairs.
+int64_t pair_queue_entries(const apss_index* ix);
+// Launch a plan's kernels (the queue counters are cleared here, the result
+// counters by the caller).
+int launch_plan(JoinPlan& P, uint64_t* out_key, float* out_sim, int64_t cap, unsigned long long* counters,
+                unsigned int* qctr, hipStream_t s);
 
 std::string& last_error();  // per calling thread
 void set_error(const char* fmt, ...);

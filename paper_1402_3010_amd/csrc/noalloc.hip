@@ -28,6 +28,8 @@ namespace {
 
 constexpr size_t kScratchBytes = (size_t)APSS_NOALLOC_SCRATCH_BYTES;
 constexpr int kMaxDevices = 64;
+// survivors queued at once in a list-pair join (12 bytes each, 24 MB)
+constexpr int64_t kQueueEntries = 2 << 20;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -128,11 +130,15 @@ extern "C" int apss_join_device_noalloc(apss_index* ix, float t, uint32_t* out_i
   if ((rc = scratch_on(dev, &base))) return rc;
 
   const QuerySet Q{ix->rows.rp.p, ix->rows.rc.p, ix->rows.mw.p, ix->n, ix->nnz, ix->rows.rp_host.data()};
+  const bool pairs = use_pairs(ix);
   JoinLayout L;
-  if ((rc = plan_layout(ix, Q, 1, L))) return rc;
-  const size_t fixed = Carve::bytes<unsigned long long>(C_NUM) + Carve::bytes<unsigned int>(8) +
+  // the list-pair kernels need no tiles, queues or cursors, but a survivor queue
+  const int64_t qcap = pairs ? std::min<int64_t>(kQueueEntries, pair_queue_entries(ix)) : 0;
+  if (pairs) L.cum.assign(1, 0);
+  else if ((rc = plan_layout(ix, Q, 1, L))) return rc;
+  const size_t fixed = Carve::bytes<unsigned long long>(C_NUM) + Carve::bytes<unsigned int>(kQueueCounters) +
                        Carve::bytes<int64_t>(L.ntiles + 1) + Carve::bytes<int64_t>((int64_t)L.cum.size()) +
-                       Carve::bytes<uint32_t>((int64_t)L.G * L.wg_stride);
+                       Carve::bytes<uint32_t>((int64_t)L.G * L.wg_stride) + Carve::bytes<uint32_t>(3 * qcap);
   if (fixed + pair_bytes(0) > kScratchBytes) {
     set_error("the join's work queues need %zu bytes of scratch; the allocation-free path holds %zu", fixed,
               kScratchBytes);
@@ -145,10 +151,11 @@ extern "C" int apss_join_device_noalloc(apss_index* ix, float t, uint32_t* out_i
 
   Carve cv{base};
   unsigned long long* counters = cv.take<unsigned long long>(C_NUM);
-  unsigned int* qctr = cv.take<unsigned int>(8);
+  unsigned int* qctr = cv.take<unsigned int>(kQueueCounters);
   int64_t* tstart = cv.take<int64_t>(L.ntiles + 1);
   int64_t* qcum = cv.take<int64_t>((int64_t)L.cum.size());
   uint32_t* wg_cur = cv.take<uint32_t>((int64_t)L.G * L.wg_stride);
+  uint32_t* queue = cv.take<uint32_t>(3 * qcap);
   uint64_t* raw_key = cv.take<uint64_t>(room);
   float* raw_sim = cv.take<float>(room);
   uint64_t* k2 = cv.take<uint64_t>(room);
@@ -161,24 +168,18 @@ extern "C" int apss_join_device_noalloc(apss_index* ix, float t, uint32_t* out_i
   }
 
   APSS_CHK(hipEventRecord(ws.ev[0], s), "event");
-  APSS_CHK(hipMemcpyAsync(tstart, L.tiles.start.data(), sizeof(int64_t) * (L.ntiles + 1), hipMemcpyHostToDevice, s),
-           "tiles");
-  APSS_CHK(hipMemcpyAsync(qcum, L.cum.data(), sizeof(int64_t) * L.cum.size(), hipMemcpyHostToDevice, s), "queues");
+  if (!pairs) {
+    APSS_CHK(hipMemcpyAsync(tstart, L.tiles.start.data(), sizeof(int64_t) * (L.ntiles + 1), hipMemcpyHostToDevice, s),
+             "tiles");
+    APSS_CHK(hipMemcpyAsync(qcum, L.cum.data(), sizeof(int64_t) * L.cum.size(), hipMemcpyHostToDevice, s), "queues");
+  }
   // the array keeps the previous call's contents: clear what starts at zero
   APSS_CHK(fill_u64((uint64_t*)counters, 0ull, C_NUM, s), "fill");
-  APSS_CHK(fill_u32(qctr, 0u, 8, s), "fill");
   JoinPlan P;
-  bind_plan(ix, Q, 1, t, nullptr, nullptr, L, tstart, qcum, qctr, wg_cur, P);
-  P.a.out_key = raw_key;
-  P.a.out_sim = raw_sim;
-  P.a.cap = room;
-  P.a.counters = counters;
-  if (!join_args_complete(P.a)) {
-    set_error("internal: join launched with a missing device buffer");
-    return APSS_EDEVICE;
-  }
+  if (pairs) bind_pairs(ix, t, qctr, queue, qcap, P);
+  else bind_plan(ix, Q, 1, t, nullptr, nullptr, L, tstart, qcum, qctr, wg_cur, P);
   APSS_CHK(hipEventRecord(ws.ev[1], s), "event");
-  APSS_CHK(launch_join(P.a, P.variant, P.G, s), "join kernel");
+  if ((rc = launch_plan(P, raw_key, raw_sim, room, counters, qctr, s))) return rc;
   APSS_CHK(hipEventRecord(ws.ev[2], s), "event");
   unsigned long long c[C_NUM];
   APSS_CHK(hipMemcpyAsync(c, counters, sizeof(c), hipMemcpyDeviceToHost, s), "read counters");

@@ -1,0 +1,115 @@
+// Launchers of the list-pair join (pairs.hip): the self-join by pairs of
+// list entries under a row-sketch bound, and the exact candidate count.
+#pragma once
+
+#include "apss_internal.h"
+
+namespace apss {
+
+// A row's sketch: its norm in each of kSkGroups groups of consecutive ranks,
+// in units of 1 / kSkScale rounded up (at most 127 for rows of norm up to
+// 1.0079; validated norms are within 1e-5 of 1).
+constexpr int kSkGroups = 128;
+constexpr double kSkScale = 126.0;
+// rows longer than kFineRow also have a sketch of kFineGroups groups
+constexpr int kFineGroups = 1024;
+constexpr int kFineRow = 256;
+// Work units of the pair tests: lists of at least kWideList entries by
+// workgroups, in blocks of kWideRows entries against at most kWideSpan blocks
+// at a time; shorter lists by waves, in blocks of kUnitRows entries, which a
+// wave takes up to kShortUnits at a time.
+constexpr int kWideList = 256;
+constexpr int kWideRows = 256;
+constexpr int kWideSpan = 16;
+constexpr int kUnitRows = 64;
+constexpr int kShortUnits = 16;
+// The candidate count: corpus rows per block, and the densest ranks with a
+// bitmap per block (one bit per row whose indexed part holds the rank).
+constexpr int kCountRows = 4096;
+constexpr int kCountWords = kCountRows / 32;
+constexpr int kCountRanks = 2048;
+
+struct PairArgs {
+  const int64_t* rp;      // [n+1] row offsets of the rank-space rows
+  const RComp* rc;        // components, densest dimension first
+  const uint8_t* sk;      // [n * kSkGroups] sketches
+  const uint16_t* gid;    // [m] fine group of each rank (its group: an eighth of that)
+  const uint32_t* fidx;   // [n] index of the row's fine sketch (long rows only)
+  const uint8_t* fsk;     // fine sketches
+  const uint32_t* dl;     // deep lists: vector ids, by rank, ascending within a rank
+  const int64_t* doff;    // [m+1] first entry of each rank's deep list
+  const uint2* wide;      // [nwide] (rank, unit of its list)
+  const uint2* shorts;    // [nshort]
+  int64_t nwide, nshort;
+  int64_t sample;         // > 0: test every sample-th unit (group of short units) only and just count
+                          // the visits and survivors; 0: the join
+  int32_t sstep;          // short units a wave takes at a time (at most kShortUnits)
+  unsigned int* uctr;     // [3] next wide unit, next short units, queued survivors (zero at launch)
+  uint32_t* queue;        // [3 * qcap] survivors to decide: two row ids and the list's rank
+  int64_t qcap;
+  float t;
+  int32_t thr;            // least sketch product of a pair that can reach t
+  int32_t bj;
+  uint64_t* out_key;      // [cap] (i << bj) | j
+  float* out_sim;         // [cap]
+  int64_t cap;
+  unsigned long long* counters;  // [C_NUM]
+};
+
+// Exact number of (query, earlier corpus row) pairs that share a dimension of
+// the row's indexed part.
+struct CountArgs {
+  const int64_t* rp;      // [n+1] query rows in rank space
+  const RComp* rc;
+  int64_t nq;
+  int32_t triangle;       // 1: query q meets corpus rows y < q only
+  const uint32_t* bm;     // [nblk * HB * kCountWords] bitmaps of ranks below HB
+  int32_t HB;
+  int64_t n;              // corpus rows
+  int64_t nblk;           // blocks of kCountRows corpus rows
+  const Post* post;       // list entries
+  const uint32_t* post4;  // their packed copy
+  const uint2* seg;       // [nblk * H] {first entry, end} of list r < H in block b
+  int32_t H;
+  const uint32_t* toff;   // [(nR+1) * m_tail] first entry of list H + rt at or after range R of rr rows
+  int32_t m_tail;
+  int64_t rr, nR;
+  const uint32_t* present;  // [nblk * present_words] bit r - H of a block: rank r >= H has an entry there
+  int64_t present_words;
+  int64_t chunk;          // queries per work item
+  unsigned long long* counters;
+};
+
+int32_t pair_threshold(float t);
+
+// gid[r] from the cumulative component counts by rank (exclusive scan cum[m], total nnz)
+hipError_t launch_groups(const int64_t* cum, const uint32_t* cnt_r, int64_t m, int64_t nnz, uint16_t* gid, hipStream_t s);
+// *out (zeroed before) = list entries an accumulating self-join visits
+hipError_t launch_visits(const uint32_t* cnt_r, const int64_t* off, int64_t m, unsigned long long* out, hipStream_t s);
+hipError_t launch_widen(const uint32_t* in, int64_t n, int64_t* out, hipStream_t s);
+// nfine: a zeroed counter; fsk: room for every row longer than kFineRow
+hipError_t launch_sketch(const int64_t* rp, const RComp* rc, const uint16_t* gid, int64_t n, uint8_t* sk,
+                         unsigned int* nfine, uint32_t* fidx, uint8_t* fsk, hipStream_t s);
+// units per rank of its deep list, as int64 for the scan, and the units
+hipError_t launch_unit_counts(const int64_t* doff, int64_t m, bool wide, int64_t* ucnt, hipStream_t s);
+hipError_t launch_unit_fill(const int64_t* doff, const int64_t* uoff, int64_t m, bool wide, uint2* units, hipStream_t s);
+hipError_t launch_bitmaps(const Post* post, const uint32_t* hoff, int32_t H, int32_t cb, int64_t nb, int32_t HB,
+                          int64_t nblk, uint32_t* bm, hipStream_t s);
+// Workgroups of the kernels that fit on the device at once.
+struct PairGroups {
+  int wide = 0, shorts = 0, decide = 0;
+};
+PairGroups pairs_resident_groups();
+// The pair tests, then the queued survivors' decisions.  Survivors past
+// a.qcap are decided by the wave that finds them, so any capacity (0 too)
+// gives the whole result.
+// (a.sstep is set here.)
+hipError_t launch_pairs(PairArgs a, const PairGroups& g, hipStream_t s);
+hipError_t launch_segments(const uint32_t* hoff, int32_t H, int32_t cb, int64_t nb, int64_t nblk, uint2* seg,
+                           hipStream_t s);
+// present must be zero before
+hipError_t launch_present(const int64_t* off, const Post* post, int32_t H, int64_t m, int64_t words, uint32_t* present,
+                          hipStream_t s);
+hipError_t launch_count(const CountArgs& a, hipStream_t s);
+
+}  // namespace apss

@@ -22,14 +22,15 @@ __device__ __forceinline__ void two_sum(float a, float b, float& s, float& e) {
   e = __fadd_rn(__fsub_rn(a, __fsub_rn(s, z)), __fsub_rn(b, z));
 }
 
-// Compensated float dot product of row y (ylen components) with the query
-// whose weight in rank r is look(r) (0 when absent).  Same value on every lane.
-template <class Lookup>
-__device__ __forceinline__ float wave_dot2(const RComp* __restrict__ y, int ylen, int lane, Lookup look) {
+// Compensated float dot product of row y (ylen components, the k-th being
+// comp(k)) with the query whose weight in the rank r of component k is
+// look(k, r) (0 when absent).  Same value on every lane.
+template <class Comp, class Lookup>
+__device__ __forceinline__ float wave_dot2_of(Comp comp, int ylen, int lane, Lookup look) {
   float hi = 0.0f, lo = 0.0f;
   for (int k = lane; k < ylen; k += 64) {
-    const RComp c = y[k];
-    const float qv = look(c.r);
+    const RComp c = comp(k);
+    const float qv = look(k, c.r);
     const float p = __fmul_rn(qv, c.w);
     const float ep = __fmaf_rn(qv, c.w, -p);
     float s2, es;
@@ -47,6 +48,12 @@ __device__ __forceinline__ float wave_dot2(const RComp* __restrict__ y, int ylen
     lo = __fadd_rn(__fadd_rn(lo, l2), e2);
   }
   return __fadd_rn(hi, lo);
+}
+
+// The same with the row in memory.
+template <class Lookup>
+__device__ __forceinline__ float wave_dot2(const RComp* __restrict__ y, int ylen, int lane, Lookup look) {
+  return wave_dot2_of([&](int k) { return y[k]; }, ylen, lane, [&](int, int32_t r) { return look(r); });
 }
 
 // The same dot product in double (products of floats are exact in double).
