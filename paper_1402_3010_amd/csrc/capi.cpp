@@ -180,7 +180,9 @@ int stage_csr(hipStream_t s, int64_t n, const int64_t* row_ptr, const int32_t* c
 
 int hoff_slot(int cb) { return cb == 1024 ? 0 : 1; }
 
-int build_lists(apss_index* ix, const uint32_t* cnt_r = nullptr);
+// cnt_r: components of each dimension, by rank (device)
+int build_lists(apss_index* ix, const uint32_t* cnt_r);
+int build_screen(apss_index* ix, int32_t head, const uint32_t* cnt_r);
 
 int build_impl(apss_index* ix, const int64_t* row_ptr, const int32_t* col, const float* val, int on_device) {
   Workspace& ws = ix->ws;
@@ -259,17 +261,23 @@ int build_impl(apss_index* ix, const int64_t* row_ptr, const int32_t* col, const
     if ((rc = sort_rows(ws, ss.k1.p, ss.v32a.p, nnz, nbits + rbits, rbits, ix->rows.rc.p, err))) return rc;
     if ((rc = check_err(s, err, nullptr, "build_index"))) return rc;
   }
-  return build_lists(ix, cnt_r.p);
+  if ((rc = build_lists(ix, cnt_r.p))) return rc;
+  if (ix->opts.screen_dims <= 0) return APSS_OK;
+  return build_screen(ix, (int32_t)std::min<int64_t>(ix->opts.screen_dims, m), cnt_r.p);
 }
 
 // An index whose self-joins may take the list-pair kernels: the default
 // algorithm with no geometry asked for (a tile variant, range width or group
-// given by the caller names the accumulating kernel).
+// given by the caller names the accumulating kernel), and the sparse pass of
+// the screened join (whose geometry is that of the accumulating kernel
+// wherever the cost rule leaves it there).
 bool pairs_eligible(const apss_index* ix) {
   const apss_opts& o = ix->opts;
-  return ix->head_cut == 0 && !o.index_all && o.local_parts <= 1 && !o.remscore && !o.screen_dims && o.variant < 0 &&
-         o.range_rows == 0 && o.range_group == 0 && !getenv("APSS_VARIANT") && !getenv("APSS_RANGE_ROWS") &&
-         !getenv("APSS_RANGE_GROUP") && ix->n > 1 && ix->n <= (1 << 25);  // (a list's units are counted in 32 bits)
+  if (o.index_all || o.local_parts > 1 || o.remscore || o.screen_dims) return false;
+  if (ix->n <= 1 || ix->n > (1 << 25)) return false;  // (a list's units are counted in 32 bits)
+  if (ix->head_cut > 0) return true;
+  return o.variant < 0 && o.range_rows == 0 && o.range_group == 0 && !getenv("APSS_VARIANT") &&
+         !getenv("APSS_RANGE_ROWS") && !getenv("APSS_RANGE_GROUP");
 }
 
 // Sketches, deep lists and work units, from the sorted list values in the
@@ -326,16 +334,18 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r) {
   ix->pair_groups = pairs_resident_groups();
   // The list-pair kernels or the accumulating one, whichever should take
   // less, by their measured rates (MI355X): the accumulating kernel visits
-  // 8e11-1e12 list entries a second (1.0e12 on 100,000 rows of mean 80 at
-  // t = 0.5, 8e11 on 500,000 of mean 120 at 0.7); the list-pair kernels test
-  // 1.5e12 pairs a second, take 1.6 ns per short unit (a wave's), decide a
-  // survivor in 0.45 ns, and count the candidates of a query in a block of
-  // 4,096 rows in 2 ns (mean 120; in proportion to the components).  Those
-  // two workloads took 30 and 490 ms with the one, 13 and 77 ms with the
-  // other.  The survivors are estimated from every k-th unit, and doubled:
-  // on rows that the sketches do not tell apart (flat weights over few
-  // dimensions) they are most pairs, and the accumulating kernel is ahead.
-  // A join at a higher threshold than the index's has fewer.
+  // 1.2e12 list entries and filters 1.1e12 pairs of rows a second; the
+  // list-pair kernels test 1.5e12 pairs a second, take 1.6 ns per short unit
+  // (a wave's), decide a survivor in 0.45 ns, and count the candidates of a
+  // query in a block of 4,096 rows in 2 ns (at 120 components with lists, in
+  // proportion to them).  Measured, accumulating and list pairs: 30 and 13 ms
+  // (100,000 rows of mean 80, t = 0.5), 490 and 77 ms (500,000 of mean 120,
+  // 0.7), 21 and 4 ms (sparse pass of 200,000 of mean 150, 0.8, where 0.28 ns
+  // per posting met count the candidates).  The
+  // survivors are estimated from every k-th unit, and doubled: on rows that
+  // the sketches do not tell apart (flat weights over few dimensions) they
+  // are most pairs, and the accumulating kernel is ahead.  A join at a higher
+  // threshold than the index's has fewer.
   DBuf<unsigned long long> cnt;
   CHK(cnt.alloc(C_NUM), "alloc");
   CHK(ws.qctr.reserve(kQueueCounters), "alloc queues");
@@ -354,8 +364,8 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r) {
   const double k = (double)plan.pa.sample;
   const double blocks = (double)((n + kCountRows - 1) / kCountRows);
   const double pairs_ms = 1e3 * (k * (double)c[C_VISITS] / 1.5e12 + 2.0 * k * (double)c[C_SURVIVORS] * 0.45e-9 +
-                                 (double)ix->nshort * 1.6e-9 + 0.5 * blocks * (double)ix->nnz * (2e-9 / 120.0));
-  const double lists_ms = 1e3 * (double)c[C_TAILVISITS] / 1e12;
+                                 (double)ix->nshort * 1.6e-9 + (ix->head_cut > 0 ? 2.8e-12 * (double)c[C_TAILVISITS] : 0.5 * blocks * (double)ix->P * (2e-9 / 110.0)));
+  const double lists_ms = 1e3 * ((double)c[C_TAILVISITS] / 1.2e12 + 0.5 * (double)n * (double)n / 1.1e12);
   // (up to one block of rows launches and waits are most of either: 0.24 ms
   // against 0.27 ms for 2,000 rows, so there only many survivors decide)
   const bool few = k * (double)c[C_SURVIVORS] <= 64.0 * (double)n;
@@ -378,7 +388,8 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r) {
 int build_bitmaps(apss_index* ix) {
   const int slot = ix->hoff[0].p ? 0 : 1;
   const int cb = slot == 0 ? 1024 : 2048;
-  ix->count_ranks = std::min<int32_t>(kCountRanks, ix->H);
+  // (the head-cut index of the screened join has no dense lists)
+  ix->count_ranks = ix->head_cut > 0 ? 0 : std::min<int32_t>(kCountRanks, ix->H);
   ix->count_blocks = (ix->n + kCountRows - 1) / kCountRows;
   CHK(ix->bm.alloc(ix->count_blocks * ix->count_ranks * kCountWords), "alloc");
   CHK(ix->seg.alloc(ix->count_blocks * ix->H), "alloc");
@@ -445,7 +456,7 @@ int build_lists(apss_index* ix, const uint32_t* cnt_r) {
   CHK(ss.v64b.reserve(P), "alloc");
   CHK(ss.hist.reserve(radix_hist_elems(P)), "alloc");
   CHK(ss.scan.reserve(radix_scan_tmp_elems(P)), "alloc");
-  const bool pairs = cnt_r && pairs_eligible(ix) && P > 0;
+  const bool pairs = pairs_eligible(ix) && P > 0;
   // rows may exceed norm 1 by 1e-5, and the scan rounds: 1e-4 covers both
   const double lim = pairs ? (double)ix->t_build * (double)ix->t_build * (1.0 - 1e-4) : -1.0;
   CHK(launch_emit_indexed(ix->rows.rp.p, ix->rows.rc.p, ix->rs.p, nidx.p, n, lim, ss.k1.p, ss.v64a.p, s), "emit");
@@ -514,7 +525,7 @@ int copy_buf(DBuf<T>& dst, const DBuf<T>& src, int64_t count, hipStream_t s) {
 
 // The head-cut index of the screened join: the same rank-space rows, with
 // every row's unindexed part set to its components of rank < head.
-int build_screen(apss_index* ix, int32_t head) {
+int build_screen(apss_index* ix, int32_t head, const uint32_t* cnt_r) {
   apss_index* sx = new (std::nothrow) apss_index();
   if (!sx) {
     set_error("host allocation failed");
@@ -542,7 +553,7 @@ int build_screen(apss_index* ix, int32_t head) {
   if ((rc = copy_buf(sx->rows.rc, ix->rows.rc, ix->nnz, s))) return rc;
   if ((rc = copy_buf(sx->mw_r, ix->mw_r, ix->m, s))) return rc;
   CHK(sx->rows.mw.alloc(ix->n), "alloc");
-  return build_lists(sx);
+  return build_lists(sx, cnt_r);
 }
 
 // Query tiles: consecutive queries, at most QT of them and, unless a single
@@ -767,10 +778,12 @@ void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue
   CountArgs& c = P.ca;
   c.rp = ix->rows.rp.p;
   c.rc = ix->rows.rc.p;
+  c.skip = ix->head_cut > 0 ? ix->rs.p : nullptr;
   c.nq = ix->n;
   c.triangle = 1;
   c.bm = ix->bm.p;
   c.HB = ix->count_ranks;
+  c.off = ix->off.p;
   c.n = ix->n;
   c.nblk = ix->count_blocks;
   c.post = ix->post.p;
@@ -1501,7 +1514,6 @@ int apss_build_index(int64_t n, int64_t m, const int64_t* row_ptr, const int32_t
     return APSS_EINVAL;
   }
   int rc = build_impl(ix, row_ptr, col, val, on_device);
-  if (!rc && o.screen_dims > 0) rc = build_screen(ix, (int32_t)std::min<int64_t>(o.screen_dims, m));
   // the join's lookup tables for the index's geometry and the call timers
   // exist from here on, so apss_join_device_noalloc needs no allocation
   if (!rc && o.screen_dims == 0 && n > 0) rc = prepare(ix, ix->ws.stream, ix->variant, ix->range_rows);

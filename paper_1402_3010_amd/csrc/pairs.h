@@ -26,6 +26,9 @@ constexpr int kShortUnits = 16;
 // The candidate count: corpus rows per block, and the densest ranks with a
 // bitmap per block (one bit per row whose indexed part holds the rank).
 constexpr int kCountRows = 4096;
+// rows whose bits a workgroup holds in LDS when there are no dense lists
+// (just under 64 KB)
+constexpr int kCountSpan = 516096;
 constexpr int kCountWords = kCountRows / 32;
 constexpr int kCountRanks = 2048;
 
@@ -61,10 +64,12 @@ struct PairArgs {
 struct CountArgs {
   const int64_t* rp;      // [n+1] query rows in rank space
   const RComp* rc;
+  const RowStat* skip;    // [nq] or NULL: the first skip[q].cut components of query q have no lists
   int64_t nq;
   int32_t triangle;       // 1: query q meets corpus rows y < q only
   const uint32_t* bm;     // [nblk * HB * kCountWords] bitmaps of ranks below HB
-  int32_t HB;
+  int32_t HB;             // 0: every list is sparse
+  const int64_t* off;     // [m+1] list offsets by rank
   int64_t n;              // corpus rows
   int64_t nblk;           // blocks of kCountRows corpus rows
   const Post* post;       // list entries

@@ -105,14 +105,14 @@ int time_config(apss_index* ix, apss_index* target, float t, int variant, long l
   int64_t cnt = 0;
   // what is tuned is the accumulating kernel, which queries and the other
   // algorithms take also where self-joins take the list-pair kernels
-  const bool off = ix->pairs_off;
-  ix->pairs_off = true;
+  const bool off = target->pairs_off;
+  target->pairs_off = true;
   int rc = ix->screen ? run_screen_join(ix, ix->ws, t, 16 * ix->n, &cnt)
                       : run_join(ix, ix->ws,
                                  QuerySet{ix->rows.rp.p, ix->rows.rc.p, ix->rows.mw.p, ix->n, ix->nnz,
                                           ix->rows.rp_host.data()},
                                  1, t, nullptr, 16 * ix->n, &cnt);
-  ix->pairs_off = off;
+  target->pairs_off = off;
   if (rc) return rc;
   *ms = ix->ws.last.ms_candidates;
   return APSS_OK;

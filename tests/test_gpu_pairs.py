@@ -142,3 +142,21 @@ def test_flat_rows_over_few_dimensions_keep_the_accumulating_kernel():
     (a, sa), (b, sb) = join(V, t), join(V, t, variant=1)
     assert all(np.array_equal(x, y) for x, y in zip(a, b))
     assert sa["candidates"] == sb["candidates"] and sa["posting_visits"] == sb["posting_visits"]
+
+
+@pytest.mark.parametrize("n,head", [(3000, 64), (20000, 256), (30001, 4096)])
+def test_sparse_pass_of_the_screened_join(n, head):
+    # pairs that share a dimension past the head, by list pairs and by the accumulating kernel: same pairs, and the
+    # same count of pairs that share one
+    V = make_corpus(spec_for("c4", n=n))
+    t = np.float32(0.6)
+    (a, sa), (b, sb) = join(V, t, pairs=True, screen_dims=head), join(V, t, variant=1)
+    for x, y in zip(a, b):
+        assert np.array_equal(np.asarray(x).view(np.uint32), np.asarray(y).view(np.uint32))
+    rank, _, _ = oracle.prefix_index(V, t)
+    import scipy.sparse as sp
+    tail = rank[V.col] >= head
+    row = np.repeat(np.arange(V.n), np.diff(V.row_ptr))[tail]
+    A = sp.csr_matrix((np.ones(len(row), np.int32), (row, V.col[tail])), shape=(V.n, V.m))
+    shared = (A @ A.T).tocsr()
+    assert sa["candidates"] == (shared.nnz - np.count_nonzero(shared.diagonal())) // 2
