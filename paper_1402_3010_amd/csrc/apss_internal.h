@@ -46,6 +46,7 @@ enum Counter {
   C_BAND,
   C_MATCHES,   // pairs emitted (may exceed the output capacity)
   C_TAILVISITS,
+  C_OVERFLOW,  // 1: a batch's sketch survivors outgrew their queue
   C_NUM = 8
 };
 

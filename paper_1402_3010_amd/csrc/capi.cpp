@@ -311,12 +311,14 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r) {
   CHK(launch_groups(tiles.p, cnt_r, m, ix->nnz, ix->gid.p, s), "groups");
   int64_t longs = 0;
   for (int64_t r = 0; r < n; ++r) longs += ix->rows.rp_host[(size_t)r + 1] - ix->rows.rp_host[(size_t)r] > kFineRow;
+  CHK(ix->mid.alloc(n * kMidGroups), "alloc");
   CHK(ix->fidx.alloc(n), "alloc");
   CHK(ix->fsk.alloc(longs * kFineGroups), "alloc");
   DBuf<unsigned int> nfine;
   CHK(nfine.alloc(1), "alloc");
   CHK(fill_u32(nfine.p, 0u, 1, s), "fill");
-  CHK(launch_sketch(ix->rows.rp.p, ix->rows.rc.p, ix->gid.p, n, ix->sk.p, nfine.p, ix->fidx.p, ix->fsk.p, s), "sketches");
+  CHK(launch_sketch(ix->rows.rp.p, ix->rows.rc.p, ix->gid.p, n, ix->sk.p, ix->mid.p, nfine.p, ix->fidx.p,
+                    ix->fsk.p, s), "sketches");
   // work units by rank
   DBuf<int64_t> stiles;
   CHK(stiles.alloc(m + 1), "alloc");
@@ -347,9 +349,9 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r) {
   // are most pairs, and the accumulating kernel is ahead.  A join at a higher
   // threshold than the index's has fewer.
   DBuf<unsigned long long> cnt;
-  CHK(cnt.alloc(C_NUM), "alloc");
+  CHK(cnt.alloc(C_NUM + kRateBins), "alloc");
   CHK(ws.qctr.reserve(kQueueCounters), "alloc queues");
-  CHK(fill_u64((uint64_t*)cnt.p, 0ull, C_NUM, s), "fill");
+  CHK(fill_u64((uint64_t*)cnt.p, 0ull, C_NUM + kRateBins, s), "fill");
   CHK(fill_u32(ws.qctr.p, 0u, kQueueCounters, s), "fill");
   JoinPlan plan;
   bind_pairs(ix, ix->t_build, ws.qctr.p, nullptr, 0, plan);
@@ -358,7 +360,19 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r) {
   plan.pa.sample = std::max<int64_t>(1, units / 4096);
   CHK(launch_pairs(plan.pa, plan.pg, s), "sample");
   CHK(launch_visits(cnt_r, ix->off.p, m, cnt.p + C_TAILVISITS, s), "sample");
-  unsigned long long c[C_NUM];
+  // ... and for queries the survivors among about 2^24 pairs of rows
+  plan.qa.sk = ix->mid.p;
+  plan.qa.n = n;
+  plan.qa.qsk = ix->mid.p;
+  plan.qa.nq = std::min<int64_t>(n, 1024);
+  plan.qa.qstride = n / plan.qa.nq;
+  plan.qa.t = ix->t_build;
+  PairArgs qsample = plan.pa;
+  qsample.counters = cnt.p + C_NUM;
+  qsample.sample = std::max<int64_t>(1, n / kWideRows / 64);
+  CHK(launch_query_sample(qsample, plan.qa, s), "sample");
+  unsigned long long c[C_NUM + kRateBins];
+  const unsigned long long* const qc = c + C_NUM;
   CHK(hipMemcpyAsync(c, cnt.p, sizeof(c), hipMemcpyDeviceToHost, s), "sample");
   CHK(hipStreamSynchronize(s), "sample");
   const double k = (double)plan.pa.sample;
@@ -371,15 +385,36 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r) {
   const bool few = k * (double)c[C_SURVIVORS] <= 64.0 * (double)n;
   ix->pairs_ready = n <= kCountRows ? few : pairs_ms < lists_ms;
   if (ix->opts.reserved[0] == kProbePairs) ix->pairs_ready = true;
+  // Queries, per pair of a query and a row: 0.32 ps for the test and 0.49 for
+  // the count at 110 indexed components a row, against 0.9 and 0.83 per list
+  // entry; 1.2 ns per survivor (4,096 queries of mean 100 over 1,000,000
+  // rows: 6.0 ms against 16.1 ms by the accumulating kernel).  The survivors
+  // are known when the thresholds are; the tables are kept if the kernels
+  // would win halfway between t_build and 1.
+  const double rows2 = (double)n * (double)n;
+  const int64_t qrows = std::min<int64_t>(n, ((n + kWideRows * qsample.sample - 1) / (kWideRows * qsample.sample)) * kWideRows);
+  double reach = 0.0;
+  for (int b = kRateBins - 1; b >= 0; --b) {
+    reach += (double)qc[b];
+    ix->rate[b] = reach / ((double)plan.qa.nq * (double)qrows);
+  }
+  ix->screen_ps = 0.32 + 0.49 * (double)ix->P / (110.0 * (double)n);
+  ix->accumulate_ps = 0.9 + 0.83 * 2.0 * (double)c[C_TAILVISITS] / rows2;
+  ix->screen_queries = ix->head_cut == 0 && ix->opts.query_safe &&
+                       (ix->screen_ps + kSurvivorPs * ix->rate[kRateBins / 2] < ix->accumulate_ps ||
+                        ix->opts.reserved[0] == kProbePairs);
   if (!ix->pairs_ready) {
     ix->sk.release();
-    ix->fsk.release();
-    ix->gid.release();
-    ix->fidx.release();
     ix->dl.release();
     ix->doff.release();
     ix->wide.release();
     ix->shorts.release();
+  }
+  if (!ix->screen_queries) ix->mid.release();
+  if (!ix->pairs_ready && !ix->screen_queries) {
+    ix->fsk.release();
+    ix->gid.release();
+    ix->fidx.release();
   }
   return APSS_OK;
 }
@@ -504,7 +539,7 @@ int build_lists(apss_index* ix, const uint32_t* cnt_r) {
   if (H > m) H = (int32_t)m;
   ix->H = H;
   if ((rc = prepare(ix, s, ix->variant, ix->range_rows))) return rc;
-  if (ix->pairs_ready && (rc = build_bitmaps(ix))) return rc;
+  if ((ix->pairs_ready || ix->screen_queries) && (rc = build_bitmaps(ix))) return rc;
   CHK(hipStreamSynchronize(s), "build_index");
   // sort scratch is re-grown on demand by the joins
   ss.k1.release();
@@ -750,37 +785,9 @@ int64_t pair_queue_entries(const apss_index* ix) {
   return std::max<int64_t>(1 << 20, std::min<int64_t>(256 * ix->n, 64ll << 20));
 }
 
-void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue_dev, int64_t qcap, JoinPlan& P) {
-  P = JoinPlan{};
-  P.pairs = true;
-  P.bj = ceil_log2((uint64_t)ix->n);
-  P.bi = P.bj;
-  P.pg = ix->pair_groups;
-  PairArgs& a = P.pa;
-  a.rp = ix->rows.rp.p;
-  a.rc = ix->rows.rc.p;
-  a.sk = ix->sk.p;
-  a.gid = ix->gid.p;
-  a.fidx = ix->fidx.p;
-  a.fsk = ix->fsk.p;
-  a.dl = ix->dl.p;
-  a.doff = ix->doff.p;
-  a.wide = ix->wide.p;
-  a.shorts = ix->shorts.p;
-  a.nwide = ix->nwide;
-  a.nshort = ix->nshort;
-  a.uctr = uctr_dev;
-  a.queue = queue_dev;
-  a.qcap = qcap;
-  a.t = t;
-  a.thr = pair_threshold(t);
-  a.bj = P.bj;
-  CountArgs& c = P.ca;
-  c.rp = ix->rows.rp.p;
-  c.rc = ix->rows.rc.p;
-  c.skip = ix->head_cut > 0 ? ix->rs.p : nullptr;
-  c.nq = ix->n;
-  c.triangle = 1;
+// The index's part of a candidate count.
+void bind_count(apss_index* ix, CountArgs& c) {
+  c = CountArgs{};
   c.bm = ix->bm.p;
   c.HB = ix->count_ranks;
   c.off = ix->off.p;
@@ -796,9 +803,110 @@ void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue
   c.nR = ix->toff_nR;
   c.present = ix->present.p;
   c.present_words = ix->present_words;
+  c.lds_ranks = kLdsRanks;
+}
+
+void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue_dev, int64_t qcap, JoinPlan& P) {
+  P = JoinPlan{};
+  P.pairs = true;
+  P.bj = ceil_log2((uint64_t)ix->n);
+  P.bi = P.bj;
+  P.pg = ix->pair_groups;
+  PairArgs& a = P.pa;
+  a.rp = ix->rows.rp.p;
+  a.rc = ix->rows.rc.p;
+  a.sk = ix->sk.p;
+  a.gid = ix->gid.p;
+  a.fidx = ix->fidx.p;
+  a.fsk = ix->fsk.p;
+  a.qrp = a.rp;
+  a.qrc = a.rc;
+  a.qfidx = a.fidx;
+  a.qfsk = a.fsk;
+  a.dl = ix->dl.p;
+  a.doff = ix->doff.p;
+  a.wide = ix->wide.p;
+  a.shorts = ix->shorts.p;
+  a.nwide = ix->nwide;
+  a.nshort = ix->nshort;
+  a.uctr = uctr_dev;
+  a.queue = queue_dev;
+  a.qcap = qcap;
+  a.t = t;
+  a.thr = pair_threshold(t);
+  a.bj = P.bj;
+  bind_count(ix, P.ca);
+  CountArgs& c = P.ca;
+  c.rp = a.rp;
+  c.rc = a.rc;
+  c.skip = ix->head_cut > 0 ? ix->rs.p : nullptr;
+  c.nq = ix->n;
+  c.triangle = 1;
   // about eight work items per compute unit, of at least a few queries per wave
   const int64_t want = ix->n * ix->count_blocks / 2 / 2048;
   c.chunk = std::max<int64_t>(64, std::min<int64_t>(4096, (want + 63) / 64 * 64));
+}
+
+// Share of a query's pairs expected to survive the sketch test at t.
+double survivor_rate(const apss_index* ix, float t) {
+  const int32_t lo = pair_threshold(ix->t_build), hi = pair_threshold(1.0f);
+  const int b = (int)((double)(pair_threshold(t) - lo) * kRateBins / (double)(hi - lo + 1));
+  return ix->rate[std::max(0, std::min(kRateBins - 1, b))];
+}
+
+// Sketches of the query rows, and the plan of testing them against the corpus.
+int plan_queries(apss_index* ix, Workspace& ws, const QuerySet& Q, float t, const float* qt_dev, JoinPlan& P) {
+  hipStream_t s = ws.stream;
+  int64_t longs = 0;
+  for (int64_t q = 0; q < Q.n; ++q) longs += Q.rp_host[q + 1] - Q.rp_host[q] > kFineRow;
+  CHK(ws.q_mid.reserve(Q.n * kMidGroups), "alloc sketches");
+  CHK(ws.q_fidx.reserve(Q.n), "alloc sketches");
+  CHK(ws.q_fsk.reserve(longs * kFineGroups), "alloc sketches");
+  CHK(ws.q_nfine.reserve(1), "alloc sketches");
+  CHK(fill_u32(ws.q_nfine.p, 0u, 1, s), "fill");
+  CHK(launch_sketch(Q.rp, Q.rc, ix->gid.p, Q.n, nullptr, ws.q_mid.p, ws.q_nfine.p, ws.q_fidx.p, ws.q_fsk.p, s),
+      "sketches");
+  CHK(ws.qctr.reserve(kQueueCounters), "alloc queues");
+  CHK(ws.counters.reserve(C_NUM), "alloc counters");
+  P = JoinPlan{};
+  P.query = true;
+  P.bj = ceil_log2((uint64_t)ix->n);
+  P.bi = ceil_log2((uint64_t)Q.n);
+  P.pg = ix->pair_groups;
+  PairArgs& a = P.pa;
+  a.rp = ix->rows.rp.p;
+  a.rc = ix->rows.rc.p;
+  a.gid = ix->gid.p;
+  a.fidx = ix->fidx.p;
+  a.fsk = ix->fsk.p;
+  a.query = 1;
+  a.qrp = Q.rp;
+  a.qrc = Q.rc;
+  a.qfidx = ws.q_fidx.p;
+  a.qfsk = ws.q_fsk.p;
+  a.qt = qt_dev;
+  a.uctr = ws.qctr.p;
+  a.t = t;
+  a.bj = P.bj;
+  QueryArgs& q = P.qa;
+  q.sk = ix->mid.p;
+  q.n = ix->n;
+  q.qsk = ws.q_mid.p;
+  q.nq = Q.n;
+  q.qstride = 1;
+  q.qt = qt_dev;
+  q.t = t;
+  bind_count(ix, P.ca);
+  CountArgs& c = P.ca;
+  c.rp = Q.rp;
+  c.rc = Q.rc;
+  c.nq = Q.n;
+  // a few work items per compute unit; a chunk of few queries reads the
+  // bitmaps it needs from L2 instead of loading LDS with all of them
+  const int64_t want = Q.n * ix->count_blocks / 1024;
+  c.chunk = std::max<int64_t>(16, std::min<int64_t>(4096, (want + 15) / 16 * 16));
+  if (c.chunk < 64) c.lds_ranks = 0;
+  return APSS_OK;
 }
 
 int launch_plan(JoinPlan& P, uint64_t* out_key, float* out_sim, int64_t cap, unsigned long long* counters,
@@ -812,6 +920,22 @@ int launch_plan(JoinPlan& P, uint64_t* out_key, float* out_sim, int64_t cap, uns
     P.ca.counters = counters;
     CHK(launch_count(P.ca, s), "count kernel");
     CHK(launch_pairs(P.pa, P.pg, s), "pair kernel");
+    return APSS_OK;
+  }
+  if (P.query) {
+    P.pa.out_key = out_key;
+    P.pa.out_sim = out_sim;
+    P.pa.cap = cap;
+    P.pa.counters = counters;
+    P.ca.counters = counters;
+    CHK(launch_count(P.ca, s), "count kernel");
+    for (size_t r = 0; r < P.qend.size(); ++r) {
+      if (r > 0) CHK(fill_u32(qctr, 0u, kQueueCounters, s), "fill");
+      QueryArgs q = P.qa;
+      q.q0 = r > 0 ? P.qend[r - 1] : 0;
+      q.nq = P.qend[r];
+      CHK(launch_query_screen(P.pa, q, P.pg, s), "query kernel");
+    }
     return APSS_OK;
   }
   JoinArgs& a = P.a;
@@ -876,15 +1000,58 @@ int start_call(Workspace& ws, bool keep_graph = false) {
 }
 
 int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, float t, const float* qt_dev,
-             int64_t cap_hint, int64_t* count) {
+             int64_t cap_hint, int64_t* count, const float* t_host) {
   hipStream_t s = ws.stream;
   *count = 0;
   int rc = start_call(ws);
   if (rc) return rc;
   if (Q.n == 0 || ix->n == 0) return APSS_OK;
   JoinPlan P;
-  if ((rc = plan_join(ix, ws, Q, triangle, t, qt_dev, nullptr, P))) return rc;
-  if ((rc = ensure_pair_capacity(ws, cap_hint))) return rc;
+  // A batch of queries takes the sketch kernels when they are expected to be
+  // ahead at its thresholds, and again the accumulating kernel if more pairs
+  // survive than the queue was sized for (twice those of the corpus's own
+  // rows).
+  bool screen = !triangle && ix->screen_queries && !ix->pairs_off && Q.n >= kScreenQueries;
+  if (screen) {
+    double survivors = 0.0;
+    for (int64_t q = 0; q < Q.n; ++q) survivors += survivor_rate(ix, t_host ? t_host[q] : t) * (double)ix->n;
+    screen = ix->opts.reserved[0] == kProbePairs ||
+             (double)Q.n * (double)ix->n * ix->screen_ps + kSurvivorPs * survivors <
+                 (double)Q.n * (double)ix->n * ix->accumulate_ps;
+    if (screen) {
+      if ((rc = ensure_pair_capacity(ws, cap_hint))) return rc;
+      if ((rc = plan_queries(ix, ws, Q, t, qt_dev, P))) return rc;
+      // survivor queue: in a server's slot the pair sort's second keys (part
+      // of the batch's reservation, free until the sort), else its own buffer
+      if (ws.slot) {
+        CHK(ws.ss.k2.reserve(ws.raw_key.n + ws.raw_key.n / 2 + 1), "alloc sort");
+        P.pa.queue = (uint32_t*)ws.ss.k2.p;
+        P.pa.qcap = ws.raw_key.n;
+      } else {
+        const double want = std::min(2.0 * survivors + 65536.0, 16.0 * (1 << 20));
+        CHK(ws.pq.reserve(3 * (int64_t)want), "alloc queues");
+        P.pa.queue = ws.pq.p;
+        P.pa.qcap = ws.pq.n / 3;
+      }
+      // runs of queries whose survivors fit the queue (whole tiles)
+      double held = 0.0;
+      for (int64_t q = 0; q < Q.n; q += kQueryTile) {
+        double tile = 0.0;
+        for (int64_t k = q; k < std::min<int64_t>(q + kQueryTile, Q.n); ++k)
+          tile += 2.0 * survivor_rate(ix, t_host ? t_host[k] : t) * (double)ix->n;
+        if (q > 0 && held + tile > (double)P.pa.qcap) {
+          P.qend.push_back(q);
+          held = 0.0;
+        }
+        held += tile;
+      }
+      P.qend.push_back(Q.n);
+    }
+  }
+  if (!screen) {
+    if ((rc = plan_join(ix, ws, Q, triangle, t, qt_dev, nullptr, P))) return rc;
+    if ((rc = ensure_pair_capacity(ws, cap_hint))) return rc;
+  }
   if (ix->opts.remscore) {
     // each query's first component that admits new candidates (remscore)
     CHK(ws.qadm.reserve(Q.n), "alloc");
@@ -899,6 +1066,13 @@ int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, flo
     unsigned long long c[C_NUM];
     CHK(hipMemcpyAsync(c, ws.counters.p, sizeof(c), hipMemcpyDeviceToHost, s), "read counters");
     CHK(hipStreamSynchronize(s), "join");
+    if (screen && c[C_OVERFLOW]) {
+      screen = false;
+      P = JoinPlan{};
+      if ((rc = plan_join(ix, ws, Q, triangle, t, qt_dev, nullptr, P))) return rc;
+      --attempt;
+      continue;
+    }
     const int64_t matches = (int64_t)c[C_MATCHES];
     if (matches > ws.raw_key.n) {
       if ((rc = ensure_pair_capacity(ws, matches + matches / 8 + 1024))) return rc;
@@ -1580,7 +1754,7 @@ int apss_query_device(apss_index* ix, int64_t nq, const int64_t* q_row_ptr, cons
   int rc = stage_queries(ix, ix->ws, nq, q_row_ptr, q_col, q_val, on_device, t_per_row, t, rows);
   if (rc) return rc;
   int64_t cnt = 0;
-  if ((rc = run_join(ix, ix->ws, staged_queries(rows), 0, t, t_per_row ? ix->ws.qt.p : nullptr, 16 * nq, &cnt)))
+  if ((rc = run_join(ix, ix->ws, staged_queries(rows), 0, t, t_per_row ? ix->ws.qt.p : nullptr, 16 * nq, &cnt, t_per_row)))
     return rc;
   return finish_device(ix->ws, cnt, ceil_log2((uint64_t)ix->n), out_i, out_j, out_sim, capacity, count);
 }
@@ -1598,7 +1772,7 @@ int apss_query(apss_index* ix, int64_t nq, const int64_t* q_row_ptr, const int32
   int rc = stage_queries(ix, ix->ws, nq, q_row_ptr, q_col, q_val, on_device, t_per_row, t, rows);
   if (rc) return rc;
   int64_t cnt = 0;
-  if ((rc = run_join(ix, ix->ws, staged_queries(rows), 0, t, t_per_row ? ix->ws.qt.p : nullptr, 16 * nq, &cnt)))
+  if ((rc = run_join(ix, ix->ws, staged_queries(rows), 0, t, t_per_row ? ix->ws.qt.p : nullptr, 16 * nq, &cnt, t_per_row)))
     return rc;
   return finish_host(ix->ws, cnt, ceil_log2((uint64_t)ix->n), out);
 }

@@ -124,6 +124,11 @@ struct Workspace {
   DBuf<int64_t> tstart, qcum;
   DBuf<unsigned int> qctr;
   DBuf<uint32_t> pq;         // survivor queue of the list-pair join
+  // query sketches
+  DBuf<uint8_t> q_mid, q_fsk;
+  DBuf<uint32_t> q_fidx;
+  DBuf<unsigned int> q_nfine;
+  bool slot = false;  // a server slot's workspace: scratch stays within the batch's reservation
   DBuf<uint32_t> wg_cur;
   DBuf<unsigned long long> counters;
   DBuf<int64_t> uniq_total;  // distinct pairs after a join with local pruning
@@ -153,7 +158,7 @@ struct Workspace {
   }
   int64_t bytes() const {
     return ss.bytes() + tstart.bytes() + qcum.bytes() + qctr.bytes() + wg_cur.bytes() + counters.bytes() +
-           raw_key.bytes() + raw_sim.bytes() + pq.bytes() + qt.bytes() + uniq_total.bytes() + qadm.bytes() + q_col.bytes() + q_val.bytes() + s_keys.bytes() + s_cand.bytes() + s_sid.bytes() +
+           raw_key.bytes() + raw_sim.bytes() + pq.bytes() + q_mid.bytes() + q_fsk.bytes() + q_fidx.bytes() + qt.bytes() + uniq_total.bytes() + qadm.bytes() + q_col.bytes() + q_val.bytes() + s_keys.bytes() + s_cand.bytes() + s_sid.bytes() +
            s_tiles.bytes() + s_nh.bytes() + s_X.bytes();
   }
 };
@@ -188,7 +193,13 @@ struct apss_index {
   // the candidate count's bitmaps; empty unless pairs_ready
   bool pairs_ready = false;
   bool pairs_off = false;  // joins take the accumulating kernel all the same (while it is tuned)
-  apss::DBuf<uint8_t> sk, fsk;
+  bool screen_queries = false;  // batches of queries may take the sketch kernels (they share the tables)
+  // costs of a (query, row) pair in ps: the sketch kernels' without and per
+  // survivor, and the accumulating kernel's; and the share of pairs of corpus
+  // rows that survive at each of kRateBins thresholds from t_build to 1
+  double screen_ps = 0.0, accumulate_ps = 0.0;
+  double rate[apss::kRateBins] = {};
+  apss::DBuf<uint8_t> sk, mid, fsk;
   apss::DBuf<uint16_t> gid;
   apss::DBuf<uint32_t> dl, bm, present, fidx;
   apss::DBuf<int64_t> doff;
@@ -235,8 +246,11 @@ struct JoinLayout {
 // A join kernel launch with every argument but its outputs and counters.
 struct JoinPlan {
   bool pairs = false;  // the list-pair join: pa and ca in place of a
+  bool query = false;  // the sketch test of queries: pa, qa and ca in place of a
   PairArgs pa{};
+  QueryArgs qa{};
   CountArgs ca{};
+  std::vector<int64_t> qend;  // ends of the runs of queries that fill the survivor queue in turn
   JoinArgs a{};
   int variant = 0;
   int G = 0;
@@ -260,6 +274,13 @@ constexpr int kQueueCounters = 8;
 // Test hook outside the ABI: apss_opts.reserved[0] of an index whose self-joins
 // take the list-pair kernels whatever the cost rule says.
 constexpr int32_t kProbePairs = 0x50414952;
+// ps per survivor of the sketch test of a query.
+constexpr double kSurvivorPs = 1200.0;
+// Fewest queries of a call that takes the sketch kernels: they read every
+// row's sketch whatever the batch, 60 us of kernels at 500,000 rows and 20
+// queries; one query's lists are fewer bytes.
+constexpr int64_t kScreenQueries = 2;
+constexpr int64_t kQueryTile = 64;  // queries a workgroup of theirs meets at a time
 // True when a self-join of the index takes the list-pair kernels.
 bool use_pairs(const apss_index* ix);
 // The list-pair self-join's kernel arguments, with 2 unit counters.
@@ -288,7 +309,7 @@ int stage_queries(apss_index* ix, Workspace& ws, int64_t nq, const int64_t* q_ro
 // Run the join kernels; sorted raw pairs in ws.raw_key / ws.raw_sim; count in
 // *count.  cap_hint: pair capacity to start with (grown and rerun on overflow).
 int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, float t, const float* qt_dev,
-             int64_t cap_hint, int64_t* count);
+             int64_t cap_hint, int64_t* count, const float* t_host = nullptr);
 // Tile variants that may be launched.  Variant 3 (4 queries x 2048 rows,
 // 256 threads) faulted on the GPU (memory aperture violation) in two tuning
 // runs on the 500k-vector workloads, intermittently and without an

@@ -11,6 +11,8 @@ namespace apss {
 // 1.0079; validated norms are within 1e-5 of 1).
 constexpr int kSkGroups = 128;
 constexpr double kSkScale = 126.0;
+// the sketch that queries are tested with (halves of those groups)
+constexpr int kMidGroups = 256;
 // rows longer than kFineRow also have a sketch of kFineGroups groups
 constexpr int kFineGroups = 1024;
 constexpr int kFineRow = 256;
@@ -29,6 +31,7 @@ constexpr int kCountRows = 4096;
 // rows whose bits a workgroup holds in LDS when there are no dense lists
 // (just under 64 KB)
 constexpr int kCountSpan = 516096;
+constexpr int kLdsRanks = 128;
 constexpr int kCountWords = kCountRows / 32;
 constexpr int kCountRanks = 2048;
 
@@ -39,6 +42,14 @@ struct PairArgs {
   const uint16_t* gid;    // [m] fine group of each rank (its group: an eighth of that)
   const uint32_t* fidx;   // [n] index of the row's fine sketch (long rows only)
   const uint8_t* fsk;     // fine sketches
+  // the rows of the pairs' second ids: the same rows in a self-join, or the
+  // query rows (query = 1: pairs are a corpus row and a query)
+  int32_t query;
+  const int64_t* qrp;
+  const RComp* qrc;
+  const uint32_t* qfidx;
+  const uint8_t* qfsk;
+  const float* qt;        // [nq] per-query threshold, or NULL: t
   const uint32_t* dl;     // deep lists: vector ids, by rank, ascending within a rank
   const int64_t* doff;    // [m+1] first entry of each rank's deep list
   const uint2* wide;      // [nwide] (rank, unit of its list)
@@ -57,6 +68,16 @@ struct PairArgs {
   float* out_sim;         // [cap]
   int64_t cap;
   unsigned long long* counters;  // [C_NUM]
+};
+
+// Query rows tested against every corpus row.
+struct QueryArgs {
+  const uint8_t* sk;   // [n * kMidGroups] corpus sketches
+  int64_t n;
+  const uint8_t* qsk;  // query q's sketch at row q * qstride
+  int64_t q0, nq, qstride;  // queries q0 .. nq - 1
+  const float* qt;     // [nq] thresholds, or NULL: t
+  float t;
 };
 
 // Exact number of (query, earlier corpus row) pairs that share a dimension of
@@ -82,19 +103,28 @@ struct CountArgs {
   const uint32_t* present;  // [nblk * present_words] bit r - H of a block: rank r >= H has an entry there
   int64_t present_words;
   int64_t chunk;          // queries per work item
+  int32_t lds_ranks;      // densest ranks whose bitmaps go through LDS (at most kLdsRanks)
   unsigned long long* counters;
 };
 
-int32_t pair_threshold(float t);
+// Least sketch product of a pair that can reach t: a pair with sim >= t has a
+// product of at least t * kSkScale^2; the 1e-3 covers the rounding of that
+// many times over.
+__host__ __device__ inline int32_t pair_threshold(float t) {
+  const double v = (double)t * kSkScale * kSkScale - 1e-3;
+  const int32_t k = (int32_t)v;
+  return (double)k < v ? k + 1 : k;
+}
 
 // gid[r] from the cumulative component counts by rank (exclusive scan cum[m], total nnz)
 hipError_t launch_groups(const int64_t* cum, const uint32_t* cnt_r, int64_t m, int64_t nnz, uint16_t* gid, hipStream_t s);
 // *out (zeroed before) = list entries an accumulating self-join visits
 hipError_t launch_visits(const uint32_t* cnt_r, const int64_t* off, int64_t m, unsigned long long* out, hipStream_t s);
 hipError_t launch_widen(const uint32_t* in, int64_t n, int64_t* out, hipStream_t s);
-// nfine: a zeroed counter; fsk: room for every row longer than kFineRow
+// sk (may be NULL), mid and fine sketches of n rows; nfine: a zeroed counter;
+// fsk: room for every row longer than kFineRow
 hipError_t launch_sketch(const int64_t* rp, const RComp* rc, const uint16_t* gid, int64_t n, uint8_t* sk,
-                         unsigned int* nfine, uint32_t* fidx, uint8_t* fsk, hipStream_t s);
+                         uint8_t* mid, unsigned int* nfine, uint32_t* fidx, uint8_t* fsk, hipStream_t s);
 // units per rank of its deep list, as int64 for the scan, and the units
 hipError_t launch_unit_counts(const int64_t* doff, int64_t m, bool wide, int64_t* ucnt, hipStream_t s);
 hipError_t launch_unit_fill(const int64_t* doff, const int64_t* uoff, int64_t m, bool wide, uint2* units, hipStream_t s);
@@ -110,6 +140,13 @@ PairGroups pairs_resident_groups();
 // gives the whole result.
 // (a.sstep is set here.)
 hipError_t launch_pairs(PairArgs a, const PairGroups& g, hipStream_t s);
+// Thresholds that a sample of the sketch products is counted at.
+constexpr int kRateBins = 32;
+// a.counters[k] += pairs with a product in the k-th of kRateBins equal parts
+// of the range from q.t to 1, over every a.sample-th 256 rows
+hipError_t launch_query_sample(const PairArgs& a, const QueryArgs& q, hipStream_t s);
+// Queries against the corpus (a.query = 1), then the survivors' decisions.
+hipError_t launch_query_screen(const PairArgs& a, const QueryArgs& q, const PairGroups& g, hipStream_t s);
 hipError_t launch_segments(const uint32_t* hoff, int32_t H, int32_t cb, int64_t nb, int64_t nblk, uint2* seg,
                            hipStream_t s);
 // present must be zero before

@@ -38,6 +38,10 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+__device__ __forceinline__ float lane_float(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 __global__ void k_groups(const int64_t* __restrict__ cum, const uint32_t* __restrict__ cnt_r, int64_t m, int64_t nnz,
@@ -78,15 +82,16 @@ __device__ __forceinline__ uint32_t norm_code(uint32_t v) {
 
 // Sketches, one wave per row.  Squared weights are summed per group as
 // integers in units of 2^-31, each rounded up, so the sums bound the squared
-// norms from above and do not depend on the order of the LDS atomics.  Rows
-// of more than kFineRow components also get a sketch of kFineGroups groups
-// (each of them an eighth of a group), in the order the waves reach them.
+// norms from above and do not depend on the order of the LDS atomics.  A row
+// has one of kMidGroups groups, one of kSkGroups (pairs of those; sk may be
+// NULL), and if it has more than kFineRow components one of kFineGroups
+// (quarters of those), in the order the waves reach them.
 __global__ __launch_bounds__(256) void k_sketch(const int64_t* __restrict__ rp, const RComp* __restrict__ rc,
                                                 const uint16_t* __restrict__ gid, int64_t n, uint8_t* __restrict__ sk,
-                                                unsigned int* __restrict__ nfine, uint32_t* __restrict__ fidx,
-                                                uint8_t* __restrict__ fsk) {
+                                                uint8_t* __restrict__ mid, unsigned int* __restrict__ nfine,
+                                                uint32_t* __restrict__ fidx, uint8_t* __restrict__ fsk) {
   __shared__ uint32_t acc[4][kFineGroups];
-  constexpr int kRatio = kFineGroups / kSkGroups;
+  static_assert(kFineGroups == 4 * kMidGroups && kMidGroups == 2 * kSkGroups && kMidGroups == 256, "group levels");
   const int lane = (int)(threadIdx.x & 63u);
   uint32_t* const mine = acc[threadIdx.x >> 6];
   for (int g = lane; g < kFineGroups; g += 64) mine[g] = 0u;
@@ -94,33 +99,39 @@ __global__ __launch_bounds__(256) void k_sketch(const int64_t* __restrict__ rp, 
   for (int64_t r = (int64_t)blockIdx.x * 4 + (int64_t)(threadIdx.x >> 6); r < n; r += (int64_t)gridDim.x * 4) {
     const int64_t a = rp[r], b = rp[r + 1];
     const bool fine = b - a > kFineRow;
-    const int shift = fine ? 0 : 3;
-    static_assert(kRatio == 8, "coarse groups");
+    const int shift = fine ? 0 : 2;
     for (int64_t k = a + lane; k < b; k += 64) {
       const RComp c = rc[k];
       atomicAdd(&mine[gid[c.r] >> shift], (uint32_t)ceil((double)c.w * (double)c.w * 2147483648.0));
     }
     wave_lds_order();
-    uint32_t v[2] = {mine[2 * lane], mine[2 * lane + 1]};
+    // lane l holds the mid groups 4 l .. 4 l + 3
+    uint32_t v[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) v[g] = mine[4 * lane + g];
     uint32_t at = 0xFFFFFFFFu;
     if (fine) {
       if (lane == 0) at = atomicAdd(nfine, 1u);
       at = (uint32_t)uni((int)at);
-      // lane l holds the fine groups 16 l .. 16 l + 15: two groups
       uint32_t word[4] = {0u, 0u, 0u, 0u};
-      v[0] = v[1] = 0u;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) v[g] = 0u;
 #pragma unroll
       for (int g = 0; g < 16; ++g) {
         const uint32_t x = mine[16 * lane + g];
-        v[g >> 3] += x;
+        v[g >> 2] += x;
         word[g >> 2] |= norm_code(x) << (8 * (g & 3));
       }
       *reinterpret_cast<uint4*>(fsk + (int64_t)at * kFineGroups + 16 * lane) = make_uint4(word[0], word[1], word[2], word[3]);
     }
     if (lane == 0) fidx[r] = at;
-    *reinterpret_cast<uint16_t*>(sk + r * kSkGroups + 2 * lane) = (uint16_t)(norm_code(v[0]) | (norm_code(v[1]) << 8));
+    *reinterpret_cast<uint32_t*>(mid + r * kMidGroups + 4 * lane) =
+        norm_code(v[0]) | (norm_code(v[1]) << 8) | (norm_code(v[2]) << 16) | (norm_code(v[3]) << 24);
+    if (sk)
+      *reinterpret_cast<uint16_t*>(sk + r * kSkGroups + 2 * lane) =
+          (uint16_t)(norm_code(v[0] + v[1]) | (norm_code(v[2] + v[3]) << 8));
     wave_lds_order();
-    for (int g = lane; g < (fine ? kFineGroups : kSkGroups); g += 64) mine[g] = 0u;
+    for (int g = lane; g < (fine ? kFineGroups : kMidGroups); g += 64) mine[g] = 0u;
     wave_lds_order();
   }
 }
@@ -239,9 +250,19 @@ struct Decided {
   unsigned long long surv = 0, ver = 0, band = 0;  // wave-uniform
 };
 
+// A pair's two rows: y, whose components the lanes take, and q, whose weights
+// are looked up -- the smaller and the larger id of a self-join's pair, or
+// the corpus row and the query, the orientations of the join kernel.
+__device__ __forceinline__ uint32_t pair_y(const PairArgs& a, uint32_t x, uint32_t z) { return a.query || x < z ? x : z; }
+__device__ __forceinline__ uint32_t pair_q(const PairArgs& a, uint32_t x, uint32_t z) { return a.query || x < z ? z : x; }
+__device__ __forceinline__ float pair_t(const PairArgs& a, uint32_t q) { return a.qt ? a.qt[q] : a.t; }
+__device__ __forceinline__ uint64_t pair_key(const PairArgs& a, uint32_t y, uint32_t q) {
+  return a.query ? ((uint64_t)q << a.bj) | (uint64_t)y : ((uint64_t)y << a.bj) | (uint64_t)q;
+}
+
 // Decide `here` (at most 64) pairs, lane l's being (x, z) from the deep list
-// of rank d, one at a time by the whole wave: the larger id's row goes to
-// LDS, the lanes take the smaller id's components and look them up there.
+// of rank d (a query's pairs: past every rank), one at a time by the whole
+// wave: row q goes to LDS, the lanes take y's components and look them up.
 // Row bounds are read for all pairs at once, and the next pair's rows (their
 // first 128 components) are loaded while a pair is decided, so that a pair of
 // ordinary rows costs LDS latencies only; a binary search in global memory
@@ -251,15 +272,16 @@ struct Decided {
 // below t is not summed again.
 __device__ __forceinline__ void decide_pairs(const PairArgs& a, StagedRow& st, int lane, int here, uint32_t x,
                                              uint32_t z, int d, WaveEmit& em, Decided& dc) {
-  // y = the smaller id, q = the larger: the orientation of the join kernel
-  uint32_t y = x < z ? x : z, q = x < z ? z : x;
+  uint32_t y = pair_y(a, x, z), q = pair_q(a, x, z);
   uint32_t ys = 0u, qs = 0u;
   int yl = 0, ql = 0;
+  float tq = 0.0f;
   if (lane < here) {
     ys = (uint32_t)a.rp[y];  // row offsets fit 32 bits (nnz < 2^32)
     yl = (int)((uint32_t)a.rp[y + 1] - ys);
-    qs = (uint32_t)a.rp[q];
-    ql = (int)((uint32_t)a.rp[q + 1] - qs);
+    qs = (uint32_t)a.qrp[q];
+    ql = (int)((uint32_t)a.qrp[q + 1] - qs);
+    tq = pair_t(a, q);
   }
   // two long rows: first the finer sketch bound, two kilobytes in place of
   // rows several times that (flat long rows pass the coarse one with each other)
@@ -269,8 +291,8 @@ __device__ __forceinline__ void decide_pairs(const PairArgs& a, StagedRow& st, i
     int gd = 0;
     if (longs) {
       fy = a.fidx[y];
-      fq = a.fidx[q];
-      gd = a.gid[d];
+      fq = a.qfidx[q];
+      gd = a.query ? kFineGroups - 1 : a.gid[d];
     }
     uint64_t lm = __ballot(longs);
     uint64_t out = 0ull;
@@ -280,14 +302,14 @@ __device__ __forceinline__ void decide_pairs(const PairArgs& a, StagedRow& st, i
       const i32x4 u = *reinterpret_cast<const i32x4*>(
           a.fsk + (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)fy, l) * kFineGroups + 16 * lane);
       const i32x4 w = *reinterpret_cast<const i32x4*>(
-          a.fsk + (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)fq, l) * kFineGroups + 16 * lane);
+          a.qfsk + (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)fq, l) * kFineGroups + 16 * lane);
       const int g = __builtin_amdgcn_readlane(gd, l);
       int dot = 0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) dot = __builtin_amdgcn_sdot4(u[i] & (int)group_mask(16 * lane + 4 * i, g), w[i], dot, false);
 #pragma unroll
       for (int o = 32; o >= 1; o >>= 1) dot += __shfl_xor(dot, o, 64);
-      if (dot < a.thr) out |= 1ull << l;
+      if (dot < pair_threshold(lane_float(tq, l))) out |= 1ull << l;
     }
     if (out) {
       // close up the pairs that are left, in order
@@ -309,15 +331,16 @@ __device__ __forceinline__ void decide_pairs(const PairArgs& a, StagedRow& st, i
       qs = (uint32_t)__shfl((int)qs, from, 64);
       yl = __shfl(yl, from, 64);
       ql = __shfl(ql, from, 64);
-      y = x < z ? x : z;
-      q = x < z ? z : x;
+      tq = __shfl(tq, from, 64);
+      y = pair_y(a, x, z);
+      q = pair_q(a, x, z);
       if (here == 0) return;
     }
   }
   RComp ny[2], nq[2];
   auto fetch = [&](int l) {
     const RComp* yrow = a.rc + (uint32_t)__builtin_amdgcn_readlane((int)ys, l);
-    const RComp* qrow = a.rc + (uint32_t)__builtin_amdgcn_readlane((int)qs, l);
+    const RComp* qrow = a.qrc + (uint32_t)__builtin_amdgcn_readlane((int)qs, l);
     const int yn = __builtin_amdgcn_readlane(yl, l), qm = __builtin_amdgcn_readlane(ql, l);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -330,9 +353,10 @@ __device__ __forceinline__ void decide_pairs(const PairArgs& a, StagedRow& st, i
   for (int l = 0; l < here; ++l) {
     const RComp cy[2] = {ny[0], ny[1]}, cq[2] = {nq[0], nq[1]};
     const RComp* yrow = a.rc + (uint32_t)__builtin_amdgcn_readlane((int)ys, l);
-    const RComp* qrow = a.rc + (uint32_t)__builtin_amdgcn_readlane((int)qs, l);
+    const RComp* qrow = a.qrc + (uint32_t)__builtin_amdgcn_readlane((int)qs, l);
     const int ylen = __builtin_amdgcn_readlane(yl, l), qlen = __builtin_amdgcn_readlane(ql, l);
     const int32_t dl = __builtin_amdgcn_readlane(d, l);
+    const float t = lane_float(tq, l);
     if (l + 1 < here) fetch(l + 1);
     const bool staged = qlen <= kStageRanks;
     int p2 = 128;
@@ -421,7 +445,7 @@ __device__ __forceinline__ void decide_pairs(const PairArgs& a, StagedRow& st, i
 #pragma unroll
       for (int o = 32; o >= 1; o >>= 1) part += __shfl_xor(part, o, 64);
       // the plain sum's error (below 1e-5) is far inside the slack
-      if (part < a.t - kSlack) {
+      if (part < t - kSlack) {
         ++dc.surv;
         wave_lds_order();
         continue;
@@ -430,14 +454,14 @@ __device__ __forceinline__ void decide_pairs(const PairArgs& a, StagedRow& st, i
                          [&](int, int32_t r) { return look(r); });
     }
     ++dc.surv;
-    if (s32 >= a.t - kSlack) ++dc.ver;
+    if (s32 >= t - kSlack) ++dc.ver;
     float sim;
     bool banded;
-    const bool keep = wave_decide(yrow, ylen, lane, look, s32, a.t, &sim, &banded);
+    const bool keep = wave_decide(yrow, ylen, lane, look, s32, t, &sim, &banded);
     if (banded) ++dc.band;
     if (keep) {
-      em.add(lane, ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)y, l) << a.bj) |
-                       (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)q, l),
+      em.add(lane, pair_key(a, (uint32_t)__builtin_amdgcn_readlane((int)y, l),
+                            (uint32_t)__builtin_amdgcn_readlane((int)q, l)),
              sim);
       if (em.n == 64) em.flush(lane, a.counters, a.out_key, a.out_sim, a.cap);
     }
@@ -448,11 +472,12 @@ __device__ __forceinline__ void decide_pairs(const PairArgs& a, StagedRow& st, i
 // The same for one pair, without the staging: what a full queue leaves to the
 // wave that found it (kept small: it shares that kernel's registers).
 __device__ __forceinline__ void decide_one(const PairArgs& a, int lane, uint32_t x, uint32_t z, int32_t d, Decided& dc) {
-  const uint32_t y = x < z ? x : z, q = x < z ? z : x;
-  const int64_t ys = a.rp[y], qs = a.rp[q];
-  const int ylen = (int)(a.rp[y + 1] - ys), qlen = (int)(a.rp[q + 1] - qs);
+  const uint32_t y = pair_y(a, x, z), q = pair_q(a, x, z);
+  const float t = pair_t(a, q);
+  const int64_t ys = a.rp[y], qs = a.qrp[q];
+  const int ylen = (int)(a.rp[y + 1] - ys), qlen = (int)(a.qrp[q + 1] - qs);
   const RComp* yrow = a.rc + ys;
-  const RComp* qrow = a.rc + qs;
+  const RComp* qrow = a.qrc + qs;
   bool rarer = false;
   auto look = [&](int32_t r) {
     const float v = row_lookup(qrow, qlen, r);
@@ -462,14 +487,14 @@ __device__ __forceinline__ void decide_one(const PairArgs& a, int lane, uint32_t
   const float s32 = wave_dot2(yrow, ylen, lane, look);
   if (__ballot(rarer)) return;
   ++dc.surv;
-  if (s32 >= a.t - kSlack) ++dc.ver;
+  if (s32 >= t - kSlack) ++dc.ver;
   float sim;
   bool banded;
-  const bool keep = wave_decide(yrow, ylen, lane, look, s32, a.t, &sim, &banded);
+  const bool keep = wave_decide(yrow, ylen, lane, look, s32, t, &sim, &banded);
   if (banded) ++dc.band;
   if (keep) {
     WaveEmit em;
-    em.add(lane, ((uint64_t)y << a.bj) | (uint64_t)q, sim);
+    em.add(lane, pair_key(a, y, q), sim);
     em.flush(lane, a.counters, a.out_key, a.out_sim, a.cap);
   }
 }
@@ -532,7 +557,8 @@ constexpr int kSteps = kSkGroups / 32;
 
 // Survivors of one wave.  They go to the global queue, where all waves of
 // k_decide share them evenly (they come in clusters: most tiles have none and
-// a few have thousands); what does not fit there is decided at once.
+// a few have thousands); what does not fit there is decided at once, or for
+// queries flagged (the call is then made by the accumulating kernel).
 struct Survivors {
   uint32_t* a;  // LDS, kPairQueue entries each
   uint32_t* b;
@@ -563,6 +589,12 @@ struct Survivors {
       o[1] = b[e];
       o[2] = d[e];
     }
+    if (pa.query) {
+      if (fit < n && lane == 0) pa.counters[C_OVERFLOW] = 1ull;
+      n = 0;
+      wave_lds_order();
+      return;
+    }
     for (int e = fit; e < n; ++e)
       decide_one(pa, lane, (uint32_t)uni((int)a[e]), (uint32_t)uni((int)b[e]), uni((int)d[e]), dc);
     n = 0;
@@ -570,22 +602,22 @@ struct Survivors {
   }
 
   // Products of 64 rows (lane l holds the id of row l) with 32 columns (lane
-  // l % 32 holds the id of its column and the number of rows before it that
-  // do not pair with it: rows from `first` to na - 1 do).
+  // l % 32 holds the id of its column, the rows that pair with it, `first` to
+  // na - 1, and the product of a survivor).
   __device__ __forceinline__ void take(const PairArgs& pa, int lane, const i32x16 (&acc)[2], uint32_t ida, uint32_t idb,
-                                       int first, int na, uint32_t rank, Decided& dc) {
+                                       int first, int na, uint32_t rank, int thr, Decided& dc) {
     // the largest product first: most tiles have no survivor
     int mx = acc[0][0];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) mx = mx > acc[i][r] ? mx : acc[i][r];
-    if (!__ballot(mx >= pa.thr)) return;
+    if (!__ballot(mx >= thr)) return;
     uint32_t hits = 0u;  // bit 16 i + r: this lane's survivors
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) hits |= acc[i][r] >= pa.thr ? 1u << (16 * i + r) : 0u;
+      for (int r = 0; r < 16; ++r) hits |= acc[i][r] >= thr ? 1u << (16 * i + r) : 0u;
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     // one survivor per lane at a time
     do {
@@ -660,7 +692,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     const int64_t base = a.doff[u.x];
     const int len = (int)(a.doff[u.x + 1] - base);
     const uint32_t* const ids = a.dl + base;
-    const int g = a.gid[u.x] >> 3;
+    const int g = a.gid[u.x] >> 3;  // kFineGroups / kSkGroups = 8
     const int ksteps = g / 32 + 1;
     int ablk, chunk;
     unit_at(u.y, &ablk, &chunk);
@@ -725,7 +757,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
             }
           }
           // each pair once: the row's entry comes after the column's
-          sv.take(a, lane, acc, ida, cid[buf][r0], b0 + r0 - a0 + 1, b0 + r0 < to ? na : 0, u.x, dc);
+          sv.take(a, lane, acc, ida, cid[buf][r0], b0 + r0 - a0 + 1, b0 + r0 < to ? na : 0, u.x, a.thr, dc);
         }
       }
     }
@@ -808,12 +840,112 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             if (na > 32) acc[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[1][ks], fb[ks], acc[1], 0, 0, 0);
           }
         const int bl = b0 + (lane & 31);
-        sv.take(a, lane, acc, ida, idb, bl - a0 + 1, na, rank, dc);
+        sv.take(a, lane, acc, ida, idb, bl - a0 + 1, na, rank, a.thr, dc);
       }
     }
   }
   sv.pass_on(a, lane, dc);
   add_counts(a, c_visit, dc);
+}
+
+// ---------------------------------------------------------------- queries
+
+// Query rows against the whole corpus by the sketch bound over all groups: a
+// product of n x 256 with 256 x nq bytes, every pair tested.  A workgroup
+// holds 256 corpus rows' sketches in registers (64 per wave) and meets the
+// queries 64 at a time through LDS (laid out as in k_pairs_wide, a step
+// ahead), so the corpus sketches are read once, in order; a few queries are
+// bound by that (128 MB for 500,000 rows), thousands by the matrix cores:
+// 4,096 queries over 1,000,000 rows take 1.29 ms (1.6e15 operations a
+// second), with the exact count 3.1 ms and the decisions 0.8 ms where the
+// accumulating kernel took 15 ms.  256 groups where a self-join's lists have
+// 128: no list narrows the pairs here.
+// SAMPLE: every a.sample-th workgroup only, counting the pairs that reach
+// each of kRateBins thresholds, evenly between s.t and 1.
+constexpr int kMidSteps = kMidGroups / 32;
+
+template <bool SAMPLE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_query_screen(PairArgs a, QueryArgs s) {
+  __shared__ i32x4 cols[2][64 * 16];
+  constexpr int kHeld = SAMPLE ? 1 : kPairQueue;
+  __shared__ uint32_t qa[4][kHeld], qb[4][kHeld], qd[4][kHeld];
+  __shared__ unsigned int bins[kRateBins];
+  const int tid = (int)threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = uni(tid >> 6);
+  Survivors sv{qa[wave], qb[wave], qd[wave]};
+  Decided dc;
+  const int64_t row0 = (int64_t)blockIdx.x * (SAMPLE ? a.sample : 1) * kWideRows + 64 * wave;
+  if (SAMPLE && tid < kRateBins) bins[tid] = 0u;
+  const int na = s.n - row0 < 64 ? (int)(s.n - row0) : 64;  // may be <= 0
+  i32x4 fa[2][kMidSteps];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    int64_t r = row0 + 32 * i + (lane & 31);
+    if (r >= s.n) r = s.n - 1;  // (results of rows past the end are not used)
+    const uint8_t* p = s.sk + r * kMidGroups + 16 * (lane >> 5);
+#pragma unroll
+    for (int ks = 0; ks < kMidSteps; ++ks) fa[i][ks] = *reinterpret_cast<const i32x4*>(p + 32 * ks);
+  }
+  // this thread's part of a step's columns: 64 groups of column tid / 4
+  const int col = tid >> 2, part = tid & 3;
+  i32x4 x[4];
+  auto fetch = [&](int64_t b0) {
+    int64_t q = b0 + col;
+    if (q >= s.nq) q = s.nq - 1;
+    const i32x4* p = reinterpret_cast<const i32x4*>(s.qsk + q * s.qstride * kMidGroups + 64 * part);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) x[c] = p[c];
+  };
+  // chunk c of column r at position c ^ (r % 16) of its row
+  auto at = [](int r, int c) { return r * 16 + (c ^ (r & 15)); };
+  fetch(s.q0);
+  int buf = 0;
+  for (int64_t b0 = s.q0; b0 < s.nq; b0 += 64, buf ^= 1) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) cols[buf][at(col, 4 * part + c)] = x[c];
+    if (b0 + 64 < s.nq) fetch(b0 + 64);
+    __syncthreads();
+    if (na > 0) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (b0 + 32 * j >= s.nq) break;
+        const int r0 = 32 * j + (lane & 31);
+        const int64_t q = b0 + r0;
+        const int thr = q < s.nq ? pair_threshold(s.qt ? s.qt[q] : s.t) : 0x7FFFFFFF;
+        i32x16 acc[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][r] = 0;
+#pragma unroll
+        for (int ks = 0; ks < kMidSteps; ++ks) {
+          const i32x4 fb = cols[buf][at(r0, 2 * ks + (lane >> 5))];
+          acc[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[0][ks], fb, acc[0], 0, 0, 0);
+          acc[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[1][ks], fb, acc[1], 0, 0, 0);
+        }
+        if (SAMPLE) {
+          const float per_bin = (float)kRateBins / (float)(pair_threshold(1.0f) - pair_threshold(s.t) + 1);
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              if (acc[i][r] >= thr && 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3) < na) {
+                const int bin = (int)((float)(acc[i][r] - thr) * per_bin);
+                atomicAdd(&bins[bin < kRateBins ? bin : kRateBins - 1], 1u);
+              }
+        } else {
+          sv.take(a, lane, acc, (uint32_t)(row0 + lane), (uint32_t)q, 0, na, 0x7FFFFFFFu, thr, dc);
+        }
+      }
+    }
+  }
+  if (SAMPLE) {
+    __syncthreads();
+    if (tid < kRateBins && bins[tid]) atomicAdd(&a.counters[tid], (unsigned long long)bins[tid]);
+  } else {
+    sv.pass_on(a, lane, dc);
+  }
 }
 
 // ---------------------------------------------------------------- candidates
@@ -889,7 +1021,6 @@ __global__ void k_segments(const uint32_t* __restrict__ hoff, int32_t H, int32_t
 // while the L2 bitmaps are, with two workgroups of 16 waves per CU.  Longer
 // spans of rows for the sparse ranks read fewer lines but miss the L2 (16,384
 // rows: 138 ms at 500,000 rows of mean 120, 65,536 rows: 209 ms).
-constexpr int kLdsRanks = 128;
 constexpr int kCountWaves = 16;
 constexpr int kChunks = 3;   // 64-component chunks of a row in registers
 constexpr int kEntries = 4;  // list entries loaded ahead per component
@@ -951,7 +1082,7 @@ __global__ __launch_bounds__(64 * kCountWaves) __attribute__((amdgpu_waves_per_e
   int64_t q0 = qbeg;
   if (a.triangle && q0 <= row0) q0 = row0 + 1;
   if (q0 >= qend) return;
-  const int hl = a.HB < kLdsRanks ? a.HB : kLdsRanks;
+  const int hl = a.HB < a.lds_ranks ? a.HB : a.lds_ranks;
   const uint32_t* const bmb = a.bm + b * (int64_t)a.HB * kCountWords;
   {
     const uint4* src = reinterpret_cast<const uint4*>(bmb);
@@ -1232,15 +1363,6 @@ unsigned row_grid(int64_t n) {
 
 }  // namespace
 
-int32_t pair_threshold(float t) {
-  // a pair with sim >= t has a sketch product of at least t * kSkScale^2; the
-  // 1e-3 covers the rounding of this product many times over
-  const double v = (double)t * kSkScale * kSkScale - 1e-3;
-  int64_t k = (int64_t)v;
-  if ((double)k < v) ++k;
-  return (int32_t)k;
-}
-
 hipError_t launch_groups(const int64_t* cum, const uint32_t* cnt_r, int64_t m, int64_t nnz, uint16_t* gid, hipStream_t s) {
   if (m <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_groups, dim3(grid1d(m)), dim3(256), 0, s, cum, cnt_r, m, nnz, gid);
@@ -1261,9 +1383,9 @@ hipError_t launch_widen(const uint32_t* in, int64_t n, int64_t* out, hipStream_t
 }
 
 hipError_t launch_sketch(const int64_t* rp, const RComp* rc, const uint16_t* gid, int64_t n, uint8_t* sk,
-                         unsigned int* nfine, uint32_t* fidx, uint8_t* fsk, hipStream_t s) {
+                         uint8_t* mid, unsigned int* nfine, uint32_t* fidx, uint8_t* fsk, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_sketch, dim3(row_grid(n)), dim3(256), 0, s, rp, rc, gid, n, sk, nfine, fidx, fsk);
+  hipLaunchKernelGGL(k_sketch, dim3(row_grid(n)), dim3(256), 0, s, rp, rc, gid, n, sk, mid, nfine, fidx, fsk);
   return hipGetLastError();
 }
 
@@ -1307,7 +1429,7 @@ PairGroups pairs_resident_groups() {
 
 hipError_t launch_pairs(PairArgs a, const PairGroups& g, hipStream_t s) {
   if (a.nwide <= 0 && a.nshort <= 0) return hipSuccess;
-  if (!a.rp || !a.rc || !a.sk || !a.gid || !a.fidx || !a.fsk || !a.dl || !a.doff || !a.wide || !a.shorts || !a.uctr ||
+  if (!a.rp || !a.rc || !a.sk || !a.gid || !a.fidx || !a.fsk || !a.qrp || !a.qrc || !a.qfidx || !a.qfsk || !a.dl || !a.doff || !a.wide || !a.shorts || !a.uctr ||
       (a.sample == 0 && (!a.out_key || !a.out_sim)) || !a.counters || (a.qcap > 0 && !a.queue) || a.nwide > 0x7FFFFFFF ||
       a.nshort > 0x7FFFFFFF)
     return hipErrorInvalidValue;
@@ -1335,6 +1457,30 @@ hipError_t launch_pairs(PairArgs a, const PairGroups& g, hipStream_t s) {
   return e;
 }
 
+hipError_t launch_query_screen(const PairArgs& a, const QueryArgs& q, const PairGroups& g, hipStream_t s) {
+  if (q.n <= 0 || q.nq <= q.q0) return hipSuccess;
+  if (!q.sk || !q.qsk || q.q0 < 0 || q.qstride <= 0 || !a.uctr || !a.counters || a.qcap <= 0 || !a.queue || !a.rp ||
+      !a.rc || !a.qrp || !a.qrc || !a.fidx || !a.fsk || !a.qfidx || !a.qfsk || !a.out_key || !a.out_sim || !a.query)
+    return hipErrorInvalidValue;
+  const int64_t grid = (q.n + kWideRows - 1) / kWideRows;
+  if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_query_screen<false>, dim3((unsigned)grid), dim3(256), 0, s, a, q);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_decide, dim3((unsigned)g.decide), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_query_sample(const PairArgs& a, const QueryArgs& q, hipStream_t s) {
+  if (q.n <= 0 || q.nq <= 0) return hipSuccess;
+  if (!q.sk || !q.qsk || q.q0 != 0 || q.qstride <= 0 || q.qt || a.sample <= 0 || !a.counters) return hipErrorInvalidValue;
+  const int64_t every = kWideRows * a.sample;
+  const int64_t grid = (q.n + every - 1) / every;
+  if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_query_screen<true>, dim3((unsigned)grid), dim3(256), 0, s, a, q);
+  return hipGetLastError();
+}
+
 hipError_t launch_segments(const uint32_t* hoff, int32_t H, int32_t cb, int64_t nb, int64_t nblk, uint2* seg,
                            hipStream_t s) {
   if (nblk <= 0 || H <= 0) return hipSuccess;
@@ -1353,7 +1499,7 @@ hipError_t launch_present(const int64_t* off, const Post* post, int32_t H, int64
 hipError_t launch_count(const CountArgs& a, hipStream_t s) {
   if (a.nq <= 0 || a.n <= 0) return hipSuccess;
   if (!a.rp || !a.rc || !a.bm || !a.present || !a.post || !a.post4 || !a.seg || !a.toff || !a.counters || a.chunk <= 0 ||
-      a.rr <= 0 || a.HB > a.H)
+      a.rr <= 0 || a.HB > a.H || a.lds_ranks < 0 || a.lds_ranks > kLdsRanks)
     return hipErrorInvalidValue;
   if (a.HB == 0) {
     if (!a.off) return hipErrorInvalidValue;

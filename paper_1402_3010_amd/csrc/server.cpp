@@ -225,7 +225,7 @@ void run_batch(apss_server* S, Workspace& ws, RankRows& rows, Staging& hs, std::
     int64_t cnt = 0;
     if (!rc) {
       const QuerySet Q{rows.rp.p, rows.rc.p, rows.mw.p, rows.n, rows.nnz, rows.rp_host.data()};
-      rc = run_join(ix, ws, Q, 0, 1.0f, ws.qt.p, cap, &cnt);
+      rc = run_join(ix, ws, Q, 0, 1.0f, ws.qt.p, cap, &cnt, tq);
     }
     if (!rc) rc = finish_host(ws, cnt, ceil_log2((uint64_t)ix->n), &all);
   }
@@ -295,6 +295,7 @@ void assemble(Request* r) {
 void worker(apss_server* S, int slot) {
   Staging hs;  // destroyed last, after the slot's stream has drained
   Workspace ws;
+  ws.slot = true;
   RankRows rows;
   int rc = APSS_OK;
   std::string msg;
