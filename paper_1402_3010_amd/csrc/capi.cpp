@@ -14,6 +14,7 @@
 
 #include "../../include/apss.h"
 #include "apss_internal.h"
+#include "finish.h"
 #include "index_build.h"
 #include "join.h"
 #include "lib.h"
@@ -999,8 +1000,46 @@ int start_call(Workspace& ws, bool keep_graph = false) {
   return APSS_OK;
 }
 
+int host_sink(Workspace& ws, Sink* sink) {
+  if (!ws.host_out.reserve((size_t)(3 * kFinishPairs))) {
+    set_error("pinned host allocation failed");
+    return APSS_ENOMEM;
+  }
+  sink->i = ws.host_out.p;
+  sink->j = sink->i + kFinishPairs;
+  sink->sim = (float*)(sink->j + kFinishPairs);
+  sink->room = kFinishPairs;
+  return APSS_OK;
+}
+
+// After a join's kernels: its counters in ws.host_counters once the stream
+// has drained, and the pairs at the sink if they are few.
+int hand_over(Workspace& ws, int bj, const Sink* sink) {
+  hipStream_t s = ws.stream;
+  if (!ws.host_counters.reserve(C_NUM)) {
+    set_error("pinned host allocation failed");
+    return APSS_ENOMEM;
+  }
+  FinishArgs f{};
+  f.key = ws.raw_key.p;
+  f.sim = ws.raw_sim.p;
+  f.cap = ws.raw_key.n;
+  f.bj = bj;
+  if (sink) {
+    f.out_i = sink->i;
+    f.out_j = sink->j;
+    f.out_sim = sink->sim;
+    f.room = sink->room;
+  }
+  f.counters = ws.counters.p;
+  f.host = ws.host_counters.p;
+  CHK(launch_finish(f, s), "finish kernel");
+  CHK(hipEventRecord(ws.ev[3], s), "event");
+  return APSS_OK;
+}
+
 int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, float t, const float* qt_dev,
-             int64_t cap_hint, int64_t* count, const float* t_host) {
+             int64_t cap_hint, int64_t* count, const float* t_host, Sink* sink) {
   hipStream_t s = ws.stream;
   *count = 0;
   int rc = start_call(ws);
@@ -1063,9 +1102,11 @@ int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, flo
     CHK(hipEventRecord(ws.ev[1], s), "event");
     if ((rc = launch_planned(ws, P))) return rc;
     CHK(hipEventRecord(ws.ev[2], s), "event");
-    unsigned long long c[C_NUM];
-    CHK(hipMemcpyAsync(c, ws.counters.p, sizeof(c), hipMemcpyDeviceToHost, s), "read counters");
+    // (a pair that several parts keep is still there several times)
+    const Sink* to = P.a.parts > 1 ? nullptr : sink;
+    if ((rc = hand_over(ws, P.bj, to))) return rc;
     CHK(hipStreamSynchronize(s), "join");
+    const unsigned long long* const c = ws.host_counters.p;
     if (screen && c[C_OVERFLOW]) {
       screen = false;
       P = JoinPlan{};
@@ -1083,6 +1124,11 @@ int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, flo
     float ms = 0.0f;
     CHK(hipEventElapsedTime(&ms, ws.ev[1], ws.ev[2]), "event");
     ws.last.ms_candidates = ms;
+    if (to && finish_delivers(matches, ws.raw_key.n, to->room)) {
+      sink->done = true;
+      *count = matches;
+      return APSS_OK;
+    }
     if ((rc = sort_pairs(ws, matches, P.bi + P.bj))) return rc;
     int64_t distinct = matches;
     if (P.a.parts > 1 && matches > 1) {
@@ -1109,7 +1155,7 @@ int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, flo
 // Screened self-join: the bf16 MFMA head screen (pairs that share no tail
 // dimension) and the sparse pass over the head-cut index (pairs that share
 // one), written into one pair buffer and sorted together.
-int run_screen_join(apss_index* ix, Workspace& ws, float t, int64_t cap_hint, int64_t* count) {
+int run_screen_join(apss_index* ix, Workspace& ws, float t, int64_t cap_hint, int64_t* count, Sink* sink) {
   apss_index* sx = ix->screen;
   hipStream_t s = ws.stream;
   *count = 0;
@@ -1249,9 +1295,9 @@ int run_screen_join(apss_index* ix, Workspace& ws, float t, int64_t cap_hint, in
     CHK(launch_screen_verify(ws.s_cand.p, nc, bj, sx->rows.rp.p, sx->rows.rc.p, head, t, ws.raw_key.p, ws.raw_sim.p,
                              ws.raw_key.n, ws.counters.p, s),
         "screen verify");
-    unsigned long long c[C_NUM];
-    CHK(hipMemcpyAsync(c, ws.counters.p, sizeof(c), hipMemcpyDeviceToHost, s), "read counters");
+    if ((rc = hand_over(ws, bj, sink))) return rc;
     CHK(hipStreamSynchronize(s), "join");
+    const unsigned long long* const c = ws.host_counters.p;
     const int64_t matches = (int64_t)c[C_MATCHES];
     if (matches > ws.raw_key.n) {
       if ((rc = ensure_pair_capacity(ws, matches + matches / 8 + 1024))) return rc;
@@ -1268,8 +1314,9 @@ int run_screen_join(apss_index* ix, Workspace& ws, float t, int64_t cap_hint, in
     float ms = 0.0f;
     CHK(hipEventElapsedTime(&ms, ws.ev[1], ws.ev[2]), "event");
     ws.last.ms_candidates = ms;
-    if ((rc = sort_pairs(ws, matches, 2 * bj))) return rc;
     *count = matches;
+    if (sink && finish_delivers(matches, ws.raw_key.n, sink->room)) sink->done = true;
+    else if ((rc = sort_pairs(ws, matches, 2 * bj))) return rc;
     return APSS_OK;
   }
   set_error("pair buffer kept overflowing");
@@ -1314,6 +1361,12 @@ int capture_join_graph(apss_index* ix, float t, uint32_t* out_i, uint32_t* out_j
     CHK(fill_u64((uint64_t*)ws.counters.p, 0ull, C_NUM, s), "fill");
     int r = launch_planned(ws, P);
     if (r) return r;
+    if (finish_delivers(cnt, ws.raw_key.n, capacity)) {
+      const FinishArgs f{ws.raw_key.p, ws.raw_sim.p, ws.raw_key.n, P.bj,     out_i, out_j,
+                         out_sim,      capacity,     ws.counters.p, g.hctr};
+      CHK(launch_finish(f, s), "finish kernel");
+      return APSS_OK;
+    }
     CHK(hipMemcpyAsync(g.hctr, ws.counters.p, sizeof(unsigned long long) * C_NUM, hipMemcpyDeviceToHost, s),
         "read counters");
     if ((r = sort_pairs(ws, cnt, P.bi + P.bj))) return r;
@@ -1370,11 +1423,12 @@ int graph_join(apss_index* ix, float t, uint32_t* out_i, uint32_t* out_j, float*
     g.reset();  // cannot happen for a deterministic join; recompute eagerly
   }
   int64_t cnt = 0;
+  Sink sink{out_i, out_j, out_sim, capacity};
   if ((rc = run_join(ix, ws, QuerySet{ix->rows.rp.p, ix->rows.rc.p, ix->rows.mw.p, ix->n, ix->nnz,
                                       ix->rows.rp_host.data()},
-                     1, t, nullptr, join_cap_hint(ix), &cnt)))
+                     1, t, nullptr, join_cap_hint(ix), &cnt, nullptr, &sink)))
     return rc;
-  if ((rc = finish_device(ws, cnt, ceil_log2((uint64_t)ix->n), out_i, out_j, out_sim, capacity, count))) return rc;
+  if ((rc = finish_device(ws, cnt, ceil_log2((uint64_t)ix->n), sink, count))) return rc;
   const apss_stats keep = ws.last;
   rc = capture_join_graph(ix, t, out_i, out_j, out_sim, capacity, cnt);
   ws.last = keep;
@@ -1406,37 +1460,24 @@ int record_total(Workspace& ws) {
   return APSS_OK;
 }
 
-int finish_device(Workspace& ws, int64_t cnt, int bj, uint32_t* out_i, uint32_t* out_j, float* out_sim,
-                  int64_t capacity, int64_t* count, bool wait) {
+int finish_device(Workspace& ws, int64_t cnt, int bj, const Sink& sink, int64_t* count, bool wait) {
   *count = cnt;
-  if (cnt > capacity) {
-    set_error("output capacity %lld too small for %lld pairs", (long long)capacity, (long long)cnt);
+  if (cnt > sink.room) {
+    set_error("output capacity %lld too small for %lld pairs", (long long)sink.room, (long long)cnt);
     return APSS_ERANGE;
   }
-  CHK(launch_unpack_pairs(ws.raw_key.p, ws.raw_sim.p, cnt, bj, out_i, out_j, out_sim, ws.stream), "unpack");
+  if (sink.done) return record_total(ws);
+  CHK(launch_unpack_pairs(ws.raw_key.p, ws.raw_sim.p, cnt, bj, sink.i, sink.j, sink.sim, ws.stream), "unpack");
   CHK(hipEventRecord(ws.ev[3], ws.stream), "event");
   if (!wait) return APSS_OK;
   CHK(hipStreamSynchronize(ws.stream), "unpack");
   return record_total(ws);
 }
 
-int finish_host(Workspace& ws, int64_t cnt, int bj, apss_pairs* out) {
+int finish_host(Workspace& ws, int64_t cnt, int bj, const Sink& sink, apss_pairs* out) {
   out->count = 0;
   out->i = out->j = nullptr;
   out->sim = nullptr;
-  // the sort's second key buffer is free once the pairs are sorted: unpack
-  // there, i, j and sim one after another, so that one copy brings them over
-  SortScratch& ss = ws.ss;
-  CHK(ss.k2.reserve(cnt + cnt / 2 + 1), "alloc");
-  uint32_t* di = (uint32_t*)ss.k2.p;
-  uint32_t* dj = di + cnt;
-  float* ds = (float*)(dj + cnt);
-  int64_t c2 = 0;
-  int rc = finish_device(ws, cnt, bj, di, dj, ds, cnt, &c2, false);
-  if (rc) {
-    (void)hipStreamSynchronize(ws.stream);
-    return rc;
-  }
   const size_t nb = (size_t)(cnt > 0 ? cnt : 1);
   out->i = (uint32_t*)malloc(nb * sizeof(uint32_t));
   out->j = (uint32_t*)malloc(nb * sizeof(uint32_t));
@@ -1450,6 +1491,26 @@ int finish_host(Workspace& ws, int64_t cnt, int bj, apss_pairs* out) {
     (void)hipStreamSynchronize(ws.stream);
     set_error("host allocation failed");
     return APSS_ENOMEM;
+  }
+  if (sink.done) {  // already in pinned memory
+    memcpy(out->i, sink.i, sizeof(uint32_t) * cnt);
+    memcpy(out->j, sink.j, sizeof(uint32_t) * cnt);
+    memcpy(out->sim, sink.sim, sizeof(float) * cnt);
+    out->count = cnt;
+    return record_total(ws);
+  }
+  // the sort's second key buffer is free once the pairs are sorted: unpack
+  // there, i, j and sim one after another, so that one copy brings them over
+  SortScratch& ss = ws.ss;
+  CHK(ss.k2.reserve(cnt + cnt / 2 + 1), "alloc");
+  uint32_t* di = (uint32_t*)ss.k2.p;
+  uint32_t* dj = di + cnt;
+  float* ds = (float*)(dj + cnt);
+  int64_t c2 = 0;
+  int rc = finish_device(ws, cnt, bj, Sink{di, dj, ds, cnt}, &c2, false);
+  if (rc) {
+    (void)hipStreamSynchronize(ws.stream);
+    return rc;
   }
   // up to 4M pairs through the workspace's pinned staging in one copy;
   // larger results straight into the output arrays
@@ -1582,9 +1643,9 @@ QuerySet staged_queries(const RankRows& r) {
   return QuerySet{r.rp.p, r.rc.p, r.mw.p, r.n, r.nnz, r.rp_host.data()};
 }
 
-int self_join(apss_index* ix, float t, int64_t* cnt) {
-  if (ix->screen) return run_screen_join(ix, ix->ws, t, join_cap_hint(ix), cnt);
-  return run_join(ix, ix->ws, corpus_queries(ix), 1, t, nullptr, join_cap_hint(ix), cnt);
+int self_join(apss_index* ix, float t, int64_t* cnt, Sink* sink) {
+  if (ix->screen) return run_screen_join(ix, ix->ws, t, join_cap_hint(ix), cnt, sink);
+  return run_join(ix, ix->ws, corpus_queries(ix), 1, t, nullptr, join_cap_hint(ix), cnt, nullptr, sink);
 }
 
 }  // namespace
@@ -1688,9 +1749,14 @@ int apss_build_index(int64_t n, int64_t m, const int64_t* row_ptr, const int32_t
     return APSS_EINVAL;
   }
   int rc = build_impl(ix, row_ptr, col, val, on_device);
-  // the join's lookup tables for the index's geometry and the call timers
-  // exist from here on, so apss_join_device_noalloc needs no allocation
+  // the join's lookup tables for the index's geometry, the call timers and
+  // the pinned counters exist from here on, so apss_join_device_noalloc needs
+  // no allocation
   if (!rc && o.screen_dims == 0 && n > 0) rc = prepare(ix, ix->ws.stream, ix->variant, ix->range_rows);
+  if (!rc && !ix->ws.host_counters.reserve(C_NUM)) {
+    set_error("pinned host allocation failed");
+    rc = APSS_ENOMEM;
+  }
   for (int e = 0; !rc && e < 6; ++e)
     if (hipEventCreateWithFlags(&ix->ws.ev[e], hipEventDefault) != hipSuccess) {
       set_error("hipEventCreateWithFlags failed");
@@ -1723,8 +1789,9 @@ int apss_join_device(apss_index* ix, float t, uint32_t* out_i, uint32_t* out_j, 
   if (ix->opts.graph && !ix->screen && ix->parts == 1 && !ix->opts.remscore && ix->n > 0)
     return graph_join(ix, t, out_i, out_j, out_sim, capacity, count);
   int64_t cnt = 0;
-  if ((rc = self_join(ix, t, &cnt))) return rc;
-  return finish_device(ix->ws, cnt, ceil_log2((uint64_t)ix->n), out_i, out_j, out_sim, capacity, count);
+  Sink sink{out_i, out_j, out_sim, capacity};
+  if ((rc = self_join(ix, t, &cnt, &sink))) return rc;
+  return finish_device(ix->ws, cnt, ceil_log2((uint64_t)ix->n), sink, count);
 }
 
 int apss_join(apss_index* ix, float t, apss_pairs* out) {
@@ -1738,8 +1805,10 @@ int apss_join(apss_index* ix, float t, apss_pairs* out) {
   int rc = check_t(ix, t);
   if (rc) return rc;
   int64_t cnt = 0;
-  if ((rc = self_join(ix, t, &cnt))) return rc;
-  return finish_host(ix->ws, cnt, ceil_log2((uint64_t)ix->n), out);
+  Sink sink;
+  if ((rc = host_sink(ix->ws, &sink))) return rc;
+  if ((rc = self_join(ix, t, &cnt, &sink))) return rc;
+  return finish_host(ix->ws, cnt, ceil_log2((uint64_t)ix->n), sink, out);
 }
 
 int apss_query_device(apss_index* ix, int64_t nq, const int64_t* q_row_ptr, const int32_t* q_col, const float* q_val,
@@ -1754,9 +1823,11 @@ int apss_query_device(apss_index* ix, int64_t nq, const int64_t* q_row_ptr, cons
   int rc = stage_queries(ix, ix->ws, nq, q_row_ptr, q_col, q_val, on_device, t_per_row, t, rows);
   if (rc) return rc;
   int64_t cnt = 0;
-  if ((rc = run_join(ix, ix->ws, staged_queries(rows), 0, t, t_per_row ? ix->ws.qt.p : nullptr, 16 * nq, &cnt, t_per_row)))
+  Sink sink{out_i, out_j, out_sim, capacity};
+  if ((rc = run_join(ix, ix->ws, staged_queries(rows), 0, t, t_per_row ? ix->ws.qt.p : nullptr, 16 * nq, &cnt, t_per_row,
+                     &sink)))
     return rc;
-  return finish_device(ix->ws, cnt, ceil_log2((uint64_t)ix->n), out_i, out_j, out_sim, capacity, count);
+  return finish_device(ix->ws, cnt, ceil_log2((uint64_t)ix->n), sink, count);
 }
 
 int apss_query(apss_index* ix, int64_t nq, const int64_t* q_row_ptr, const int32_t* q_col, const float* q_val,
@@ -1772,9 +1843,12 @@ int apss_query(apss_index* ix, int64_t nq, const int64_t* q_row_ptr, const int32
   int rc = stage_queries(ix, ix->ws, nq, q_row_ptr, q_col, q_val, on_device, t_per_row, t, rows);
   if (rc) return rc;
   int64_t cnt = 0;
-  if ((rc = run_join(ix, ix->ws, staged_queries(rows), 0, t, t_per_row ? ix->ws.qt.p : nullptr, 16 * nq, &cnt, t_per_row)))
+  Sink sink;
+  if ((rc = host_sink(ix->ws, &sink))) return rc;
+  if ((rc = run_join(ix, ix->ws, staged_queries(rows), 0, t, t_per_row ? ix->ws.qt.p : nullptr, 16 * nq, &cnt, t_per_row,
+                     &sink)))
     return rc;
-  return finish_host(ix->ws, cnt, ceil_log2((uint64_t)ix->n), out);
+  return finish_host(ix->ws, cnt, ceil_log2((uint64_t)ix->n), sink, out);
 }
 
 void apss_pairs_free(apss_pairs* p) {

@@ -149,6 +149,7 @@ struct Workspace {
   DBuf<uint16_t> s_X;
   JoinGraph graph;
   PinnedBuf<uint32_t> host_out;  // staging of result pairs copied to the host
+  PinnedBuf<unsigned long long> host_counters;  // [C_NUM] written by the device
   apss_stats last;
   int64_t regrows = 0;  // joins rerun because the pair buffer was too small
   hipEvent_t ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -306,10 +307,21 @@ int64_t default_range_rows(int variant);
 // Query rows -> rank space on ws's stream (validates; t_per_row is host memory or NULL).
 int stage_queries(apss_index* ix, Workspace& ws, int64_t nq, const int64_t* q_row_ptr, const int32_t* q_col,
                   const float* q_val, int on_device, const float* t_per_row, float t, RankRows& rows);
+// Where a call's pairs go: room entries of device memory, or a pinned buffer
+// of the workspace (host_sink).  `done` once they are there; if there are
+// more than one launch hands over they are left sorted in the workspace.
+struct Sink {
+  uint32_t* i = nullptr;
+  uint32_t* j = nullptr;
+  float* sim = nullptr;
+  int64_t room = 0;
+  bool done = false;
+};
+int host_sink(Workspace& ws, Sink* sink);
 // Run the join kernels; sorted raw pairs in ws.raw_key / ws.raw_sim; count in
 // *count.  cap_hint: pair capacity to start with (grown and rerun on overflow).
 int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, float t, const float* qt_dev,
-             int64_t cap_hint, int64_t* count, const float* t_host = nullptr);
+             int64_t cap_hint, int64_t* count, const float* t_host = nullptr, Sink* sink = nullptr);
 // Tile variants that may be launched.  Variant 3 (4 queries x 2048 rows,
 // 256 threads) faulted on the GPU (memory aperture violation) in two tuning
 // runs on the 500k-vector workloads, intermittently and without an
@@ -317,14 +329,14 @@ int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, flo
 inline bool variant_available(int variant) { return variant != 3; }
 inline bool screen_variant_ok(int variant) { return variant_available(variant); }
 // Screened self-join of an index built with screen_dims > 0 (ix->screen set).
-int run_screen_join(apss_index* ix, Workspace& ws, float t, int64_t cap_hint, int64_t* count);
-// Unpack the sorted raw pairs into device arrays / library-owned host arrays.
+int run_screen_join(apss_index* ix, Workspace& ws, float t, int64_t cap_hint, int64_t* count, Sink* sink = nullptr);
+// Unpack the sorted raw pairs into the sink (unless they are there already)
+// / into library-owned host arrays.
 // finish_device waits for the unpack unless wait is false (then the caller
 // synchronises the stream and calls record_total).
-int finish_device(Workspace& ws, int64_t cnt, int bj, uint32_t* out_i, uint32_t* out_j, float* out_sim,
-                  int64_t capacity, int64_t* count, bool wait = true);
+int finish_device(Workspace& ws, int64_t cnt, int bj, const Sink& sink, int64_t* count, bool wait = true);
 int record_total(Workspace& ws);
-int finish_host(Workspace& ws, int64_t cnt, int bj, apss_pairs* out);
+int finish_host(Workspace& ws, int64_t cnt, int bj, const Sink& sink, apss_pairs* out);
 
 }  // namespace apss
 

@@ -20,6 +20,7 @@
 #include <mutex>
 
 #include "apss_internal.h"
+#include "finish.h"
 #include "join.h"
 #include "lib.h"
 
@@ -125,6 +126,10 @@ extern "C" int apss_join_device_noalloc(apss_index* ix, float t, uint32_t* out_i
       set_error("the index's timers are missing");
       return APSS_EINVAL;
     }
+  if (!ws.host_counters.p) {
+    set_error("the index's pinned counters are missing");
+    return APSS_EINVAL;
+  }
 
   unsigned char* base = nullptr;
   if ((rc = scratch_on(dev, &base))) return rc;
@@ -181,9 +186,11 @@ extern "C" int apss_join_device_noalloc(apss_index* ix, float t, uint32_t* out_i
   APSS_CHK(hipEventRecord(ws.ev[1], s), "event");
   if ((rc = launch_plan(P, raw_key, raw_sim, room, counters, qctr, s))) return rc;
   APSS_CHK(hipEventRecord(ws.ev[2], s), "event");
-  unsigned long long c[C_NUM];
-  APSS_CHK(hipMemcpyAsync(c, counters, sizeof(c), hipMemcpyDeviceToHost, s), "read counters");
+  const FinishArgs f{raw_key, raw_sim, room, P.bj, out_i, out_j, out_sim, capacity, counters, ws.host_counters.p};
+  APSS_CHK(launch_finish(f, s), "finish kernel");
+  APSS_CHK(hipEventRecord(ws.ev[3], s), "event");
   APSS_CHK(hipStreamSynchronize(s), "join");
+  const unsigned long long* const c = ws.host_counters.p;
   const int64_t matches = (int64_t)c[C_MATCHES];
   *count = matches;
   if (matches > capacity) {
@@ -195,10 +202,12 @@ extern "C" int apss_join_device_noalloc(apss_index* ix, float t, uint32_t* out_i
               (long long)matches, (long long)room, kScratchBytes);
     return APSS_ENOMEM;
   }
-  APSS_CHK(radix_sort_u64_u32(raw_key, (uint32_t*)raw_sim, k2, v2, matches, P.bi + P.bj, hist, scan, s), "pair sort");
-  APSS_CHK(launch_unpack_pairs(raw_key, raw_sim, matches, P.bj, out_i, out_j, out_sim, s), "unpack");
-  APSS_CHK(hipEventRecord(ws.ev[3], s), "event");
-  APSS_CHK(hipStreamSynchronize(s), "unpack");
+  if (!finish_delivers(matches, room, capacity)) {
+    APSS_CHK(radix_sort_u64_u32(raw_key, (uint32_t*)raw_sim, k2, v2, matches, P.bi + P.bj, hist, scan, s), "pair sort");
+    APSS_CHK(launch_unpack_pairs(raw_key, raw_sim, matches, P.bj, out_i, out_j, out_sim, s), "unpack");
+    APSS_CHK(hipEventRecord(ws.ev[3], s), "event");
+    APSS_CHK(hipStreamSynchronize(s), "unpack");
+  }
   ws.last.posting_visits = (int64_t)(c[C_VISITS] + c[C_TAILVISITS]);
   ws.last.candidates = (int64_t)c[C_CANDIDATES];
   ws.last.bound_survivors = (int64_t)c[C_SURVIVORS];
