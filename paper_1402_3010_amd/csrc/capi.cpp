@@ -272,13 +272,18 @@ int build_impl(apss_index* ix, const int64_t* row_ptr, const int32_t* col, const
 // given by the caller names the accumulating kernel), and the sparse pass of
 // the screened join (whose geometry is that of the accumulating kernel
 // wherever the cost rule leaves it there).
+// (no tile variant, range width or group asked for)
+bool default_geometry(const apss_index* ix) {
+  const apss_opts& o = ix->opts;
+  return o.variant < 0 && o.range_rows == 0 && o.range_group == 0 && !getenv("APSS_VARIANT") &&
+         !getenv("APSS_RANGE_ROWS") && !getenv("APSS_RANGE_GROUP");
+}
+
 bool pairs_eligible(const apss_index* ix) {
   const apss_opts& o = ix->opts;
   if (o.index_all || o.local_parts > 1 || o.remscore || o.screen_dims) return false;
   if (ix->n <= 1 || ix->n > (1 << 25)) return false;  // (a list's units are counted in 32 bits)
-  if (ix->head_cut > 0) return true;
-  return o.variant < 0 && o.range_rows == 0 && o.range_group == 0 && !getenv("APSS_VARIANT") &&
-         !getenv("APSS_RANGE_ROWS") && !getenv("APSS_RANGE_GROUP");
+  return ix->head_cut > 0 || default_geometry(ix);
 }
 
 // Sketches, deep lists and work units, from the sorted list values in the
@@ -848,6 +853,47 @@ void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue
   c.chunk = std::max<int64_t>(64, std::min<int64_t>(4096, (want + 63) / 64 * 64));
 }
 
+// True when a batch of nq queries takes the few-query kernel: default
+// algorithm and geometry, and list offsets at its row bounds.
+bool takes_few(const apss_index* ix, int64_t nq) {
+  return nq <= kFewQueries && ix->opts.reserved[0] != kProbePairs && ix->parts == 1 && !ix->opts.remscore && ix->head_cut == 0 && default_geometry(ix) &&
+         ix->toff_rows > 0 && ix->toff_rows % kFewRows == 0;
+}
+
+int plan_few(apss_index* ix, Workspace& ws, const QuerySet& Q, float t, const float* qt_dev, JoinPlan& P) {
+  CHK(ws.qctr.reserve(kQueueCounters), "alloc queues");
+  CHK(ws.counters.reserve(C_NUM), "alloc counters");
+  P = JoinPlan{};
+  P.few = true;
+  P.bj = ceil_log2((uint64_t)ix->n);
+  P.bi = ceil_log2((uint64_t)Q.n);
+  const int slot = ix->hoff[0].p ? 0 : 1;
+  FewArgs& a = P.fa;
+  a.rp = ix->rows.rp.p;
+  a.rc = ix->rows.rc.p;
+  a.rs = ix->rs.p;
+  a.pn8 = ix->pn8.p;
+  a.n = ix->n;
+  a.off = ix->off.p;
+  a.post = ix->post.p;
+  a.hoff = ix->hoff[slot].p;
+  a.H = ix->H;
+  a.cb = slot == 0 ? 1024 : 2048;
+  a.nb = ix->hoff_nb[slot];
+  a.toff = ix->toff.p;
+  a.m_tail = ix->m - ix->H;
+  a.rr = ix->toff_rows;
+  a.nR = ix->toff_nR;
+  a.qrp = Q.rp;
+  a.qrc = Q.rc;
+  a.qmw = Q.mw;
+  a.qt = qt_dev;
+  a.t = t;
+  a.nq = Q.n;
+  a.bj = P.bj;
+  return APSS_OK;
+}
+
 // Share of a query's pairs expected to survive the sketch test at t.
 double survivor_rate(const apss_index* ix, float t) {
   const int32_t lo = pair_threshold(ix->t_build), hi = pair_threshold(1.0f);
@@ -937,6 +983,14 @@ int launch_plan(JoinPlan& P, uint64_t* out_key, float* out_sim, int64_t cap, uns
       q.nq = P.qend[r];
       CHK(launch_query_screen(P.pa, q, P.pg, s), "query kernel");
     }
+    return APSS_OK;
+  }
+  if (P.few) {
+    P.fa.out_key = out_key;
+    P.fa.out_sim = out_sim;
+    P.fa.cap = cap;
+    P.fa.counters = counters;
+    CHK(launch_few(P.fa, s), "query kernel");
     return APSS_OK;
   }
   JoinArgs& a = P.a;
@@ -1050,7 +1104,8 @@ int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, flo
   // ahead at its thresholds, and again the accumulating kernel if more pairs
   // survive than the queue was sized for (twice those of the corpus's own
   // rows).
-  bool screen = !triangle && ix->screen_queries && !ix->pairs_off && Q.n >= kScreenQueries;
+  const bool few = !triangle && takes_few(ix, Q.n);
+  bool screen = !triangle && !few && ix->screen_queries && !ix->pairs_off;
   if (screen) {
     double survivors = 0.0;
     for (int64_t q = 0; q < Q.n; ++q) survivors += survivor_rate(ix, t_host ? t_host[q] : t) * (double)ix->n;
@@ -1088,7 +1143,8 @@ int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, flo
     }
   }
   if (!screen) {
-    if ((rc = plan_join(ix, ws, Q, triangle, t, qt_dev, nullptr, P))) return rc;
+    rc = few ? plan_few(ix, ws, Q, t, qt_dev, P) : plan_join(ix, ws, Q, triangle, t, qt_dev, nullptr, P);
+    if (rc) return rc;
     if ((rc = ensure_pair_capacity(ws, cap_hint))) return rc;
   }
   if (ix->opts.remscore) {

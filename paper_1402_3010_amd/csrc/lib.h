@@ -10,6 +10,7 @@
 
 #include "../../include/apss.h"
 #include "apss_internal.h"
+#include "few.h"
 #include "join.h"
 #include "pairs.h"
 
@@ -248,6 +249,8 @@ struct JoinLayout {
 struct JoinPlan {
   bool pairs = false;  // the list-pair join: pa and ca in place of a
   bool query = false;  // the sketch test of queries: pa, qa and ca in place of a
+  bool few = false;    // few queries: fa in place of a
+  FewArgs fa{};
   PairArgs pa{};
   QueryArgs qa{};
   CountArgs ca{};
@@ -273,14 +276,16 @@ void bind_plan(apss_index* ix, const QuerySet& Q, int triangle, float t, const f
 // list-pair join's units and survivors (3).
 constexpr int kQueueCounters = 8;
 // Test hook outside the ABI: apss_opts.reserved[0] of an index whose self-joins
-// take the list-pair kernels whatever the cost rule says.
+// take the list-pair kernels, and its queries the sketch kernels, whatever the
+// cost rules say.
 constexpr int32_t kProbePairs = 0x50414952;
+// Most queries of a call that takes the few-query kernel, whose work grows
+// with them (kernels over 500,000 rows of mean 100: 30 us for one query where
+// the join kernel took 123; 8 queries 82 us and by the sketch kernels 206, 16
+// queries 154 and 172, 32 queries 282 and 231).
+constexpr int64_t kFewQueries = 16;
 // ps per survivor of the sketch test of a query.
 constexpr double kSurvivorPs = 1200.0;
-// Fewest queries of a call that takes the sketch kernels: they read every
-// row's sketch whatever the batch, 60 us of kernels at 500,000 rows and 20
-// queries; one query's lists are fewer bytes.
-constexpr int64_t kScreenQueries = 2;
 constexpr int64_t kQueryTile = 64;  // queries a workgroup of theirs meets at a time
 // True when a self-join of the index takes the list-pair kernels.
 bool use_pairs(const apss_index* ix);
