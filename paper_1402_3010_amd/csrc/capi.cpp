@@ -106,26 +106,27 @@ int sort_rows(Workspace& ws, uint64_t* keys, uint32_t* vals, int64_t nnz, int ke
   return APSS_OK;
 }
 
+int check_bits(uint32_t err, unsigned long long bad, const char* what) {
+  if (!err) return APSS_OK;
+  if (bad != ~0ull) set_error("%s: %s (row %llu)", what, err_bits_text(err), bad);
+  else set_error("%s: %s", what, err_bits_text(err));
+  return APSS_EINVAL;
+}
+
 int check_err(hipStream_t s, uint32_t* err_dev, unsigned long long* bad_dev, const char* what) {
   uint32_t err = 0;
   unsigned long long bad = ~0ull;
   CHK(hipMemcpyAsync(&err, err_dev, sizeof(err), hipMemcpyDeviceToHost, s), what);
   if (bad_dev) CHK(hipMemcpyAsync(&bad, bad_dev, sizeof(bad), hipMemcpyDeviceToHost, s), what);
   CHK(hipStreamSynchronize(s), what);
-  if (err) {
-    if (bad != ~0ull) set_error("%s: %s (row %llu)", what, err_bits_text(err), bad);
-    else set_error("%s: %s", what, err_bits_text(err));
-    return APSS_EINVAL;
-  }
-  return APSS_OK;
+  return check_bits(err, bad, what);
 }
 
 // Cleared error flag and first-bad-row slot of a workspace.
 int reset_err(Workspace& ws) {
-  CHK(ws.err.reserve(1), "alloc");
-  CHK(ws.bad.reserve(1), "alloc");
-  CHK(fill_u32(ws.err.p, 0u, 1, ws.stream), "fill");
-  CHK(fill_u64((uint64_t*)ws.bad.p, ~0ull, 1, ws.stream), "fill");
+  CHK(ws.checks.reserve(2), "alloc");
+  CHK(fill_u64((uint64_t*)ws.checks.p, 0ull, 1, ws.stream), "fill");
+  CHK(fill_u64((uint64_t*)ws.bad(), ~0ull, 1, ws.stream), "fill");
   return APSS_OK;
 }
 
@@ -196,8 +197,8 @@ int build_impl(apss_index* ix, const int64_t* row_ptr, const int32_t* col, const
   ix->nnz = nnz;
 
   if ((rc = reset_err(ws))) return rc;
-  uint32_t* err = ws.err.p;
-  unsigned long long* bad = ws.bad.p;
+  uint32_t* err = ws.err();
+  unsigned long long* bad = ws.bad();
   DBuf<unsigned long long> longest_dev;
   CHK(longest_dev.alloc(1), "alloc");
   CHK(fill_u64((uint64_t*)longest_dev.p, 0ull, 1, s), "fill");
@@ -356,11 +357,11 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r) {
   // threshold than the index's has fewer.
   DBuf<unsigned long long> cnt;
   CHK(cnt.alloc(C_NUM + kRateBins), "alloc");
-  CHK(ws.qctr.reserve(kQueueCounters), "alloc queues");
+  if (int rc = reserve_control(ws)) return rc;
   CHK(fill_u64((uint64_t*)cnt.p, 0ull, C_NUM + kRateBins, s), "fill");
-  CHK(fill_u32(ws.qctr.p, 0u, kQueueCounters, s), "fill");
+  CHK(fill_u32(ws.qctr, 0u, kQueueCounters, s), "fill");
   JoinPlan plan;
-  bind_pairs(ix, ix->t_build, ws.qctr.p, nullptr, 0, plan);
+  bind_pairs(ix, ix->t_build, ws.qctr, nullptr, 0, plan);
   plan.pa.counters = cnt.p;
   const int64_t units = ix->nwide + ix->nshort / kShortUnits;
   plan.pa.sample = std::max<int64_t>(1, units / 4096);
@@ -763,10 +764,9 @@ int plan_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, fl
   int rc0 = prepare(ix, s, ix->variant, ix->range_rows);
   if (rc0) return rc0;
   if (triangle && use_pairs(ix)) {
-    CHK(ws.qctr.reserve(kQueueCounters), "alloc queues");
-    CHK(ws.counters.reserve(C_NUM), "alloc counters");
+    if (int rc = reserve_control(ws)) return rc;
     CHK(ws.pq.reserve(3 * pair_queue_entries(ix)), "alloc queues");
-    bind_pairs(ix, t, ws.qctr.p, ws.pq.p, ws.pq.n / 3, P);
+    bind_pairs(ix, t, ws.qctr, ws.pq.p, ws.pq.n / 3, P);
     return APSS_OK;
   }
   JoinLayout L;
@@ -776,10 +776,9 @@ int plan_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, fl
       "tiles");
   CHK(ws.qcum.reserve((int64_t)L.cum.size()), "alloc queues");
   CHK(hipMemcpyAsync(ws.qcum.p, L.cum.data(), sizeof(int64_t) * L.cum.size(), hipMemcpyHostToDevice, s), "queues");
-  CHK(ws.qctr.reserve(kQueueCounters), "alloc queues");
-  CHK(ws.counters.reserve(C_NUM), "alloc counters");
+  if (int rc = reserve_control(ws)) return rc;
   CHK(ws.wg_cur.reserve((int64_t)L.G * L.wg_stride), "alloc cursors");
-  bind_plan(ix, Q, triangle, t, qt_dev, qrs, L, ws.tstart.p, ws.qcum.p, ws.qctr.p, ws.wg_cur.p, P);
+  bind_plan(ix, Q, triangle, t, qt_dev, qrs, L, ws.tstart.p, ws.qcum.p, ws.qctr, ws.wg_cur.p, P);
   return APSS_OK;
 }
 
@@ -861,8 +860,7 @@ bool takes_few(const apss_index* ix, int64_t nq) {
 }
 
 int plan_few(apss_index* ix, Workspace& ws, const QuerySet& Q, float t, const float* qt_dev, JoinPlan& P) {
-  CHK(ws.qctr.reserve(kQueueCounters), "alloc queues");
-  CHK(ws.counters.reserve(C_NUM), "alloc counters");
+  if (int rc = reserve_control(ws)) return rc;
   P = JoinPlan{};
   P.few = true;
   P.bj = ceil_log2((uint64_t)ix->n);
@@ -909,12 +907,10 @@ int plan_queries(apss_index* ix, Workspace& ws, const QuerySet& Q, float t, cons
   CHK(ws.q_mid.reserve(Q.n * kMidGroups), "alloc sketches");
   CHK(ws.q_fidx.reserve(Q.n), "alloc sketches");
   CHK(ws.q_fsk.reserve(longs * kFineGroups), "alloc sketches");
-  CHK(ws.q_nfine.reserve(1), "alloc sketches");
-  CHK(fill_u32(ws.q_nfine.p, 0u, 1, s), "fill");
-  CHK(launch_sketch(Q.rp, Q.rc, ix->gid.p, Q.n, nullptr, ws.q_mid.p, ws.q_nfine.p, ws.q_fidx.p, ws.q_fsk.p, s),
+  if (int rc = reserve_control(ws)) return rc;
+  CHK(launch_sketch(Q.rp, Q.rc, ix->gid.p, Q.n, nullptr, ws.q_mid.p, ws.nfine, ws.q_fidx.p, ws.q_fsk.p, s),
       "sketches");
-  CHK(ws.qctr.reserve(kQueueCounters), "alloc queues");
-  CHK(ws.counters.reserve(C_NUM), "alloc counters");
+  if (int rc = reserve_control(ws)) return rc;
   P = JoinPlan{};
   P.query = true;
   P.bj = ceil_log2((uint64_t)ix->n);
@@ -932,7 +928,7 @@ int plan_queries(apss_index* ix, Workspace& ws, const QuerySet& Q, float t, cons
   a.qfidx = ws.q_fidx.p;
   a.qfsk = ws.q_fsk.p;
   a.qt = qt_dev;
-  a.uctr = ws.qctr.p;
+  a.uctr = ws.qctr;
   a.t = t;
   a.bj = P.bj;
   QueryArgs& q = P.qa;
@@ -956,9 +952,9 @@ int plan_queries(apss_index* ix, Workspace& ws, const QuerySet& Q, float t, cons
   return APSS_OK;
 }
 
+// The caller has cleared the counters and queue counters.
 int launch_plan(JoinPlan& P, uint64_t* out_key, float* out_sim, int64_t cap, unsigned long long* counters,
                 unsigned int* qctr, hipStream_t s) {
-  CHK(fill_u32(qctr, 0u, kQueueCounters, s), "fill");
   if (P.pairs) {
     P.pa.out_key = out_key;
     P.pa.out_sim = out_sim;
@@ -1009,7 +1005,15 @@ int launch_plan(JoinPlan& P, uint64_t* out_key, float* out_sim, int64_t cap, uns
 
 // Launch a planned join writing pairs into ws.raw_key / raw_sim through ws.counters.
 int launch_planned(Workspace& ws, JoinPlan& P) {
-  return launch_plan(P, ws.raw_key.p, ws.raw_sim.p, ws.raw_key.n, ws.counters.p, ws.qctr.p, ws.stream);
+  return launch_plan(P, ws.raw_key.p, ws.raw_sim.p, ws.raw_key.n, ws.counters.p, ws.qctr, ws.stream);
+}
+
+int reserve_control(Workspace& ws) {
+  static_assert(kQueueCounters % 2 == 0, "control words");
+  CHK(ws.counters.reserve(kControlWords), "alloc counters");
+  ws.qctr = (unsigned int*)(ws.counters.p + C_NUM);
+  ws.nfine = ws.qctr + kQueueCounters;
+  return APSS_OK;
 }
 
 int ensure_pair_capacity(Workspace& ws, int64_t cap) {
@@ -1068,9 +1072,9 @@ int host_sink(Workspace& ws, Sink* sink) {
 
 // After a join's kernels: its counters in ws.host_counters once the stream
 // has drained, and the pairs at the sink if they are few.
-int hand_over(Workspace& ws, int bj, const Sink* sink) {
+int hand_over(Workspace& ws, int bj, const Sink* sink, const unsigned long long* checks = nullptr) {
   hipStream_t s = ws.stream;
-  if (!ws.host_counters.reserve(C_NUM)) {
+  if (!ws.host_counters.reserve(C_NUM + 2)) {
     set_error("pinned host allocation failed");
     return APSS_ENOMEM;
   }
@@ -1086,6 +1090,7 @@ int hand_over(Workspace& ws, int bj, const Sink* sink) {
     f.room = sink->room;
   }
   f.counters = ws.counters.p;
+  f.checks = checks;
   f.host = ws.host_counters.p;
   CHK(launch_finish(f, s), "finish kernel");
   CHK(hipEventRecord(ws.ev[3], s), "event");
@@ -1098,7 +1103,17 @@ int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, flo
   *count = 0;
   int rc = start_call(ws);
   if (rc) return rc;
-  if (Q.n == 0 || ix->n == 0) return APSS_OK;
+  // what the staging of a batch of queries leaves to this call
+  const unsigned long long* const checks = ws.pending;
+  const bool cleared = ws.cleared;
+  ws.pending = nullptr;
+  ws.cleared = false;
+  if (Q.n == 0) return APSS_OK;
+  if (ix->n == 0) return checks ? check_err(s, (uint32_t*)checks, (unsigned long long*)checks + 1, "query") : APSS_OK;
+  if (!cleared) {
+    if ((rc = reserve_control(ws))) return rc;
+    CHK(fill_u64((uint64_t*)ws.counters.p, 0ull, kControlWords, s), "fill");
+  }
   JoinPlan P;
   // A batch of queries takes the sketch kernels when they are expected to be
   // ahead at its thresholds, and again the accumulating kernel if more pairs
@@ -1153,21 +1168,21 @@ int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, flo
     CHK(launch_admit_pos(Q.rp, Q.rc, ix->mw_r.p, qt_dev, t, Q.n, ws.qadm.p, s), "admission");
     P.a.qadm = ws.qadm.p;
   }
-  for (int attempt = 0; attempt < 2; ++attempt) {
-    CHK(fill_u64((uint64_t*)ws.counters.p, 0ull, C_NUM, s), "fill");
+  for (int attempt = 0; attempt < 3; ++attempt) {  // (once more with the other kernel, once with more room)
+    if (attempt > 0) CHK(fill_u64((uint64_t*)ws.counters.p, 0ull, kControlWords, s), "fill");
     CHK(hipEventRecord(ws.ev[1], s), "event");
     if ((rc = launch_planned(ws, P))) return rc;
     CHK(hipEventRecord(ws.ev[2], s), "event");
     // (a pair that several parts keep is still there several times)
     const Sink* to = P.a.parts > 1 ? nullptr : sink;
-    if ((rc = hand_over(ws, P.bj, to))) return rc;
+    if ((rc = hand_over(ws, P.bj, to, checks))) return rc;
     CHK(hipStreamSynchronize(s), "join");
     const unsigned long long* const c = ws.host_counters.p;
+    if (checks && (rc = check_bits((uint32_t)c[C_NUM], c[C_NUM + 1], "query"))) return rc;
     if (screen && c[C_OVERFLOW]) {
       screen = false;
       P = JoinPlan{};
       if ((rc = plan_join(ix, ws, Q, triangle, t, qt_dev, nullptr, P))) return rc;
-      --attempt;
       continue;
     }
     const int64_t matches = (int64_t)c[C_MATCHES];
@@ -1344,7 +1359,7 @@ int run_screen_join(apss_index* ix, Workspace& ws, float t, int64_t cap_hint, in
     return rc;
   if ((rc = ensure_pair_capacity(ws, cap_hint))) return rc;
   for (int attempt = 0; attempt < 2; ++attempt) {
-    CHK(fill_u64((uint64_t*)ws.counters.p, 0ull, C_NUM, s), "fill");
+    CHK(fill_u64((uint64_t*)ws.counters.p, 0ull, kControlWords, s), "fill");
     CHK(hipEventRecord(ws.ev[1], s), "event");
     if ((rc = launch_planned(ws, P))) return rc;
     CHK(hipEventRecord(ws.ev[2], s), "event");
@@ -1390,7 +1405,7 @@ namespace {
 int64_t join_cap_hint(const apss_index* ix) { return std::max<int64_t>(1 << 20, 32 * ix->n); }
 
 std::vector<const void*> graph_buffers(const apss_index* ix, const Workspace& ws) {
-  return {ws.tstart.p, ws.qcum.p, ws.qctr.p, ws.counters.p, ws.wg_cur.p, ws.pq.p, ws.raw_key.p, ws.raw_sim.p, ws.ss.k2.p,
+  return {ws.tstart.p, ws.qcum.p, ws.qctr, ws.counters.p, ws.wg_cur.p, ws.pq.p, ws.raw_key.p, ws.raw_sim.p, ws.ss.k2.p,
           ws.ss.v32b.p, ws.ss.hist.p, ws.ss.scan.p, ix->toff.p, ix->hoff[0].p, ix->hoff[1].p,
           (const void*)(intptr_t)ix->variant, (const void*)(intptr_t)ix->range_rows,
           (const void*)(intptr_t)ix->range_group};
@@ -1404,7 +1419,7 @@ int capture_join_graph(apss_index* ix, float t, uint32_t* out_i, uint32_t* out_j
   hipStream_t s = ws.stream;
   g.reset();
   if (!s) return APSS_OK;  // the legacy default stream cannot be captured
-  if (!g.hctr) CHK(hipHostMalloc((void**)&g.hctr, sizeof(unsigned long long) * C_NUM, hipHostMallocDefault),
+  if (!g.hctr) CHK(hipHostMalloc((void**)&g.hctr, sizeof(unsigned long long) * (C_NUM + 2), hipHostMallocDefault),
                    "pinned counters");
   JoinPlan P;
   int rc = plan_join(ix, ws, QuerySet{ix->rows.rp.p, ix->rows.rc.p, ix->rows.mw.p, ix->n, ix->nnz,
@@ -1414,12 +1429,12 @@ int capture_join_graph(apss_index* ix, float t, uint32_t* out_i, uint32_t* out_j
   CHK(hipStreamSynchronize(s), "graph capture");
   CHK(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal), "graph capture");
   auto body = [&]() -> int {
-    CHK(fill_u64((uint64_t*)ws.counters.p, 0ull, C_NUM, s), "fill");
+    CHK(fill_u64((uint64_t*)ws.counters.p, 0ull, kControlWords, s), "fill");
     int r = launch_planned(ws, P);
     if (r) return r;
     if (finish_delivers(cnt, ws.raw_key.n, capacity)) {
-      const FinishArgs f{ws.raw_key.p, ws.raw_sim.p, ws.raw_key.n, P.bj,     out_i, out_j,
-                         out_sim,      capacity,     ws.counters.p, g.hctr};
+      const FinishArgs f{ws.raw_key.p, ws.raw_sim.p, ws.raw_key.n,  P.bj,    out_i, out_j,
+                         out_sim,      capacity,     ws.counters.p, nullptr, g.hctr};
       CHK(launch_finish(f, s), "finish kernel");
       return APSS_OK;
     }
@@ -1606,30 +1621,27 @@ int stage_queries(apss_index* ix, Workspace& ws, int64_t nq, const int64_t* q_ro
     int rc = check_t(ix, t);
     if (rc) return rc;
   }
-  int64_t nnz = 0;
   int rc;
-  if ((rc = reset_err(ws))) return rc;
-  uint32_t* err = ws.err.p;
-  unsigned long long* bad = ws.bad.p;
-  const int64_t* prp;
-  const int32_t* pcol;
-  const float* pval;
-  CsrDev in;
   rows.n = nq;
+  const int64_t* rp_host = q_row_ptr;
+  int64_t nnz = 0;
   if (on_device) {
-    if ((rc = stage_csr(s, nq, q_row_ptr, q_col, q_val, on_device, &nnz, in))) return rc;
-    CHK(launch_check_rowptr(in.prp, nq, nnz, err, bad, nullptr, s), "check row_ptr");
-    if ((rc = check_err(s, err, bad, "query"))) return rc;
-    CHK(rows.rp.reserve(nq + 1), "alloc");
-    CHK(hipMemcpyAsync(rows.rp.p, in.prp, sizeof(int64_t) * (nq + 1), hipMemcpyDeviceToDevice, s), "copy");
-    rows.rp_host.resize((size_t)nq + 1);
-    CHK(hipMemcpyAsync(rows.rp_host.data(), in.prp, sizeof(int64_t) * (nq + 1), hipMemcpyDeviceToHost, s), "copy");
-    prp = in.prp;
-    pcol = in.pcol;
-    pval = in.pval;
+    if (!ws.host_in.reserve(sizeof(int64_t) * (size_t)(nq + 1))) {
+      set_error("pinned host allocation failed");
+      return APSS_ENOMEM;
+    }
+    CHK(hipMemcpyAsync(ws.host_in.p, q_row_ptr, sizeof(int64_t) * (nq + 1), hipMemcpyDeviceToHost, s), "read row_ptr");
+    CHK(hipStreamSynchronize(s), "read row_ptr");
+    rp_host = (const int64_t*)ws.host_in.p;
+    nnz = rp_host[nq];
+    if (nnz < 0 || nnz >= (1ll << 32)) {
+      set_error("nnz must be in [0, 2^32)");
+      return APSS_EINVAL;
+    }
+    for (int64_t r = 0; r <= nq; ++r)
+      if ((r == 0 && rp_host[0] != 0) || (r < nq && rp_host[r + 1] < rp_host[r]))
+        return check_bits(ERR_ROWPTR, (unsigned long long)r, "query");
   } else {
-    // host rows: checked here, copied into the workspace's kept buffers,
-    // with no synchronisation before the single error check below
     nnz = q_row_ptr[nq];
     if (q_row_ptr[0] != 0 || nnz < 0 || nnz >= (1ll << 32)) {
       set_error("row_ptr must start at 0 and end at nnz in [0, 2^32)");
@@ -1640,41 +1652,95 @@ int stage_queries(apss_index* ix, Workspace& ws, int64_t nq, const int64_t* q_ro
         set_error("row_ptr must be non-decreasing (row %lld)", (long long)r);
         return APSS_EINVAL;
       }
-    // every buffer is reserved before the first copy of the caller's
-    // memory is queued, so no early return leaves such a copy in flight
-    CHK(rows.rp.reserve(nq + 1), "alloc");
-    CHK(ws.q_col.reserve(nnz), "alloc");
-    CHK(ws.q_val.reserve(nnz), "alloc");
-    CHK(rows.rc.reserve(nnz), "alloc");
-    CHK(rows.mw.reserve(nq), "alloc");
-    CHK(ws.ss.k1.reserve(nnz), "alloc");
-    CHK(ws.ss.v32a.reserve(nnz), "alloc");
-    CHK(ws.ss.k2.reserve(nnz), "sort scratch");
-    CHK(ws.ss.v32b.reserve(nnz), "sort scratch");
-    CHK(ws.ss.hist.reserve(radix_hist_elems(nnz)), "sort scratch");
-    CHK(ws.ss.scan.reserve(radix_scan_tmp_elems(nnz)), "sort scratch");
-    CHK(ws.ss.seg.reserve(nq + 2), "sort scratch");
-    if (t_per_row) CHK(ws.qt.reserve(nq), "alloc");
-    CHK(hipMemcpyAsync(rows.rp.p, q_row_ptr, sizeof(int64_t) * (nq + 1), hipMemcpyHostToDevice, s), "copy csr");
-    if (nnz) {
-      CHK(hipMemcpyAsync(ws.q_col.p, q_col, sizeof(int32_t) * nnz, hipMemcpyHostToDevice, s), "copy csr");
-      CHK(hipMemcpyAsync(ws.q_val.p, q_val, sizeof(float) * nnz, hipMemcpyHostToDevice, s), "copy csr");
-    }
-    rows.rp_host.assign(q_row_ptr, q_row_ptr + nq + 1);
-    prp = rows.rp.p;
-    pcol = ws.q_col.p;
-    pval = ws.q_val.p;
   }
   rows.nnz = nnz;
-  if (t_per_row) {
-    CHK(ws.qt.reserve(nq), "alloc");
-    CHK(hipMemcpyAsync(ws.qt.p, t_per_row, sizeof(float) * nq, hipMemcpyHostToDevice, s), "copy thresholds");
-  }
+  rows.rp_host.assign(rp_host, rp_host + nq + 1);
+  int64_t longest = 0;
+  for (int64_t r = 0; r < nq; ++r) longest = std::max(longest, rows.rp_host[(size_t)r + 1] - rows.rp_host[(size_t)r]);
+  // One copy brings what is small: the cleared check words, the thresholds
+  // and row_ptr, and the components of a batch of up to 128 KB (larger ones
+  // straight from the caller's memory).
+  constexpr size_t kPacked = 128 << 10;
+  const size_t t_at = 2 * sizeof(unsigned long long);
+  const size_t rp_at = t_at + ((t_per_row ? sizeof(float) * (size_t)nq : 0) + 7) / 8 * 8;
+  const size_t col_at = rp_at + sizeof(int64_t) * (size_t)(nq + 1);
+  const bool packed = !on_device && 2 * sizeof(float) * (size_t)nnz <= kPacked;
+  const size_t val_at = col_at + (packed ? sizeof(int32_t) * (size_t)nnz : 0);
+  const size_t total = val_at + (packed ? sizeof(float) * (size_t)nnz : 0);
+  // every buffer is reserved before the first copy of the caller's memory is
+  // queued, so no early return leaves such a copy in flight
+  CHK(rows.rp.reserve(nq + 1), "alloc");
   CHK(rows.rc.reserve(nnz), "alloc");
   CHK(rows.mw.reserve(nq), "alloc");
+  CHK(ws.q_in.reserve((int64_t)total), "alloc");
+  if (t_per_row) CHK(ws.qt.reserve(nq), "alloc");
+  if (!on_device && !packed) {
+    CHK(ws.q_col.reserve(nnz), "alloc");
+    CHK(ws.q_val.reserve(nnz), "alloc");
+  }
+  if ((rc = reserve_control(ws))) return rc;
+  const bool lds = longest <= kQueryRow;
   SortScratch& ss = ws.ss;
-  CHK(ss.k1.reserve(nnz), "alloc");
-  CHK(ss.v32a.reserve(nnz), "alloc");
+  if (!lds) {
+    CHK(ss.k1.reserve(nnz), "alloc");
+    CHK(ss.v32a.reserve(nnz), "alloc");
+    CHK(ss.k2.reserve(nnz), "sort scratch");
+    CHK(ss.v32b.reserve(nnz), "sort scratch");
+    CHK(ss.hist.reserve(radix_hist_elems(nnz)), "sort scratch");
+    CHK(ss.scan.reserve(radix_scan_tmp_elems(nnz)), "sort scratch");
+    CHK(ss.seg.reserve(nq + 2), "sort scratch");
+  }
+  if (!ws.host_in.reserve(total)) {
+    set_error("pinned host allocation failed");
+    return APSS_ENOMEM;
+  }
+  unsigned char* const h = ws.host_in.p;
+  const unsigned long long clear[2] = {0ull, ~0ull};
+  memcpy(h, clear, sizeof(clear));
+  if (t_per_row) memcpy(h + t_at, t_per_row, sizeof(float) * (size_t)nq);
+  memcpy(h + rp_at, rows.rp_host.data(), sizeof(int64_t) * (size_t)(nq + 1));
+  if (packed && nnz) {
+    memcpy(h + col_at, q_col, sizeof(int32_t) * (size_t)nnz);
+    memcpy(h + val_at, q_val, sizeof(float) * (size_t)nnz);
+  }
+  unsigned char* const in = ws.q_in.p;
+  CHK(hipMemcpyAsync(in, h, total, hipMemcpyHostToDevice, s), "copy csr");
+  if (!on_device && !packed) {
+    CHK(hipMemcpyAsync(ws.q_col.p, q_col, sizeof(int32_t) * nnz, hipMemcpyHostToDevice, s), "copy csr");
+    CHK(hipMemcpyAsync(ws.q_val.p, q_val, sizeof(float) * nnz, hipMemcpyHostToDevice, s), "copy csr");
+  }
+  const int64_t* const prp = (const int64_t*)(in + rp_at);
+  const int32_t* const pcol = on_device ? q_col : packed ? (const int32_t*)(in + col_at) : ws.q_col.p;
+  const float* const pval = on_device ? q_val : packed ? (const float*)(in + val_at) : ws.q_val.p;
+  uint32_t* const err = (uint32_t*)in;
+  unsigned long long* const bad = (unsigned long long*)in + 1;
+  if (lds) {
+    // the flags come over with the call's counters: rows that fail a check
+    // meet nothing
+    QueryRowsArgs a{};
+    a.rp = prp;
+    a.col = pcol;
+    a.val = pval;
+    a.t = t_per_row ? (const float*)(in + t_at) : nullptr;
+    a.rank = ix->rank.p;
+    a.nq = nq;
+    a.m = ix->m;
+    a.tol = 1e-5;
+    a.rc = rows.rc.p;
+    a.qmw = rows.mw.p;
+    a.rp_out = rows.rp.p;
+    a.t_out = t_per_row ? ws.qt.p : nullptr;
+    a.zero = ws.counters.p;
+    a.zeros = (int32_t)kControlWords;
+    a.err = err;
+    a.bad = bad;
+    CHK(launch_query_rows(a, longest, s), "query rows");
+    ws.pending = (const unsigned long long*)in;
+    ws.cleared = nq > 0;
+    return APSS_OK;
+  }
+  CHK(hipMemcpyAsync(rows.rp.p, prp, sizeof(int64_t) * (nq + 1), hipMemcpyDeviceToDevice, s), "copy");
+  if (t_per_row) CHK(hipMemcpyAsync(ws.qt.p, in + t_at, sizeof(float) * nq, hipMemcpyDeviceToDevice, s), "copy");
   const int rbits = ceil_log2((uint64_t)ix->m);
   const int nbits = ceil_log2((uint64_t)std::max<int64_t>(nq, 1));
   // invalid dimensions get a valid key, so the sort runs before the check
@@ -1682,9 +1748,7 @@ int stage_queries(apss_index* ix, Workspace& ws, int64_t nq, const int64_t* q_ro
       "query keys");
   if ((rc = sort_rows(ws, ss.k1.p, ss.v32a.p, nnz, nbits + rbits, rbits, rows.rc.p, err, rows.rp_host.data(), nq)))
     return rc;
-  // also completes the copies of the caller's host buffers (borrowed)
-  if ((rc = check_err(s, err, bad, "query"))) return rc;
-  return APSS_OK;
+  return check_err(s, err, bad, "query");
 }
 
 }  // namespace apss
@@ -1809,7 +1873,7 @@ int apss_build_index(int64_t n, int64_t m, const int64_t* row_ptr, const int32_t
   // the pinned counters exist from here on, so apss_join_device_noalloc needs
   // no allocation
   if (!rc && o.screen_dims == 0 && n > 0) rc = prepare(ix, ix->ws.stream, ix->variant, ix->range_rows);
-  if (!rc && !ix->ws.host_counters.reserve(C_NUM)) {
+  if (!rc && !ix->ws.host_counters.reserve(C_NUM + 2)) {
     set_error("pinned host allocation failed");
     rc = APSS_ENOMEM;
   }
@@ -1875,14 +1939,16 @@ int apss_query_device(apss_index* ix, int64_t nq, const int64_t* q_row_ptr, cons
     set_error("NULL or invalid argument");
     return APSS_EINVAL;
   }
-  RankRows rows;
+  RankRows& rows = ix->ws.q_rows;
   int rc = stage_queries(ix, ix->ws, nq, q_row_ptr, q_col, q_val, on_device, t_per_row, t, rows);
   if (rc) return rc;
   int64_t cnt = 0;
   Sink sink{out_i, out_j, out_sim, capacity};
   if ((rc = run_join(ix, ix->ws, staged_queries(rows), 0, t, t_per_row ? ix->ws.qt.p : nullptr, 16 * nq, &cnt, t_per_row,
-                     &sink)))
+                     &sink))) {
+    (void)hipStreamSynchronize(ix->ws.stream);  // (the caller's rows may still be read)
     return rc;
+  }
   return finish_device(ix->ws, cnt, ceil_log2((uint64_t)ix->n), sink, count);
 }
 
@@ -1895,15 +1961,17 @@ int apss_query(apss_index* ix, int64_t nq, const int64_t* q_row_ptr, const int32
   out->count = 0;
   out->i = out->j = nullptr;
   out->sim = nullptr;
-  RankRows rows;
-  int rc = stage_queries(ix, ix->ws, nq, q_row_ptr, q_col, q_val, on_device, t_per_row, t, rows);
-  if (rc) return rc;
-  int64_t cnt = 0;
   Sink sink;
-  if ((rc = host_sink(ix->ws, &sink))) return rc;
+  int rc = host_sink(ix->ws, &sink);
+  if (rc) return rc;
+  RankRows& rows = ix->ws.q_rows;
+  if ((rc = stage_queries(ix, ix->ws, nq, q_row_ptr, q_col, q_val, on_device, t_per_row, t, rows))) return rc;
+  int64_t cnt = 0;
   if ((rc = run_join(ix, ix->ws, staged_queries(rows), 0, t, t_per_row ? ix->ws.qt.p : nullptr, 16 * nq, &cnt, t_per_row,
-                     &sink)))
+                     &sink))) {
+    (void)hipStreamSynchronize(ix->ws.stream);  // (the caller's rows may still be read)
     return rc;
+  }
   return finish_host(ix->ws, cnt, ceil_log2((uint64_t)ix->n), sink, out);
 }
 

@@ -18,10 +18,11 @@ struct FinishArgs {
   float* out_sim;
   int64_t room;
   const unsigned long long* counters;  // [C_NUM]
-  unsigned long long* host;            // [C_NUM] pinned host copy of the counters
+  const unsigned long long* checks;    // [2] error bits and first bad row of the call's rows, or NULL
+  unsigned long long* host;            // [C_NUM + 2] pinned host copy of the counters and the checks
 };
 
-// The counters to the host; and, if there are at most kFinishPairs, cap and
+// The counters (and 0, 0 for checks that there are not) to the host; and, if there are at most kFinishPairs, cap and
 // room pairs, the pairs in order of (i, j) to out_*.
 hipError_t launch_finish(const FinishArgs& a, hipStream_t s);
 // True when launch_finish delivered a join's pairs.

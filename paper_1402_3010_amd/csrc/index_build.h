@@ -58,6 +58,28 @@ hipError_t launch_deep_offsets(const int64_t* off, const uint32_t* pos, int64_t 
                                int64_t* doff, hipStream_t s);
 hipError_t launch_block_offsets(const int64_t* off, const Post* post, int32_t H, int64_t nb, int32_t CB,
                                 uint32_t* hoff, hipStream_t s);
+// Query rows of at most kQueryRow components (longest: the longest one) in rank
+// space.  err and bad are set up before; the rest is optional (NULL, 0).
+constexpr int kQueryRow = 4096;
+struct QueryRowsArgs {
+  const int64_t* rp;
+  const int32_t* col;
+  const float* val;
+  const float* t;
+  const int32_t* rank;
+  int64_t nq, m;
+  double tol;
+  RComp* rc;
+  float* qmw;
+  int64_t* rp_out;  // copy of rp
+  float* t_out;     // copy of t
+  unsigned long long* zero;  // cleared
+  int32_t zeros;
+  uint32_t* err;
+  unsigned long long* bad;
+};
+hipError_t launch_query_rows(const QueryRowsArgs& a, int64_t longest, hipStream_t s);
+// The same for any rows, as keys (row, rank) to be sorted
 hipError_t launch_query_keys(const int64_t* rp, const int32_t* col, const float* val, const int32_t* rank, int64_t nq,
                              int64_t m, int rbits, double tol, uint64_t* keys, uint32_t* vals, float* qmw,
                              uint32_t* err, unsigned long long* bad, hipStream_t s);

@@ -11,6 +11,7 @@
 //                                     the head-cut index of the screened join, the
 //                                     components of rank < head)
 //  k_emit_indexed / k_list_offsets    inverted lists of the indexed parts, by vector id
+//  k_query_rows                       external query rows: checked, ranked, sorted
 //  k_block_offsets                    where each dense list enters each corpus block
 #include "apss_internal.h"
 #include "index_build.h"
@@ -563,6 +564,91 @@ __global__ void k_query_keys(const int64_t* __restrict__ rp, const int32_t* __re
   }
 }
 
+// Query rows of at most kQueryRow components in rank space, one workgroup per
+// row: checked, ranks gathered and sorted in LDS (n2: the longest row's length
+// as a power of two) and written once, with the row's largest weight.  A row
+// that fails a check is written with zero weights, which meet nothing, so the
+// kernels that follow need not wait for the host to read the flags.  Also
+// makes the call's copies of row_ptr and the thresholds and clears its
+// counters: a small batch is bound by launches and copies (keys, sort,
+// unpacking, fills and copies of the parts were 100 us of a query's 167).
+__global__ __launch_bounds__(256) void k_query_rows(QueryRowsArgs a, int n2max) {
+  extern __shared__ uint64_t row[];
+  __shared__ double ssq[4];
+  __shared__ float smx[4];
+  __shared__ uint32_t flags;
+  const int tid = (int)threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  if (blockIdx.x == 0)
+    for (int k = tid; k < a.zeros; k += 256) a.zero[k] = 0ull;
+  for (int64_t r = blockIdx.x; r < a.nq; r += gridDim.x) {
+    const int64_t beg = a.rp[r];
+    const int len = (int)(a.rp[r + 1] - beg);
+    if (tid == 0) {
+      flags = 0u;
+      if (a.rp_out) {
+        a.rp_out[r] = beg;
+        if (r + 1 == a.nq) a.rp_out[a.nq] = beg + len;
+      }
+      if (a.t_out) a.t_out[r] = a.t[r];
+    }
+    int n2 = 1;
+    while (n2 < len) n2 <<= 1;
+    if (n2 > n2max) n2 = n2max;  // (never: the host has the longest row)
+    uint32_t e = 0u;
+    double ss = 0.0;
+    float mx = 0.0f;
+    for (int i = tid; i < n2; i += 256) {
+      uint64_t c = ~0ull;  // above every component
+      if (i < len) {
+        const int32_t d = a.col[beg + i];
+        const float w = a.val[beg + i];
+        uint32_t rk = 0u;
+        if (d < 0 || (int64_t)d >= a.m) e |= ERR_DIM;
+        else rk = (uint32_t)a.rank[d];
+        if (!(w > 0.0f) || !isfinite(w)) e |= ERR_WEIGHT;
+        ss += (double)w * (double)w;
+        mx = fmaxf(mx, w);
+        c = ((uint64_t)rk << 32) | (uint64_t)__float_as_uint(w);
+      }
+      row[i] = c;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      ss += __shfl_xor(ss, o, 64);
+      mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    }
+    if (lane == 0) {
+      ssq[wave] = ss;
+      smx[wave] = mx;
+    }
+    __syncthreads();
+    if (e) atomicOr(&flags, e);
+    for (int size = 2; size <= n2; size <<= 1)
+      for (int stride = size >> 1; stride > 0; stride >>= 1) {
+        for (int i = tid; i < n2 / 2; i += 256) compare_exchange(row, i, stride, size);
+        __syncthreads();
+      }
+    ss = ssq[0] + ssq[1] + ssq[2] + ssq[3];
+    bool dup = false;
+    for (int i = tid + 1; i < len; i += 256) dup = dup || (uint32_t)(row[i - 1] >> 32) == (uint32_t)(row[i] >> 32);
+    if (dup) atomicOr(&flags, ERR_DUP);
+    if (tid == 0 && len > 0 && !(fabs(sqrt(ss) - 1.0) <= a.tol)) atomicOr(&flags, ERR_NORM);
+    __syncthreads();
+    const uint32_t f = flags;
+    for (int i = tid; i < len; i += 256)
+      a.rc[beg + i] = RComp{(int32_t)(row[i] >> 32), f ? 0.0f : __uint_as_float((uint32_t)row[i])};
+    if (tid == 0) {
+      a.qmw[r] = f ? 0.0f : fmaxf(fmaxf(smx[0], smx[1]), fmaxf(smx[2], smx[3]));
+      if (f) {
+        atomicOr(a.err, f);
+        atomicMin(a.bad, (unsigned long long)r);
+      }
+    }
+    __syncthreads();
+  }
+}
+
 unsigned grid(int64_t n, int threads = 256) {
   int64_t g = (n + threads - 1) / threads;
   if (g > 32768) g = 32768;
@@ -695,6 +781,18 @@ hipError_t launch_block_offsets(const int64_t* off, const Post* post, int32_t H,
                                 uint32_t* hoff, hipStream_t s) {
   LAUNCH(k_block_offsets, (nb + 1) * (int64_t)H, off, post, H, nb, CB, hoff);
   return hipSuccess;
+}
+
+hipError_t launch_query_rows(const QueryRowsArgs& a, int64_t longest, hipStream_t s) {
+  if (a.nq <= 0) return hipSuccess;
+  if (!a.rp || !a.rank || !a.rc || !a.qmw || !a.err || !a.bad || longest < 0 || longest > kQueryRow ||
+      (longest > 0 && (!a.col || !a.val)) || (a.zeros > 0 && !a.zero) || (a.t_out && !a.t))
+    return hipErrorInvalidValue;
+  int n2 = 1;
+  while (n2 < longest) n2 <<= 1;
+  hipLaunchKernelGGL(k_query_rows, dim3((unsigned)(a.nq < 16384 ? a.nq : 16384)), dim3(256),
+                     sizeof(uint64_t) * (size_t)n2, s, a, n2);
+  return hipGetLastError();
 }
 
 hipError_t launch_query_keys(const int64_t* rp, const int32_t* col, const float* val, const int32_t* rank, int64_t nq,

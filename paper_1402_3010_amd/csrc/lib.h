@@ -123,15 +123,17 @@ struct Workspace {
   hipStream_t stream = nullptr;
   SortScratch ss;
   DBuf<int64_t> tstart, qcum;
-  DBuf<unsigned int> qctr;
   DBuf<uint32_t> pq;         // survivor queue of the list-pair join
   // query sketches
   DBuf<uint8_t> q_mid, q_fsk;
   DBuf<uint32_t> q_fidx;
-  DBuf<unsigned int> q_nfine;
   bool slot = false;  // a server slot's workspace: scratch stays within the batch's reservation
   DBuf<uint32_t> wg_cur;
+  // a call's counters [C_NUM], its queue counters and the query sketches'
+  // counter of long rows: one block, cleared at once
   DBuf<unsigned long long> counters;
+  unsigned int* qctr = nullptr;
+  unsigned int* nfine = nullptr;
   DBuf<int64_t> uniq_total;  // distinct pairs after a join with local pruning
   DBuf<int32_t> qadm;        // remscore: first admitting component of each query
   DBuf<uint64_t> raw_key;
@@ -140,8 +142,14 @@ struct Workspace {
   // query CSR copied from the host (kept between calls)
   DBuf<int32_t> q_col;
   DBuf<float> q_val;
-  DBuf<uint32_t> err;
-  DBuf<unsigned long long> bad;
+  DBuf<unsigned char> q_in;          // a small host batch, copied in one piece
+  PinnedBuf<unsigned char> host_in;  // its staging
+  RankRows q_rows;                   // the index's own queries (a server's slots have theirs)
+  DBuf<unsigned long long> checks;   // error bits and first bad row of a call's rows
+  const unsigned long long* pending = nullptr;  // checks of staged queries, read at the join's end
+  bool cleared = false;                         // the staging has cleared the counters
+  uint32_t* err() const { return (uint32_t*)checks.p; }
+  unsigned long long* bad() const { return checks.p + 1; }
   // head screen of the screened join
   DBuf<uint64_t> s_keys, s_cand;
   DBuf<unsigned long long> s_cnt;
@@ -150,7 +158,7 @@ struct Workspace {
   DBuf<uint16_t> s_X;
   JoinGraph graph;
   PinnedBuf<uint32_t> host_out;  // staging of result pairs copied to the host
-  PinnedBuf<unsigned long long> host_counters;  // [C_NUM] written by the device
+  PinnedBuf<unsigned long long> host_counters;  // [C_NUM + 2] written by the device
   apss_stats last;
   int64_t regrows = 0;  // joins rerun because the pair buffer was too small
   hipEvent_t ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -159,7 +167,7 @@ struct Workspace {
       if (ev[e]) (void)hipEventDestroy(ev[e]);
   }
   int64_t bytes() const {
-    return ss.bytes() + tstart.bytes() + qcum.bytes() + qctr.bytes() + wg_cur.bytes() + counters.bytes() +
+    return ss.bytes() + tstart.bytes() + qcum.bytes() + q_in.bytes() + wg_cur.bytes() + counters.bytes() +
            raw_key.bytes() + raw_sim.bytes() + pq.bytes() + q_mid.bytes() + q_fsk.bytes() + q_fidx.bytes() + qt.bytes() + uniq_total.bytes() + qadm.bytes() + q_col.bytes() + q_val.bytes() + s_keys.bytes() + s_cand.bytes() + s_sid.bytes() +
            s_tiles.bytes() + s_nh.bytes() + s_X.bytes();
   }
@@ -275,6 +283,8 @@ void bind_plan(apss_index* ix, const QuerySet& Q, int triangle, float t, const f
 // Work queue counters of a launch: 8 queues of the accumulating join, or the
 // list-pair join's units and survivors (3).
 constexpr int kQueueCounters = 8;
+constexpr int64_t kControlWords = C_NUM + kQueueCounters / 2 + 1;
+int reserve_control(Workspace& ws);
 // Test hook outside the ABI: apss_opts.reserved[0] of an index whose self-joins
 // take the list-pair kernels, and its queries the sketch kernels, whatever the
 // cost rules say.

@@ -141,7 +141,8 @@ extern "C" int apss_join_device_noalloc(apss_index* ix, float t, uint32_t* out_i
   const int64_t qcap = pairs ? std::min<int64_t>(kQueueEntries, pair_queue_entries(ix)) : 0;
   if (pairs) L.cum.assign(1, 0);
   else if ((rc = plan_layout(ix, Q, 1, L))) return rc;
-  const size_t fixed = Carve::bytes<unsigned long long>(C_NUM) + Carve::bytes<unsigned int>(kQueueCounters) +
+  constexpr int64_t kWords = C_NUM + kQueueCounters / 2;  // counters, then queue counters
+  const size_t fixed = Carve::bytes<unsigned long long>(kWords) +
                        Carve::bytes<int64_t>(L.ntiles + 1) + Carve::bytes<int64_t>((int64_t)L.cum.size()) +
                        Carve::bytes<uint32_t>((int64_t)L.G * L.wg_stride) + Carve::bytes<uint32_t>(3 * qcap);
   if (fixed + pair_bytes(0) > kScratchBytes) {
@@ -155,8 +156,8 @@ extern "C" int apss_join_device_noalloc(apss_index* ix, float t, uint32_t* out_i
   if (room > capacity) room = capacity;
 
   Carve cv{base};
-  unsigned long long* counters = cv.take<unsigned long long>(C_NUM);
-  unsigned int* qctr = cv.take<unsigned int>(kQueueCounters);
+  unsigned long long* counters = cv.take<unsigned long long>(kWords);
+  unsigned int* qctr = (unsigned int*)(counters + C_NUM);
   int64_t* tstart = cv.take<int64_t>(L.ntiles + 1);
   int64_t* qcum = cv.take<int64_t>((int64_t)L.cum.size());
   uint32_t* wg_cur = cv.take<uint32_t>((int64_t)L.G * L.wg_stride);
@@ -179,14 +180,15 @@ extern "C" int apss_join_device_noalloc(apss_index* ix, float t, uint32_t* out_i
     APSS_CHK(hipMemcpyAsync(qcum, L.cum.data(), sizeof(int64_t) * L.cum.size(), hipMemcpyHostToDevice, s), "queues");
   }
   // the array keeps the previous call's contents: clear what starts at zero
-  APSS_CHK(fill_u64((uint64_t*)counters, 0ull, C_NUM, s), "fill");
+  APSS_CHK(fill_u64((uint64_t*)counters, 0ull, kWords, s), "fill");
   JoinPlan P;
   if (pairs) bind_pairs(ix, t, qctr, queue, qcap, P);
   else bind_plan(ix, Q, 1, t, nullptr, nullptr, L, tstart, qcum, qctr, wg_cur, P);
   APSS_CHK(hipEventRecord(ws.ev[1], s), "event");
   if ((rc = launch_plan(P, raw_key, raw_sim, room, counters, qctr, s))) return rc;
   APSS_CHK(hipEventRecord(ws.ev[2], s), "event");
-  const FinishArgs f{raw_key, raw_sim, room, P.bj, out_i, out_j, out_sim, capacity, counters, ws.host_counters.p};
+  const FinishArgs f{raw_key, raw_sim, room,     P.bj,    out_i,               out_j, out_sim,
+                     capacity, counters, nullptr, ws.host_counters.p};
   APSS_CHK(launch_finish(f, s), "finish kernel");
   APSS_CHK(hipEventRecord(ws.ev[3], s), "event");
   APSS_CHK(hipStreamSynchronize(s), "join");

@@ -221,13 +221,14 @@ void run_batch(apss_server* S, Workspace& ws, RankRows& rows, Staging& hs, std::
   apss_pairs all{0, nullptr, nullptr, nullptr};
   int rc = APSS_OK;
   if (nq > 0) {
-    rc = stage_queries(ix, ws, nq, rp, col, val, 0, tq, 1.0f, rows);
     int64_t cnt = 0;
     Sink sink;
-    if (!rc) rc = host_sink(ws, &sink);
+    rc = host_sink(ws, &sink);
+    if (!rc) rc = stage_queries(ix, ws, nq, rp, col, val, 0, tq, 1.0f, rows);
     if (!rc) {
       const QuerySet Q{rows.rp.p, rows.rc.p, rows.mw.p, rows.n, rows.nnz, rows.rp_host.data()};
       rc = run_join(ix, ws, Q, 0, 1.0f, ws.qt.p, cap, &cnt, tq, &sink);
+      if (rc) (void)hipStreamSynchronize(ws.stream);
     }
     if (!rc) rc = finish_host(ws, cnt, ceil_log2((uint64_t)ix->n), sink, &all);
   }
