@@ -132,7 +132,7 @@ hipError_t launch_bitmaps(const Post* post, const uint32_t* hoff, int32_t H, int
                           int64_t nblk, uint32_t* bm, hipStream_t s);
 // Workgroups of the kernels that fit on the device at once.
 struct PairGroups {
-  int wide = 0, shorts = 0, decide = 0;
+  int wide = 0, shorts = 0, screen = 0, decide = 0;
 };
 PairGroups pairs_resident_groups();
 // The pair tests, then the queued survivors' decisions.  Survivors past

@@ -522,6 +522,26 @@ __device__ __forceinline__ void add_counts(const PairArgs& a, unsigned long long
   }
 }
 
+// The pairs that a workgroup's waves still hold, with one reservation (see
+// add_counts for what one per wave costs).  Called by all threads.
+__device__ __forceinline__ void flush_all(const PairArgs& a, int lane, int wave, WaveEmit& em) {
+  __shared__ unsigned int held[4];
+  __shared__ unsigned long long base;
+  if (lane == 0) held[wave] = (unsigned int)em.n;
+  __syncthreads();
+  const unsigned int total = held[0] + held[1] + held[2] + held[3];
+  if (total == 0u) return;
+  if (threadIdx.x == 0) base = atomicAdd(&a.counters[C_MATCHES], (unsigned long long)total);
+  __syncthreads();
+  int64_t k = (int64_t)base + lane;
+  for (int w = 0; w < wave; ++w) k += held[w];
+  if (lane < em.n && k < a.cap) {
+    a.out_key[k] = em.key;
+    a.out_sim[k] = em.sim;
+  }
+  em.n = 0;
+}
+
 // The queued survivors: consecutive ones (which share rows) to each wave, 64
 // at a time, or fewer (at least 8) when there are not enough for every wave.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_decide(PairArgs a) {
@@ -546,7 +566,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
     decide_pairs(a, rows[wave], lane, here, x, z, (int)d, em, dc);
   }
-  em.flush(lane, a.counters, a.out_key, a.out_sim, a.cap);
+  flush_all(a, lane, wave, em);
   add_counts(a, 0ull, dc);
 }
 
@@ -583,12 +603,7 @@ struct Survivors {
     at = (unsigned int)uni((int)at);
     const int64_t room = pa.qcap - (int64_t)at;
     const int fit = room <= 0 ? 0 : (room < n ? (int)room : n);
-    for (int e = lane; e < fit; e += 64) {
-      uint32_t* const o = pa.queue + 3 * ((int64_t)at + e);
-      o[0] = a[e];
-      o[1] = b[e];
-      o[2] = d[e];
-    }
+    put(pa, lane, at, fit);
     if (pa.query) {
       if (fit < n && lane == 0) pa.counters[C_OVERFLOW] = 1ull;
       n = 0;
@@ -599,6 +614,54 @@ struct Survivors {
       decide_one(pa, lane, (uint32_t)uni((int)a[e]), (uint32_t)uni((int)b[e]), uni((int)d[e]), dc);
     n = 0;
     wave_lds_order();
+  }
+
+  __device__ __forceinline__ void put(const PairArgs& pa, int lane, unsigned int at, int fit) const {
+    for (int e = lane; e < fit; e += 64) {
+      uint32_t* const o = pa.queue + 3 * ((int64_t)at + e);
+      o[0] = a[e];
+      o[1] = b[e];
+      o[2] = d[e];
+    }
+  }
+
+  // What the waves of a workgroup still hold, with one reservation; if that
+  // does not fit, wave by wave.  Called by all threads.
+  __device__ __forceinline__ void pass_on_all(const PairArgs& pa, int lane, int wave, Decided& dc) {
+    __shared__ unsigned int held[4];
+    __shared__ unsigned int base;
+    if (lane == 0) held[wave] = (unsigned int)n;
+    __syncthreads();
+    const unsigned int total = held[0] + held[1] + held[2] + held[3];
+    if (total == 0u) return;
+    if (threadIdx.x == 0) {
+      unsigned int at = 0xFFFFFFFFu;
+      if (pa.sample == 0) {
+        at = __hip_atomic_load(&pa.uctr[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        at = (int64_t)at + (int64_t)total <= pa.qcap ? atomicAdd(&pa.uctr[2], total) : 0xFFFFFFFFu;
+      }
+      base = at;
+    }
+    __syncthreads();
+    unsigned int at = base;
+    if (at == 0xFFFFFFFFu) {
+      pass_on(pa, lane, dc);
+      return;
+    }
+    // (others may have taken the room between the load and the reservation)
+    for (int w = 0; w < wave; ++w) at += held[w];
+    const int64_t room = pa.qcap - (int64_t)at;
+    const int fit = room <= 0 ? 0 : (room < n ? (int)room : n);
+    put(pa, lane, at, fit);
+    if (fit < n) {
+      if (pa.query) {
+        if (lane == 0) pa.counters[C_OVERFLOW] = 1ull;
+      } else {
+        for (int e = fit; e < n; ++e)
+          decide_one(pa, lane, (uint32_t)uni((int)a[e]), (uint32_t)uni((int)b[e]), uni((int)d[e]), dc);
+      }
+    }
+    n = 0;
   }
 
   // Products of 64 rows (lane l holds the id of row l) with 32 columns (lane
@@ -762,7 +825,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       }
     }
   }
-  sv.pass_on(a, lane, dc);
+  sv.pass_on_all(a, lane, wave, dc);
   add_counts(a, c_visit, dc);
 }
 
@@ -844,7 +907,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
       }
     }
   }
-  sv.pass_on(a, lane, dc);
+  sv.pass_on_all(a, lane, wave, dc);
   add_counts(a, c_visit, dc);
 }
 
@@ -854,7 +917,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // product of n x 256 with 256 x nq bytes, every pair tested.  A workgroup
 // holds 256 corpus rows' sketches in registers (64 per wave) and meets the
 // queries 64 at a time through LDS (laid out as in k_pairs_wide, a step
-// ahead), so the corpus sketches are read once, in order; a few queries are
+// ahead), so the corpus sketches are read once, in order, by the workgroups
+// that fit the device, each for several blocks of rows (their last survivors
+// cost an atomic each: one per wave of 1,954 workgroups was 150 of 184 us for
+// 64 queries over 500,000 rows); a few queries are
 // bound by that (128 MB for 500,000 rows), thousands by the matrix cores:
 // 4,096 queries over 1,000,000 rows take 1.29 ms (1.6e15 operations a
 // second), with the exact count 3.1 ms and the decisions 0.8 ms where the
@@ -875,18 +941,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   const int wave = uni(tid >> 6);
   Survivors sv{qa[wave], qb[wave], qd[wave]};
   Decided dc;
-  const int64_t row0 = (int64_t)blockIdx.x * (SAMPLE ? a.sample : 1) * kWideRows + 64 * wave;
   if (SAMPLE && tid < kRateBins) bins[tid] = 0u;
-  const int na = s.n - row0 < 64 ? (int)(s.n - row0) : 64;  // may be <= 0
-  i32x4 fa[2][kMidSteps];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    int64_t r = row0 + 32 * i + (lane & 31);
-    if (r >= s.n) r = s.n - 1;  // (results of rows past the end are not used)
-    const uint8_t* p = s.sk + r * kMidGroups + 16 * (lane >> 5);
-#pragma unroll
-    for (int ks = 0; ks < kMidSteps; ++ks) fa[i][ks] = *reinterpret_cast<const i32x4*>(p + 32 * ks);
-  }
   // this thread's part of a step's columns: 64 groups of column tid / 4
   const int col = tid >> 2, part = tid & 3;
   i32x4 x[4];
@@ -899,43 +954,57 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   };
   // chunk c of column r at position c ^ (r % 16) of its row
   auto at = [](int r, int c) { return r * 16 + (c ^ (r & 15)); };
-  fetch(s.q0);
+  const int64_t step = (int64_t)gridDim.x * kWideRows * (SAMPLE ? a.sample : 1);
   int buf = 0;
-  for (int64_t b0 = s.q0; b0 < s.nq; b0 += 64, buf ^= 1) {
+  for (int64_t block0 = (int64_t)blockIdx.x * kWideRows * (SAMPLE ? a.sample : 1); block0 < s.n; block0 += step) {
+    const int64_t row0 = block0 + 64 * wave;
+    const int na = s.n - row0 < 64 ? (int)(s.n - row0) : 64;  // may be <= 0
+    i32x4 fa[2][kMidSteps];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) cols[buf][at(col, 4 * part + c)] = x[c];
-    if (b0 + 64 < s.nq) fetch(b0 + 64);
-    __syncthreads();
-    if (na > 0) {
+    for (int i = 0; i < 2; ++i) {
+      int64_t r = row0 + 32 * i + (lane & 31);
+      if (r >= s.n) r = s.n - 1;  // (results of rows past the end are not used)
+      const uint8_t* p = s.sk + r * kMidGroups + 16 * (lane >> 5);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        if (b0 + 32 * j >= s.nq) break;
-        const int r0 = 32 * j + (lane & 31);
-        const int64_t q = b0 + r0;
-        const int thr = q < s.nq ? pair_threshold(s.qt ? s.qt[q] : s.t) : 0x7FFFFFFF;
-        i32x16 acc[2];
+      for (int ks = 0; ks < kMidSteps; ++ks) fa[i][ks] = *reinterpret_cast<const i32x4*>(p + 32 * ks);
+    }
+    fetch(s.q0);
+    for (int64_t b0 = s.q0; b0 < s.nq; b0 += 64, buf ^= 1) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+      for (int c = 0; c < 4; ++c) cols[buf][at(col, 4 * part + c)] = x[c];
+      if (b0 + 64 < s.nq) fetch(b0 + 64);
+      __syncthreads();
+      if (na > 0) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][r] = 0;
-#pragma unroll
-        for (int ks = 0; ks < kMidSteps; ++ks) {
-          const i32x4 fb = cols[buf][at(r0, 2 * ks + (lane >> 5))];
-          acc[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[0][ks], fb, acc[0], 0, 0, 0);
-          acc[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[1][ks], fb, acc[1], 0, 0, 0);
-        }
-        if (SAMPLE) {
-          const float per_bin = (float)kRateBins / (float)(pair_threshold(1.0f) - pair_threshold(s.t) + 1);
+        for (int j = 0; j < 2; ++j) {
+          if (b0 + 32 * j >= s.nq) break;
+          const int r0 = 32 * j + (lane & 31);
+          const int64_t q = b0 + r0;
+          const int thr = q < s.nq ? pair_threshold(s.qt ? s.qt[q] : s.t) : 0x7FFFFFFF;
+          i32x16 acc[2];
 #pragma unroll
           for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-              if (acc[i][r] >= thr && 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3) < na) {
-                const int bin = (int)((float)(acc[i][r] - thr) * per_bin);
-                atomicAdd(&bins[bin < kRateBins ? bin : kRateBins - 1], 1u);
-              }
-        } else {
-          sv.take(a, lane, acc, (uint32_t)(row0 + lane), (uint32_t)q, 0, na, 0x7FFFFFFFu, thr, dc);
+            for (int r = 0; r < 16; ++r) acc[i][r] = 0;
+#pragma unroll
+          for (int ks = 0; ks < kMidSteps; ++ks) {
+            const i32x4 fb = cols[buf][at(r0, 2 * ks + (lane >> 5))];
+            acc[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[0][ks], fb, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[1][ks], fb, acc[1], 0, 0, 0);
+          }
+          if (SAMPLE) {
+            const float per_bin = (float)kRateBins / (float)(pair_threshold(1.0f) - pair_threshold(s.t) + 1);
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+              for (int r = 0; r < 16; ++r)
+                if (acc[i][r] >= thr && 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3) < na) {
+                  const int bin = (int)((float)(acc[i][r] - thr) * per_bin);
+                  atomicAdd(&bins[bin < kRateBins ? bin : kRateBins - 1], 1u);
+                }
+          } else {
+            sv.take(a, lane, acc, (uint32_t)(row0 + lane), (uint32_t)q, 0, na, 0x7FFFFFFFu, thr, dc);
+          }
         }
       }
     }
@@ -944,7 +1013,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     __syncthreads();
     if (tid < kRateBins && bins[tid]) atomicAdd(&a.counters[tid], (unsigned long long)bins[tid]);
   } else {
-    sv.pass_on(a, lane, dc);
+    sv.pass_on_all(a, lane, wave, dc);
   }
 }
 
@@ -1423,6 +1492,7 @@ PairGroups pairs_resident_groups() {
   PairGroups g;
   g.wide = resident(reinterpret_cast<const void*>(&k_pairs_wide));
   g.shorts = resident(reinterpret_cast<const void*>(&k_pairs_short));
+  g.screen = resident(reinterpret_cast<const void*>(&k_query_screen<false>));
   g.decide = resident(reinterpret_cast<const void*>(&k_decide));
   return g;
 }
@@ -1462,9 +1532,8 @@ hipError_t launch_query_screen(const PairArgs& a, const QueryArgs& q, const Pair
   if (!q.sk || !q.qsk || q.q0 < 0 || q.qstride <= 0 || !a.uctr || !a.counters || a.qcap <= 0 || !a.queue || !a.rp ||
       !a.rc || !a.qrp || !a.qrc || !a.fidx || !a.fsk || !a.qfidx || !a.qfsk || !a.out_key || !a.out_sim || !a.query)
     return hipErrorInvalidValue;
-  const int64_t grid = (q.n + kWideRows - 1) / kWideRows;
-  if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_query_screen<false>, dim3((unsigned)grid), dim3(256), 0, s, a, q);
+  const int64_t blocks = (q.n + kWideRows - 1) / kWideRows;
+  hipLaunchKernelGGL(k_query_screen<false>, dim3((unsigned)(blocks < g.screen ? blocks : g.screen)), dim3(256), 0, s, a, q);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_decide, dim3((unsigned)g.decide), dim3(256), 0, s, a);
