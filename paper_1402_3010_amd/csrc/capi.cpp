@@ -8,6 +8,8 @@
 
 #include <algorithm>
 #include <array>
+#include <cstddef>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -44,6 +46,112 @@ int dev_err(hipError_t e, const char* what) {
   }
   set_error("%s: %s", what, hipGetErrorString(e));
   return APSS_EDEVICE;
+}
+
+namespace {
+
+struct Spare {
+  void* p;
+  size_t size;
+  int device;
+  uint64_t stamp;  // requests made before it was put here
+};
+// (never destroyed: indexes may end after the library's statics)
+std::mutex& g_spare_mu = *new std::mutex;
+std::vector<Spare>& g_spare = *new std::vector<Spare>;  // oldest first
+uint64_t g_spare_requests = 0;
+constexpr uint64_t kSpareAge = 32;
+
+// Most bytes kept on a device.  Locked.
+size_t spare_limit(int device) {
+  static std::vector<size_t>& limit = *new std::vector<size_t>;
+  if ((size_t)device >= limit.size()) limit.resize((size_t)device + 1, 0);
+  if (!limit[(size_t)device]) {
+    hipDeviceProp_t prop;
+    limit[(size_t)device] =
+        hipGetDeviceProperties(&prop, device) == hipSuccess ? std::max<size_t>(prop.totalGlobalMem / 32, 1) : 1;
+  }
+  return limit[(size_t)device];
+}
+
+// Take out (into gone) what is old and what exceeds the device's limit.  Locked.
+void spare_trim(int device, std::vector<void*>& gone) {
+  const size_t limit = spare_limit(device);
+  size_t held = 0;
+  for (const Spare& c : g_spare) held += c.device == device ? c.size : 0;
+  for (size_t k = 0; k < g_spare.size();) {
+    const Spare& c = g_spare[k];
+    if (g_spare_requests - c.stamp > kSpareAge || (c.device == device && held > limit)) {
+      held -= c.device == device ? c.size : 0;
+      gone.push_back(c.p);
+      g_spare.erase(g_spare.begin() + (std::ptrdiff_t)k);
+    } else {
+      ++k;
+    }
+  }
+}
+
+}  // namespace
+
+hipError_t spare_take(size_t bytes, void** p, size_t* size, int* device_out) {
+  // (sizes in steps of up to a sixteenth, so that builds of like inputs match)
+  size_t step = 1 << 20;
+  while (step * 32 <= bytes) step *= 2;
+  bytes = (bytes + step - 1) / step * step;
+  int device = 0;
+  hipError_t e = hipGetDevice(&device);
+  if (e != hipSuccess) return e;
+  *device_out = device;
+  std::vector<void*> gone;
+  *p = nullptr;
+  {
+    std::lock_guard<std::mutex> lock(g_spare_mu);
+    ++g_spare_requests;
+    size_t best = g_spare.size();
+    for (size_t k = 0; k < g_spare.size(); ++k)
+      if (g_spare[k].device == device && g_spare[k].size >= bytes && g_spare[k].size <= bytes + bytes / 4 &&
+          (best == g_spare.size() || g_spare[k].size < g_spare[best].size))
+        best = k;
+    if (best < g_spare.size()) {
+      *p = g_spare[best].p;
+      *size = g_spare[best].size;
+      g_spare.erase(g_spare.begin() + (std::ptrdiff_t)best);
+    }
+    spare_trim(device, gone);
+  }
+  for (void* q : gone) (void)hipFree(q);
+  if (*p) return hipSuccess;
+  e = hipMalloc(p, bytes);
+  if (e != hipSuccess) {
+    spare_release();
+    e = hipMalloc(p, bytes);
+  }
+  if (e != hipSuccess) {
+    *p = nullptr;
+    return e;
+  }
+  *size = bytes;
+  return hipSuccess;
+}
+
+void spare_put(void* p, size_t size, int device) {
+  if (!p) return;
+  std::vector<void*> gone;
+  {
+    std::lock_guard<std::mutex> lock(g_spare_mu);
+    g_spare.push_back(Spare{p, size, device, g_spare_requests});
+    spare_trim(device, gone);
+  }
+  for (void* q : gone) (void)hipFree(q);
+}
+
+void spare_release() {
+  std::vector<Spare> all;
+  {
+    std::lock_guard<std::mutex> lock(g_spare_mu);
+    all.swap(g_spare);
+  }
+  for (const Spare& c : all) (void)hipFree(c.p);
 }
 
 namespace {
@@ -113,20 +221,20 @@ int check_bits(uint32_t err, unsigned long long bad, const char* what) {
   return APSS_EINVAL;
 }
 
-int check_err(hipStream_t s, uint32_t* err_dev, unsigned long long* bad_dev, const char* what) {
-  uint32_t err = 0;
-  unsigned long long bad = ~0ull;
-  CHK(hipMemcpyAsync(&err, err_dev, sizeof(err), hipMemcpyDeviceToHost, s), what);
-  if (bad_dev) CHK(hipMemcpyAsync(&bad, bad_dev, sizeof(bad), hipMemcpyDeviceToHost, s), what);
+// The checks' words on the device: error bits, first bad row, longest row.
+int check_err(hipStream_t s, const unsigned long long* checks, const char* what, bool row = true,
+              unsigned long long* longest = nullptr) {
+  unsigned long long w[3] = {0ull, ~0ull, 0ull};
+  CHK(hipMemcpyAsync(w, checks, sizeof(unsigned long long) * (longest ? 3 : 2), hipMemcpyDeviceToHost, s), what);
   CHK(hipStreamSynchronize(s), what);
-  return check_bits(err, bad, what);
+  if (longest) *longest = w[2];
+  return check_bits((uint32_t)w[0], row ? w[1] : ~0ull, what);
 }
 
-// Cleared error flag and first-bad-row slot of a workspace.
 int reset_err(Workspace& ws) {
-  CHK(ws.checks.reserve(2), "alloc");
-  CHK(fill_u64((uint64_t*)ws.checks.p, 0ull, 1, ws.stream), "fill");
-  CHK(fill_u64((uint64_t*)ws.bad(), ~0ull, 1, ws.stream), "fill");
+  static const unsigned long long clear[3] = {0ull, ~0ull, 0ull};
+  CHK(ws.checks.reserve(3), "alloc");
+  CHK(hipMemcpyAsync(ws.checks.p, clear, sizeof(clear), hipMemcpyHostToDevice, ws.stream), "clear checks");
   return APSS_OK;
 }
 
@@ -140,29 +248,26 @@ struct CsrDev {
   const float* pval = nullptr;
 };
 
-int stage_csr(hipStream_t s, int64_t n, const int64_t* row_ptr, const int32_t* col, const float* val, int on_device,
-              int64_t* nnz_out, CsrDev& d) {
-  int64_t nnz = 0;
+int read_nnz(hipStream_t s, int64_t n, const int64_t* row_ptr, int on_device, int64_t* nnz) {
+  if (!on_device) {
+    *nnz = row_ptr[n];
+    return APSS_OK;
+  }
+  CHK(hipMemcpyAsync(nnz, row_ptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, s), "read nnz");
+  CHK(hipStreamSynchronize(s), "read nnz");
+  return APSS_OK;
+}
+
+int stage_csr(hipStream_t s, int64_t n, int64_t nnz, const int64_t* row_ptr, const int32_t* col, const float* val,
+              int on_device, Arena& tmp, CsrDev& d) {
   if (on_device) {
-    CHK(hipMemcpyAsync(&nnz, row_ptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, s), "read nnz");
-    CHK(hipStreamSynchronize(s), "read nnz");
     d.prp = row_ptr;
     d.pcol = col;
     d.pval = val;
   } else {
-    nnz = row_ptr[n];
-    if (row_ptr[0] != 0 || nnz < 0) {
-      set_error("row_ptr must start at 0 and end at nnz >= 0");
-      return APSS_EINVAL;
-    }
-    for (int64_t r = 0; r < n; ++r)
-      if (row_ptr[r + 1] < row_ptr[r]) {
-        set_error("row_ptr must be non-decreasing (row %lld)", (long long)r);
-        return APSS_EINVAL;
-      }
-    CHK(d.rp.alloc(n + 1), "alloc csr");
-    CHK(d.col.alloc(nnz), "alloc csr");
-    CHK(d.val.alloc(nnz), "alloc csr");
+    CHK(d.rp.take(tmp, n + 1), "alloc csr");
+    CHK(d.col.take(tmp, nnz), "alloc csr");
+    CHK(d.val.take(tmp, nnz), "alloc csr");
     CHK(hipMemcpyAsync(d.rp.p, row_ptr, sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice, s), "copy csr");
     if (nnz) {
       CHK(hipMemcpyAsync(d.col.p, col, sizeof(int32_t) * nnz, hipMemcpyHostToDevice, s), "copy csr");
@@ -172,100 +277,134 @@ int stage_csr(hipStream_t s, int64_t n, const int64_t* row_ptr, const int32_t* c
     d.pcol = d.col.p;
     d.pval = d.val.p;
   }
-  if (nnz < 0 || nnz >= (1ll << 32)) {
-    set_error("nnz must be in [0, 2^32)");
-    return APSS_EINVAL;
-  }
-  *nnz_out = nnz;
   return APSS_OK;
 }
 
 int hoff_slot(int cb) { return cb == 1024 ? 0 : 1; }
 
 // cnt_r: components of each dimension, by rank (device)
-int build_lists(apss_index* ix, const uint32_t* cnt_r);
-int build_screen(apss_index* ix, int32_t head, const uint32_t* cnt_r);
+int build_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp);
+int build_screen(apss_index* ix, int32_t head, const uint32_t* cnt_r, Arena& tmp);
 
 int build_impl(apss_index* ix, const int64_t* row_ptr, const int32_t* col, const float* val, int on_device) {
   Workspace& ws = ix->ws;
   hipStream_t s = ws.stream;
   const int64_t n = ix->n, m = ix->m;
-  CsrDev in;
   int64_t nnz = 0;
-  int rc = stage_csr(s, n, row_ptr, col, val, on_device, &nnz, in);
+  int rc = read_nnz(s, n, row_ptr, on_device, &nnz);
   if (rc) return rc;
-  ix->nnz = nnz;
-
+  if (!on_device && (row_ptr[0] != 0 || nnz < 0)) {
+    set_error("row_ptr must start at 0 and end at nnz >= 0");
+    return APSS_EINVAL;
+  }
+  if (nnz < 0 || nnz >= (1ll << 32)) {
+    set_error("nnz must be in [0, 2^32)");
+    return APSS_EINVAL;
+  }
   if ((rc = reset_err(ws))) return rc;
   uint32_t* err = ws.err();
   unsigned long long* bad = ws.bad();
-  DBuf<unsigned long long> longest_dev;
-  CHK(longest_dev.alloc(1), "alloc");
-  CHK(fill_u64((uint64_t*)longest_dev.p, 0ull, 1, s), "fill");
   unsigned long long longest = 0;
-  CHK(launch_check_rowptr(in.prp, n, nnz, err, bad, longest_dev.p, s), "check row_ptr");
-  CHK(hipMemcpyAsync(&longest, longest_dev.p, sizeof(longest), hipMemcpyDeviceToHost, s), "longest row");
-  if ((rc = check_err(s, err, bad, "build_index"))) return rc;
+  if (on_device) {
+    CHK(launch_check_rowptr(row_ptr, n, nnz, err, bad, ws.checks.p + 2, s), "check row_ptr");
+    if ((rc = check_err(s, ws.checks.p, "build_index", true, &longest))) return rc;
+  } else {
+    for (int64_t r = 0; r < n; ++r) {
+      if (row_ptr[r + 1] < row_ptr[r]) {
+        set_error("row_ptr must be non-decreasing (row %lld)", (long long)r);
+        return APSS_EINVAL;
+      }
+      longest = std::max(longest, (unsigned long long)(row_ptr[r + 1] - row_ptr[r]));
+    }
+  }
+  // the build's scratch, sized for the list sort too (at most nnz postings)
+  const int64_t big = std::max<int64_t>(nnz, m);
+  Arena tmp;
+  struct Scratch {  // (the sort buffers are pieces of tmp, and end before it)
+    SortScratch& ss;
+    hipStream_t s;
+    ~Scratch() {
+      (void)hipStreamSynchronize(s);
+      for (DBuf<uint64_t>* b : {&ss.k1, &ss.k2, &ss.v64a, &ss.v64b}) b->release();
+      for (DBuf<uint32_t>* b : {&ss.v32a, &ss.v32b}) b->release();
+      for (DBuf<int64_t>* b : {&ss.hist, &ss.scan}) b->release();
+    }
+  } scratch{ws.ss, s};
+  CHK(tmp.reserve(4 * Arena::bytes<uint64_t>(big) + Arena::bytes<int64_t>(radix_hist_elems(big)) +
+                  Arena::bytes<int64_t>(radix_scan_tmp_elems(big)) + 3 * Arena::bytes<uint32_t>(m) +
+                  Arena::bytes<uint32_t>(nnz / kWaveRow + 1) + Arena::bytes<int64_t>(n + 1) +
+                  Arena::bytes<int64_t>(scan_tmp_elems(n + 1)) + 3 * Arena::bytes<int64_t>(std::max(list_tiles(nnz), m + 1)) +
+                  (on_device ? 0 : Arena::bytes<int64_t>(n + 1) + 2 * Arena::bytes<float>(nnz)) + 64 * 256),
+      "alloc scratch");
+  CHK(ix->mem.reserve(Arena::bytes<int64_t>(n + 1) + Arena::bytes<RComp>(nnz) + 3 * Arena::bytes<uint32_t>(m) +
+                      Arena::bytes<RowStat>(n) + Arena::bytes<float>(n) + Arena::bytes<uint8_t>(n) +
+                      Arena::bytes<uint32_t>(m + n)),
+      "alloc index");
+  CsrDev in;
+  if ((rc = stage_csr(s, n, nnz, row_ptr, col, val, on_device, tmp, in))) return rc;
+  ix->nnz = nnz;
 
   // the remaining checks, density order and maxweight_d(V)
   DBuf<uint32_t> cnt, mwbits, cnt_r;
-  CHK(cnt.alloc(m), "alloc");
-  CHK(mwbits.alloc(m), "alloc");
-  CHK(cnt_r.alloc(m), "alloc");
+  CHK(cnt.take(tmp, m), "alloc");
+  CHK(mwbits.take(tmp, m), "alloc");
+  CHK(cnt_r.take(tmp, m), "alloc");
   CHK(fill_u32(cnt.p, 0u, m, s), "fill");
   CHK(fill_u32(mwbits.p, 0u, m, s), "fill");
   CHK(launch_validate_count(in.prp, in.pcol, in.pval, n, m, 1e-5, cnt.p, mwbits.p, err, bad, s), "validate");
-  if ((rc = check_err(s, err, bad, "build_index"))) return rc;
+  if ((rc = check_err(s, ws.checks.p, "build_index"))) return rc;
   const int dbits = ceil_log2((uint64_t)m);
   const int cbits = ceil_log2((uint64_t)n + 1);
   SortScratch& ss = ws.ss;
-  // sized for the list sort too (at most nnz postings), so that it grows once
-  const int64_t big = std::max<int64_t>(nnz, m);
-  CHK(ss.k1.reserve(big), "alloc sort");
-  CHK(ss.v64a.reserve(big), "alloc sort");
-  CHK(ss.k2.reserve(big), "alloc sort");
-  CHK(ss.v64b.reserve(big), "alloc sort");
-  CHK(ss.hist.reserve(radix_hist_elems(big)), "alloc sort");
-  CHK(ss.scan.reserve(radix_scan_tmp_elems(big)), "alloc sort");
+  CHK(ss.k1.take(tmp, big), "alloc sort");
+  CHK(ss.v64a.take(tmp, big), "alloc sort");
+  CHK(ss.k2.take(tmp, big), "alloc sort");
+  CHK(ss.v64b.take(tmp, big), "alloc sort");
+  CHK(ss.hist.take(tmp, radix_hist_elems(big)), "alloc sort");
+  CHK(ss.scan.take(tmp, radix_scan_tmp_elems(big)), "alloc sort");
   CHK(launch_dim_keys(cnt.p, m, n, dbits, ss.k1.p, ss.v64a.p, s), "dim keys");
   CHK(radix_sort_u64(ss.k1.p, ss.v64a.p, ss.k2.p, ss.v64b.p, m, dbits + cbits, ss.hist.p, ss.scan.p, s), "dim sort");
-  CHK(ix->rank.alloc(m), "alloc");
-  CHK(ix->inv.alloc(m), "alloc");
-  CHK(ix->mw_r.alloc(m), "alloc");
+  CHK(ix->rank.take(ix->mem, m), "alloc");
+  CHK(ix->inv.take(ix->mem, m), "alloc");
+  CHK(ix->mw_r.take(ix->mem, m), "alloc");
   CHK(launch_rank_from_sorted(ss.v64a.p, m, cnt.p, mwbits.p, ix->rank.p, ix->inv.p, ix->mw_r.p, cnt_r.p, s),
       "ranks");
+
+  CHK(ix->out.take(ix->mem, m + n), "alloc");
 
   // rows in rank space, densest dimension first
   const int rbits = dbits;
   const int nbits = ceil_log2((uint64_t)std::max<int64_t>(n, 1));
   ix->rows.n = n;
   ix->rows.nnz = nnz;
-  CHK(ix->rows.rp.alloc(n + 1), "alloc");
+  CHK(ix->rows.rp.take(ix->mem, n + 1), "alloc");
   CHK(hipMemcpyAsync(ix->rows.rp.p, in.prp, sizeof(int64_t) * (n + 1), hipMemcpyDeviceToDevice, s), "copy");
   ix->rows.rp_host.resize((size_t)n + 1);
-  CHK(hipMemcpyAsync(ix->rows.rp_host.data(), in.prp, sizeof(int64_t) * (n + 1), hipMemcpyDeviceToHost, s), "copy");
-  CHK(ix->rows.rc.alloc(nnz), "alloc");
+  if (on_device)
+    CHK(hipMemcpyAsync(ix->rows.rp_host.data(), in.prp, sizeof(int64_t) * (n + 1), hipMemcpyDeviceToHost, s), "copy");
+  else memcpy(ix->rows.rp_host.data(), row_ptr, sizeof(int64_t) * (size_t)(n + 1));
+  CHK(ix->rows.rc.take(ix->mem, nnz), "alloc");
   if (longest <= (unsigned long long)kLongRow) {
     DBuf<unsigned int> nlong;
     DBuf<uint32_t> longs;
-    CHK(nlong.alloc(1), "alloc");
-    CHK(longs.alloc(nnz / kWaveRow + 1), "alloc");
+    CHK(nlong.take(tmp, 1), "alloc");
+    CHK(longs.take(tmp, nnz / kWaveRow + 1), "alloc");
     CHK(fill_u32(nlong.p, 0u, 1, s), "fill");
     CHK(launch_sort_rows(in.prp, in.pcol, in.pval, ix->rank.p, n, (int64_t)longest, ix->rows.rc.p, err, nlong.p,
                          longs.p, s),
         "row sort");
-    if ((rc = check_err(s, err, nullptr, "build_index"))) return rc;
+    if ((rc = check_err(s, ws.checks.p, "build_index", false))) return rc;
   } else {
     // a row past one workgroup's LDS: radix passes over (row, rank) keys
     CHK(ss.k1.reserve(nnz), "alloc sort");
     CHK(ss.v32a.reserve(nnz), "alloc");
     CHK(launch_row_keys(in.prp, in.pcol, in.pval, ix->rank.p, n, rbits, ss.k1.p, ss.v32a.p, s), "row keys");
     if ((rc = sort_rows(ws, ss.k1.p, ss.v32a.p, nnz, nbits + rbits, rbits, ix->rows.rc.p, err))) return rc;
-    if ((rc = check_err(s, err, nullptr, "build_index"))) return rc;
+    if ((rc = check_err(s, ws.checks.p, "build_index", false))) return rc;
   }
-  if ((rc = build_lists(ix, cnt_r.p))) return rc;
+  if ((rc = build_lists(ix, cnt_r.p, tmp))) return rc;
   if (ix->opts.screen_dims <= 0) return APSS_OK;
-  return build_screen(ix, (int32_t)std::min<int64_t>(ix->opts.screen_dims, m), cnt_r.p);
+  return build_screen(ix, (int32_t)std::min<int64_t>(ix->opts.screen_dims, m), cnt_r.p, tmp);
 }
 
 // An index whose self-joins may take the list-pair kernels: the default
@@ -287,9 +426,21 @@ bool pairs_eligible(const apss_index* ix) {
   return ix->head_cut > 0 || default_geometry(ix);
 }
 
+int32_t dense_ranks(const apss_index* ix) {
+  return (int32_t)std::min<int64_t>(ix->opts.head_dims > 0 ? ix->opts.head_dims : 32768, ix->m);
+}
+
+// Bytes of the candidate count's tables.
+int64_t count_bytes(const apss_index* ix) {
+  const int64_t H = dense_ranks(ix), blocks = (ix->n + kCountRows - 1) / kCountRows;
+  return Arena::bytes<uint32_t>(blocks * std::min<int64_t>(kCountRanks, H) * kCountWords) +
+         Arena::bytes<uint2>(blocks * H) +
+         Arena::bytes<uint32_t>(blocks * std::max<int64_t>(1, (ix->m - H + 31) / 32));
+}
+
 // Sketches, deep lists and work units, from the sorted list values in the
 // sort scratch (with the lists of every index).
-int build_pair_lists(apss_index* ix, const uint32_t* cnt_r) {
+int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   Workspace& ws = ix->ws;
   hipStream_t s = ws.stream;
   SortScratch& ss = ws.ss;
@@ -297,38 +448,42 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r) {
   const int64_t nt = list_tiles(P);
   const int64_t longest = std::max(nt, m + 1);
   DBuf<int64_t> tiles, scan, total;
-  CHK(tiles.alloc(longest), "alloc");
-  CHK(scan.alloc(scan_tmp_elems(longest)), "alloc");
-  CHK(total.alloc(1), "alloc");
+  CHK(tiles.take(tmp, longest), "alloc");
+  CHK(scan.take(tmp, scan_tmp_elems(longest)), "alloc");
+  CHK(total.take(tmp, 1), "alloc");
   int64_t deep = 0;
   CHK(launch_count_deep(ss.v64a.p, P, tiles.p, s), "deep lists");
   CHK(exclusive_scan_i64(tiles.p, nt, scan.p, total.p, s), "scan");
   CHK(hipMemcpyAsync(&deep, total.p, sizeof(int64_t), hipMemcpyDeviceToHost, s), "deep lists");
   CHK(hipStreamSynchronize(s), "deep lists");
-  CHK(ix->dl.alloc(deep), "alloc");
-  CHK(ix->doff.alloc(m + 1), "alloc");
+  int64_t longs = 0;
+  for (int64_t r = 0; r < n; ++r) longs += ix->rows.rp_host[(size_t)r + 1] - ix->rows.rp_host[(size_t)r] > kFineRow;
+  CHK(ix->pair_mem.reserve(Arena::bytes<uint32_t>(deep) + Arena::bytes<int64_t>(m + 1) + Arena::bytes<uint16_t>(m) +
+                           Arena::bytes<uint8_t>(n * kSkGroups) + Arena::bytes<uint8_t>(n * kMidGroups) +
+                           Arena::bytes<uint32_t>(n) + Arena::bytes<uint8_t>(longs * kFineGroups)),
+      "alloc tables");
+  CHK(ix->dl.take(ix->pair_mem, deep), "alloc");
+  CHK(ix->doff.take(ix->pair_mem, m + 1), "alloc");
   uint32_t* pos = (uint32_t*)ss.k2.p;  // the sort's second keys are free
   CHK(launch_lists(ss.v64a.p, P, ix->post.p, ix->post4.p, tiles.p, pos, ix->dl.p, s), "lists");
   CHK(launch_deep_offsets(ix->off.p, pos, P, m, deep, ix->doff.p, s), "deep lists");
   // groups of ranks of about equal component counts, and the sketches
-  CHK(ix->gid.alloc(m), "alloc");
-  CHK(ix->sk.alloc(n * kSkGroups), "alloc");
+  CHK(ix->gid.take(ix->pair_mem, m), "alloc");
+  CHK(ix->sk.take(ix->pair_mem, n * kSkGroups), "alloc");
   CHK(launch_widen(cnt_r, m, tiles.p, s), "groups");
   CHK(exclusive_scan_i64(tiles.p, m, scan.p, nullptr, s), "scan");
   CHK(launch_groups(tiles.p, cnt_r, m, ix->nnz, ix->gid.p, s), "groups");
-  int64_t longs = 0;
-  for (int64_t r = 0; r < n; ++r) longs += ix->rows.rp_host[(size_t)r + 1] - ix->rows.rp_host[(size_t)r] > kFineRow;
-  CHK(ix->mid.alloc(n * kMidGroups), "alloc");
-  CHK(ix->fidx.alloc(n), "alloc");
-  CHK(ix->fsk.alloc(longs * kFineGroups), "alloc");
+  CHK(ix->mid.take(ix->pair_mem, n * kMidGroups), "alloc");
+  CHK(ix->fidx.take(ix->pair_mem, n), "alloc");
+  CHK(ix->fsk.take(ix->pair_mem, longs * kFineGroups), "alloc");
   DBuf<unsigned int> nfine;
-  CHK(nfine.alloc(1), "alloc");
+  CHK(nfine.take(tmp, 1), "alloc");
   CHK(fill_u32(nfine.p, 0u, 1, s), "fill");
   CHK(launch_sketch(ix->rows.rp.p, ix->rows.rc.p, ix->gid.p, n, ix->sk.p, ix->mid.p, nfine.p, ix->fidx.p,
                     ix->fsk.p, s), "sketches");
   // work units by rank
   DBuf<int64_t> stiles;
-  CHK(stiles.alloc(m + 1), "alloc");
+  CHK(stiles.take(tmp, m + 1), "alloc");
   CHK(launch_unit_counts(ix->doff.p, m, true, tiles.p, s), "units");
   CHK(launch_unit_counts(ix->doff.p, m, false, stiles.p, s), "units");
   CHK(exclusive_scan_i64(tiles.p, m, scan.p, total.p, s), "scan");
@@ -336,8 +491,11 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r) {
   CHK(exclusive_scan_i64(stiles.p, m, scan.p, total.p, s), "scan");
   CHK(hipMemcpyAsync(&ix->nshort, total.p, sizeof(int64_t), hipMemcpyDeviceToHost, s), "units");
   CHK(hipStreamSynchronize(s), "units");
-  CHK(ix->wide.alloc(ix->nwide), "alloc");
-  CHK(ix->shorts.alloc(ix->nshort), "alloc");
+  // (with the candidate count's tables: see build_bitmaps)
+  CHK(ix->pair_mem.reserve(Arena::bytes<uint2>(ix->nwide) + Arena::bytes<uint2>(ix->nshort) + count_bytes(ix)),
+      "alloc tables");
+  CHK(ix->wide.take(ix->pair_mem, ix->nwide), "alloc");
+  CHK(ix->shorts.take(ix->pair_mem, ix->nshort), "alloc");
   CHK(launch_unit_fill(ix->doff.p, tiles.p, m, true, ix->wide.p, s), "units");
   CHK(launch_unit_fill(ix->doff.p, stiles.p, m, false, ix->shorts.p, s), "units");
   ix->pair_groups = pairs_resident_groups();
@@ -356,7 +514,7 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r) {
   // are most pairs, and the accumulating kernel is ahead.  A join at a higher
   // threshold than the index's has fewer.
   DBuf<unsigned long long> cnt;
-  CHK(cnt.alloc(C_NUM + kRateBins), "alloc");
+  CHK(cnt.take(tmp, C_NUM + kRateBins), "alloc");
   if (int rc = reserve_control(ws)) return rc;
   CHK(fill_u64((uint64_t*)cnt.p, 0ull, C_NUM + kRateBins, s), "fill");
   CHK(fill_u32(ws.qctr, 0u, kQueueCounters, s), "fill");
@@ -391,6 +549,7 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r) {
   // against 0.27 ms for 2,000 rows, so there only many survivors decide)
   const bool few = k * (double)c[C_SURVIVORS] <= 64.0 * (double)n;
   ix->pairs_ready = n <= kCountRows ? few : pairs_ms < lists_ms;
+  ix->pair_survivors = k * (double)c[C_SURVIVORS];
   if (ix->opts.reserved[0] == kProbePairs) ix->pairs_ready = true;
   // Queries, per pair of a query and a row: 0.32 ps for the test and 0.49 for
   // the count at 110 indexed components a row, against 0.9 and 0.83 per list
@@ -410,18 +569,13 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r) {
   ix->screen_queries = ix->head_cut == 0 && ix->opts.query_safe &&
                        (ix->screen_ps + kSurvivorPs * ix->rate[kRateBins / 2] < ix->accumulate_ps ||
                         ix->opts.reserved[0] == kProbePairs);
-  if (!ix->pairs_ready) {
-    ix->sk.release();
-    ix->dl.release();
-    ix->doff.release();
-    ix->wide.release();
-    ix->shorts.release();
-  }
-  if (!ix->screen_queries) ix->mid.release();
   if (!ix->pairs_ready && !ix->screen_queries) {
-    ix->fsk.release();
+    for (DBuf<uint8_t>* b : {&ix->sk, &ix->mid, &ix->fsk}) b->release();
+    for (DBuf<uint32_t>* b : {&ix->dl, &ix->fidx}) b->release();
+    for (DBuf<uint2>* b : {&ix->wide, &ix->shorts}) b->release();
     ix->gid.release();
-    ix->fidx.release();
+    ix->doff.release();
+    ix->pair_mem.release();  // (the stream has drained)
   }
   return APSS_OK;
 }
@@ -433,13 +587,13 @@ int build_bitmaps(apss_index* ix) {
   // (the head-cut index of the screened join has no dense lists)
   ix->count_ranks = ix->head_cut > 0 ? 0 : std::min<int32_t>(kCountRanks, ix->H);
   ix->count_blocks = (ix->n + kCountRows - 1) / kCountRows;
-  CHK(ix->bm.alloc(ix->count_blocks * ix->count_ranks * kCountWords), "alloc");
-  CHK(ix->seg.alloc(ix->count_blocks * ix->H), "alloc");
+  CHK(ix->bm.take(ix->pair_mem, ix->count_blocks * ix->count_ranks * kCountWords), "alloc");
+  CHK(ix->seg.take(ix->pair_mem, ix->count_blocks * ix->H), "alloc");
   CHK(launch_segments(ix->hoff[slot].p, ix->H, cb, ix->hoff_nb[slot], ix->count_blocks, ix->seg.p, ix->ws.stream),
       "bitmaps");
   ix->present_words = std::max<int64_t>(1, (ix->m - ix->H + 31) / 32);
   const int64_t nw = ix->count_blocks * ix->present_words;
-  CHK(ix->present.alloc(nw), "alloc");
+  CHK(ix->present.take(ix->pair_mem, nw), "alloc");
   CHK(fill_u32(ix->present.p, 0u, nw, ix->ws.stream), "fill");
   CHK(launch_present(ix->off.p, ix->post.p, ix->H, ix->m, ix->present_words, ix->present.p, ix->ws.stream), "bitmaps");
   CHK(launch_bitmaps(ix->post.p, ix->hoff[slot].p, ix->H, cb, ix->hoff_nb[slot], ix->count_ranks, ix->count_blocks,
@@ -450,7 +604,7 @@ int build_bitmaps(apss_index* ix) {
 
 // From the rank-space rows on: cutoff of every row, the inverted lists of
 // the indexed parts and the lookup tables of the join.
-int build_lists(apss_index* ix, const uint32_t* cnt_r) {
+int build_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   Workspace& ws = ix->ws;
   hipStream_t s = ws.stream;
   SortScratch& ss = ws.ss;
@@ -459,12 +613,12 @@ int build_lists(apss_index* ix, const uint32_t* cnt_r) {
   int rc = APSS_OK;
 
   // cutoff of the unindexed part
-  CHK(ix->rs.alloc(n), "alloc");
-  CHK(ix->rows.mw.alloc(n), "alloc");
+  CHK(ix->rs.take(ix->mem, n), "alloc");
+  CHK(ix->rows.mw.take(ix->mem, n), "alloc");
   DBuf<int64_t> nidx, scan_tmp, total;
-  CHK(nidx.alloc(n + 1), "alloc");
-  CHK(scan_tmp.alloc(scan_tmp_elems(n + 1)), "alloc");
-  CHK(total.alloc(1), "alloc");
+  CHK(nidx.take(tmp, n + 1), "alloc");
+  CHK(scan_tmp.take(tmp, scan_tmp_elems(n + 1)), "alloc");
+  CHK(total.take(tmp, 1), "alloc");
   // head >= 0: the unindexed part of every row is its components of rank
   // below head (the screened join's head cut, or nothing at all for the
   // all-pairs-0-array index); -1: the paper's cutoff
@@ -472,8 +626,8 @@ int build_lists(apss_index* ix, const uint32_t* cnt_r) {
   // (with the largest unindexed-part norm and each row's as a byte: the
   // hashed filter's tests before it reads a row's statistics)
   DBuf<uint32_t> pmax;
-  CHK(pmax.alloc(1), "alloc");
-  CHK(ix->pn8.alloc(std::max<int64_t>(n, 1)), "alloc");
+  CHK(pmax.take(tmp, 1), "alloc");
+  CHK(ix->pn8.take(ix->mem, std::max<int64_t>(n, 1)), "alloc");
   CHK(fill_u32(pmax.p, 0u, 1, s), "fill");
   CHK(launch_cutoff(ix->rows.rp.p, ix->rows.rc.p, ix->mw_r.p, n, ix->t_build, ix->opts.query_safe ? 1 : 0, head,
                     ix->rs.p, ix->rows.mw.p, nidx.p, pmax.p, ix->pn8.p, s),
@@ -491,6 +645,15 @@ int build_lists(apss_index* ix, const uint32_t* cnt_r) {
     return APSS_EINVAL;
   }
 
+  {
+    int qt = 0, cb = 1024;
+    (void)join_variant_geometry(ix->variant, &qt, &cb);
+    const int64_t H = dense_ranks(ix), nb = (n + cb - 1) / cb;
+    const int64_t K = std::max<int64_t>(1, ix->range_rows / cb), nR = (nb + K - 1) / K;
+    CHK(ix->mem.reserve(Arena::bytes<int64_t>(m + 1) + Arena::bytes<Post>(P + 2) + Arena::bytes<uint32_t>(P + kPost4Pad) +
+                        Arena::bytes<uint32_t>((nb + 1) * H) + Arena::bytes<uint32_t>((nR + 1) * std::max<int64_t>(m - H, 1))),
+        "alloc index");
+  }
   // inverted lists of the indexed parts: stable sort by rank keeps vector ids ascending
   CHK(ss.k1.reserve(P), "alloc");
   CHK(ss.k2.reserve(P), "alloc");
@@ -503,19 +666,19 @@ int build_lists(apss_index* ix, const uint32_t* cnt_r) {
   const double lim = pairs ? (double)ix->t_build * (double)ix->t_build * (1.0 - 1e-4) : -1.0;
   CHK(launch_emit_indexed(ix->rows.rp.p, ix->rows.rc.p, ix->rs.p, nidx.p, n, lim, ss.k1.p, ss.v64a.p, s), "emit");
   CHK(radix_sort_u64(ss.k1.p, ss.v64a.p, ss.k2.p, ss.v64b.p, P, rbits, ss.hist.p, ss.scan.p, s), "list sort");
-  CHK(ix->off.alloc(m + 1), "alloc");
+  CHK(ix->off.take(ix->mem, m + 1), "alloc");
   CHK(launch_list_offsets(ss.k1.p, P, m, ix->off.p, s), "list offsets");
   // two padding entries after the last list let the join read positions p
   // and p + 1 for any p <= P (p = 0 too when there are no lists)
-  CHK(ix->post.alloc(P + 2), "alloc");
+  CHK(ix->post.take(ix->mem, P + 2), "alloc");
   CHK(fill_u64((uint64_t*)ix->post.p + P, ~0ull, 2, s), "fill");
   // the join's list loads put a chunk's base in the scalar offset, which the
   // hardware range check does not cover: 64 zero entries after the last list
   // keep a chunk's lanes past its end inside the allocation
-  CHK(ix->post4.alloc(P + kPost4Pad), "alloc");
+  CHK(ix->post4.take(ix->mem, P + kPost4Pad), "alloc");
   CHK(fill_u32(ix->post4.p + P, 0u, kPost4Pad, s), "fill");
   if (pairs) {
-    if ((rc = build_pair_lists(ix, cnt_r))) return rc;
+    if ((rc = build_pair_lists(ix, cnt_r, tmp))) return rc;
   } else {
     CHK(launch_lists(ss.v64a.p, P, ix->post.p, ix->post4.p, nullptr, nullptr, nullptr, s), "lists");
   }
@@ -535,17 +698,18 @@ int build_lists(apss_index* ix, const uint32_t* cnt_r) {
       ix->part_lo_host[(size_t)r] = (int32_t)std::max<int64_t>(ix->part_lo_host[(size_t)r - 1], std::min<int64_t>(k, m));
     }
     ix->part_lo_host[(size_t)ix->parts] = (int32_t)m;
-    CHK(ix->part_lo.alloc(ix->parts + 1), "alloc");
+    CHK(ix->part_lo.take(ix->mem, ix->parts + 1), "alloc");
     CHK(hipMemcpyAsync(ix->part_lo.p, ix->part_lo_host.data(), sizeof(int32_t) * (ix->parts + 1),
                        hipMemcpyHostToDevice, s),
         "parts");
   }
 
   // per-block offsets of the dense lists, for the default tile variant
-  int32_t H = ix->opts.head_dims > 0 ? ix->opts.head_dims : 32768;
-  if (H > m) H = (int32_t)m;
-  ix->H = H;
-  if ((rc = prepare(ix, s, ix->variant, ix->range_rows))) return rc;
+  ix->H = dense_ranks(ix);
+  ix->building = true;
+  rc = prepare(ix, s, ix->variant, ix->range_rows);
+  ix->building = false;
+  if (rc) return rc;
   if ((ix->pairs_ready || ix->screen_queries) && (rc = build_bitmaps(ix))) return rc;
   CHK(hipStreamSynchronize(s), "build_index");
   // sort scratch is re-grown on demand by the joins
@@ -559,15 +723,15 @@ int build_lists(apss_index* ix, const uint32_t* cnt_r) {
 }
 
 template <typename T>
-int copy_buf(DBuf<T>& dst, const DBuf<T>& src, int64_t count, hipStream_t s) {
-  CHK(dst.alloc(count), "alloc");
+int copy_buf(Arena& a, DBuf<T>& dst, const DBuf<T>& src, int64_t count, hipStream_t s) {
+  CHK(dst.take(a, count), "alloc");
   if (count > 0) CHK(hipMemcpyAsync(dst.p, src.p, sizeof(T) * count, hipMemcpyDeviceToDevice, s), "copy");
   return APSS_OK;
 }
 
 // The head-cut index of the screened join: the same rank-space rows, with
 // every row's unindexed part set to its components of rank < head.
-int build_screen(apss_index* ix, int32_t head, const uint32_t* cnt_r) {
+int build_screen(apss_index* ix, int32_t head, const uint32_t* cnt_r, Arena& tmp) {
   apss_index* sx = new (std::nothrow) apss_index();
   if (!sx) {
     set_error("host allocation failed");
@@ -591,11 +755,10 @@ int build_screen(apss_index* ix, int32_t head, const uint32_t* cnt_r) {
   sx->rows.nnz = ix->rows.nnz;
   sx->rows.rp_host = ix->rows.rp_host;
   int rc;
-  if ((rc = copy_buf(sx->rows.rp, ix->rows.rp, ix->n + 1, s))) return rc;
-  if ((rc = copy_buf(sx->rows.rc, ix->rows.rc, ix->nnz, s))) return rc;
-  if ((rc = copy_buf(sx->mw_r, ix->mw_r, ix->m, s))) return rc;
-  CHK(sx->rows.mw.alloc(ix->n), "alloc");
-  return build_lists(sx, cnt_r);
+  if ((rc = copy_buf(sx->mem, sx->rows.rp, ix->rows.rp, ix->n + 1, s))) return rc;
+  if ((rc = copy_buf(sx->mem, sx->rows.rc, ix->rows.rc, ix->nnz, s))) return rc;
+  if ((rc = copy_buf(sx->mem, sx->mw_r, ix->mw_r, ix->m, s))) return rc;
+    return build_lists(sx, cnt_r, tmp);
 }
 
 // Query tiles: consecutive queries, at most QT of them and, unless a single
@@ -644,7 +807,8 @@ int prepare(apss_index* ix, hipStream_t s, int variant, int64_t range_rows) {
   const int slot = hoff_slot(cb);
   if (!ix->hoff[slot].p) {
     const int64_t nb = (ix->n + cb - 1) / cb;
-    CHK(ix->hoff[slot].alloc((nb + 1) * (int64_t)ix->H), "alloc block offsets");
+    const int64_t words = (nb + 1) * (int64_t)ix->H;
+    CHK(ix->building ? ix->hoff[slot].take(ix->mem, words) : ix->hoff[slot].alloc(words), "alloc block offsets");
     CHK(launch_block_offsets(ix->off.p, ix->post.p, ix->H, nb, cb, ix->hoff[slot].p, s), "block offsets");
     ix->hoff_nb[slot] = nb;
     built = true;
@@ -652,7 +816,8 @@ int prepare(apss_index* ix, hipStream_t s, int variant, int64_t range_rows) {
   if (!ix->toff.p || ix->toff_rows != range_rows) {
     const int64_t nb = (ix->n + cb - 1) / cb;
     const int64_t nR = (nb + K - 1) / K;
-    CHK(ix->toff.alloc((nR + 1) * std::max<int64_t>(ix->m - ix->H, 1)), "alloc range offsets");
+    const int64_t words = (nR + 1) * std::max<int64_t>(ix->m - ix->H, 1);
+    CHK(ix->building ? ix->toff.take(ix->mem, words) : ix->toff.alloc(words), "alloc range offsets");
     CHK(launch_range_offsets(ix->off.p, ix->post.p, ix->H, ix->m, nR, range_rows, ix->toff.p, s), "range offsets");
     ix->toff_rows = range_rows;
     ix->toff_nR = nR;
@@ -784,10 +949,10 @@ int plan_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, fl
 
 bool use_pairs(const apss_index* ix) { return ix->pairs_ready && !ix->pairs_off; }
 
-// 256 per row covers the survivors of the million-vector workloads many times
-// over; between 1M and 64M entries of 12 bytes.
+// Twice the survivors that the sample foretells for the lowest threshold; up
+// to 64M entries of 12 bytes.
 int64_t pair_queue_entries(const apss_index* ix) {
-  return std::max<int64_t>(1 << 20, std::min<int64_t>(256 * ix->n, 64ll << 20));
+  return (int64_t)std::min(2.0 * ix->pair_survivors + 65536.0, 64.0 * (1 << 20));
 }
 
 // The index's part of a candidate count.
@@ -1058,12 +1223,15 @@ int start_call(Workspace& ws, bool keep_graph = false) {
   return APSS_OK;
 }
 
+int reserve_host(Workspace& ws) {
+  if (ws.host_counters.reserve(kHostWords)) return APSS_OK;
+  set_error("pinned host allocation failed");
+  return APSS_ENOMEM;
+}
+
 int host_sink(Workspace& ws, Sink* sink) {
-  if (!ws.host_out.reserve((size_t)(3 * kFinishPairs))) {
-    set_error("pinned host allocation failed");
-    return APSS_ENOMEM;
-  }
-  sink->i = ws.host_out.p;
+  if (int rc = reserve_host(ws)) return rc;
+  sink->i = (uint32_t*)(ws.host_counters.p + C_NUM + 2);
   sink->j = sink->i + kFinishPairs;
   sink->sim = (float*)(sink->j + kFinishPairs);
   sink->room = kFinishPairs;
@@ -1074,10 +1242,7 @@ int host_sink(Workspace& ws, Sink* sink) {
 // has drained, and the pairs at the sink if they are few.
 int hand_over(Workspace& ws, int bj, const Sink* sink, const unsigned long long* checks = nullptr) {
   hipStream_t s = ws.stream;
-  if (!ws.host_counters.reserve(C_NUM + 2)) {
-    set_error("pinned host allocation failed");
-    return APSS_ENOMEM;
-  }
+  if (int rc = reserve_host(ws)) return rc;
   FinishArgs f{};
   f.key = ws.raw_key.p;
   f.sim = ws.raw_sim.p;
@@ -1109,7 +1274,7 @@ int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, flo
   ws.pending = nullptr;
   ws.cleared = false;
   if (Q.n == 0) return APSS_OK;
-  if (ix->n == 0) return checks ? check_err(s, (uint32_t*)checks, (unsigned long long*)checks + 1, "query") : APSS_OK;
+  if (ix->n == 0) return checks ? check_err(s, checks, "query") : APSS_OK;
   if (!cleared) {
     if ((rc = reserve_control(ws))) return rc;
     CHK(fill_u64((uint64_t*)ws.counters.p, 0ull, kControlWords, s), "fill");
@@ -1748,7 +1913,7 @@ int stage_queries(apss_index* ix, Workspace& ws, int64_t nq, const int64_t* q_ro
       "query keys");
   if ((rc = sort_rows(ws, ss.k1.p, ss.v32a.p, nnz, nbits + rbits, rbits, rows.rc.p, err, rows.rp_host.data(), nq)))
     return rc;
-  return check_err(s, err, bad, "query");
+  return check_err(s, (const unsigned long long*)in, "query");
 }
 
 }  // namespace apss
@@ -1873,10 +2038,7 @@ int apss_build_index(int64_t n, int64_t m, const int64_t* row_ptr, const int32_t
   // the pinned counters exist from here on, so apss_join_device_noalloc needs
   // no allocation
   if (!rc && o.screen_dims == 0 && n > 0) rc = prepare(ix, ix->ws.stream, ix->variant, ix->range_rows);
-  if (!rc && !ix->ws.host_counters.reserve(C_NUM + 2)) {
-    set_error("pinned host allocation failed");
-    rc = APSS_ENOMEM;
-  }
+  if (!rc) rc = reserve_host(ix->ws);
   for (int e = 0; !rc && e < 6; ++e)
     if (hipEventCreateWithFlags(&ix->ws.ev[e], hipEventDefault) != hipSuccess) {
       set_error("hipEventCreateWithFlags failed");
@@ -2001,24 +2163,15 @@ int apss_index_export(const apss_index* ix, int32_t* rank, float* maxweight, int
   }
   hipStream_t s = ix->ws.stream;
   if (rank) CHK(hipMemcpyAsync(rank, ix->rank.p, sizeof(int32_t) * ix->m, hipMemcpyDeviceToHost, s), "export");
-  std::vector<float> mwr;
-  std::vector<int32_t> inv;
-  if (maxweight) {
-    mwr.resize((size_t)ix->m);
-    inv.resize((size_t)ix->m);
-    CHK(hipMemcpyAsync(mwr.data(), ix->mw_r.p, sizeof(float) * ix->m, hipMemcpyDeviceToHost, s), "export");
-    CHK(hipMemcpyAsync(inv.data(), ix->inv.p, sizeof(int32_t) * ix->m, hipMemcpyDeviceToHost, s), "export");
-  }
-  std::vector<RowStat> st;
-  if (cut && ix->n) {
-    st.resize((size_t)ix->n);
-    CHK(hipMemcpyAsync(st.data(), ix->rs.p, sizeof(RowStat) * ix->n, hipMemcpyDeviceToHost, s), "export");
+  if (maxweight || (cut && ix->n)) {
+    float* const mw = (float*)ix->out.p;
+    int32_t* const cuts = (int32_t*)ix->out.p + ix->m;
+    CHK(launch_export(ix->rank.p, ix->mw_r.p, ix->m, ix->rs.p, ix->n, maxweight ? mw : nullptr, cut ? cuts : nullptr, s),
+        "export");
+    if (maxweight) CHK(hipMemcpyAsync(maxweight, mw, sizeof(float) * ix->m, hipMemcpyDeviceToHost, s), "export");
+    if (cut && ix->n) CHK(hipMemcpyAsync(cut, cuts, sizeof(int32_t) * ix->n, hipMemcpyDeviceToHost, s), "export");
   }
   CHK(hipStreamSynchronize(s), "export");
-  if (maxweight)
-    for (int64_t r = 0; r < ix->m; ++r) maxweight[inv[(size_t)r]] = mwr[(size_t)r];
-  if (cut)
-    for (int64_t i = 0; i < ix->n; ++i) cut[i] = st[(size_t)i].cut;
   return APSS_OK;
 }
 

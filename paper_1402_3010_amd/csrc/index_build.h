@@ -58,6 +58,9 @@ hipError_t launch_deep_offsets(const int64_t* off, const uint32_t* pos, int64_t 
                                int64_t* doff, hipStream_t s);
 hipError_t launch_block_offsets(const int64_t* off, const Post* post, int32_t H, int64_t nb, int32_t CB,
                                 uint32_t* hoff, hipStream_t s);
+// mw[d] = maxweight of dimension d, cut[i] = unindexed components of row i (either may be NULL)
+hipError_t launch_export(const int32_t* rank, const float* mw_r, int64_t m, const RowStat* rs, int64_t n, float* mw,
+                         int32_t* cut, hipStream_t s);
 // Query rows of at most kQueryRow components (longest: the longest one) in rank
 // space.  err and bad are set up before; the rest is optional (NULL, 0).
 constexpr int kQueryRow = 4096;

@@ -649,6 +649,15 @@ __global__ __launch_bounds__(256) void k_query_rows(QueryRowsArgs a, int n2max) 
   }
 }
 
+// maxweight by dimension id, and the rows' cuts
+__global__ void k_export(const int32_t* __restrict__ rank, const float* __restrict__ mw_r, int64_t m,
+                         const RowStat* __restrict__ rs, int64_t n, float* __restrict__ mw, int32_t* __restrict__ cut) {
+  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < m || k < n; k += (int64_t)gridDim.x * blockDim.x) {
+    if (mw && k < m) mw[k] = mw_r[rank[k]];
+    if (cut && k < n) cut[k] = rs[k].cut;
+  }
+}
+
 unsigned grid(int64_t n, int threads = 256) {
   int64_t g = (n + threads - 1) / threads;
   if (g > 32768) g = 32768;
@@ -781,6 +790,12 @@ hipError_t launch_block_offsets(const int64_t* off, const Post* post, int32_t H,
                                 uint32_t* hoff, hipStream_t s) {
   LAUNCH(k_block_offsets, (nb + 1) * (int64_t)H, off, post, H, nb, CB, hoff);
   return hipSuccess;
+}
+
+hipError_t launch_export(const int32_t* rank, const float* mw_r, int64_t m, const RowStat* rs, int64_t n, float* mw,
+                         int32_t* cut, hipStream_t s) {
+  hipLaunchKernelGGL(k_export, dim3(grid(m > n ? m : n)), dim3(256), 0, s, rank, mw_r, m, rs, n, mw, cut);
+  return hipGetLastError();
 }
 
 hipError_t launch_query_rows(const QueryRowsArgs& a, int64_t longest, hipStream_t s) {

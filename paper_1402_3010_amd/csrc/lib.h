@@ -11,29 +11,112 @@
 #include "../../include/apss.h"
 #include "apss_internal.h"
 #include "few.h"
+#include "finish.h"
 #include "join.h"
 #include "pairs.h"
 
 namespace apss {
 
 // Owned device allocation.
+// Device memory that ended builds and indexes leave to the next ones
+// (capi.cpp): at most 1/32 of the device's, given back when it has not been
+// taken for 32 requests, when it exceeds that, and when memory runs out.  A
+// chunk is put there only once nothing that uses it is in flight; its
+// contents are whatever its last owner left.  Any thread may call these.
+hipError_t spare_take(size_t bytes, void** p, size_t* size, int* device);
+void spare_put(void* p, size_t size, int device);
+void spare_release();
+
+// Device memory of one owner, handed out in pieces and given back all at once
+// when it ends: an allocation of some size costs 30 to 100 us and its release
+// (which waits for the device) 20 to 300, and an index is made of forty; and
+// once a process has used as much memory as the device has, the driver clears
+// what it hands out again at some 50 GB a second, which made 70 of the 86 ms
+// of building an index of 500,000 rows (2 GB and as much scratch).  The owner
+// says how much it is about to take; what does not fit gets a chunk of its
+// own.  It ends after its stream has drained.
+class Arena {
+ public:
+  Arena() = default;
+  Arena(const Arena&) = delete;
+  Arena& operator=(const Arena&) = delete;
+  ~Arena() { release(); }
+  void release() {
+    for (const Chunk& c : chunks_) spare_put(c.p, c.size, c.device);
+    chunks_.clear();
+    at_ = end_ = nullptr;
+  }
+  // bytes that count elements of a buffer take
+  template <typename T>
+  static int64_t bytes(int64_t count) {
+    return ((count > 0 ? count : 1) * (int64_t)sizeof(T) + 255) / 256 * 256;
+  }
+  hipError_t reserve(int64_t bytes) {
+    if (end_ - at_ >= bytes) return hipSuccess;
+    Chunk c;
+    const hipError_t e = spare_take((size_t)bytes, &c.p, &c.size, &c.device);
+    if (e != hipSuccess) return e;
+    chunks_.push_back(c);
+    at_ = (char*)c.p;
+    end_ = at_ + c.size;
+    return hipSuccess;
+  }
+  template <typename T>
+  hipError_t take(int64_t count, T** out) {
+    const int64_t b = bytes<T>(count);
+    const hipError_t e = reserve(b);
+    if (e != hipSuccess) return e;
+    *out = (T*)at_;
+    at_ += b;
+    return hipSuccess;
+  }
+
+ private:
+  struct Chunk {
+    void* p = nullptr;
+    size_t size = 0;
+    int device = 0;
+  };
+  std::vector<Chunk> chunks_;
+  char* at_ = nullptr;
+  char* end_ = nullptr;
+};
+
 template <typename T>
 struct DBuf {
   T* p = nullptr;
   int64_t n = 0;
+  bool owned = true;  // else a piece of an arena
   DBuf() = default;
   DBuf(const DBuf&) = delete;
   DBuf& operator=(const DBuf&) = delete;
   ~DBuf() { release(); }
   void release() {
-    if (p) (void)hipFree(p);
+    if (p && owned) (void)hipFree(p);
     p = nullptr;
     n = 0;
+    owned = true;
+  }
+  hipError_t take(Arena& a, int64_t count) {
+    release();
+    if (count <= 0) count = 1;
+    const hipError_t e = a.take(count, &p);
+    if (e != hipSuccess) {
+      p = nullptr;
+      return e;
+    }
+    n = count;
+    owned = false;
+    return hipSuccess;
   }
   hipError_t alloc(int64_t count) {
     release();
     if (count <= 0) count = 1;
     hipError_t e = hipMalloc((void**)&p, sizeof(T) * (size_t)count);
+    if (e != hipSuccess) {
+      spare_release();
+      e = hipMalloc((void**)&p, sizeof(T) * (size_t)count);
+    }
     if (e != hipSuccess) {
       p = nullptr;
       return e;
@@ -158,7 +241,8 @@ struct Workspace {
   DBuf<uint16_t> s_X;
   JoinGraph graph;
   PinnedBuf<uint32_t> host_out;  // staging of result pairs copied to the host
-  PinnedBuf<unsigned long long> host_counters;  // [C_NUM + 2] written by the device
+  // written by the device: counters and checks [C_NUM + 2], then a few pairs (host_sink)
+  PinnedBuf<unsigned long long> host_counters;
   apss_stats last;
   int64_t regrows = 0;  // joins rerun because the pair buffer was too small
   hipEvent_t ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -187,7 +271,12 @@ struct apss_index {
   int32_t range_group = 1;  // ranges per work item
   int32_t head_cut = 0;     // > 0: the unindexed part of every row is its components of rank < head_cut
   apss_index* screen = nullptr;  // head-cut index over the same rows (screened join), owned
+  // the index's tables, and those that only the list-pair and sketch kernels
+  // read (given back if neither is used)
+  apss::Arena mem, pair_mem;
+  bool building = false;  // tables come from mem
   apss::RankRows rows;  // corpus rows in rank space (densest dimension first)
+  apss::DBuf<uint32_t> out;  // [m + n] staging of apss_index_export
   apss::DBuf<apss::RowStat> rs;
   apss::DBuf<int32_t> rank, inv;
   apss::DBuf<float> mw_r;  // maxweight by rank
@@ -215,6 +304,7 @@ struct apss_index {
   apss::DBuf<int64_t> doff;
   apss::DBuf<uint2> wide, shorts, seg;
   int64_t nwide = 0, nshort = 0, count_blocks = 0, present_words = 0;
+  double pair_survivors = 0.0;  // expected of a self-join at t_build
   int32_t count_ranks = 0;
   apss::PairGroups pair_groups;
   // lazily built tables (guarded by prep_mu)
@@ -332,6 +422,7 @@ struct Sink {
   int64_t room = 0;
   bool done = false;
 };
+int reserve_host(Workspace& ws);
 int host_sink(Workspace& ws, Sink* sink);
 // Run the join kernels; sorted raw pairs in ws.raw_key / ws.raw_sim; count in
 // *count.  cap_hint: pair capacity to start with (grown and rerun on overflow).
@@ -345,6 +436,7 @@ inline bool variant_available(int variant) { return variant != 3; }
 inline bool screen_variant_ok(int variant) { return variant_available(variant); }
 // Screened self-join of an index built with screen_dims > 0 (ix->screen set).
 int run_screen_join(apss_index* ix, Workspace& ws, float t, int64_t cap_hint, int64_t* count, Sink* sink = nullptr);
+constexpr size_t kHostWords = C_NUM + 2 + (3 * kFinishPairs + 1) / 2;
 // Unpack the sorted raw pairs into the sink (unless they are there already)
 // / into library-owned host arrays.
 // finish_device waits for the unpack unless wait is false (then the caller

@@ -64,16 +64,6 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_add(int64_t* __restrict__
   }
 }
 
-__global__ void k_scan_total(const int64_t* __restrict__ sums_scanned, const int64_t* __restrict__ sums_raw_last,
-                             int64_t nb, int64_t* __restrict__ total) {
-  // total = scanned[nb-1] + raw[nb-1]; raw value was saved before the sub-scan
-  if (threadIdx.x == 0 && blockIdx.x == 0) *total = sums_scanned[nb - 1] + *sums_raw_last;
-}
-
-__global__ void k_copy1(const int64_t* __restrict__ src, int64_t* __restrict__ dst) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *dst = *src;
-}
-
 }  // namespace
 
 int64_t scan_tmp_elems(int64_t n) {
@@ -90,28 +80,20 @@ static __global__ void k_zero1(int64_t* __restrict__ dst) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *dst = 0;
 }
 
-// Recursive three-phase scan.  tmp layout per level: [sums (nb) | raw total of the last chunk (1)].
+// Recursive three-phase scan.  tmp layout per level: the chunks' sums, whose
+// own total is the grand total.
 hipError_t exclusive_scan_i64(int64_t* data, int64_t n, int64_t* tmp, int64_t* total_dev, hipStream_t s) {
   if (n <= 0) {
     if (total_dev) hipLaunchKernelGGL(k_zero1, dim3(1), dim3(64), 0, s, total_dev);
     return hipGetLastError();
   }
   const int64_t nb = (n + kScanChunk - 1) / kScanChunk;
-  int64_t* sums = tmp;
-  int64_t* saved = tmp + nb;
+  int64_t* const sums = nb == 1 && total_dev ? total_dev : tmp;
   hipLaunchKernelGGL(k_scan_chunk, dim3((unsigned)nb), dim3(kScanThreads), 0, s, data, n, sums);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  // keep the raw total of the last chunk so the grand total can be formed after the sub-scan
-  hipLaunchKernelGGL(k_copy1, dim3(1), dim3(64), 0, s, sums + nb - 1, saved);
-  if (nb > 1) {
-    e = exclusive_scan_i64(sums, nb, tmp + nb + 1, nullptr, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(kScanThreads), 0, s, data, n, sums);
-    if (total_dev) hipLaunchKernelGGL(k_scan_total, dim3(1), dim3(64), 0, s, sums, saved, nb, total_dev);
-  } else if (total_dev) {
-    hipLaunchKernelGGL(k_copy1, dim3(1), dim3(64), 0, s, saved, total_dev);
-  }
+  if (e != hipSuccess || nb == 1) return e;
+  if ((e = exclusive_scan_i64(sums, nb, tmp + nb, total_dev, s)) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(kScanThreads), 0, s, data, n, sums);
   return hipGetLastError();
 }
 
