@@ -458,14 +458,16 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   CHK(hipStreamSynchronize(s), "deep lists");
   int64_t longs = 0;
   for (int64_t r = 0; r < n; ++r) longs += ix->rows.rp_host[(size_t)r + 1] - ix->rows.rp_host[(size_t)r] > kFineRow;
-  CHK(ix->pair_mem.reserve(Arena::bytes<uint32_t>(deep) + Arena::bytes<int64_t>(m + 1) + Arena::bytes<uint16_t>(m) +
+  CHK(ix->pair_mem.reserve(2 * Arena::bytes<uint32_t>(deep) + Arena::bytes<int64_t>(m + 1) + Arena::bytes<uint16_t>(m) +
                            Arena::bytes<uint8_t>(n * kSkGroups) + Arena::bytes<uint8_t>(n * kMidGroups) +
                            Arena::bytes<uint32_t>(n) + Arena::bytes<uint8_t>(longs * kFineGroups)),
       "alloc tables");
+  ix->ndeep = deep;
   CHK(ix->dl.take(ix->pair_mem, deep), "alloc");
+  CHK(ix->dlr.take(ix->pair_mem, deep), "alloc");
   CHK(ix->doff.take(ix->pair_mem, m + 1), "alloc");
   uint32_t* pos = (uint32_t*)ss.k2.p;  // the sort's second keys are free
-  CHK(launch_lists(ss.v64a.p, P, ix->post.p, ix->post4.p, tiles.p, pos, ix->dl.p, s), "lists");
+  CHK(launch_lists(ss.k1.p, ss.v64a.p, P, ix->post.p, ix->post4.p, tiles.p, pos, ix->dl.p, ix->dlr.p, s), "lists");
   CHK(launch_deep_offsets(ix->off.p, pos, P, m, deep, ix->doff.p, s), "deep lists");
   // groups of ranks of about equal component counts, and the sketches
   CHK(ix->gid.take(ix->pair_mem, m), "alloc");
@@ -521,7 +523,8 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   JoinPlan plan;
   bind_pairs(ix, ix->t_build, ws.qctr, nullptr, 0, plan);
   plan.pa.counters = cnt.p;
-  const int64_t units = ix->nwide + ix->nshort / kShortUnits;
+  const int64_t windows = (ix->ndeep + kTinyList - 1) / kTinyList;
+  const int64_t units = ix->nwide + ix->nshort / kShortUnits + windows / 64;
   plan.pa.sample = std::max<int64_t>(1, units / 4096);
   CHK(launch_pairs(plan.pa, plan.pg, s), "sample");
   CHK(launch_visits(cnt_r, ix->off.p, m, cnt.p + C_TAILVISITS, s), "sample");
@@ -543,7 +546,7 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   const double k = (double)plan.pa.sample;
   const double blocks = (double)((n + kCountRows - 1) / kCountRows);
   const double pairs_ms = 1e3 * (k * (double)c[C_VISITS] / 1.5e12 + 2.0 * k * (double)c[C_SURVIVORS] * 0.45e-9 +
-                                 (double)ix->nshort * 1.6e-9 + (ix->head_cut > 0 ? 2.8e-12 * (double)c[C_TAILVISITS] : 0.5 * blocks * (double)ix->P * (2e-9 / 110.0)));
+                                 (double)ix->nshort * 1.6e-9 + (double)windows * 0.4e-9 + (ix->head_cut > 0 ? 2.8e-12 * (double)c[C_TAILVISITS] : 0.5 * blocks * (double)ix->P * (2e-9 / 110.0)));
   const double lists_ms = 1e3 * ((double)c[C_TAILVISITS] / 1.2e12 + 0.5 * (double)n * (double)n / 1.1e12);
   // (up to one block of rows launches and waits are most of either: 0.24 ms
   // against 0.27 ms for 2,000 rows, so there only many survivors decide)
@@ -571,7 +574,7 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
                         ix->opts.reserved[0] == kProbePairs);
   if (!ix->pairs_ready && !ix->screen_queries) {
     for (DBuf<uint8_t>* b : {&ix->sk, &ix->mid, &ix->fsk}) b->release();
-    for (DBuf<uint32_t>* b : {&ix->dl, &ix->fidx}) b->release();
+    for (DBuf<uint32_t>* b : {&ix->dl, &ix->dlr, &ix->fidx}) b->release();
     for (DBuf<uint2>* b : {&ix->wide, &ix->shorts}) b->release();
     ix->gid.release();
     ix->doff.release();
@@ -680,7 +683,7 @@ int build_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   if (pairs) {
     if ((rc = build_pair_lists(ix, cnt_r, tmp))) return rc;
   } else {
-    CHK(launch_lists(ss.v64a.p, P, ix->post.p, ix->post4.p, nullptr, nullptr, nullptr, s), "lists");
+    CHK(launch_lists(nullptr, ss.v64a.p, P, ix->post.p, ix->post4.p, nullptr, nullptr, nullptr, nullptr, s), "lists");
   }
 
   // local pruning: split the indexed ranks into parts of about equal
@@ -995,6 +998,8 @@ void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue
   a.qfsk = a.fsk;
   a.dl = ix->dl.p;
   a.doff = ix->doff.p;
+  a.dlr = ix->dlr.p;
+  a.ndeep = ix->ndeep;
   a.wide = ix->wide.p;
   a.shorts = ix->shorts.p;
   a.nwide = ix->nwide;
@@ -1012,9 +1017,16 @@ void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue
   c.skip = ix->head_cut > 0 ? ix->rs.p : nullptr;
   c.nq = ix->n;
   c.triangle = 1;
-  // about eight work items per compute unit, of at least a few queries per wave
+  // about eight work items per compute unit, of at least a few queries per
+  // wave; where that leaves the device idle one query per wave, which reads
+  // the bitmaps it needs from L2 instead of loading LDS with all of them
+  // (3,001 rows: 47 us for 70; 20,011 rows: 257 us for 235)
   const int64_t want = ix->n * ix->count_blocks / 2 / 2048;
   c.chunk = std::max<int64_t>(64, std::min<int64_t>(4096, (want + 63) / 64 * 64));
+  if (ix->n * ix->count_blocks / 2 / c.chunk < 512) {
+    c.chunk = 16;
+    c.lds_ranks = 0;
+  }
 }
 
 // True when a batch of nq queries takes the few-query kernel: default
@@ -1240,7 +1252,7 @@ int host_sink(Workspace& ws, Sink* sink) {
 
 // After a join's kernels: its counters in ws.host_counters once the stream
 // has drained, and the pairs at the sink if they are few.
-int hand_over(Workspace& ws, int bj, const Sink* sink, const unsigned long long* checks = nullptr) {
+int hand_over(Workspace& ws, int bj, int bits, const Sink* sink, const unsigned long long* checks = nullptr) {
   hipStream_t s = ws.stream;
   if (int rc = reserve_host(ws)) return rc;
   FinishArgs f{};
@@ -1248,6 +1260,7 @@ int hand_over(Workspace& ws, int bj, const Sink* sink, const unsigned long long*
   f.sim = ws.raw_sim.p;
   f.cap = ws.raw_key.n;
   f.bj = bj;
+  f.bits = bits;
   if (sink) {
     f.out_i = sink->i;
     f.out_j = sink->j;
@@ -1340,7 +1353,7 @@ int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, flo
     CHK(hipEventRecord(ws.ev[2], s), "event");
     // (a pair that several parts keep is still there several times)
     const Sink* to = P.a.parts > 1 ? nullptr : sink;
-    if ((rc = hand_over(ws, P.bj, to, checks))) return rc;
+    if ((rc = hand_over(ws, P.bj, P.bi + P.bj, to, checks))) return rc;
     CHK(hipStreamSynchronize(s), "join");
     const unsigned long long* const c = ws.host_counters.p;
     if (checks && (rc = check_bits((uint32_t)c[C_NUM], c[C_NUM + 1], "query"))) return rc;
@@ -1531,7 +1544,7 @@ int run_screen_join(apss_index* ix, Workspace& ws, float t, int64_t cap_hint, in
     CHK(launch_screen_verify(ws.s_cand.p, nc, bj, sx->rows.rp.p, sx->rows.rc.p, head, t, ws.raw_key.p, ws.raw_sim.p,
                              ws.raw_key.n, ws.counters.p, s),
         "screen verify");
-    if ((rc = hand_over(ws, bj, sink))) return rc;
+    if ((rc = hand_over(ws, bj, 2 * bj, sink))) return rc;
     CHK(hipStreamSynchronize(s), "join");
     const unsigned long long* const c = ws.host_counters.p;
     const int64_t matches = (int64_t)c[C_MATCHES];
@@ -1598,8 +1611,8 @@ int capture_join_graph(apss_index* ix, float t, uint32_t* out_i, uint32_t* out_j
     int r = launch_planned(ws, P);
     if (r) return r;
     if (finish_delivers(cnt, ws.raw_key.n, capacity)) {
-      const FinishArgs f{ws.raw_key.p, ws.raw_sim.p, ws.raw_key.n,  P.bj,    out_i, out_j,
-                         out_sim,      capacity,     ws.counters.p, nullptr, g.hctr};
+      const FinishArgs f{ws.raw_key.p, ws.raw_sim.p, ws.raw_key.n, P.bj,          P.bi + P.bj, out_i,
+                         out_j,        out_sim,      capacity,     ws.counters.p, nullptr,     g.hctr};
       CHK(launch_finish(f, s), "finish kernel");
       return APSS_OK;
     }

@@ -6,13 +6,14 @@
 namespace apss {
 
 // Most pairs that one launch sorts and hands over.
-constexpr int64_t kFinishPairs = 16384;
+constexpr int64_t kFinishPairs = 32768;
 
 struct FinishArgs {
   const uint64_t* key;  // raw pairs of the join kernels, in any order, distinct
   const float* sim;
   int64_t cap;          // raw pairs that the buffers hold
   int bj;               // key = i << bj | j
+  int bits;             // keys are below 2^bits
   uint32_t* out_i;      // room entries each (device or pinned host memory)
   uint32_t* out_j;
   float* out_sim;

@@ -18,9 +18,11 @@ constexpr int kWaves = 16;
 // Each of a workgroup's 64 pairs is placed by the number of smaller keys,
 // which its 16 waves count over shares of all keys, 64 at a time out of a
 // register that readlane broadcasts from: no barriers and no passes over
-// memory.  n^2 compares of the whole device (7,000 pairs: 12 us, 16,384: 35;
-// the 91 barriers of a one-workgroup bitonic sort of 8,192: 75, four radix
-// passes: 100 and more).
+// memory, n^2 compares of the whole device.  With NARROW keys (below 2^32)
+// 1,500 pairs take 5 us, 7,000 12 and 21,000 64, where a one-workgroup bitonic
+// sort of 8,192 took 75 for its 91 barriers and four radix passes take 150;
+// both are even at some 32,000.
+template <bool NARROW>
 __global__ __launch_bounds__(64 * kWaves) void k_finish(FinishArgs a) {
   __shared__ uint32_t place[kOwn];
   const int tid = (int)threadIdx.x;
@@ -44,9 +46,13 @@ __global__ __launch_bounds__(64 * kWaves) void k_finish(FinishArgs a) {
     const int lo = (int)(uint32_t)other, hi = (int)(uint32_t)(other >> 32);
 #pragma unroll
     for (int l = 0; l < 64; ++l) {
-      const uint64_t k = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, l) << 32) |
-                         (uint64_t)(uint32_t)__builtin_amdgcn_readlane(lo, l);
-      less += k < key ? 1u : 0u;
+      const uint32_t kl = (uint32_t)__builtin_amdgcn_readlane(lo, l);
+      if constexpr (NARROW) {
+        less += kl < (uint32_t)key ? 1u : 0u;
+      } else {
+        const uint64_t k = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, l) << 32) | (uint64_t)kl;
+        less += k < key ? 1u : 0u;
+      }
     }
   }
   if (less) atomicAdd(&place[lane], less);
@@ -62,12 +68,15 @@ __global__ __launch_bounds__(64 * kWaves) void k_finish(FinishArgs a) {
 }  // namespace
 
 hipError_t launch_finish(const FinishArgs& a, hipStream_t s) {
-  if (!a.key || !a.sim || a.cap < 0 || a.room < 0 || !a.counters || !a.host || a.bj < 0 || a.bj > 63 ||
+  if (!a.key || !a.sim || a.cap < 0 || a.room < 0 || !a.counters || !a.host || a.bj < 0 || a.bj > 63 || a.bits < 0 ||
       (a.room > 0 && (!a.out_i || !a.out_j || !a.out_sim)))
     return hipErrorInvalidValue;
   const int64_t most = a.room < a.cap ? a.room : a.cap;
   const int64_t grid = ((most < kFinishPairs ? most : kFinishPairs) + kOwn - 1) / kOwn;
-  hipLaunchKernelGGL(k_finish, dim3((unsigned)(grid < 1 ? 1 : grid)), dim3(64 * kWaves), 0, s, a);
+  if (a.bits <= 32)
+    hipLaunchKernelGGL(k_finish<true>, dim3((unsigned)(grid < 1 ? 1 : grid)), dim3(64 * kWaves), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_finish<false>, dim3((unsigned)(grid < 1 ? 1 : grid)), dim3(64 * kWaves), 0, s, a);
   return hipGetLastError();
 }
 

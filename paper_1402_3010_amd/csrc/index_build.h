@@ -48,12 +48,12 @@ hipError_t launch_emit_indexed(const int64_t* rp, const RComp* rc, const RowStat
 // off[r] = first position of the sorted keys[0, P) that is >= r, r = 0..m
 hipError_t launch_list_offsets(const uint64_t* keys, int64_t P, int64_t m, int64_t* off, hipStream_t s);
 // Lists from the sorted values: entries and their packed copy; with dl, the
-// marked entries' ids (tiles: exclusive scan of launch_count_deep's
+// marked entries' ids and ranks (tiles: exclusive scan of launch_count_deep's
 // list_tiles(P) counts) and the marked entries before each position
 int64_t list_tiles(int64_t P);
 hipError_t launch_count_deep(const uint64_t* vals, int64_t P, int64_t* tiles, hipStream_t s);
-hipError_t launch_lists(const uint64_t* vals, int64_t P, Post* post, uint32_t* post4, const int64_t* tiles,
-                        uint32_t* pos, uint32_t* dl, hipStream_t s);
+hipError_t launch_lists(const uint64_t* keys, const uint64_t* vals, int64_t P, Post* post, uint32_t* post4,
+                        const int64_t* tiles, uint32_t* pos, uint32_t* dl, uint32_t* dlr, hipStream_t s);
 hipError_t launch_deep_offsets(const int64_t* off, const uint32_t* pos, int64_t P, int64_t m, int64_t deep,
                                int64_t* doff, hipStream_t s);
 hipError_t launch_block_offsets(const int64_t* off, const Post* post, int32_t H, int64_t nb, int32_t CB,

@@ -444,11 +444,13 @@ __global__ __launch_bounds__(256) void k_count_deep(const uint64_t* __restrict__
 // = vector id mod 2^16 (its offset inside any power-of-two block), high 16
 // bits = the weight in units of 2^-15 rounded up (w * 2^15 is exact in float,
 // so the ceiling is the smallest such unit count not below w).  DEEP: the
-// marked entries' ids close up into dl, and pos[k] counts those before k.
+// marked entries' ids close up into dl and their ranks (the keys) into dlr,
+// and pos[k] counts those before k.
 template <bool DEEP>
-__global__ __launch_bounds__(256) void k_lists(const uint64_t* __restrict__ vals, int64_t P, Post* __restrict__ post,
-                                               uint32_t* __restrict__ post4, const int64_t* __restrict__ tiles,
-                                               uint32_t* __restrict__ pos, uint32_t* __restrict__ dl) {
+__global__ __launch_bounds__(256) void k_lists(const uint64_t* __restrict__ keys, const uint64_t* __restrict__ vals,
+                                               int64_t P, Post* __restrict__ post, uint32_t* __restrict__ post4,
+                                               const int64_t* __restrict__ tiles, uint32_t* __restrict__ pos,
+                                               uint32_t* __restrict__ dl, uint32_t* __restrict__ dlr) {
   __shared__ uint32_t wtot[4];
   const int lane = (int)(threadIdx.x & 63u), wave = (int)(threadIdx.x >> 6);
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -487,7 +489,10 @@ __global__ __launch_bounds__(256) void k_lists(const uint64_t* __restrict__ vals
       const int64_t k = base + it * 64;
       const uint32_t here = at + (uint32_t)__popcll(m[it] & lt);
       if (k < P) pos[k] = here;
-      if ((m[it] >> lane) & 1ull) dl[here] = y[it];
+      if ((m[it] >> lane) & 1ull) {
+        dl[here] = y[it];
+        dlr[here] = (uint32_t)keys[k];
+      }
       at += (uint32_t)__popcll(m[it]);
     }
   }
@@ -769,14 +774,14 @@ hipError_t launch_count_deep(const uint64_t* vals, int64_t P, int64_t* tiles, hi
   return hipGetLastError();
 }
 
-hipError_t launch_lists(const uint64_t* vals, int64_t P, Post* post, uint32_t* post4, const int64_t* tiles,
-                        uint32_t* pos, uint32_t* dl, hipStream_t s) {
+hipError_t launch_lists(const uint64_t* keys, const uint64_t* vals, int64_t P, Post* post, uint32_t* post4,
+                        const int64_t* tiles, uint32_t* pos, uint32_t* dl, uint32_t* dlr, hipStream_t s) {
   if (P <= 0) return hipSuccess;
   const unsigned g = (unsigned)list_tiles(P);
   if (dl)
-    hipLaunchKernelGGL(k_lists<true>, dim3(g), dim3(256), 0, s, vals, P, post, post4, tiles, pos, dl);
+    hipLaunchKernelGGL(k_lists<true>, dim3(g), dim3(256), 0, s, keys, vals, P, post, post4, tiles, pos, dl, dlr);
   else
-    hipLaunchKernelGGL(k_lists<false>, dim3(g), dim3(256), 0, s, vals, P, post, post4, tiles, pos, dl);
+    hipLaunchKernelGGL(k_lists<false>, dim3(g), dim3(256), 0, s, keys, vals, P, post, post4, tiles, pos, dl, dlr);
   return hipGetLastError();
 }
 

@@ -300,10 +300,10 @@ struct apss_index {
   double rate[apss::kRateBins] = {};
   apss::DBuf<uint8_t> sk, mid, fsk;
   apss::DBuf<uint16_t> gid;
-  apss::DBuf<uint32_t> dl, bm, present, fidx;
+  apss::DBuf<uint32_t> dl, dlr, bm, present, fidx;
   apss::DBuf<int64_t> doff;
   apss::DBuf<uint2> wide, shorts, seg;
-  int64_t nwide = 0, nshort = 0, count_blocks = 0, present_words = 0;
+  int64_t ndeep = 0, nwide = 0, nshort = 0, count_blocks = 0, present_words = 0;
   double pair_survivors = 0.0;  // expected of a self-join at t_build
   int32_t count_ranks = 0;
   apss::PairGroups pair_groups;

@@ -187,8 +187,8 @@ extern "C" int apss_join_device_noalloc(apss_index* ix, float t, uint32_t* out_i
   APSS_CHK(hipEventRecord(ws.ev[1], s), "event");
   if ((rc = launch_plan(P, raw_key, raw_sim, room, counters, qctr, s))) return rc;
   APSS_CHK(hipEventRecord(ws.ev[2], s), "event");
-  const FinishArgs f{raw_key, raw_sim, room,     P.bj,    out_i,               out_j, out_sim,
-                     capacity, counters, nullptr, ws.host_counters.p};
+  const FinishArgs f{raw_key, raw_sim, room,     P.bj,     P.bi + P.bj, out_i,
+                     out_j,   out_sim, capacity, counters, nullptr,     ws.host_counters.p};
   APSS_CHK(launch_finish(f, s), "finish kernel");
   APSS_CHK(hipEventRecord(ws.ev[3], s), "event");
   APSS_CHK(hipStreamSynchronize(s), "join");

@@ -19,11 +19,13 @@ constexpr int kFineRow = 256;
 // Work units of the pair tests: lists of at least kWideList entries by
 // workgroups, in blocks of kWideRows entries against at most kWideSpan blocks
 // at a time; shorter lists by waves, in blocks of kUnitRows entries, which a
-// wave takes up to kShortUnits at a time.
+// wave takes up to kShortUnits at a time; lists of at most kTinyList entries
+// several to a tile.
 constexpr int kWideList = 256;
 constexpr int kWideRows = 256;
 constexpr int kWideSpan = 16;
 constexpr int kUnitRows = 64;
+constexpr int kTinyList = 32;
 constexpr int kShortUnits = 16;
 // The candidate count: corpus rows per block, and the densest ranks with a
 // bitmap per block (one bit per row whose indexed part holds the rank).
@@ -52,6 +54,8 @@ struct PairArgs {
   const float* qt;        // [nq] per-query threshold, or NULL: t
   const uint32_t* dl;     // deep lists: vector ids, by rank, ascending within a rank
   const int64_t* doff;    // [m+1] first entry of each rank's deep list
+  const uint32_t* dlr;    // [ndeep] the entries' ranks
+  int64_t ndeep;
   const uint2* wide;      // [nwide] (rank, unit of its list)
   const uint2* shorts;    // [nshort]
   int64_t nwide, nshort;

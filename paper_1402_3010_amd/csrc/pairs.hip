@@ -22,6 +22,8 @@
 // reported and their similarities are those of the accumulating join.
 #include "apss_internal.h"
 #include "join.h"
+#include <algorithm>
+
 #include "pairs.h"
 #include "rescore.h"
 
@@ -161,7 +163,7 @@ __device__ __forceinline__ int64_t wide_count(int64_t len) {
   return len < kWideList ? 0 : units_before((len + kWideRows - 1) / kWideRows);
 }
 __device__ __forceinline__ int64_t short_count(int64_t len) {
-  return len < 2 || len >= kWideList ? 0 : (len + kUnitRows - 1) / kUnitRows;
+  return len <= kTinyList || len >= kWideList ? 0 : (len + kUnitRows - 1) / kUnitRows;
 }
 
 template <bool WIDE>
@@ -543,7 +545,7 @@ __device__ __forceinline__ void flush_all(const PairArgs& a, int lane, int wave,
 }
 
 // The queued survivors: consecutive ones (which share rows) to each wave, 64
-// at a time, or fewer (at least 8) when there are not enough for every wave.
+// at a time, or fewer (at least 4) when there are not enough for every wave.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_decide(PairArgs a) {
   __shared__ StagedRow rows[4];
   const int lane = (int)(threadIdx.x & 63u);
@@ -552,7 +554,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   const int64_t waves = (int64_t)gridDim.x * 4;
   const int64_t even = (held + waves - 1) / waves;
   // (each wave ends with atomics on the same few counters)
-  const int per = even < 8 ? 8 : (even < 64 ? (int)even : 64);
+  const int per = even < 4 ? 4 : (even < 64 ? (int)even : 64);
   WaveEmit em;
   Decided dc;
   for (int64_t e0 = ((int64_t)blockIdx.x * 4 + wave) * per; e0 < held; e0 += waves * per) {
@@ -834,6 +836,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 // unit's ids while the unit before is tested, so that a unit costs one round
 // of sketch loads.  A list of one block meets itself only, from the same
 // registers.
+//
+// Lists of at most kTinyList entries, most of them two or three, share tiles:
+// a wave takes the 64 consecutive entries from a multiple of 32 on and tests
+// the lists that begin in the first half of them, each row masked to its own
+// list's groups, each column meeting the later rows of its own list: 41 us for
+// 3,001 rows and 97 for 20,011, where a wave per list took 61 and 217.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_pairs_short(PairArgs a) {
   __shared__ uint32_t qa[4][kPairQueue], qb[4][kPairQueue], qd[4][kPairQueue];
   const int lane = (int)(threadIdx.x & 63u);
@@ -905,6 +913,66 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         const int bl = b0 + (lane & 31);
         sv.take(a, lane, acc, ida, idb, bl - a0 + 1, na, rank, a.thr, dc);
       }
+    }
+  }
+  const int64_t windows = (a.ndeep + kTinyList - 1) / kTinyList;
+  const int64_t every = a.sample > 0 ? a.sample : 1;
+  for (int64_t w = ((int64_t)blockIdx.x * 4 + wave) * every; w < windows; w += (int64_t)gridDim.x * 4 * every) {
+    const int64_t e0 = w * kTinyList;
+    const int64_t e = e0 + lane;
+    uint32_t r = 0u, id = 0u;
+    int beg = -1, end = 0, g = 0;  // of this lane's entry's list, from e0
+    if (e < a.ndeep) {
+      r = a.dlr[e];
+      id = a.dl[e];
+      const int64_t st = a.doff[r], len = a.doff[r + 1] - st;
+      if (len >= 2 && len <= kTinyList && st >= e0 && st < e0 + kTinyList) {
+        beg = (int)(st - e0);
+        end = beg + (int)len;
+        g = a.gid[r] >> 3;
+        c_visit += (unsigned long long)(lane - beg);
+      }
+    }
+    const uint64_t own = __ballot(beg >= 0);
+    if (!own) continue;
+    int gmax = beg >= 0 ? g : 0;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      const int v = __shfl_xor(gmax, o, 64);
+      gmax = v > gmax ? v : gmax;
+    }
+    const int ksteps = uni(gmax) / 32 + 1;
+    const bool upper = (own >> 32) != 0ull;
+    i32x4 fa[2][kSteps];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int row = 32 * i + (lane & 31);
+      const uint32_t rid = (uint32_t)__shfl((int)id, row, 64);
+      if ((own >> row) & 1ull) {
+        load_sketch(a, lane, rid, ksteps, fa[i]);
+      } else {
+#pragma unroll
+        for (int ks = 0; ks < kSteps; ++ks) fa[i][ks] = i32x4{0, 0, 0, 0};
+      }
+      mask_sketch(lane, __shfl(g, row, 64), fa[i]);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      if (j == 1 && !upper) break;
+      i32x16 acc[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int k = 0; k < 16; ++k) acc[i][k] = 0;
+#pragma unroll
+      for (int ks = 0; ks < kSteps; ++ks)
+        if (ks < ksteps) {
+          if (j == 0) acc[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[0][ks], fa[0][ks], acc[0], 0, 0, 0);
+          if (upper) acc[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[1][ks], fa[j][ks], acc[1], 0, 0, 0);
+        }
+      const int col = 32 * j + (lane & 31);
+      sv.take(a, lane, acc, id, (uint32_t)__shfl((int)id, col, 64), col + 1, __shfl(end, col, 64),
+              (uint32_t)__shfl((int)r, col, 64), a.thr, dc);
     }
   }
   sv.pass_on_all(a, lane, wave, dc);
@@ -1498,8 +1566,8 @@ PairGroups pairs_resident_groups() {
 }
 
 hipError_t launch_pairs(PairArgs a, const PairGroups& g, hipStream_t s) {
-  if (a.nwide <= 0 && a.nshort <= 0) return hipSuccess;
-  if (!a.rp || !a.rc || !a.sk || !a.gid || !a.fidx || !a.fsk || !a.qrp || !a.qrc || !a.qfidx || !a.qfsk || !a.dl || !a.doff || !a.wide || !a.shorts || !a.uctr ||
+  if (a.ndeep <= 0) return hipSuccess;
+  if (!a.dlr || !a.rp || !a.rc || !a.sk || !a.gid || !a.fidx || !a.fsk || !a.qrp || !a.qrc || !a.qfidx || !a.qfsk || !a.dl || !a.doff || !a.wide || !a.shorts || !a.uctr ||
       (a.sample == 0 && (!a.out_key || !a.out_sim)) || !a.counters || (a.qcap > 0 && !a.queue) || a.nwide > 0x7FFFFFFF ||
       a.nshort > 0x7FFFFFFF)
     return hipErrorInvalidValue;
@@ -1511,11 +1579,13 @@ hipError_t launch_pairs(PairArgs a, const PairGroups& g, hipStream_t s) {
     hipLaunchKernelGGL(k_pairs_wide, dim3((unsigned)n), dim3(256), 0, s, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if (a.nshort > 0) {
+  {
     // every resident wave gets some units, where there are enough
+    const int64_t windows = (a.ndeep + kTinyList - 1) / kTinyList;
     const int64_t even = a.nshort / every / ((int64_t)g.shorts * 4);
     a.sstep = (int32_t)(even < 1 ? 1 : (even < kShortUnits ? even : kShortUnits));
-    const int64_t need = (a.nshort + 4 * a.sstep * every - 1) / (4 * a.sstep * every);
+    const int64_t turns = std::max((a.nshort + a.sstep * every - 1) / (a.sstep * every), (windows + every - 1) / every);
+    const int64_t need = (turns + 3) / 4;
     const int64_t n = need < g.shorts ? need : g.shorts;
     hipLaunchKernelGGL(k_pairs_short, dim3((unsigned)n), dim3(256), 0, s, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;

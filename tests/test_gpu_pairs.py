@@ -160,3 +160,23 @@ def test_sparse_pass_of_the_screened_join(n, head):
     A = sp.csr_matrix((np.ones(len(row), np.int32), (row, V.col[tail])), shape=(V.n, V.m))
     shared = (A @ A.T).tocsr()
     assert sa["candidates"] == (shared.nnz - np.count_nonzero(shared.diagonal())) // 2
+
+
+@pytest.mark.parametrize("lens", [(2,) * 40, (32, 33, 31), (3, 5, 30, 2, 2, 32, 34), (33, 2, 33, 2, 64, 1, 1, 32)])
+def test_tiny_lists_share_tiles(lens):
+    # lists of exactly these lengths one after another (each of rows with a dimension of their own), from every offset
+    for lead in (0, 1, 17, 31):
+        rng = np.random.default_rng(len(lens) + lead)
+        m, rows = 2000, []
+        for g, k in enumerate((lead,) + lens):
+            w = rng.uniform(0.9, 1.1, size=8)
+            rows += [(np.concatenate([[g], np.sort(rng.choice(900, size=7, replace=False)) + 1000]),
+                      np.concatenate([[4.0], w[1:]])) for _ in range(k)]
+        rng.shuffle(rows)
+        V = csr(rows, m)
+        t = np.float32(0.7)
+        (a, sa), (b, sb) = join(V, t, pairs=True), join(V, t, variant=1)
+        for x, y in zip(a, b):
+            assert np.array_equal(np.asarray(x).view(np.uint32), np.asarray(y).view(np.uint32))
+        assert sa["candidates"] == sb["candidates"]
+        assert_parity(*a, oracle.join_plain(V, t), float(t), V)
