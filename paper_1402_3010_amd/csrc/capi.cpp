@@ -1122,8 +1122,10 @@ int plan_queries(apss_index* ix, Workspace& ws, const QuerySet& Q, float t, cons
   c.rc = Q.rc;
   c.nq = Q.n;
   // a few work items per compute unit; a chunk of few queries reads the
-  // bitmaps it needs from L2 instead of loading LDS with all of them
-  const int64_t want = Q.n * ix->count_blocks / 1024;
+  // bitmaps it needs from L2 instead of loading LDS with all of them.  From
+  // 1,024 queries on, 64 of a block's items (as many as run on an XCD at
+  // once) take the batch, so that they share one block's bitmaps in its L2
+  const int64_t want = Q.n >= 1024 ? std::max<int64_t>(64, Q.n / 64) : Q.n * ix->count_blocks / 1024;
   c.chunk = std::max<int64_t>(16, std::min<int64_t>(4096, (want + 15) / 16 * 16));
   if (c.chunk < 64) c.lds_ranks = 0;
   return APSS_OK;

@@ -506,6 +506,9 @@ __global__ void k_deep_offsets(const int64_t* __restrict__ off, const uint32_t* 
 }
 
 // hoff[b * H + r] = first position in list r whose vector id is >= b * CB.
+// (Several offsets of a list by one thread in turn, as in k_range_offsets, are
+// slower here: 1.20 ms against 0.93 for 500,000 rows, the lists are long and
+// there are fewer threads.)
 __global__ void k_block_offsets(const int64_t* __restrict__ off, const Post* __restrict__ post, int32_t H, int64_t nb,
                                 int32_t CB, uint32_t* __restrict__ hoff) {
   const int64_t total = (nb + 1) * (int64_t)H;

@@ -1393,23 +1393,48 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE)))
   if (tid < C_NUM && tid != C_MATCHES && sm.cnt[tid]) atomicAdd(&a.counters[tid], sm.cnt[tid]);
 }
 
+// First position in post[lo, hi) (ascending ids) with an id of at least y:
+// probes that double from lo on, then bisection, so that a caller that
+// advances in small steps pays for their length and not for the list's.
+__device__ __forceinline__ int64_t advance_to(const Post* __restrict__ post, int64_t lo, int64_t hi, uint64_t y) {
+  for (int64_t step = 1;; step *= 2) {
+    if (lo >= hi || (uint64_t)post[lo].y >= y) return lo;
+    ++lo;  // (post[lo - 1] is below y)
+    const int64_t at = lo + step - 1;
+    if (at >= hi) break;
+    if ((uint64_t)post[at].y >= y) {
+      hi = at;
+      break;
+    }
+    lo = at + 1;
+  }
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) >> 1;
+    if ((uint64_t)post[mid].y < y) lo = mid + 1;
+    else hi = mid;
+  }
+  return lo;
+}
+
+// Consecutive offsets of a list that one thread finds in turn.
+constexpr int kOffsetSpan = 16;
+
 // toff[R * (m - H) + (r - H)] = first position in sparse list r whose vector
-// id is >= R * range_rows.
+// id is >= R * range_rows, kOffsetSpan ranges by a thread in turn (500,000
+// rows, 31 million offsets of short lists: 0.38 ms, by bisections 0.94).
 __global__ void k_range_offsets(const int64_t* __restrict__ off, const Post* __restrict__ post, int32_t H, int64_t m,
                                 int64_t nR, int64_t range_rows, uint32_t* __restrict__ toff) {
   const int64_t mt = m - H;
-  const int64_t total = (nR + 1) * mt;
+  const int64_t total = (nR / kOffsetSpan + 1) * mt;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t R = e / mt;
-    const int64_t r = H + (e - R * mt);
-    int64_t lo = off[r], hi = off[r + 1];
-    const uint64_t y0 = (uint64_t)R * (uint64_t)range_rows;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if ((uint64_t)post[mid].y < y0) lo = mid + 1;
-      else hi = mid;
+    const int64_t c = e / mt;
+    const int64_t k = e - c * mt;
+    int64_t lo = off[H + k];
+    const int64_t hi = off[H + k + 1];
+    for (int64_t R = c * kOffsetSpan; R <= nR && R < (c + 1) * kOffsetSpan; ++R) {
+      lo = advance_to(post, lo, hi, (uint64_t)R * (uint64_t)range_rows);
+      toff[R * mt + k] = (uint32_t)lo;
     }
-    toff[e] = (uint32_t)lo;
   }
 }
 
@@ -1551,7 +1576,7 @@ int join_resident_groups(int variant, bool remscore) {
 
 hipError_t launch_range_offsets(const int64_t* off, const Post* post, int32_t H, int64_t m, int64_t nR,
                                 int64_t range_rows, uint32_t* toff, hipStream_t s) {
-  const int64_t total = (nR + 1) * (m - H);
+  const int64_t total = (nR / kOffsetSpan + 1) * (m - H);
   if (total <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_range_offsets, dim3(grid(total)), dim3(256), 0, s, off, post, H, m, nR, range_rows, toff);
   return hipGetLastError();

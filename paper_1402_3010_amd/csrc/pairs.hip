@@ -1585,7 +1585,9 @@ hipError_t launch_pairs(PairArgs a, const PairGroups& g, hipStream_t s) {
     const int64_t even = a.nshort / every / ((int64_t)g.shorts * 4);
     a.sstep = (int32_t)(even < 1 ? 1 : (even < kShortUnits ? even : kShortUnits));
     const int64_t turns = std::max((a.nshort + a.sstep * every - 1) / (a.sstep * every), (windows + every - 1) / every);
-    const int64_t need = (turns + 3) / 4;
+    // (a workgroup ends with atomics on the same counters, 20 ns each: one
+    // turn per wave only as far as 256 of them, then four)
+    const int64_t need = std::max((turns + 15) / 16, std::min<int64_t>((turns + 3) / 4, 256));
     const int64_t n = need < g.shorts ? need : g.shorts;
     hipLaunchKernelGGL(k_pairs_short, dim3((unsigned)n), dim3(256), 0, s, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
