@@ -180,3 +180,31 @@ def test_tiny_lists_share_tiles(lens):
             assert np.array_equal(np.asarray(x).view(np.uint32), np.asarray(y).view(np.uint32))
         assert sa["candidates"] == sb["candidates"]
         assert_parity(*a, oracle.join_plain(V, t), float(t), V)
+
+
+@pytest.mark.parametrize("n", [3001, 5000])
+def test_replays_count_beside_the_tests(n):
+    # the captured join counts candidates on a branch of its own: pairs and counters of every replay are the eager call's
+    import torch
+
+    import paper_1402_3010_amd as apss
+    V = make_corpus(spec_for("c2", n=n))
+    t = np.float32(0.6)
+    ref, st = join(V, t)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    ix = apss.Index.build(V, t, stream=stream.cuda_stream, graph=True)
+    try:
+        out = [torch.zeros(len(ref[0]) + 3, dtype=d, device="cuda") for d in (torch.int32, torch.int32, torch.float32)]
+        for k in range(5):
+            for o in out:
+                o.zero_()
+            torch.cuda.synchronize()
+            assert ix.join_device(t, *out) == len(ref[0])
+            for x, y in zip(out, ref):
+                assert np.array_equal(x[:len(y)].cpu().numpy().view(np.uint32), np.asarray(y).view(np.uint32))
+            now = ix.stats()
+            for key in ("candidates", "bound_survivors", "verified", "band", "matches", "posting_visits"):
+                assert now[key] == st[key], key
+    finally:
+        ix.close()
