@@ -1338,9 +1338,9 @@ int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, flo
   // A batch of queries takes the sketch kernels when they are expected to be
   // ahead at its thresholds, and again the accumulating kernel if more pairs
   // survive than the queue was sized for (twice those of the corpus's own
-  // rows).
+  // rows).  (More than 2^24 queries would need 4 GB of sketches.)
   const bool few = !triangle && takes_few(ix, Q.n);
-  bool screen = !triangle && !few && ix->screen_queries && !ix->pairs_off;
+  bool screen = !triangle && !few && ix->screen_queries && !ix->pairs_off && Q.n <= (1 << 24);
   if (screen) {
     double survivors = 0.0;
     for (int64_t q = 0; q < Q.n; ++q) survivors += survivor_rate(ix, t_host ? t_host[q] : t) * (double)ix->n;

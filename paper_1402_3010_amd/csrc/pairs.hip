@@ -309,8 +309,7 @@ __device__ __forceinline__ void decide_pairs(const PairArgs& a, StagedRow& st, i
       int dot = 0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) dot = __builtin_amdgcn_sdot4(u[i] & (int)group_mask(16 * lane + 4 * i, g), w[i], dot, false);
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) dot += __shfl_xor(dot, o, 64);
+      dot = wave_sum(dot);
       if (dot < pair_threshold(lane_float(tq, l))) out |= 1ull << l;
     }
     if (out) {
@@ -361,15 +360,15 @@ __device__ __forceinline__ void decide_pairs(const PairArgs& a, StagedRow& st, i
     const float t = lane_float(tq, l);
     if (l + 1 < here) fetch(l + 1);
     const bool staged = qlen <= kStageRanks;
-    int p2 = 128;
+    int p2 = 64;
     if (staged) {
       while (p2 < qlen) p2 <<= 1;
       int32_t* const ranks = st.v;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int k = 64 * h + lane;
-        ranks[k] = k < qlen ? cq[h].r : 0x7FFFFFFF;
-        ranks[kStageRow + k] = __float_as_int(cq[h].w);
+      ranks[lane] = lane < qlen ? cq[0].r : 0x7FFFFFFF;
+      ranks[kStageRow + lane] = __float_as_int(cq[0].w);
+      if (qlen > 64) {
+        ranks[64 + lane] = 64 + lane < qlen ? cq[1].r : 0x7FFFFFFF;
+        ranks[kStageRow + 64 + lane] = __float_as_int(cq[1].w);
       }
       const bool both = qlen <= kStageRow;
       for (int k0 = 128; k0 < p2; k0 += 256) {
@@ -405,9 +404,17 @@ __device__ __forceinline__ void decide_pairs(const PairArgs& a, StagedRow& st, i
     };
     float s32;
     if (staged && ylen <= 128) {
+      // (most rows of ordinary corpora have one chunk: the vector units bind)
       const int32_t rr[2] = {lane < ylen ? cy[0].r : -1, 64 + lane < ylen ? cy[1].r : -1};
-      float vv[2];
-      staged_lookup<2>(st, qrow, qlen, p2, rr, vv);
+      float vv[2] = {0.0f, 0.0f};
+      if (ylen <= 64) {
+        const int32_t r1[1] = {rr[0]};
+        float v1[1];
+        staged_lookup<1>(st, qrow, qlen, p2, r1, v1);
+        vv[0] = v1[0];
+      } else {
+        staged_lookup<2>(st, qrow, qlen, p2, rr, vv);
+      }
       rarer = (rr[0] > dl && vv[0] != 0.0f) || (rr[1] > dl && vv[1] != 0.0f);
       if (__ballot(rarer)) {
         wave_lds_order();
@@ -444,8 +451,7 @@ __device__ __forceinline__ void decide_pairs(const PairArgs& a, StagedRow& st, i
         wave_lds_order();
         continue;
       }
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) part += __shfl_xor(part, o, 64);
+      part = wave_sum(part);
       // the plain sum's error (below 1e-5) is far inside the slack
       if (part < t - kSlack) {
         ++dc.surv;
