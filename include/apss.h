@@ -62,7 +62,11 @@ typedef struct {
                             index answers apss_query; 0: the paper's cutoff only (join only) */
   int32_t variant;       /* compiled tile variant of the join kernel (queries per tile x corpus
                             rows per block): 0, 1 or 2 (3 is withdrawn: APSS_EINVAL); -1 = the
-                            library's default.  The environment variable APSS_VARIANT overrides it. */
+                            library's default, with which self-joins and queries take whichever of
+                            their kernels (accumulating, list pairs, sketches) is expected to be
+                            faster; a variant, range_rows or range_group given here names the
+                            accumulating join kernel.  The environment variable APSS_VARIANT
+                            overrides it. */
   int32_t head_dims;     /* densest dimensions that get per-block list offsets (0 = default) */
   int32_t range_rows;    /* corpus rows per work item of the join (rounded down to a multiple of the
                             variant's block rows; 0 = default 16384).  The environment variable
@@ -106,7 +110,9 @@ void apss_default_opts(apss_opts* opts);
  * leading part x' (densest dimensions first, while the running bound
  * sum x[d] * maxweight_d(V) stays below t_build) and its indexed rest, and
  * inverted lists of the indexed parts ordered by vector id.
- * The index owns device memory until apss_index_free.
+ * The index owns device memory until apss_index_free; up to 1/32 of the
+ * device's memory then stays with the library for the next index, until it has
+ * gone unused for a while or memory runs out.
  * Errors: APSS_EINVAL (bad CSR, n < 0, m <= 0, nnz >= 2^32, n >= 2^31),
  * APSS_ETHRESH (t_build outside (0, 1]), APSS_ENOMEM, APSS_EDEVICE. */
 int apss_build_index(int64_t n, int64_t m, const int64_t* row_ptr, const int32_t* col, const float* val,
@@ -176,13 +182,15 @@ void apss_pairs_free(apss_pairs* p);
 
 /* Counters and device times of the last join or query on this index. */
 typedef struct {
-  int64_t posting_visits;   /* inverted-list entries streamed into accumulators */
+  int64_t posting_visits;   /* inverted-list entries streamed into accumulators; pairs of list entries
+                               tested by the list-pair self-join; 0 for a batch of queries that took
+                               the sketch kernels */
   int64_t candidates;       /* distinct (x, y) pairs with an accumulated indexed score */
-  int64_t bound_survivors;  /* candidates passing the size, max-weight and L2 bounds */
+  int64_t bound_survivors;  /* candidates passing the bounds (size, max-weight and L2, or the sketches') */
   int64_t verified;         /* survivors whose completed score A + dot(x, y') reached t - slack */
   int64_t band;             /* pairs rescored in double (float rescore within 1e-5 of t) */
   int64_t matches;          /* pairs returned */
-  double ms_candidates;     /* device time of the candidate/filter/verify kernel */
+  double ms_candidates;     /* device time of the kernels that count, filter and verify candidates */
   double ms_total;          /* device time of the whole call (kernels + sort) */
   /* screened join only (zero otherwise) */
   int64_t screen_rows;        /* rows whose head norm reaches t */
