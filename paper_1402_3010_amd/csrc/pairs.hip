@@ -1155,7 +1155,9 @@ __global__ void k_segments(const uint32_t* __restrict__ hoff, int32_t H, int32_t
 // takes a query at a time and forms the union of its dimensions' lists over
 // the block, 64 rows in each lane: bitmaps of the densest ranks from LDS, of
 // the next ones from L2, and the entries of the sparse lists by lane.  What
-// binds is cache lines per query and the latency of reading them.  A block's
+// binds is reading bitmaps and lines through the L1, whose address units are
+// busy 80% of the time (500,000 rows of mean 120: 64 ms, of which the bitmaps
+// alone, with the rest taken out, were 54).  A block's
 // bitmaps, list entries and offsets fit an XCD's L2, except the offsets of
 // the ranks >= H (8 bytes of every one of them): one bit per (block, rank)
 // says which have an entry there at all, about a fifth of a query's.  A
@@ -1163,7 +1165,8 @@ __global__ void k_segments(const uint32_t* __restrict__ hoff, int32_t H, int32_t
 // list offsets while the LDS bitmaps are read, and its first list entries
 // while the L2 bitmaps are, with two workgroups of 16 waves per CU.  Longer
 // spans of rows for the sparse ranks read fewer lines but miss the L2 (16,384
-// rows: 138 ms at 500,000 rows of mean 120, 65,536 rows: 209 ms).
+// rows: 138 ms, 65,536 rows: 209 ms), and the sparse ranks by whole lists,
+// through a buffer of bits, take longer by themselves (100 ms).
 constexpr int kCountWaves = 16;
 constexpr int kChunks = 3;   // 64-component chunks of a row in registers
 constexpr int kEntries = 4;  // list entries loaded ahead per component
