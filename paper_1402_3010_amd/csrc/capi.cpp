@@ -412,7 +412,6 @@ int build_impl(apss_index* ix, const int64_t* row_ptr, const int32_t* col, const
 // given by the caller names the accumulating kernel), and the sparse pass of
 // the screened join (whose geometry is that of the accumulating kernel
 // wherever the cost rule leaves it there).
-// (no tile variant, range width or group asked for)
 bool default_geometry(const apss_index* ix) {
   const apss_opts& o = ix->opts;
   return o.variant < 0 && o.range_rows == 0 && o.range_group == 0 && !getenv("APSS_VARIANT") &&
@@ -1049,7 +1048,6 @@ int plan_few(apss_index* ix, Workspace& ws, const QuerySet& Q, float t, const fl
   a.rs = ix->rs.p;
   a.pn8 = ix->pn8.p;
   a.n = ix->n;
-  a.off = ix->off.p;
   a.post = ix->post.p;
   a.hoff = ix->hoff[slot].p;
   a.H = ix->H;

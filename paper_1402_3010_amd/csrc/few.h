@@ -11,7 +11,6 @@ struct FewArgs {
   const RowStat* rs;
   const uint8_t* pn8;
   int64_t n;
-  const int64_t* off;     // [m+1] lists
   const Post* post;
   const uint32_t* hoff;   // [(nb+1) * H] first entry of a dense list in each block of cb rows
   int32_t H;

@@ -1,6 +1,6 @@
 """Results of few pairs are sorted and handed over by one kernel: the same pairs as a larger result's sort gives.
 
-The limit is 16,384 pairs: copies of one row make any number of them (k rows: k (k - 1) / 2 pairs).
+Copies of one row make any number of them (k rows: k (k - 1) / 2 pairs).
 """
 import numpy as np
 import pytest
