@@ -513,7 +513,14 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   // survivors are estimated from every k-th unit, and doubled: on rows that
   // the sketches do not tell apart (flat weights over few dimensions) they
   // are most pairs, and the accumulating kernel is ahead.  A join at a higher
-  // threshold than the index's has fewer.
+  // threshold than the index's has fewer.  In the sparse pass of a screened
+  // join the accumulating kernel pays for such pairs too: its bound there adds
+  // a product of the head's norms to what it has accumulated, and what passes
+  // is rescored one pair at a time.  Measured on flat, short, text and heavy
+  // rows with heads of 512 to 4096, it took 9 to 220 ns per survivor of the
+  // sketches beyond its visits (31,340 flat rows, t = 0.505, head 4096: 24.6
+  // ms against 3.3 by list pairs; head 512: 6.3 against 2.6; 100,000 text
+  // rows, 0.505, head 2048: 497 against 63), so 9 ns are counted.
   DBuf<unsigned long long> cnt;
   CHK(cnt.take(tmp, C_NUM + kRateBins), "alloc");
   if (int rc = reserve_control(ws)) return rc;
@@ -546,11 +553,12 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   const double blocks = (double)((n + kCountRows - 1) / kCountRows);
   const double pairs_ms = 1e3 * (k * (double)c[C_VISITS] / 1.5e12 + 2.0 * k * (double)c[C_SURVIVORS] * 0.45e-9 +
                                  (double)ix->nshort * 1.6e-9 + (double)windows * 0.4e-9 + (ix->head_cut > 0 ? 2.8e-12 * (double)c[C_TAILVISITS] : 0.5 * blocks * (double)ix->P * (2e-9 / 110.0)));
-  const double lists_ms = 1e3 * ((double)c[C_TAILVISITS] / 1.2e12 + 0.5 * (double)n * (double)n / 1.1e12);
+  const double lists_ms = 1e3 * ((double)c[C_TAILVISITS] / 1.2e12 + 0.5 * (double)n * (double)n / 1.1e12 +
+                                 (ix->head_cut > 0 ? k * (double)c[C_SURVIVORS] * 9e-9 : 0.0));
   // (up to one block of rows launches and waits are most of either: 0.24 ms
   // against 0.27 ms for 2,000 rows, so there only many survivors decide)
   const bool few = k * (double)c[C_SURVIVORS] <= 64.0 * (double)n;
-  ix->pairs_ready = n <= kCountRows ? few : pairs_ms < lists_ms;
+  ix->pairs_ready = (n <= kCountRows && (few || ix->head_cut == 0)) ? few : pairs_ms < lists_ms;
   ix->pair_survivors = k * (double)c[C_SURVIVORS];
   if (ix->opts.reserved[0] == kProbePairs) ix->pairs_ready = true;
   // Queries, per pair of a query and a row: 0.32 ps for the test and 0.49 for
