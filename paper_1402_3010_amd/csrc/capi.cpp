@@ -1137,25 +1137,6 @@ int plan_queries(apss_index* ix, Workspace& ws, const QuerySet& Q, float t, cons
   return APSS_OK;
 }
 
-// The candidate count of a plan, on its second stream if it has one: it and
-// the tests meet only in the counters.
-int start_count(JoinPlan& P, hipStream_t s) {
-  if (!P.aux) {
-    CHK(launch_count(P.ca, s), "count kernel");
-    return APSS_OK;
-  }
-  CHK(hipEventRecord(P.fork, s), "event");
-  CHK(hipStreamWaitEvent(P.aux, P.fork, 0), "event");
-  CHK(launch_count(P.ca, P.aux), "count kernel");
-  CHK(hipEventRecord(P.join, P.aux), "event");
-  return APSS_OK;
-}
-
-int end_count(JoinPlan& P, hipStream_t s) {
-  if (P.aux) CHK(hipStreamWaitEvent(s, P.join, 0), "event");
-  return APSS_OK;
-}
-
 // The caller has cleared the counters and queue counters.
 int launch_plan(JoinPlan& P, uint64_t* out_key, float* out_sim, int64_t cap, unsigned long long* counters,
                 unsigned int* qctr, hipStream_t s) {
@@ -1165,9 +1146,9 @@ int launch_plan(JoinPlan& P, uint64_t* out_key, float* out_sim, int64_t cap, uns
     P.pa.cap = cap;
     P.pa.counters = counters;
     P.ca.counters = counters;
-    if (int rc = start_count(P, s)) return rc;
+    CHK(launch_count(P.ca, s), "count kernel");
     CHK(launch_pairs(P.pa, P.pg, s), "pair kernel");
-    return end_count(P, s);
+    return APSS_OK;
   }
   if (P.query) {
     P.pa.out_key = out_key;
@@ -1175,7 +1156,7 @@ int launch_plan(JoinPlan& P, uint64_t* out_key, float* out_sim, int64_t cap, uns
     P.pa.cap = cap;
     P.pa.counters = counters;
     P.ca.counters = counters;
-    if (int rc = start_count(P, s)) return rc;
+    CHK(launch_count(P.ca, s), "count kernel");
     for (size_t r = 0; r < P.qend.size(); ++r) {
       if (r > 0) CHK(fill_u32(qctr, 0u, kQueueCounters, s), "fill");
       QueryArgs q = P.qa;
@@ -1183,7 +1164,7 @@ int launch_plan(JoinPlan& P, uint64_t* out_key, float* out_sim, int64_t cap, uns
       q.nq = P.qend[r];
       CHK(launch_query_screen(P.pa, q, P.pg, s), "query kernel");
     }
-    return end_count(P, s);
+    return APSS_OK;
   }
   if (P.few) {
     P.fa.out_key = out_key;
@@ -1217,27 +1198,6 @@ int reserve_control(Workspace& ws) {
   CHK(ws.counters.reserve(kControlWords), "alloc counters");
   ws.qctr = (unsigned int*)(ws.counters.p + C_NUM);
   ws.nfine = ws.qctr + kQueueCounters;
-  return APSS_OK;
-}
-
-int reserve_aux(Workspace& ws) {
-  if (!ws.aux) CHK(hipStreamCreateWithFlags(&ws.aux, hipStreamNonBlocking), "stream");
-  if (!ws.fork) CHK(hipEventCreateWithFlags(&ws.fork, hipEventDisableTiming), "event");
-  if (!ws.join) CHK(hipEventCreateWithFlags(&ws.join, hipEventDisableTiming), "event");
-  return APSS_OK;
-}
-
-// The plan's count beside its tests, for a captured graph: a branch that costs
-// the replay nothing (3,001 rows: 128 -> 112 us).  Called eagerly the events
-// cost a small join what they save (2,000 rows: 83 -> 103 us), and the count
-// of a large one fills the device (100,000 rows: 13.2 ms, and between 13.5 and
-// 16 beside the rest).
-int count_beside(Workspace& ws, JoinPlan& P) {
-  if (!P.pairs) return APSS_OK;
-  if (int rc = reserve_aux(ws)) return rc;
-  P.aux = ws.aux;
-  P.fork = ws.fork;
-  P.join = ws.join;
   return APSS_OK;
 }
 
@@ -1651,7 +1611,6 @@ int capture_join_graph(apss_index* ix, float t, uint32_t* out_i, uint32_t* out_j
   int rc = plan_join(ix, ws, QuerySet{ix->rows.rp.p, ix->rows.rc.p, ix->rows.mw.p, ix->n, ix->nnz,
                                       ix->rows.rp_host.data()},
                      1, t, nullptr, nullptr, P);
-  if (!rc) rc = count_beside(ws, P);
   if (rc) return rc;
   CHK(hipStreamSynchronize(s), "graph capture");
   CHK(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal), "graph capture");

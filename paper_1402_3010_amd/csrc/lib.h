@@ -246,14 +246,7 @@ struct Workspace {
   apss_stats last;
   int64_t regrows = 0;  // joins rerun because the pair buffer was too small
   hipEvent_t ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-  // a second stream for kernels that run beside the call's own; it starts and
-  // ends within the call (between the two events)
-  hipStream_t aux = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr;
   ~Workspace() {
-    if (fork) (void)hipEventDestroy(fork);
-    if (join) (void)hipEventDestroy(join);
-    if (aux) (void)hipStreamDestroy(aux);
     for (int e = 0; e < 6; ++e)
       if (ev[e]) (void)hipEventDestroy(ev[e]);
   }
@@ -354,9 +347,6 @@ struct JoinLayout {
 struct JoinPlan {
   bool pairs = false;  // the list-pair join: pa and ca in place of a
   bool query = false;  // the sketch test of queries: pa, qa and ca in place of a
-  // the count runs on aux beside the rest, where that is set
-  hipStream_t aux = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr;
   bool few = false;    // few queries: fa in place of a
   FewArgs fa{};
   PairArgs pa{};
@@ -385,8 +375,6 @@ void bind_plan(apss_index* ix, const QuerySet& Q, int triangle, float t, const f
 constexpr int kQueueCounters = 8;
 constexpr int64_t kControlWords = C_NUM + kQueueCounters / 2 + 1;
 int reserve_control(Workspace& ws);
-// Second stream of a workspace.
-int reserve_aux(Workspace& ws);
 // Test hook outside the ABI: apss_opts.reserved[0] of an index whose self-joins
 // take the list-pair kernels, and its queries the sketch kernels, whatever the
 // cost rules say.

@@ -183,8 +183,8 @@ def test_tiny_lists_share_tiles(lens):
 
 
 @pytest.mark.parametrize("n", [3001, 5000])
-def test_replays_count_beside_the_tests(n):
-    # the captured join counts candidates on a branch of its own: pairs and counters of every replay are the eager call's
+def test_replays_of_a_captured_join(n):
+    # pairs and counters of every replay are the eager call's
     import torch
 
     import paper_1402_3010_amd as apss
