@@ -1025,9 +1025,9 @@ void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue
   c.nq = ix->n;
   c.triangle = 1;
   // about eight work items per compute unit, of at least a few queries per
-  // wave; where that leaves the device idle one query per wave, which reads
-  // the bitmaps it needs from L2 instead of loading LDS with all of them
-  // (3,001 rows: 47 us for 70; 20,011 rows: 257 us for 235)
+  // wave; where that leaves the device idle one query per wave, counted by
+  // pieces of rows (a replay of 12,000 rows of mean 80: 350 us by the larger
+  // items, 269 so; 30,000 of mean 150: 1,069 us and 1,241; about even at 20,000)
   const int64_t want = ix->n * ix->count_blocks / 2 / 2048;
   c.chunk = std::max<int64_t>(64, std::min<int64_t>(4096, (want + 63) / 64 * 64));
   if (ix->n * ix->count_blocks / 2 / c.chunk < 512) {
@@ -1127,13 +1127,18 @@ int plan_queries(apss_index* ix, Workspace& ws, const QuerySet& Q, float t, cons
   c.rp = Q.rp;
   c.rc = Q.rc;
   c.nq = Q.n;
-  // a few work items per compute unit; a chunk of few queries reads the
-  // bitmaps it needs from L2 instead of loading LDS with all of them.  From
-  // 1,024 queries on, 64 of a block's items (as many as run on an XCD at
-  // once) take the batch, so that they share one block's bitmaps in its L2
+  // a few work items per compute unit; where those are of few queries, of one
+  // per wave, counted by pieces of rows (500,000 rows: 250 queries 424 -> 378
+  // us, 600 592 -> 600; 1,000,000 rows: 150 queries 544 -> 460, 400 740 ->
+  // 754; 200,000 rows: 400 queries 301 -> 263).  From 1,024 queries on, 64 of
+  // a block's items (as many as run on an XCD at once) take the batch, so that
+  // they share one block's bitmaps in its L2
   const int64_t want = Q.n >= 1024 ? std::max<int64_t>(64, Q.n / 64) : Q.n * ix->count_blocks / 1024;
   c.chunk = std::max<int64_t>(16, std::min<int64_t>(4096, (want + 15) / 16 * 16));
-  if (c.chunk < 64) c.lds_ranks = 0;
+  if (c.chunk < 64) {
+    c.chunk = 16;
+    c.lds_ranks = 0;
+  }
   return APSS_OK;
 }
 

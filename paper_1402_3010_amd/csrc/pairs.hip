@@ -1203,6 +1203,19 @@ __device__ __forceinline__ void entry_rows(const CountArgs& a, uint32_t p, uint3
   }
 }
 
+// Block and chunk of a workgroup: those of an XCD (round-robin over blockIdx)
+// take whole blocks; few blocks are spread over all of them.
+__device__ __forceinline__ void count_item(const CountArgs& a, int64_t nchunk, int64_t* b, int64_t* j) {
+  *j = (int64_t)(blockIdx.x >> 3);
+  if (a.nblk < kSpreadBlocks) {
+    *b = (int64_t)blockIdx.x % a.nblk;
+    *j = (int64_t)blockIdx.x / a.nblk;
+  } else {
+    *b = (int64_t)(blockIdx.x & 7u) + 8 * (*j / nchunk);
+    *j %= nchunk;
+  }
+}
+
 template <bool PACKED>
 __global__ __launch_bounds__(64 * kCountWaves) __attribute__((amdgpu_waves_per_eu(8))) void k_count(CountArgs a,
                                                                                                    int64_t nchunk) {
@@ -1211,16 +1224,8 @@ __global__ __launch_bounds__(64 * kCountWaves) __attribute__((amdgpu_waves_per_e
   const int tid = (int)threadIdx.x;
   const int lane = tid & 63;
   const int wave = uni(tid >> 6);
-  // the workgroups of an XCD (round-robin over blockIdx) take whole blocks;
-  // few blocks are spread over all of them
-  int64_t b, j = (int64_t)(blockIdx.x >> 3);
-  if (a.nblk < kSpreadBlocks) {
-    b = (int64_t)blockIdx.x % a.nblk;
-    j = (int64_t)blockIdx.x / a.nblk;
-  } else {
-    b = (int64_t)(blockIdx.x & 7u) + 8 * (j / nchunk);
-    j %= nchunk;
-  }
+  int64_t b, j;
+  count_item(a, nchunk, &b, &j);
   if (b >= a.nblk) return;
   const int64_t row0 = b * kCountRows;
   const int64_t qbeg = j * a.chunk;
@@ -1401,6 +1406,122 @@ __global__ __launch_bounds__(64 * kCountWaves) __attribute__((amdgpu_waves_per_e
   if (lane == 0 && c) atomicAdd(total, c);
   __syncthreads();
   if (tid == 0 && *total) atomicAdd(&a.counters[C_CANDIDATES], *total);
+}
+
+// The same count for few rows (a chunk has one query per wave, and no bitmaps
+// go to LDS): what binds there is the longest row of a workgroup, whose
+// bitmaps a wave reads at some 20 ns a component.  So the rows' components
+// are cut into pieces of 64, the waves take them in turn, and the unions meet
+// in LDS; eight bitmaps are loaded at once, since few waves run.
+// A captured self-join with it, and with a wave for each row: 3,001 rows of
+// mean 80 (up to 2,000) 89 us and 116, 4,000 of mean 120 109 and 170, 12,000
+// of mean 150 233 and 300, 8,960 of 10 to 60 components 95 and 95; 64 queries
+// of 500,000 rows 187 and 199.
+template <bool PACKED>
+__global__ __launch_bounds__(64 * kCountWaves) void k_count_pieces(CountArgs a, int64_t nchunk) {
+  __shared__ uint32_t bits[kCountWaves][kCountWords];
+  __shared__ unsigned long long total;
+  const int tid = (int)threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = uni(tid >> 6);
+  int64_t b, j;
+  count_item(a, nchunk, &b, &j);
+  if (b >= a.nblk) return;
+  const int64_t row0 = b * kCountRows;
+  int64_t q0 = j * a.chunk;
+  const int64_t qend = q0 + a.chunk < a.nq ? q0 + a.chunk : a.nq;
+  if (a.triangle && q0 <= row0) q0 = row0 + 1;
+  if (q0 >= qend) return;
+  uint32_t* const own = bits[wave];
+  own[2 * lane] = 0u;
+  own[2 * lane + 1] = 0u;
+  if (tid == 0) total = 0ull;
+  // lane i: the i-th query's components, and the pieces up to and with it
+  int64_t s = 0;
+  int len = 0;
+  if (lane < kCountWaves && q0 + lane < qend) {
+    s = a.rp[q0 + lane] + (a.skip ? (int64_t)a.skip[q0 + lane].cut : 0);
+    len = (int)(a.rp[q0 + lane + 1] - s);
+  }
+  const int own_pieces = (len + 63) >> 6;
+  int upto = own_pieces;
+#pragma unroll
+  for (int o = 1; o < kCountWaves; o <<= 1) {
+    const int x = __shfl_up(upto, o, 64);
+    if (lane >= o) upto += x;
+  }
+  const int pieces = __builtin_amdgcn_readlane(upto, kCountWaves - 1);
+  const uint32_t* const bmb = a.bm + b * (int64_t)a.HB * kCountWords;
+  const uint2* const bm2 = reinterpret_cast<const uint2*>(bmb) + lane;
+  const uint2* const seg = a.seg + b * (int64_t)a.H;
+  const int64_t rg0 = row0 / a.rr;
+  int64_t rg1 = (row0 + kCountRows + a.rr - 1) / a.rr;
+  if (rg1 > a.nR) rg1 = a.nR;
+  const uint32_t* const t0 = a.toff + rg0 * (int64_t)a.m_tail;
+  const uint32_t* const t1 = a.toff + rg1 * (int64_t)a.m_tail;
+  const uint32_t* const present = a.present + b * a.present_words;
+  __syncthreads();
+
+  for (int t = wave; t < pieces; t += kCountWaves) {
+    const int i = (int)__popcll(__ballot(lane < kCountWaves && upto <= t));
+    const int k = 64 * (t - __builtin_amdgcn_readlane(upto - own_pieces, i)) + lane;
+    const int64_t si = __shfl(s, i, 64);  // (from a lane that has to be active)
+    const int r = k < __builtin_amdgcn_readlane(len, i) ? a.rc[si + k].r : kNoRank;
+    uint32_t p = 0u, pe = 0u;
+    if (r >= a.H && r != kNoRank) {
+      if ((present[(r - a.H) >> 5] >> ((r - a.H) & 31)) & 1u) {
+        p = t0[r - a.H];
+        pe = t1[r - a.H];
+      }
+    } else if (r >= a.HB && r != kNoRank) {
+      const uint2 g = seg[r];
+      p = g.x;
+      pe = g.y;
+    }
+    uint32_t y[kEntries];
+    entry_rows<PACKED>(a, p, pe, (uint32_t)row0, y);
+    // ranks ascend: the bitmaps' are the first lanes (one read twice changes nothing)
+    uint2 v = make_uint2(0u, 0u);
+    const int n = (int)__popcll(__ballot(r < a.HB));
+    for (int c = 0; c < n; c += 8) {
+      uint2 x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        x[u] = bm2[__builtin_amdgcn_readlane(r, c + u < n ? c + u : n - 1) * (kCountWords / 2)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        v.x |= x[u].x;
+        v.y |= x[u].y;
+      }
+    }
+    uint32_t* const to = bits[i];
+    if (v.x) atomicOr(&to[2 * lane], v.x);
+    if (v.y) atomicOr(&to[2 * lane + 1], v.y);
+    while (true) {
+#pragma unroll
+      for (int u = 0; u < kEntries; ++u)
+        if (y[u] < (uint32_t)kCountRows) atomicOr(&to[y[u] >> 5], 1u << (y[u] & 31u));
+      if (p >= pe || pe - p <= (uint32_t)kEntries) break;
+      p += kEntries;
+      entry_rows<PACKED>(a, p, pe, (uint32_t)row0, y);
+    }
+  }
+  __syncthreads();
+  const int64_t q = q0 + wave;
+  unsigned long long c = 0ull;
+  if (q < qend) {
+    uint64_t v = (uint64_t)own[2 * lane] | ((uint64_t)own[2 * lane + 1] << 32);
+    if (a.triangle && q < row0 + kCountRows) {
+      const int lim = (int)(q - row0) - 64 * lane;  // rows of this lane's 64 before q
+      v &= lim <= 0 ? 0ull : (lim >= 64 ? ~0ull : (1ull << lim) - 1ull);
+    }
+    c = (unsigned long long)__popcll(v);
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o, 64);
+  if (lane == 0 && c) atomicAdd(&total, c);
+  __syncthreads();
+  if (tid == 0 && total) atomicAdd(&a.counters[C_CANDIDATES], total);
 }
 
 // The same count where every list is sparse (the head-cut index of the
@@ -1671,7 +1792,12 @@ hipError_t launch_count(const CountArgs& a, hipStream_t s) {
   if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
   // a segment spans at most the ranges that meet a block
   const bool packed = kCountRows + 2 * a.rr <= 65536;
-  if (packed)
+  const bool pieces = a.chunk <= kCountWaves && a.lds_ranks == 0;
+  if (pieces && packed)
+    hipLaunchKernelGGL(k_count_pieces<true>, dim3((unsigned)grid), dim3(64 * kCountWaves), 0, s, a, nchunk);
+  else if (pieces)
+    hipLaunchKernelGGL(k_count_pieces<false>, dim3((unsigned)grid), dim3(64 * kCountWaves), 0, s, a, nchunk);
+  else if (packed)
     hipLaunchKernelGGL(k_count<true>, dim3((unsigned)grid), dim3(64 * kCountWaves), 0, s, a, nchunk);
   else
     hipLaunchKernelGGL(k_count<false>, dim3((unsigned)grid), dim3(64 * kCountWaves), 0, s, a, nchunk);

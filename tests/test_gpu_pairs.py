@@ -208,3 +208,19 @@ def test_replays_of_a_captured_join(n):
                 assert now[key] == st[key], key
     finally:
         ix.close()
+
+
+@pytest.mark.parametrize("lens", [(1, 63, 64, 65, 128, 129), (1,) * 15 + (1100,), (1500, 2, 64, 700), (64,) * 33])
+def test_count_of_few_rows_by_pieces(lens):
+    # rows around multiples of 64 components, long ones among short, and workgroups of fewer than 16 rows
+    rng = np.random.default_rng(sum(lens))
+    m, n = 2000, 2 * 4096 + 17
+    rows = []
+    for k in range(n):
+        c = np.sort(rng.choice(m, size=min(lens[k % len(lens)] if k % 97 < 33 else 5, m), replace=False))
+        rows.append((c, rng.lognormal(0.0, 1.0, size=len(c))))
+    V = csr(rows, m)
+    t = np.float32(0.8)
+    (a, sa), (b, sb) = join(V, t, pairs=True), join(V, t, variant=1)
+    assert all(np.array_equal(np.asarray(x).view(np.uint32), np.asarray(y).view(np.uint32)) for x, y in zip(a, b))
+    assert sa["candidates"] == sb["candidates"]
