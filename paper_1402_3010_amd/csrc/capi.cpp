@@ -123,6 +123,7 @@ hipError_t spare_take(size_t bytes, void** p, size_t* size, int* device_out) {
   if (*p) return hipSuccess;
   e = hipMalloc(p, bytes);
   if (e != hipSuccess) {
+    (void)hipGetLastError();  // (kept until asked for: the next launch's check would find it)
     spare_release();
     e = hipMalloc(p, bytes);
   }

@@ -114,6 +114,7 @@ struct DBuf {
     if (count <= 0) count = 1;
     hipError_t e = hipMalloc((void**)&p, sizeof(T) * (size_t)count);
     if (e != hipSuccess) {
+      (void)hipGetLastError();  // (kept until asked for: the next launch's check would find it)
       spare_release();
       e = hipMalloc((void**)&p, sizeof(T) * (size_t)count);
     }
@@ -154,6 +155,7 @@ struct PinnedBuf {
     p = nullptr;
     n = 0;
     if (hipHostMalloc((void**)&p, (k > 0 ? k : 1) * sizeof(T), hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
       p = nullptr;
       return false;
     }
