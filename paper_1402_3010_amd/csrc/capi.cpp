@@ -319,7 +319,7 @@ int build_impl(apss_index* ix, const int64_t* row_ptr, const int32_t* col, const
     }
   }
   // the build's scratch, sized for the list sort too (at most nnz postings)
-  const int64_t big = std::max<int64_t>(nnz, m);
+  const int64_t big = std::max<int64_t>(nnz, m + 1);
   Arena tmp;
   struct Scratch {  // (the sort buffers are pieces of tmp, and end before it)
     SortScratch& ss;
@@ -331,13 +331,15 @@ int build_impl(apss_index* ix, const int64_t* row_ptr, const int32_t* col, const
       for (DBuf<int64_t>* b : {&ss.hist, &ss.scan}) b->release();
     }
   } scratch{ws.ss, s};
+  const int lists = ix->opts.screen_dims > 0 ? 2 : 1;  // (with the head-cut index's)
   CHK(tmp.reserve(4 * Arena::bytes<uint64_t>(big) + Arena::bytes<int64_t>(radix_hist_elems(big)) +
                   Arena::bytes<int64_t>(radix_scan_tmp_elems(big)) + 3 * Arena::bytes<uint32_t>(m) +
-                  Arena::bytes<uint32_t>(nnz / kWaveRow + 1) + Arena::bytes<int64_t>(n + 1) +
-                  Arena::bytes<int64_t>(scan_tmp_elems(n + 1)) + 3 * Arena::bytes<int64_t>(std::max(list_tiles(nnz), m + 1)) +
+                  Arena::bytes<uint32_t>(nnz / kWaveRow + 1) +
+                  lists * (Arena::bytes<int64_t>(n + 1) + Arena::bytes<int64_t>(scan_tmp_elems(n + 1)) +
+                           Arena::bytes<int64_t>(scan_tmp_elems(big))) +
                   (on_device ? 0 : Arena::bytes<int64_t>(n + 1) + 2 * Arena::bytes<float>(nnz)) + 64 * 256),
       "alloc scratch");
-  CHK(ix->mem.reserve(Arena::bytes<int64_t>(n + 1) + Arena::bytes<RComp>(nnz) + 3 * Arena::bytes<uint32_t>(m) +
+  CHK(ix->mem.reserve(Arena::bytes<int64_t>(n + 1) + Arena::bytes<RComp>(nnz) + 2 * Arena::bytes<uint32_t>(m) +
                       Arena::bytes<RowStat>(n) + Arena::bytes<float>(n) + Arena::bytes<uint8_t>(n) +
                       Arena::bytes<uint32_t>(m + n)),
       "alloc index");
@@ -366,10 +368,8 @@ int build_impl(apss_index* ix, const int64_t* row_ptr, const int32_t* col, const
   CHK(launch_dim_keys(cnt.p, m, n, dbits, ss.k1.p, ss.v64a.p, s), "dim keys");
   CHK(radix_sort_u64(ss.k1.p, ss.v64a.p, ss.k2.p, ss.v64b.p, m, dbits + cbits, ss.hist.p, ss.scan.p, s), "dim sort");
   CHK(ix->rank.take(ix->mem, m), "alloc");
-  CHK(ix->inv.take(ix->mem, m), "alloc");
   CHK(ix->mw_r.take(ix->mem, m), "alloc");
-  CHK(launch_rank_from_sorted(ss.v64a.p, m, cnt.p, mwbits.p, ix->rank.p, ix->inv.p, ix->mw_r.p, cnt_r.p, s),
-      "ranks");
+  CHK(launch_rank_from_sorted(ss.v64a.p, m, cnt.p, mwbits.p, ix->rank.p, ix->mw_r.p, cnt_r.p, s), "ranks");
 
   CHK(ix->out.take(ix->mem, m + n), "alloc");
 
@@ -438,43 +438,75 @@ int64_t count_bytes(const apss_index* ix) {
          Arena::bytes<uint32_t>(blocks * std::max<int64_t>(1, (ix->m - H + 31) / 32));
 }
 
+// An index without the list-pair and sketch tables: its joins and queries take
+// the accumulating kernel.
+int drop_pair_tables(apss_index* ix) {
+  CHK(hipStreamSynchronize(ix->ws.stream), "build_index");
+  ix->pairs_ready = ix->screen_queries = false;
+  for (DBuf<uint8_t>* b : {&ix->sk, &ix->mid, &ix->fsk}) b->release();
+  for (DBuf<uint32_t>* b : {&ix->dl, &ix->dlr, &ix->fidx}) b->release();
+  for (DBuf<uint2>* b : {&ix->wide, &ix->shorts}) b->release();
+  ix->gid.release();
+  ix->doff.release();
+  ix->ndeep = ix->nwide = ix->nshort = 0;
+  ix->pair_mem.release();
+  return APSS_OK;
+}
+
+// Memory for those tables.  *have is false, and the index does without them,
+// if the device has too little.
+int reserve_pair_tables(apss_index* ix, int64_t bytes, bool* have) {
+  const hipError_t e = ix->pair_mem.reserve(bytes);
+  *have = e == hipSuccess;
+  if (*have) return APSS_OK;
+  const int rc = dev_err(e, "alloc tables");
+  return rc == APSS_ENOMEM ? drop_pair_tables(ix) : rc;
+}
+
 // Sketches, deep lists and work units, from the sorted list values in the
-// sort scratch (with the lists of every index).
+// sort scratch (with the lists of every index).  The sort's other buffers, of
+// at least m + 1 entries, hold what is passing.
 int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   Workspace& ws = ix->ws;
   hipStream_t s = ws.stream;
   SortScratch& ss = ws.ss;
   const int64_t n = ix->n, m = ix->m, P = ix->P;
   const int64_t nt = list_tiles(P);
-  const int64_t longest = std::max(nt, m + 1);
-  DBuf<int64_t> tiles, scan, total;
-  CHK(tiles.take(tmp, longest), "alloc");
-  CHK(scan.take(tmp, scan_tmp_elems(longest)), "alloc");
+  int64_t* const tiles = (int64_t*)ss.v64b.p;
+  DBuf<int64_t> scan, total;
+  CHK(scan.take(tmp, scan_tmp_elems(std::max(nt, m + 1))), "alloc");
   CHK(total.take(tmp, 1), "alloc");
   int64_t deep = 0;
-  CHK(launch_count_deep(ss.v64a.p, P, tiles.p, s), "deep lists");
-  CHK(exclusive_scan_i64(tiles.p, nt, scan.p, total.p, s), "scan");
+  CHK(launch_count_deep(ss.v64a.p, P, tiles, s), "deep lists");
+  CHK(exclusive_scan_i64(tiles, nt, scan.p, total.p, s), "scan");
   CHK(hipMemcpyAsync(&deep, total.p, sizeof(int64_t), hipMemcpyDeviceToHost, s), "deep lists");
   CHK(hipStreamSynchronize(s), "deep lists");
   int64_t longs = 0;
   for (int64_t r = 0; r < n; ++r) longs += ix->rows.rp_host[(size_t)r + 1] - ix->rows.rp_host[(size_t)r] > kFineRow;
-  CHK(ix->pair_mem.reserve(2 * Arena::bytes<uint32_t>(deep) + Arena::bytes<int64_t>(m + 1) + Arena::bytes<uint16_t>(m) +
-                           Arena::bytes<uint8_t>(n * kSkGroups) + Arena::bytes<uint8_t>(n * kMidGroups) +
-                           Arena::bytes<uint32_t>(n) + Arena::bytes<uint8_t>(longs * kFineGroups)),
-      "alloc tables");
+  bool have = false;
+  int rc = reserve_pair_tables(ix, 2 * Arena::bytes<uint32_t>(deep) + Arena::bytes<int64_t>(m + 1) +
+                                       Arena::bytes<uint16_t>(m) + Arena::bytes<uint8_t>(n * kSkGroups) +
+                                       Arena::bytes<uint8_t>(n * kMidGroups) + Arena::bytes<uint32_t>(n) +
+                                       Arena::bytes<uint8_t>(longs * kFineGroups),
+                               &have);
+  if (rc) return rc;
+  if (!have) {
+    CHK(launch_lists(nullptr, ss.v64a.p, P, ix->post.p, ix->post4.p, nullptr, nullptr, nullptr, nullptr, s), "lists");
+    return APSS_OK;
+  }
   ix->ndeep = deep;
   CHK(ix->dl.take(ix->pair_mem, deep), "alloc");
   CHK(ix->dlr.take(ix->pair_mem, deep), "alloc");
   CHK(ix->doff.take(ix->pair_mem, m + 1), "alloc");
-  uint32_t* pos = (uint32_t*)ss.k2.p;  // the sort's second keys are free
-  CHK(launch_lists(ss.k1.p, ss.v64a.p, P, ix->post.p, ix->post4.p, tiles.p, pos, ix->dl.p, ix->dlr.p, s), "lists");
+  uint32_t* pos = (uint32_t*)ss.k2.p;
+  CHK(launch_lists(ss.k1.p, ss.v64a.p, P, ix->post.p, ix->post4.p, tiles, pos, ix->dl.p, ix->dlr.p, s), "lists");
   CHK(launch_deep_offsets(ix->off.p, pos, P, m, deep, ix->doff.p, s), "deep lists");
   // groups of ranks of about equal component counts, and the sketches
   CHK(ix->gid.take(ix->pair_mem, m), "alloc");
   CHK(ix->sk.take(ix->pair_mem, n * kSkGroups), "alloc");
-  CHK(launch_widen(cnt_r, m, tiles.p, s), "groups");
-  CHK(exclusive_scan_i64(tiles.p, m, scan.p, nullptr, s), "scan");
-  CHK(launch_groups(tiles.p, cnt_r, m, ix->nnz, ix->gid.p, s), "groups");
+  CHK(launch_widen(cnt_r, m, tiles, s), "groups");
+  CHK(exclusive_scan_i64(tiles, m, scan.p, nullptr, s), "scan");
+  CHK(launch_groups(tiles, cnt_r, m, ix->nnz, ix->gid.p, s), "groups");
   CHK(ix->mid.take(ix->pair_mem, n * kMidGroups), "alloc");
   CHK(ix->fidx.take(ix->pair_mem, n), "alloc");
   CHK(ix->fsk.take(ix->pair_mem, longs * kFineGroups), "alloc");
@@ -484,22 +516,23 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   CHK(launch_sketch(ix->rows.rp.p, ix->rows.rc.p, ix->gid.p, n, ix->sk.p, ix->mid.p, nfine.p, ix->fidx.p,
                     ix->fsk.p, s), "sketches");
   // work units by rank
-  DBuf<int64_t> stiles;
-  CHK(stiles.take(tmp, m + 1), "alloc");
-  CHK(launch_unit_counts(ix->doff.p, m, true, tiles.p, s), "units");
-  CHK(launch_unit_counts(ix->doff.p, m, false, stiles.p, s), "units");
-  CHK(exclusive_scan_i64(tiles.p, m, scan.p, total.p, s), "scan");
+  int64_t* const stiles = (int64_t*)ss.k1.p;
+  CHK(launch_unit_counts(ix->doff.p, m, true, tiles, s), "units");
+  CHK(launch_unit_counts(ix->doff.p, m, false, stiles, s), "units");
+  CHK(exclusive_scan_i64(tiles, m, scan.p, total.p, s), "scan");
   CHK(hipMemcpyAsync(&ix->nwide, total.p, sizeof(int64_t), hipMemcpyDeviceToHost, s), "units");
-  CHK(exclusive_scan_i64(stiles.p, m, scan.p, total.p, s), "scan");
+  CHK(exclusive_scan_i64(stiles, m, scan.p, total.p, s), "scan");
   CHK(hipMemcpyAsync(&ix->nshort, total.p, sizeof(int64_t), hipMemcpyDeviceToHost, s), "units");
   CHK(hipStreamSynchronize(s), "units");
-  // (with the candidate count's tables: see build_bitmaps)
-  CHK(ix->pair_mem.reserve(Arena::bytes<uint2>(ix->nwide) + Arena::bytes<uint2>(ix->nshort) + count_bytes(ix)),
-      "alloc tables");
+  // (with the candidate count's tables: see build_bitmaps.  The kernels count
+  // units in 31 bits; whole-corpus lists of some 20 million rows have more)
+  if (ix->nwide > kMaxUnits || ix->nshort > kMaxUnits) return drop_pair_tables(ix);
+  rc = reserve_pair_tables(ix, Arena::bytes<uint2>(ix->nwide) + Arena::bytes<uint2>(ix->nshort) + count_bytes(ix), &have);
+  if (rc || !have) return rc;
   CHK(ix->wide.take(ix->pair_mem, ix->nwide), "alloc");
   CHK(ix->shorts.take(ix->pair_mem, ix->nshort), "alloc");
-  CHK(launch_unit_fill(ix->doff.p, tiles.p, m, true, ix->wide.p, s), "units");
-  CHK(launch_unit_fill(ix->doff.p, stiles.p, m, false, ix->shorts.p, s), "units");
+  CHK(launch_unit_fill(ix->doff.p, tiles, m, true, ix->wide.p, s), "units");
+  CHK(launch_unit_fill(ix->doff.p, stiles, m, false, ix->shorts.p, s), "units");
   ix->pair_groups = pairs_resident_groups();
   // The list-pair kernels or the accumulating one, whichever should take
   // less, by their measured rates (MI355X): the accumulating kernel visits
@@ -580,14 +613,7 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   ix->screen_queries = ix->head_cut == 0 && ix->opts.query_safe &&
                        (ix->screen_ps + kSurvivorPs * ix->rate[kRateBins / 2] < ix->accumulate_ps ||
                         ix->opts.reserved[0] == kProbePairs);
-  if (!ix->pairs_ready && !ix->screen_queries) {
-    for (DBuf<uint8_t>* b : {&ix->sk, &ix->mid, &ix->fsk}) b->release();
-    for (DBuf<uint32_t>* b : {&ix->dl, &ix->dlr, &ix->fidx}) b->release();
-    for (DBuf<uint2>* b : {&ix->wide, &ix->shorts}) b->release();
-    ix->gid.release();
-    ix->doff.release();
-    ix->pair_mem.release();  // (the stream has drained)
-  }
+  if (!ix->pairs_ready && !ix->screen_queries) return drop_pair_tables(ix);
   return APSS_OK;
 }
 
@@ -666,13 +692,14 @@ int build_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
         "alloc index");
   }
   // inverted lists of the indexed parts: stable sort by rank keeps vector ids ascending
-  CHK(ss.k1.reserve(P), "alloc");
+  const bool pairs = pairs_eligible(ix) && P > 0;
+  const int64_t room = pairs ? std::max<int64_t>(P, m + 1) : P;
+  CHK(ss.k1.reserve(room), "alloc");
   CHK(ss.k2.reserve(P), "alloc");
   CHK(ss.v64a.reserve(P), "alloc");
-  CHK(ss.v64b.reserve(P), "alloc");
+  CHK(ss.v64b.reserve(room), "alloc");
   CHK(ss.hist.reserve(radix_hist_elems(P)), "alloc");
   CHK(ss.scan.reserve(radix_scan_tmp_elems(P)), "alloc");
-  const bool pairs = pairs_eligible(ix) && P > 0;
   // rows may exceed norm 1 by 1e-5, and the scan rounds: 1e-4 covers both
   const double lim = pairs ? (double)ix->t_build * (double)ix->t_build * (1.0 - 1e-4) : -1.0;
   CHK(launch_emit_indexed(ix->rows.rp.p, ix->rows.rc.p, ix->rs.p, nidx.p, n, lim, ss.k1.p, ss.v64a.p, s), "emit");

@@ -31,7 +31,7 @@ hipError_t launch_sort_rows(const int64_t* rp, const int32_t* col, const float* 
 hipError_t launch_dim_keys(const uint32_t* cnt, int64_t m, int64_t n, int dbits, uint64_t* keys, uint64_t* vals,
                            hipStream_t s);
 hipError_t launch_rank_from_sorted(const uint64_t* vals, int64_t m, const uint32_t* cnt, const uint32_t* mwbits,
-                                   int32_t* rank, int32_t* inv, float* mw_r, uint32_t* cnt_r, hipStream_t s);
+                                   int32_t* rank, float* mw_r, uint32_t* cnt_r, hipStream_t s);
 hipError_t launch_row_keys(const int64_t* rp, const int32_t* col, const float* val, const int32_t* rank, int64_t n,
                            int rbits, uint64_t* keys, uint32_t* vals, hipStream_t s);
 hipError_t launch_unpack_rows(const uint64_t* keys, const uint32_t* vals, int64_t nnz, int rbits, RComp* rc,

@@ -148,12 +148,10 @@ __global__ void k_dim_keys(const uint32_t* __restrict__ cnt, int64_t m, int64_t 
 
 __global__ void k_rank_from_sorted(const uint64_t* __restrict__ vals, int64_t m, const uint32_t* __restrict__ cnt,
                                    const uint32_t* __restrict__ mwbits, int32_t* __restrict__ rank,
-                                   int32_t* __restrict__ inv, float* __restrict__ mw_by_rank,
-                                   uint32_t* __restrict__ cnt_by_rank) {
+                                   float* __restrict__ mw_by_rank, uint32_t* __restrict__ cnt_by_rank) {
   for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < m; r += (int64_t)gridDim.x * blockDim.x) {
     const int32_t d = (int32_t)vals[r];
     rank[d] = (int32_t)r;
-    inv[r] = d;
     mw_by_rank[r] = __uint_as_float(mwbits[d]);
     cnt_by_rank[r] = cnt[d];
   }
@@ -728,8 +726,8 @@ hipError_t launch_dim_keys(const uint32_t* cnt, int64_t m, int64_t n, int dbits,
 }
 
 hipError_t launch_rank_from_sorted(const uint64_t* vals, int64_t m, const uint32_t* cnt, const uint32_t* mwbits,
-                                   int32_t* rank, int32_t* inv, float* mw_r, uint32_t* cnt_r, hipStream_t s) {
-  LAUNCH(k_rank_from_sorted, m, vals, m, cnt, mwbits, rank, inv, mw_r, cnt_r);
+                                   int32_t* rank, float* mw_r, uint32_t* cnt_r, hipStream_t s) {
+  LAUNCH(k_rank_from_sorted, m, vals, m, cnt, mwbits, rank, mw_r, cnt_r);
   return hipSuccess;
 }
 

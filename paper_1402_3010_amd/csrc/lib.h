@@ -280,7 +280,7 @@ struct apss_index {
   apss::RankRows rows;  // corpus rows in rank space (densest dimension first)
   apss::DBuf<uint32_t> out;  // [m + n] staging of apss_index_export
   apss::DBuf<apss::RowStat> rs;
-  apss::DBuf<int32_t> rank, inv;
+  apss::DBuf<int32_t> rank;
   apss::DBuf<float> mw_r;  // maxweight by rank
   apss::DBuf<int64_t> off;
   apss::DBuf<apss::Post> post;

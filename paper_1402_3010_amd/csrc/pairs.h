@@ -27,6 +27,7 @@ constexpr int kWideSpan = 16;
 constexpr int kUnitRows = 64;
 constexpr int kTinyList = 32;
 constexpr int kShortUnits = 16;
+constexpr int64_t kMaxUnits = 0x7FFFFFFF;  // of either kind
 // The candidate count: corpus rows per block, and the densest ranks with a
 // bitmap per block (one bit per row whose indexed part holds the rank).
 constexpr int kCountRows = 4096;

@@ -1698,8 +1698,8 @@ PairGroups pairs_resident_groups() {
 hipError_t launch_pairs(PairArgs a, const PairGroups& g, hipStream_t s) {
   if (a.ndeep <= 0) return hipSuccess;
   if (!a.dlr || !a.rp || !a.rc || !a.sk || !a.gid || !a.fidx || !a.fsk || !a.qrp || !a.qrc || !a.qfidx || !a.qfsk || !a.dl || !a.doff || !a.wide || !a.shorts || !a.uctr ||
-      (a.sample == 0 && (!a.out_key || !a.out_sim)) || !a.counters || (a.qcap > 0 && !a.queue) || a.nwide > 0x7FFFFFFF ||
-      a.nshort > 0x7FFFFFFF)
+      (a.sample == 0 && (!a.out_key || !a.out_sim)) || !a.counters || (a.qcap > 0 && !a.queue) || a.nwide > kMaxUnits ||
+      a.nshort > kMaxUnits)
     return hipErrorInvalidValue;
   hipError_t e = hipSuccess;
   const int64_t every = a.sample > 0 ? a.sample : 1;

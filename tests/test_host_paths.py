@@ -22,3 +22,78 @@ for k in range(fake.fake_mallocs()):
     reached += fake.fake_mallocs() > k  # (memory that is kept needs no call)
 assert reached > 4
 """)
+
+
+# An index with postings: k_cutoff indexes every component, scans add up, and the deep lists hold `deep` entries in
+# `units` wide units.
+LISTS = """
+deep, units = 600, 1 << 20
+P64 = ctypes.POINTER(ctypes.c_int64)
+arg = lambda args, k, t: ctypes.cast(args[k], ctypes.POINTER(t))[0]
+at = lambda args, k: arg(args, k, P64)
+
+@ctypes.CFUNCTYPE(None, ctypes.c_char_p, ctypes.POINTER(ctypes.c_void_p))
+def hook(name, args):
+    name = name.decode()
+    if "k_cutoff" in name:
+        rp, nidx = at(args, 0), at(args, 9)
+        for r in range(arg(args, 3, ctypes.c_int64)):
+            nidx[r] = rp[r + 1] - rp[r]
+    elif "k_scan_chunk" in name:
+        data, n, total = at(args, 0), arg(args, 1, ctypes.c_int64), 0
+        assert n <= 2048
+        for k in range(n):
+            data[k], total = total, total + data[k]
+        at(args, 2)[0] = total
+    elif "k_count_deep" in name:
+        at(args, 2)[0] = deep
+    elif "k_unit_countsILb1E" in name:
+        at(args, 2)[0] = units
+
+fake.fake_hook(hook)
+
+def joined(ix):
+    launches()
+    ix.join(0.5)
+    return launches()
+
+ran = lambda kernel, names: any(kernel in k for k in names)
+"""
+
+
+def test_an_index_without_room_for_pair_lists_is_built_without(tmp_path):
+    # each allocation of a build fails in turn, for good: the index's own end the build with APSS_ENOMEM, those of the
+    # list-pair tables alone leave an index whose joins take the accumulating kernel
+    fake_device.run(tmp_path, LISTS + """
+import os
+
+def outcome(k):  # of a build, in a process of its own, whose k-th allocation and its repetition fail
+    fake.fake_fail_mallocs(k, 2)
+    try:
+        ix = index(600)
+    except apss.ApssError as e:
+        assert e.code == apss.APSS_ENOMEM
+        return 1
+    reached = fake.fake_mallocs() > k
+    fake.fake_fail_mallocs(0, 0)
+    names = joined(ix)
+    assert ran("k_pairs_wide", names) != reached and ran("k_join", names) == reached
+    return 2 if reached else 3
+
+got = []
+while 3 not in got:
+    if not (pid := os.fork()):
+        os._exit(outcome(len(got)))
+    got.append(os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]))
+    assert got[-1] in (1, 2, 3) and len(got) < 30
+assert got.count(2) == 2 and got.count(1) >= 3, got
+""")
+
+
+def test_more_units_than_the_pair_kernels_count(tmp_path):
+    # lists so long that their pairs make 2^31 work units (22 million rows over few dimensions): the accumulating kernel
+    fake_device.run(tmp_path, LISTS + """
+for units in (2**31, 9 * 2**31):
+    names = joined(index(600))
+    assert ran("k_join", names) and not ran("k_pairs", names)
+""")
