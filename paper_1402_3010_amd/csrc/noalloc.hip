@@ -2,11 +2,12 @@
 //
 // For callers that cannot allocate during the call (code under stream
 // capture, tight serving loops, harnesses that forbid allocation).  The
-// work is that of apss_join_device on a plain index -- the same join kernel,
-// pair sort and unpack -- but every scratch buffer of the call (queue
-// counters, query tiles and work queues, per-workgroup cursors, raw pairs,
-// sort scratch) is carved out of one fixed device array, `scratch`, which
-// each device holds from the library's load until the process ends.
+// work is that of apss_join_device on a plain index -- the list-pair or the
+// accumulating kernels, pair sort and unpack -- but every scratch buffer of the
+// call (queue counters, query tiles and work queues, per-workgroup cursors, raw
+// pairs, survivors, sort scratch) is carved out of one fixed device array,
+// `scratch`, which each device holds from the library's load until the process
+// ends.
 //
 // In host code the array's name is not a device address; its address on a
 // device comes from hipGetSymbolAddress, taken once per device with that
@@ -29,8 +30,6 @@ namespace {
 
 constexpr size_t kScratchBytes = (size_t)APSS_NOALLOC_SCRATCH_BYTES;
 constexpr int kMaxDevices = 64;
-// survivors queued at once in a list-pair join (12 bytes each, 24 MB)
-constexpr int64_t kQueueEntries = 2 << 20;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -137,14 +136,13 @@ extern "C" int apss_join_device_noalloc(apss_index* ix, float t, uint32_t* out_i
   const QuerySet Q{ix->rows.rp.p, ix->rows.rc.p, ix->rows.mw.p, ix->n, ix->nnz, ix->rows.rp_host.data()};
   const bool pairs = use_pairs(ix);
   JoinLayout L;
-  // the list-pair kernels need no tiles, queues or cursors, but a survivor queue
-  const int64_t qcap = pairs ? std::min<int64_t>(kQueueEntries, pair_queue_entries(ix)) : 0;
+  // the list-pair kernels need no tiles, queues or cursors
   if (pairs) L.cum.assign(1, 0);
   else if ((rc = plan_layout(ix, Q, 1, L))) return rc;
   constexpr int64_t kWords = C_NUM + kQueueCounters / 2;  // counters, then queue counters
   const size_t fixed = Carve::bytes<unsigned long long>(kWords) +
                        Carve::bytes<int64_t>(L.ntiles + 1) + Carve::bytes<int64_t>((int64_t)L.cum.size()) +
-                       Carve::bytes<uint32_t>((int64_t)L.G * L.wg_stride) + Carve::bytes<uint32_t>(3 * qcap);
+                       Carve::bytes<uint32_t>((int64_t)L.G * L.wg_stride);
   if (fixed + pair_bytes(0) > kScratchBytes) {
     set_error("the join's work queues need %zu bytes of scratch; the allocation-free path holds %zu", fixed,
               kScratchBytes);
@@ -161,9 +159,12 @@ extern "C" int apss_join_device_noalloc(apss_index* ix, float t, uint32_t* out_i
   int64_t* tstart = cv.take<int64_t>(L.ntiles + 1);
   int64_t* qcum = cv.take<int64_t>((int64_t)L.cum.size());
   uint32_t* wg_cur = cv.take<uint32_t>((int64_t)L.G * L.wg_stride);
-  uint32_t* queue = cv.take<uint32_t>(3 * qcap);
   uint64_t* raw_key = cv.take<uint64_t>(room);
   float* raw_sim = cv.take<float>(room);
+  // but a survivor queue: from here to the array's end until the sort (a queue
+  // beside the sort's buffers would take the room of a million pairs)
+  uint32_t* const queue = (uint32_t*)(base + cv.used);
+  const int64_t qcap = std::min<int64_t>((int64_t)((kScratchBytes - cv.used) / 12), pair_queue_entries(ix));
   uint64_t* k2 = cv.take<uint64_t>(room);
   uint32_t* v2 = cv.take<uint32_t>(room);
   int64_t* hist = cv.take<int64_t>(radix_hist_elems(room));
