@@ -565,7 +565,8 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   plan.pa.counters = cnt.p;
   const int64_t windows = (ix->ndeep + kTinyList - 1) / kTinyList;
   const int64_t units = ix->nwide + ix->nshort / kShortUnits + windows / 64;
-  plan.pa.sample = std::max<int64_t>(1, units / 4096);
+  plan.pa.sample = 1;
+  plan.pa.every = std::max<int64_t>(1, units / 4096);
   CHK(launch_pairs(plan.pa, plan.pg, s), "sample");
   CHK(launch_visits(cnt_r, ix->off.p, m, cnt.p + C_TAILVISITS, s), "sample");
   // ... and for queries the survivors among about 2^24 pairs of rows
@@ -577,13 +578,13 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   plan.qa.t = ix->t_build;
   PairArgs qsample = plan.pa;
   qsample.counters = cnt.p + C_NUM;
-  qsample.sample = std::max<int64_t>(1, n / kWideRows / 64);
+  qsample.every = std::max<int64_t>(1, n / kWideRows / 64);
   CHK(launch_query_sample(qsample, plan.qa, s), "sample");
   unsigned long long c[C_NUM + kRateBins];
   const unsigned long long* const qc = c + C_NUM;
   CHK(hipMemcpyAsync(c, cnt.p, sizeof(c), hipMemcpyDeviceToHost, s), "sample");
   CHK(hipStreamSynchronize(s), "sample");
-  const double k = (double)plan.pa.sample;
+  const double k = (double)plan.pa.every;
   const double blocks = (double)((n + kCountRows - 1) / kCountRows);
   const double pairs_ms = 1e3 * (k * (double)c[C_VISITS] / 1.5e12 + 2.0 * k * (double)c[C_SURVIVORS] * 0.45e-9 +
                                  (double)ix->nshort * 1.6e-9 + (double)windows * 0.4e-9 + (ix->head_cut > 0 ? 2.8e-12 * (double)c[C_TAILVISITS] : 0.5 * blocks * (double)ix->P * (2e-9 / 110.0)));
@@ -602,7 +603,7 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   // are known when the thresholds are; the tables are kept if the kernels
   // would win halfway between t_build and 1.
   const double rows2 = (double)n * (double)n;
-  const int64_t qrows = std::min<int64_t>(n, ((n + kWideRows * qsample.sample - 1) / (kWideRows * qsample.sample)) * kWideRows);
+  const int64_t qrows = std::min<int64_t>(n, ((n + kWideRows * qsample.every - 1) / (kWideRows * qsample.every)) * kWideRows);
   double reach = 0.0;
   for (int b = kRateBins - 1; b >= 0; --b) {
     reach += (double)qc[b];
@@ -968,7 +969,14 @@ int plan_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, fl
   if (rc0) return rc0;
   if (triangle && use_pairs(ix)) {
     if (int rc = reserve_control(ws)) return rc;
-    CHK(ws.pq.reserve(3 * pair_queue_entries(ix)), "alloc queues");
+    // (a smaller queue where memory is short: it is filled more often)
+    int64_t entries = pair_queue_entries(ix);
+    hipError_t e = ws.pq.reserve(3 * entries);
+    while (e != hipSuccess && (entries /= 4) >= (1 << 16)) {
+      (void)hipGetLastError();
+      e = ws.pq.reserve(3 * entries);
+    }
+    CHK(e, "alloc queues");
     bind_pairs(ix, t, ws.qctr, ws.pq.p, ws.pq.n / 3, P);
     return APSS_OK;
   }
@@ -987,10 +995,21 @@ int plan_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, fl
 
 bool use_pairs(const apss_index* ix) { return ix->pairs_ready && !ix->pairs_off; }
 
-// Twice the survivors that the sample foretells for the lowest threshold; up
-// to 64M entries of 12 bytes.
+// Twice the survivors that the sample foretells for the lowest threshold, up
+// to kPairQueueMost entries of 12 bytes.
 int64_t pair_queue_entries(const apss_index* ix) {
-  return (int64_t)std::min(2.0 * ix->pair_survivors + 65536.0, 64.0 * (1 << 20));
+  return (int64_t)std::min(2.0 * ix->pair_survivors + 65536.0, (double)kPairQueueMost);
+}
+
+// Turns that a queue of qcap entries is filled in, where it does not hold one
+// and a half times those survivors.  What is past a full queue is decided from
+// memory, some 4 us a pair and wave: 60,000 rows of mean 80 at t = 0.5, 5
+// million pairs' room in the fixed scratch beside 0.4 of 6 million survivors,
+// took 54 ms where the accumulating kernel takes 11.3, in turns 5.2; 300,000
+// such rows, 64M entries for 150 million, 645 ms, 266 and 102.  Turns cost
+// little (150,000 rows in two 27.1 ms, in one 26.3; 16M entries 29.5).
+int64_t pair_turns(const apss_index* ix, int64_t qcap) {
+  return qcap > 0 ? 1 + (int64_t)((1.5 * ix->pair_survivors) / (double)qcap) : 1;
 }
 
 // The index's part of a candidate count.
@@ -1042,6 +1061,7 @@ void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue
   a.uctr = uctr_dev;
   a.queue = queue_dev;
   a.qcap = qcap;
+  a.turns = pair_turns(ix, qcap);
   a.t = t;
   a.thr = pair_threshold(t);
   a.bj = P.bj;

@@ -394,6 +394,7 @@ bool use_pairs(const apss_index* ix);
 // The list-pair self-join's kernel arguments, with 2 unit counters.
 void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue_dev, int64_t qcap, JoinPlan& P);
 // Survivor queue entries (3 words each) of a self-join by list pairs.
+constexpr int64_t kPairQueueMost = 64ll << 20;
 int64_t pair_queue_entries(const apss_index* ix);
 // Launch a plan's kernels (the queue counters are cleared here, the result
 // counters by the caller).

@@ -63,10 +63,12 @@ struct PairArgs {
   const uint2* wide;      // [nwide] (rank, unit of its list)
   const uint2* shorts;    // [nshort]
   int64_t nwide, nshort;
-  int64_t sample;         // > 0: test every sample-th unit (group of short units) only and just count
-                          // the visits and survivors; 0: the join
+  int32_t sample;         // 1: just count the visits and survivors of units 0, every, 2 every, ...
+  int64_t turns;          // times that the queue is filled and decided, each with the units of one turn
+  int64_t every, first;   // wide units, groups of short units and windows first, first + every, ...
+                          // (of a join set from turns by its launcher)
   int32_t sstep;          // short units a wave takes at a time (at most kShortUnits)
-  unsigned int* uctr;     // [3] next wide unit, next short units, queued survivors (zero at launch)
+  unsigned int* uctr;     // [3] next wide unit, unused, queued survivors (zero at launch)
   uint32_t* queue;        // [3 * qcap] survivors to decide: two row ids and the list's rank
   int64_t qcap;
   float t;
@@ -143,15 +145,15 @@ struct PairGroups {
   int wide = 0, shorts = 0, screen = 0, decide = 0;
 };
 PairGroups pairs_resident_groups();
-// The pair tests, then the queued survivors' decisions.  Survivors past
-// a.qcap are decided by the wave that finds them, so any capacity (0 too)
-// gives the whole result.
-// (a.sstep is set here.)
+// The pair tests, then the queued survivors' decisions, a.turns times.
+// Survivors past a.qcap are decided by the wave that finds them, so any
+// capacity (0 too) gives the whole result; but one at a time and from memory,
+// some fifty times slower: hence the turns.  (a.sstep is set here.)
 hipError_t launch_pairs(PairArgs a, const PairGroups& g, hipStream_t s);
 // Thresholds that a sample of the sketch products is counted at.
 constexpr int kRateBins = 32;
 // a.counters[k] += pairs with a product in the k-th of kRateBins equal parts
-// of the range from q.t to 1, over every a.sample-th 256 rows
+// of the range from q.t to 1, over every a.every-th 256 rows
 hipError_t launch_query_sample(const PairArgs& a, const QueryArgs& q, hipStream_t s);
 // Queries against the corpus (a.query = 1), then the survivors' decisions.
 hipError_t launch_query_screen(const PairArgs& a, const QueryArgs& q, const PairGroups& g, hipStream_t s);

@@ -595,7 +595,7 @@ struct Survivors {
 
   __device__ __forceinline__ void pass_on(const PairArgs& pa, int lane, Decided& dc) {
     if (n == 0) return;
-    if (pa.sample > 0) {  // counted only
+    if (pa.sample) {  // counted only
       dc.surv += (unsigned long long)n;
       n = 0;
       return;
@@ -644,7 +644,7 @@ struct Survivors {
     if (total == 0u) return;
     if (threadIdx.x == 0) {
       unsigned int at = 0xFFFFFFFFu;
-      if (pa.sample == 0) {
+      if (!pa.sample) {
         at = __hip_atomic_load(&pa.uctr[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         at = (int64_t)at + (int64_t)total <= pa.qcap ? atomicAdd(&pa.uctr[2], total) : 0xFFFFFFFFu;
       }
@@ -756,8 +756,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     __syncthreads();
     if (tid == 0) next = atomicAdd(&a.uctr[0], 1u);
     __syncthreads();
-    int64_t un = (int64_t)(unsigned int)uni((int)next);
-    if (a.sample > 0) un *= a.sample;
+    const int64_t un = (int64_t)(unsigned int)uni((int)next) * a.every + a.first;
     if (un >= a.nwide) break;
     const uint2 u = a.wide[un];
     const int64_t base = a.doff[u.x];
@@ -857,8 +856,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   unsigned long long c_visit = 0;
   static_assert(kShortUnits <= 64, "a unit per lane");
   // (units are alike, and a shared counter costs more than it evens out)
-  const int64_t turn = (int64_t)a.sstep * (a.sample > 0 ? a.sample : 1);
-  for (int64_t u0 = ((int64_t)blockIdx.x * 4 + wave) * turn; u0 < a.nshort; u0 += (int64_t)gridDim.x * 4 * turn) {
+  const int64_t step = (int64_t)a.sstep * a.every;
+  for (int64_t u0 = ((int64_t)blockIdx.x * 4 + wave) * step + a.first * a.sstep; u0 < a.nshort;
+       u0 += (int64_t)gridDim.x * 4 * step) {
     const int cnt = a.nshort - u0 < a.sstep ? (int)(a.nshort - u0) : a.sstep;
     uint2 un = make_uint2(0u, 0u);
     uint32_t ubase = 0u;
@@ -922,8 +922,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
   }
   const int64_t windows = (a.ndeep + kTinyList - 1) / kTinyList;
-  const int64_t every = a.sample > 0 ? a.sample : 1;
-  for (int64_t w = ((int64_t)blockIdx.x * 4 + wave) * every; w < windows; w += (int64_t)gridDim.x * 4 * every) {
+  for (int64_t w = ((int64_t)blockIdx.x * 4 + wave) * a.every + a.first; w < windows;
+       w += (int64_t)gridDim.x * 4 * a.every) {
     const int64_t e0 = w * kTinyList;
     const int64_t e = e0 + lane;
     uint32_t r = 0u, id = 0u;
@@ -1000,7 +1000,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // second), with the exact count 3.1 ms and the decisions 0.8 ms where the
 // accumulating kernel took 15 ms.  256 groups where a self-join's lists have
 // 128: no list narrows the pairs here.
-// SAMPLE: every a.sample-th workgroup only, counting the pairs that reach
+// SAMPLE: every a.every-th workgroup only, counting the pairs that reach
 // each of kRateBins thresholds, evenly between s.t and 1.
 constexpr int kMidSteps = kMidGroups / 32;
 
@@ -1028,9 +1028,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   };
   // chunk c of column r at position c ^ (r % 16) of its row
   auto at = [](int r, int c) { return r * 16 + (c ^ (r & 15)); };
-  const int64_t step = (int64_t)gridDim.x * kWideRows * (SAMPLE ? a.sample : 1);
+  const int64_t step = (int64_t)gridDim.x * kWideRows * (SAMPLE ? a.every : 1);
   int buf = 0;
-  for (int64_t block0 = (int64_t)blockIdx.x * kWideRows * (SAMPLE ? a.sample : 1); block0 < s.n; block0 += step) {
+  for (int64_t block0 = (int64_t)blockIdx.x * kWideRows * (SAMPLE ? a.every : 1); block0 < s.n; block0 += step) {
     const int64_t row0 = block0 + 64 * wave;
     const int na = s.n - row0 < 64 ? (int)(s.n - row0) : 64;  // may be <= 0
     i32x4 fa[2][kMidSteps];
@@ -1698,33 +1698,34 @@ PairGroups pairs_resident_groups() {
 hipError_t launch_pairs(PairArgs a, const PairGroups& g, hipStream_t s) {
   if (a.ndeep <= 0) return hipSuccess;
   if (!a.dlr || !a.rp || !a.rc || !a.sk || !a.gid || !a.fidx || !a.fsk || !a.qrp || !a.qrc || !a.qfidx || !a.qfsk || !a.dl || !a.doff || !a.wide || !a.shorts || !a.uctr ||
-      (a.sample == 0 && (!a.out_key || !a.out_sim)) || !a.counters || (a.qcap > 0 && !a.queue) || a.nwide > kMaxUnits ||
+      (!a.sample && (!a.out_key || !a.out_sim || a.turns < 1)) || (a.sample && (a.every < 1 || a.first)) || !a.counters || (a.qcap > 0 && !a.queue) || a.nwide > kMaxUnits ||
       a.nshort > kMaxUnits)
     return hipErrorInvalidValue;
   hipError_t e = hipSuccess;
-  const int64_t every = a.sample > 0 ? a.sample : 1;
-  if (a.nwide > 0) {
-    const int64_t units = (a.nwide + every - 1) / every;
-    const int64_t n = units < g.wide ? units : g.wide;
-    hipLaunchKernelGGL(k_pairs_wide, dim3((unsigned)n), dim3(256), 0, s, a);
+  if (!a.sample) a.every = a.turns;
+  const int64_t every = a.every, turns = a.sample ? 1 : a.turns;
+  const int64_t wide = (a.nwide + every - 1) / every;
+  // every resident wave gets some units, where there are enough
+  const int64_t windows = (a.ndeep + kTinyList - 1) / kTinyList;
+  const int64_t even = a.nshort / every / ((int64_t)g.shorts * 4);
+  a.sstep = (int32_t)(even < 1 ? 1 : (even < kShortUnits ? even : kShortUnits));
+  const int64_t steps = std::max((a.nshort + a.sstep * every - 1) / (a.sstep * every), (windows + every - 1) / every);
+  // (a workgroup ends with atomics on the same counters, 20 ns each: one
+  // step per wave only as far as 256 of them, then four)
+  const int64_t need = std::max((steps + 15) / 16, std::min<int64_t>((steps + 3) / 4, 256));
+  for (int64_t turn = 0; turn < turns; ++turn) {
+    if (!a.sample) a.first = turn;
+    if (turn > 0 && (e = fill_u32(a.uctr, 0u, 3, s)) != hipSuccess) return e;
+    if (wide > 0) {
+      hipLaunchKernelGGL(k_pairs_wide, dim3((unsigned)(wide < g.wide ? wide : g.wide)), dim3(256), 0, s, a);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_pairs_short, dim3((unsigned)(need < g.shorts ? need : g.shorts)), dim3(256), 0, s, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  {
-    // every resident wave gets some units, where there are enough
-    const int64_t windows = (a.ndeep + kTinyList - 1) / kTinyList;
-    const int64_t even = a.nshort / every / ((int64_t)g.shorts * 4);
-    a.sstep = (int32_t)(even < 1 ? 1 : (even < kShortUnits ? even : kShortUnits));
-    const int64_t turns = std::max((a.nshort + a.sstep * every - 1) / (a.sstep * every), (windows + every - 1) / every);
-    // (a workgroup ends with atomics on the same counters, 20 ns each: one
-    // turn per wave only as far as 256 of them, then four)
-    const int64_t need = std::max((turns + 15) / 16, std::min<int64_t>((turns + 3) / 4, 256));
-    const int64_t n = need < g.shorts ? need : g.shorts;
-    hipLaunchKernelGGL(k_pairs_short, dim3((unsigned)n), dim3(256), 0, s, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  if (a.qcap > 0 && a.sample == 0) {
-    hipLaunchKernelGGL(k_decide, dim3((unsigned)g.decide), dim3(256), 0, s, a);
-    e = hipGetLastError();
+    if (a.qcap > 0 && !a.sample) {
+      hipLaunchKernelGGL(k_decide, dim3((unsigned)g.decide), dim3(256), 0, s, a);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
   }
   return e;
 }
@@ -1744,8 +1745,8 @@ hipError_t launch_query_screen(const PairArgs& a, const QueryArgs& q, const Pair
 
 hipError_t launch_query_sample(const PairArgs& a, const QueryArgs& q, hipStream_t s) {
   if (q.n <= 0 || q.nq <= 0) return hipSuccess;
-  if (!q.sk || !q.qsk || q.q0 != 0 || q.qstride <= 0 || q.qt || a.sample <= 0 || !a.counters) return hipErrorInvalidValue;
-  const int64_t every = kWideRows * a.sample;
+  if (!q.sk || !q.qsk || q.q0 != 0 || q.qstride <= 0 || q.qt || a.every < 1 || !a.counters) return hipErrorInvalidValue;
+  const int64_t every = kWideRows * a.every;
   const int64_t grid = (q.n + every - 1) / every;
   if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_query_screen<true>, dim3((unsigned)grid), dim3(256), 0, s, a, q);

@@ -39,3 +39,32 @@ def test_pairs_near_the_scratch_limit(copies):
     assert sa["posting_visits"] < sb["posting_visits"]  # (the list-pair kernels ran)
     for x, y in zip(a, b):
         assert torch.equal(x.view(torch.int32), y.view(torch.int32))
+
+
+def test_more_survivors_than_the_queue_in_turns():
+    # the queue is filled and decided several times; one that is not was 5 times slower than the accumulating kernel
+    import torch
+
+    import paper_1402_3010_amd as apss
+    V = make_corpus(spec_for("c2", n=60000))
+    t = np.float32(0.5)
+    got = []
+    for pairs in (True, False):
+        o = apss.default_opts(apss.current_stream_handle(), variant=-1 if pairs else 1)
+        o.reserved[0] = PROBE_PAIRS if pairs else 0
+        ix = apss.Index(apss.build_index(V.n, V.m, V.row_ptr, V.col, V.val, t, o), V.n, V.m)
+        try:
+            # (room for five million pairs: the queue is what is left beside them)
+            out = [torch.zeros(5_000_000, dtype=d, device="cuda") for d in (torch.int32, torch.int32, torch.float32)]
+            ms = []
+            for _ in range(3):
+                cnt = ix.join_device_noalloc(t, *out)
+                ms.append(ix.stats()["ms_candidates"])
+            got.append((cnt, out, ix.stats(), min(ms)))
+        finally:
+            ix.close()
+    (ca, a, sa, ma), (cb, b, sb, mb) = got
+    assert ca == cb and sa["candidates"] == sb["candidates"]
+    for x, y in zip(a, b):
+        assert torch.equal(x.view(torch.int32), y.view(torch.int32))
+    assert ma < 2 * mb
