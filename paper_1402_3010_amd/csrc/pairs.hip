@@ -556,6 +556,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   __shared__ StagedRow rows[4];
   const int lane = (int)(threadIdx.x & 63u);
   const int wave = uni((int)(threadIdx.x >> 6));
+  if (a.counters[C_OVERFLOW]) return;  // (the call is made by the accumulating kernel)
   const int64_t held = (int64_t)a.uctr[2] < a.qcap ? (int64_t)a.uctr[2] : a.qcap;
   const int64_t waves = (int64_t)gridDim.x * 4;
   const int64_t even = (held + waves - 1) / waves;
@@ -1000,6 +1001,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // second), with the exact count 3.1 ms and the decisions 0.8 ms where the
 // accumulating kernel took 15 ms.  256 groups where a self-join's lists have
 // 128: no list narrows the pairs here.
+// Once the survivors have outgrown their queue the rest of the rows is left
+// out: thread 0 reads the flag with each block's sketches, and the others see
+// it behind the block's barriers (in two words in turn: a block has a barrier,
+// so nobody still reads the word that is written).
 // SAMPLE: every a.every-th workgroup only, counting the pairs that reach
 // each of kRateBins thresholds, evenly between s.t and 1.
 constexpr int kMidSteps = kMidGroups / 32;
@@ -1010,6 +1015,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   constexpr int kHeld = SAMPLE ? 1 : kPairQueue;
   __shared__ uint32_t qa[4][kHeld], qb[4][kHeld], qd[4][kHeld];
   __shared__ unsigned int bins[kRateBins];
+  __shared__ unsigned int full[2];
   const int tid = (int)threadIdx.x;
   const int lane = tid & 63;
   const int wave = uni(tid >> 6);
@@ -1029,8 +1035,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   // chunk c of column r at position c ^ (r % 16) of its row
   auto at = [](int r, int c) { return r * 16 + (c ^ (r & 15)); };
   const int64_t step = (int64_t)gridDim.x * kWideRows * (SAMPLE ? a.every : 1);
-  int buf = 0;
-  for (int64_t block0 = (int64_t)blockIdx.x * kWideRows * (SAMPLE ? a.every : 1); block0 < s.n; block0 += step) {
+  int buf = 0, turn = 0;
+  for (int64_t block0 = (int64_t)blockIdx.x * kWideRows * (SAMPLE ? a.every : 1); block0 < s.n;
+       block0 += step, turn ^= 1) {
+    unsigned long long flag = 0ull;
+    if (!SAMPLE && tid == 0)
+      flag = __hip_atomic_load(&a.counters[C_OVERFLOW], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int64_t row0 = block0 + 64 * wave;
     const int na = s.n - row0 < 64 ? (int)(s.n - row0) : 64;  // may be <= 0
     i32x4 fa[2][kMidSteps];
@@ -1043,6 +1053,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       for (int ks = 0; ks < kMidSteps; ++ks) fa[i][ks] = *reinterpret_cast<const i32x4*>(p + 32 * ks);
     }
     fetch(s.q0);
+    if (!SAMPLE && tid == 0) full[turn] = flag != 0ull ? 1u : 0u;
     for (int64_t b0 = s.q0; b0 < s.nq; b0 += 64, buf ^= 1) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) cols[buf][at(col, 4 * part + c)] = x[c];
@@ -1082,6 +1093,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         }
       }
     }
+    if (!SAMPLE && full[turn]) break;
   }
   if (SAMPLE) {
     __syncthreads();
@@ -1226,7 +1238,7 @@ __global__ __launch_bounds__(64 * kCountWaves) __attribute__((amdgpu_waves_per_e
   const int wave = uni(tid >> 6);
   int64_t b, j;
   count_item(a, nchunk, &b, &j);
-  if (b >= a.nblk) return;
+  if (b >= a.nblk || a.counters[C_OVERFLOW]) return;
   const int64_t row0 = b * kCountRows;
   const int64_t qbeg = j * a.chunk;
   const int64_t qend = qbeg + a.chunk < a.nq ? qbeg + a.chunk : a.nq;
@@ -1426,7 +1438,7 @@ __global__ __launch_bounds__(64 * kCountWaves) void k_count_pieces(CountArgs a, 
   const int wave = uni(tid >> 6);
   int64_t b, j;
   count_item(a, nchunk, &b, &j);
-  if (b >= a.nblk) return;
+  if (b >= a.nblk || a.counters[C_OVERFLOW]) return;
   const int64_t row0 = b * kCountRows;
   int64_t q0 = j * a.chunk;
   const int64_t qend = q0 + a.chunk < a.nq ? q0 + a.chunk : a.nq;

@@ -97,3 +97,27 @@ for units in (2**31, 9 * 2**31):
     names = joined(index(600))
     assert ran("k_join", names) and not ran("k_pairs", names)
 """)
+
+
+def test_a_batch_that_overflows_is_not_counted_before(tmp_path):
+    # the sketch tests come before the exact count, which is as long; a flagged batch is made again by the other kernel
+    fake_device.run(tmp_path, LISTS + """
+o = apss.default_opts()
+o.reserved[0] = 0x50414952  # sketches whatever the cost rule says
+ix = apss.Index(apss.build_index(600, 64, *rows(600), 0.5, o), 600, 64)
+flags = [1]
+
+@ctypes.CFUNCTYPE(None, ctypes.c_char_p, ctypes.POINTER(ctypes.c_void_p))
+def finish(name, args):
+    if b"k_finish" in name:
+        host = ctypes.cast(args[0] + 80, ctypes.POINTER(P64))[0]  # FinishArgs.host
+        host[7] = flags.pop() if flags else 0  # C_OVERFLOW
+
+fake.fake_hook(finish)
+launches()
+q = rows(40)
+apss.query(ix.handle, 40, *q, 0.5)
+names = [k for k in launches() if any(x in k for x in ("k_query_screen", "k_decide", "k_count", "k_join", "k_finish"))]
+order = ["k_query_screen", "k_decide", "k_count", "k_finish", "k_join", "k_finish"]
+assert len(names) == len(order) and all(o in k for o, k in zip(order, names)), names
+""")
