@@ -262,6 +262,14 @@ __device__ __forceinline__ uint64_t pair_key(const PairArgs& a, uint32_t y, uint
   return a.query ? ((uint64_t)q << a.bj) | (uint64_t)y : ((uint64_t)y << a.bj) | (uint64_t)q;
 }
 
+// Longest row whose plain sum drops a pair: 64 chains of its components and a
+// butterfly of six levels add, each step within 2^-24 of a sum of at most
+// 1 + 1e-5, so the error stays below (ceil(k / 64) + 6) 2^-24, for this many a
+// third of the slack.  (At a million components it can be three times the
+// slack.)
+constexpr int kPlainRow = 32768;
+static_assert((kPlainRow / 64 + 6) * 0x1p-24 < 0.5f * kSlack, "plain sums decide inside the slack");
+
 // Decide `here` (at most 64) pairs, lane l's being (x, z) from the deep list
 // of rank d (a query's pairs: past every rank), one at a time by the whole
 // wave: row q goes to LDS, the lanes take y's components and look them up.
@@ -452,8 +460,7 @@ __device__ __forceinline__ void decide_pairs(const PairArgs& a, StagedRow& st, i
         continue;
       }
       part = wave_sum(part);
-      // the plain sum's error (below 1e-5) is far inside the slack
-      if (part < t - kSlack) {
+      if (ylen <= kPlainRow && part < t - kSlack) {
         ++dc.surv;
         wave_lds_order();
         continue;
