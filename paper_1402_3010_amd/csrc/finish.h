@@ -24,7 +24,7 @@ struct FinishArgs {
 };
 
 // The counters (and 0, 0 for checks that there are not) to the host; and, if there are at most kFinishPairs, cap and
-// room pairs, the pairs in order of (i, j) to out_*.
+// room pairs and no check has failed, the pairs in order of (i, j) to out_*.
 hipError_t launch_finish(const FinishArgs& a, hipStream_t s);
 // True when launch_finish delivered a join's pairs.
 inline bool finish_delivers(int64_t matches, int64_t cap, int64_t room) {

@@ -32,7 +32,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_finish(FinishArgs a) {
   if (blockIdx.x == 0 && tid >= C_NUM && tid < C_NUM + 2) a.host[tid] = a.checks ? a.checks[tid - C_NUM] : 0ull;
   const unsigned long long matches = a.counters[C_MATCHES];
   if (matches > (unsigned long long)kFinishPairs || matches > (unsigned long long)a.cap ||
-      matches > (unsigned long long)a.room || a.counters[C_OVERFLOW])
+      matches > (unsigned long long)a.room || a.counters[C_OVERFLOW] || (a.checks && (uint32_t)a.checks[0] != 0u))
     return;
   const int n = (int)matches;
   const int own = (int)blockIdx.x * kOwn + lane;
