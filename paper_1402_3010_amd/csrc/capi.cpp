@@ -1327,7 +1327,7 @@ int hand_over(Workspace& ws, int bj, int bits, const Sink* sink, const unsigned 
     f.out_i = sink->i;
     f.out_j = sink->j;
     f.out_sim = sink->sim;
-    f.room = sink->room;
+    f.room = std::max<int64_t>(sink->room, 0);  // (a negative capacity is refused by finish_device)
   }
   f.counters = ws.counters.p;
   f.checks = checks;

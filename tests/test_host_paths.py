@@ -121,3 +121,18 @@ names = [k for k in launches() if any(x in k for x in ("k_query_screen", "k_deci
 order = ["k_query_screen", "k_decide", "k_count", "k_finish", "k_join", "k_finish"]
 assert len(names) == len(order) and all(o in k for o, k in zip(order, names)), names
 """)
+
+
+def test_negative_capacities_are_too_small(tmp_path):
+    fake_device.run(tmp_path, """
+ix, q, cnt = index(300), rows(20), ctypes.c_int64(7)
+lib = apss.load()
+for n in (300, 0):
+    ix = index(n) if n else apss.Index(apss.build_index(0, 64, np.zeros(1, np.int64), q[1], q[2], 0.5, apss.default_opts()), 0, 64)
+    assert lib.apss_join_device(ix.handle, 0.5, None, None, None, -1, ctypes.byref(cnt)) == apss.APSS_ERANGE
+    assert cnt.value == 0 and "capacity -1" in apss.last_error()
+    for nq in (1, 20):
+        assert lib.apss_query_device(ix.handle, nq, *[x.ctypes.data for x in q], 0, None, 0.5, None, None, None, -5,
+                                     ctypes.byref(cnt)) == apss.APSS_ERANGE
+    assert lib.apss_join_device(ix.handle, 0.5, None, None, None, 0, ctypes.byref(cnt)) == apss.APSS_OK
+""")
