@@ -1896,6 +1896,10 @@ int stage_queries(apss_index* ix, Workspace& ws, int64_t nq, const int64_t* q_ro
         return APSS_EINVAL;
       }
   }
+  if (nnz > 0 && (!q_col || !q_val)) {
+    set_error("NULL argument");
+    return APSS_EINVAL;
+  }
   rows.nnz = nnz;
   rows.rp_host.assign(rp_host, rp_host + nq + 1);
   int64_t longest = 0;

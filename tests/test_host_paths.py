@@ -136,3 +136,20 @@ for n in (300, 0):
                                      ctypes.byref(cnt)) == apss.APSS_ERANGE
     assert lib.apss_join_device(ix.handle, 0.5, None, None, None, 0, ctypes.byref(cnt)) == apss.APSS_OK
 """)
+
+
+def test_query_rows_without_components_arrays(tmp_path):
+    # NULL arrays of a batch that has components: refused, small batches (which are packed on the host) and large ones
+    fake_device.run(tmp_path, """
+ix, p = index(300), apss.Pairs()
+lib = apss.load()
+for nq in (1, 20, 20000):
+    q = rows(nq)
+    rp, c, v = [x.ctypes.data for x in q]
+    for args in ((rp, None, v), (rp, c, None), (rp, None, None)):
+        for device in (0, 1):
+            assert lib.apss_query(ix.handle, nq, *args, device, None, 0.5, ctypes.byref(p)) == apss.APSS_EINVAL
+    assert lib.apss_query(ix.handle, nq, rp, c, v, 0, None, 0.5, ctypes.byref(p)) == apss.APSS_OK
+empty = np.zeros(4, np.int64)
+assert lib.apss_query(ix.handle, 3, empty.ctypes.data, None, None, 0, None, 0.5, ctypes.byref(p)) == apss.APSS_OK
+""")
