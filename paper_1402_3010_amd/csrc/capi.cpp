@@ -1341,13 +1341,13 @@ int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, flo
              int64_t cap_hint, int64_t* count, const float* t_host, Sink* sink) {
   hipStream_t s = ws.stream;
   *count = 0;
-  int rc = start_call(ws);
-  if (rc) return rc;
-  // what the staging of a batch of queries leaves to this call
+  // what the staging of a batch of queries leaves to this call, and to no other
   const unsigned long long* const checks = ws.pending;
   const bool cleared = ws.cleared;
   ws.pending = nullptr;
   ws.cleared = false;
+  int rc = start_call(ws);
+  if (rc) return rc;
   if (Q.n == 0) return APSS_OK;
   if (ix->n == 0) return checks ? check_err(s, checks, "query") : APSS_OK;
   if (!cleared) {

@@ -153,3 +153,29 @@ for nq in (1, 20, 20000):
 empty = np.zeros(4, np.int64)
 assert lib.apss_query(ix.handle, 3, empty.ctypes.data, None, None, 0, None, 0.5, ctypes.byref(p)) == apss.APSS_OK
 """)
+
+
+def test_a_query_that_fails_leaves_nothing_to_the_next_call(tmp_path):
+    # a query whose rows were staged, and which then failed before its kernels: the next call clears its own counters
+    fake_device.run(tmp_path, """
+ix, q = index(300), rows(20)
+cnt = ctypes.c_int64()
+ix.join(0.5)
+for call in (lambda: ix.join(0.5), lambda: apss.load().apss_join_device(ix.handle, 0.5, None, None, None, 0, ctypes.byref(cnt))):
+    launches()
+    call()
+    want = launches()
+    for nq in (1, 20):
+        for event in (0, 1):
+            fake.fake_fail_events(event, 1)
+            try:
+                apss.query(ix.handle, nq, q[0][:nq + 1], q[1][:2 * nq], q[2][:2 * nq], 0.5)
+                assert False
+            except apss.ApssError as e:
+                assert e.code == apss.APSS_EDEVICE
+            fake.fake_fail_events(0, 0)
+            fake.hipGetLastError()
+            launches()
+            call()
+            assert launches() == want
+""")
