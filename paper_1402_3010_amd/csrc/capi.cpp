@@ -176,6 +176,11 @@ using namespace apss;
 
 namespace {
 
+// True when rows of at most longest entries are sorted by segments.
+bool sorts_segments(int64_t nnz, int64_t longest, int key_bits) {
+  return nnz > kSortSegment && longest <= kSortSegment && key_bits <= 51;
+}
+
 // Sort (row, rank) keys with float payload into rank-space rows; checks for duplicates.
 // Rows are contiguous in row-major order, so with the row index in the key's
 // high bits sorting groups of whole rows independently sorts the whole
@@ -1130,18 +1135,25 @@ double survivor_rate(const apss_index* ix, float t) {
   return ix->rate[std::max(0, std::min(kRateBins - 1, b))];
 }
 
-// Sketches of the query rows, and the plan of testing them against the corpus.
-int plan_queries(apss_index* ix, Workspace& ws, const QuerySet& Q, float t, const float* qt_dev, JoinPlan& P) {
-  hipStream_t s = ws.stream;
+// Bytes of the sketches of a batch: every row's, long rows' fine ones, and
+// which of those a row has.
+int64_t sketch_bytes(const QuerySet& Q) {
   int64_t longs = 0;
   for (int64_t q = 0; q < Q.n; ++q) longs += Q.rp_host[q + 1] - Q.rp_host[q] > kFineRow;
-  CHK(ws.q_mid.reserve(Q.n * kMidGroups), "alloc sketches");
-  CHK(ws.q_fidx.reserve(Q.n), "alloc sketches");
-  CHK(ws.q_fsk.reserve(longs * kFineGroups), "alloc sketches");
+  return Q.n * kMidGroups + longs * kFineGroups + Q.n * (int64_t)sizeof(uint32_t);
+}
+
+// Sketches of the query rows, and the plan of testing them against the corpus.
+// The sketches lie where the pair sort has its second values, after the tests.
+int plan_queries(apss_index* ix, Workspace& ws, const QuerySet& Q, float t, const float* qt_dev, JoinPlan& P) {
+  hipStream_t s = ws.stream;
+  const int64_t bytes = sketch_bytes(Q);
+  CHK(ws.ss.v32b.reserve((bytes + 3) / 4), "alloc sketches");
+  uint8_t* const mid = (uint8_t*)ws.ss.v32b.p;
+  uint8_t* const fsk = mid + Q.n * kMidGroups;
+  uint32_t* const fidx = (uint32_t*)(mid + bytes) - Q.n;
   if (int rc = reserve_control(ws)) return rc;
-  CHK(launch_sketch(Q.rp, Q.rc, ix->gid.p, Q.n, nullptr, ws.q_mid.p, ws.nfine, ws.q_fidx.p, ws.q_fsk.p, s),
-      "sketches");
-  if (int rc = reserve_control(ws)) return rc;
+  CHK(launch_sketch(Q.rp, Q.rc, ix->gid.p, Q.n, nullptr, mid, ws.nfine, fidx, fsk, s), "sketches");
   P = JoinPlan{};
   P.query = true;
   P.bj = ceil_log2((uint64_t)ix->n);
@@ -1156,8 +1168,8 @@ int plan_queries(apss_index* ix, Workspace& ws, const QuerySet& Q, float t, cons
   a.query = 1;
   a.qrp = Q.rp;
   a.qrc = Q.rc;
-  a.qfidx = ws.q_fidx.p;
-  a.qfsk = ws.q_fsk.p;
+  a.qfidx = fidx;
+  a.qfsk = fsk;
   a.qt = qt_dev;
   a.uctr = ws.qctr;
   a.t = t;
@@ -1165,7 +1177,7 @@ int plan_queries(apss_index* ix, Workspace& ws, const QuerySet& Q, float t, cons
   QueryArgs& q = P.qa;
   q.sk = ix->mid.p;
   q.n = ix->n;
-  q.qsk = ws.q_mid.p;
+  q.qsk = mid;
   q.nq = Q.n;
   q.qstride = 1;
   q.qt = qt_dev;
@@ -1372,6 +1384,15 @@ int run_join(apss_index* ix, Workspace& ws, const QuerySet& Q, int triangle, flo
                  (double)Q.n * (double)ix->n * ix->accumulate_ps;
     if (screen) {
       if ((rc = ensure_pair_capacity(ws, cap_hint))) return rc;
+      // a server's slot holds no more than its batch's reservation: the sketches
+      // fit the sort's second values (of pairs or components) or, where the rows
+      // were sorted in LDS, those and the row sort's 24 bytes a component; else,
+      // few pairs and rows of a few components, the accumulating kernel
+      if (ws.slot)
+        screen = sketch_bytes(Q) <=
+                 (cleared ? 4 * ws.raw_key.n + 24 * Q.nnz : 4 * std::max<int64_t>(ws.raw_key.n, Q.nnz));
+    }
+    if (screen) {
       if ((rc = plan_queries(ix, ws, Q, t, qt_dev, P))) return rc;
       // survivor queue: in a server's slot the pair sort's second keys (part
       // of the batch's reservation, free until the sort), else its own buffer
@@ -1928,13 +1949,17 @@ int stage_queries(apss_index* ix, Workspace& ws, int64_t nq, const int64_t* q_ro
   if ((rc = reserve_control(ws))) return rc;
   const bool lds = longest <= kQueryRow;
   SortScratch& ss = ws.ss;
+  const int rbits = ceil_log2((uint64_t)ix->m);
+  const int nbits = ceil_log2((uint64_t)std::max<int64_t>(nq, 1));
   if (!lds) {
     CHK(ss.k1.reserve(nnz), "alloc");
     CHK(ss.v32a.reserve(nnz), "alloc");
-    CHK(ss.k2.reserve(nnz), "sort scratch");
-    CHK(ss.v32b.reserve(nnz), "sort scratch");
-    CHK(ss.hist.reserve(radix_hist_elems(nnz)), "sort scratch");
-    CHK(ss.scan.reserve(radix_scan_tmp_elems(nnz)), "sort scratch");
+    if (!sorts_segments(nnz, longest, nbits + rbits)) {
+      CHK(ss.k2.reserve(nnz), "sort scratch");
+      CHK(ss.v32b.reserve(nnz), "sort scratch");
+      CHK(ss.hist.reserve(radix_hist_elems(nnz)), "sort scratch");
+      CHK(ss.scan.reserve(radix_scan_tmp_elems(nnz)), "sort scratch");
+    }
     CHK(ss.seg.reserve(nq + 2), "sort scratch");
   }
   if (!ws.host_in.reserve(total)) {
@@ -1988,8 +2013,6 @@ int stage_queries(apss_index* ix, Workspace& ws, int64_t nq, const int64_t* q_ro
   }
   CHK(hipMemcpyAsync(rows.rp.p, prp, sizeof(int64_t) * (nq + 1), hipMemcpyDeviceToDevice, s), "copy");
   if (t_per_row) CHK(hipMemcpyAsync(ws.qt.p, in + t_at, sizeof(float) * nq, hipMemcpyDeviceToDevice, s), "copy");
-  const int rbits = ceil_log2((uint64_t)ix->m);
-  const int nbits = ceil_log2((uint64_t)std::max<int64_t>(nq, 1));
   // invalid dimensions get a valid key, so the sort runs before the check
   CHK(launch_query_keys(prp, pcol, pval, ix->rank.p, nq, ix->m, rbits, 1e-5, ss.k1.p, ss.v32a.p, rows.mw.p, err, bad, s),
       "query keys");

@@ -209,9 +209,6 @@ struct Workspace {
   SortScratch ss;
   DBuf<int64_t> tstart, qcum;
   DBuf<uint32_t> pq;         // survivor queue of the list-pair join
-  // query sketches
-  DBuf<uint8_t> q_mid, q_fsk;
-  DBuf<uint32_t> q_fidx;
   bool slot = false;  // a server slot's workspace: scratch stays within the batch's reservation
   DBuf<uint32_t> wg_cur;
   // a call's counters [C_NUM], its queue counters and the query sketches'
@@ -254,8 +251,8 @@ struct Workspace {
   }
   int64_t bytes() const {
     return ss.bytes() + tstart.bytes() + qcum.bytes() + q_in.bytes() + wg_cur.bytes() + counters.bytes() +
-           raw_key.bytes() + raw_sim.bytes() + pq.bytes() + q_mid.bytes() + q_fsk.bytes() + q_fidx.bytes() + qt.bytes() + uniq_total.bytes() + qadm.bytes() + q_col.bytes() + q_val.bytes() + s_keys.bytes() + s_cand.bytes() + s_sid.bytes() +
-           s_tiles.bytes() + s_nh.bytes() + s_X.bytes();
+           raw_key.bytes() + raw_sim.bytes() + pq.bytes() + qt.bytes() + uniq_total.bytes() + qadm.bytes() + q_col.bytes() +
+           q_val.bytes() + s_keys.bytes() + s_cand.bytes() + s_sid.bytes() + s_tiles.bytes() + s_nh.bytes() + s_X.bytes();
   }
 };
 
