@@ -111,14 +111,20 @@ void apss_default_opts(apss_opts* opts);
  * sum x[d] * maxweight_d(V) stays below t_build) and its indexed rest, and
  * inverted lists of the indexed parts ordered by vector id.
  * The index owns device memory until apss_index_free; up to 1/32 of the
- * device's memory then stays with the library for the next index, until it has
- * gone unused for a while or memory runs out.
+ * device's memory then stays with the library for the next index.  It goes back
+ * to the device when 32 later requests of index builds have not taken it, when
+ * an allocation of the library fails, or by apss_release_memory.
  * Errors: APSS_EINVAL (bad CSR, n < 0, m <= 0, nnz >= 2^32, n >= 2^31),
  * APSS_ETHRESH (t_build outside (0, 1]), APSS_ENOMEM, APSS_EDEVICE. */
 int apss_build_index(int64_t n, int64_t m, const int64_t* row_ptr, const int32_t* col, const float* val,
                      int on_device, float t_build, const apss_opts* opts, apss_index** out);
 
 void apss_index_free(apss_index* idx);
+
+/* Give the device memory that ended indexes have left to the library back, for
+ * other allocators of the process; any thread may call it at any time (it waits
+ * for work on the device, as hipFree does).  Returns the bytes given back. */
+int64_t apss_release_memory(void);
 
 /* Self-join (Algorithm 1 driving Find-Matches, Algorithm 2, with partial
  * indexing): every pair i < j with sim(v_i, v_j) >= t, written to caller

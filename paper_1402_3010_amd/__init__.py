@@ -112,6 +112,8 @@ def load(path: str = LIB_PATH):
     lib.apss_build_index.restype = ctypes.c_int
     lib.apss_index_free.argtypes = [P]
     lib.apss_index_free.restype = None
+    lib.apss_release_memory.argtypes = []
+    lib.apss_release_memory.restype = i64
     lib.apss_join_device.argtypes = [P, f32, P, P, P, i64, ctypes.POINTER(i64)]
     lib.apss_join_device.restype = ctypes.c_int
     lib.apss_join_device_noalloc.argtypes = [P, f32, P, P, P, i64, ctypes.POINTER(i64)]
@@ -158,7 +160,7 @@ def load(path: str = LIB_PATH):
     return lib
 
 
-EXPORTED = ("apss_default_opts", "apss_build_index", "apss_index_free", "apss_join_device",
+EXPORTED = ("apss_default_opts", "apss_build_index", "apss_index_free", "apss_release_memory", "apss_join_device",
             "apss_join_device_noalloc", "apss_join",
             "apss_query", "apss_query_device", "apss_pairs_free", "apss_last_stats", "apss_index_export",
             "apss_index_sizes", "apss_strerror", "apss_last_error", "apss_autotune", "apss_server_default_opts",
@@ -253,6 +255,11 @@ def build_index(n: int, m: int, row_ptr, col, val, t_build: float, opts: Optiona
 
 def index_free(h: int):
     load().apss_index_free(h)
+
+
+def release_memory() -> int:
+    """apss_release_memory: device memory that closed indexes left to the library goes back; returns its bytes."""
+    return load().apss_release_memory()
 
 
 def join(h: int, t: float):

@@ -146,13 +146,18 @@ void spare_put(void* p, size_t size, int device) {
   for (void* q : gone) (void)hipFree(q);
 }
 
-void spare_release() {
+size_t spare_release() {
   std::vector<Spare> all;
   {
     std::lock_guard<std::mutex> lock(g_spare_mu);
     all.swap(g_spare);
   }
-  for (const Spare& c : all) (void)hipFree(c.p);
+  size_t bytes = 0;
+  for (const Spare& c : all) {
+    (void)hipFree(c.p);
+    bytes += c.size;
+  }
+  return bytes;
 }
 
 namespace {
@@ -2164,6 +2169,8 @@ void apss_index_free(apss_index* idx) {
   apss_index_free(idx->screen);
   delete idx;
 }
+
+int64_t apss_release_memory(void) { return (int64_t)spare_release(); }
 
 int apss_join_device(apss_index* ix, float t, uint32_t* out_i, uint32_t* out_j, float* out_sim, int64_t capacity,
                      int64_t* count) {

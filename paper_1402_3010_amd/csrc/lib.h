@@ -17,15 +17,15 @@
 
 namespace apss {
 
-// Owned device allocation.
 // Device memory that ended builds and indexes leave to the next ones
 // (capi.cpp): at most 1/32 of the device's, given back when it has not been
-// taken for 32 requests, when it exceeds that, and when memory runs out.  A
-// chunk is put there only once nothing that uses it is in flight; its
-// contents are whatever its last owner left.  Any thread may call these.
+// taken for 32 requests, when it exceeds that, when an allocation here fails,
+// and by apss_release_memory.  A chunk is put there only once nothing that uses
+// it is in flight; its contents are whatever its last owner left.  Any thread
+// may call these.
 hipError_t spare_take(size_t bytes, void** p, size_t* size, int* device);
 void spare_put(void* p, size_t size, int device);
-void spare_release();
+size_t spare_release();  // bytes given back
 
 // Device memory of one owner, handed out in pieces and given back all at once
 // when it ends: an allocation of some size costs 30 to 100 us and its release
@@ -82,6 +82,7 @@ class Arena {
   char* end_ = nullptr;
 };
 
+// Owned device allocation, or a piece of an arena.
 template <typename T>
 struct DBuf {
   T* p = nullptr;
@@ -142,7 +143,6 @@ struct RankRows {
   std::vector<int64_t> rp_host;  // host copy of rp (tile formation)
 };
 
-// Sort scratch sized for the largest sort done so far.
 // Page-locked host buffer that only grows (copies from and to it run
 // asynchronously by DMA).
 template <class T>
@@ -167,6 +167,7 @@ struct PinnedBuf {
   }
 };
 
+// Sort scratch sized for the largest sort done so far.
 struct SortScratch {
   DBuf<uint64_t> k1, k2, v64a, v64b;
   DBuf<uint32_t> v32a, v32b;

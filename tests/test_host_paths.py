@@ -179,3 +179,19 @@ for call in (lambda: ix.join(0.5), lambda: apss.load().apss_join_device(ix.handl
             call()
             assert launches() == want
 """)
+
+
+def test_kept_memory_goes_back_when_asked(tmp_path):
+    fake_device.run(tmp_path, """
+assert apss.release_memory() == 0
+for _ in range(2):
+    a, b = index(300), index(5000)
+    a.close()
+    c = index(300)  # (from what the first one left)
+    c.join(0.5)
+    b.close()
+    c.close()
+    assert fake.fake_live() > 0  # kept for the next index
+    assert apss.release_memory() >= 3 << 20
+    assert fake.fake_live() == 0 and apss.release_memory() == 0
+""")
