@@ -117,7 +117,10 @@ hipError_t spare_take(size_t bytes, void** p, size_t* size, int* device_out) {
       *size = g_spare[best].size;
       g_spare.erase(g_spare.begin() + (std::ptrdiff_t)best);
     }
-    spare_trim(device, gone);
+    try {
+      spare_trim(device, gone);
+    } catch (const std::bad_alloc&) {  // (the next request's turn)
+    }
   }
   for (void* q : gone) (void)hipFree(q);
   if (*p) return hipSuccess;
@@ -140,9 +143,14 @@ void spare_put(void* p, size_t size, int device) {
   std::vector<void*> gone;
   {
     std::lock_guard<std::mutex> lock(g_spare_mu);
-    g_spare.push_back(Spare{p, size, device, g_spare_requests});
-    spare_trim(device, gone);
+    try {  // (called by destructors)
+      g_spare.push_back(Spare{p, size, device, g_spare_requests});
+      p = nullptr;
+      spare_trim(device, gone);
+    } catch (const std::bad_alloc&) {
+    }
   }
+  if (p) (void)hipFree(p);
   for (void* q : gone) (void)hipFree(q);
 }
 

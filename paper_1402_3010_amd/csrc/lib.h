@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -53,6 +54,11 @@ class Arena {
   }
   hipError_t reserve(int64_t bytes) {
     if (end_ - at_ >= bytes) return hipSuccess;
+    try {
+      chunks_.reserve(chunks_.size() + 1);
+    } catch (const std::bad_alloc&) {
+      return hipErrorOutOfMemory;
+    }
     Chunk c;
     const hipError_t e = spare_take((size_t)bytes, &c.p, &c.size, &c.device);
     if (e != hipSuccess) return e;

@@ -12,6 +12,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PRELUDE = """
 import ctypes, sys
 sys.path.insert(0, %(root)r)
+%(before)s
 fake = ctypes.CDLL(%(lib)r, ctypes.RTLD_GLOBAL)
 fake.fake_launch.restype = ctypes.c_char_p
 for f in (fake.fake_mallocs, fake.fake_live):
@@ -39,12 +40,12 @@ def index(n, t=0.5, **kw):
 """
 
 
-def run(tmp_path, script):
+def run(tmp_path, script, before=""):
     lib = os.path.join(str(tmp_path), "fake_hip.so")
     subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
                     os.path.join(ROOT, "tests", "fake_hip.c"), "-o", lib], check=True)
     env = {k: v for k, v in os.environ.items() if not k.startswith("APSS_")}
-    r = subprocess.run([sys.executable, "-c", PRELUDE % dict(root=ROOT, lib=lib) + script], capture_output=True,
+    r = subprocess.run([sys.executable, "-c", PRELUDE % dict(root=ROOT, lib=lib, before=before) + script], capture_output=True,
                        text=True, timeout=300, env=env)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
     return r.stdout

@@ -1,4 +1,6 @@
 """Host code of the library against a stand-in runtime (no GPU): what a failed call leaves, and which kernels run."""
+import subprocess
+
 from tests import fake_device
 
 
@@ -195,3 +197,35 @@ for _ in range(2):
     assert apss.release_memory() >= 3 << 20
     assert fake.fake_live() == 0 and apss.release_memory() == 0
 """)
+
+
+def test_ending_an_index_needs_no_host_memory(tmp_path):
+    # operator new fails in apss_index_free, at each of its calls in turn: the chunks are freed in place of kept
+    src = tmp_path / "new.cpp"
+    src.write_text("""
+#include <cstdlib>
+#include <new>
+static long calls, from = -1;
+extern "C" void fake_fail_news(long k) { calls = 0; from = k; }
+extern "C" long fake_news() { return calls; }
+void* operator new(std::size_t n) {
+  if (from >= 0 && calls++ >= from) throw std::bad_alloc();
+  return std::malloc(n);
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, std::size_t) noexcept { std::free(p); }
+""")
+    lib = tmp_path / "new.so"
+    subprocess.run(["g++", "-shared", "-fPIC", "-O1", str(src), "-o", str(lib)], check=True)
+    fake_device.run(tmp_path, """
+for k in range(3):
+    ixs = [index(n) for n in (300, 5000, 70000)]
+    news.fake_fail_news(ctypes.c_long(k))
+    for ix in ixs:
+        ix.close()
+    used = news.fake_news()
+    news.fake_fail_news(ctypes.c_long(-1))
+    assert k > 0 or (used > 0 and fake.fake_live() == 0)
+    apss.release_memory()
+    assert fake.fake_live() == 0
+""", before="news = ctypes.CDLL(%r, ctypes.RTLD_GLOBAL)\n" % str(lib))
