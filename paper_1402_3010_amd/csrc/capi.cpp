@@ -426,22 +426,23 @@ int build_impl(apss_index* ix, const int64_t* row_ptr, const int32_t* col, const
   return build_screen(ix, (int32_t)std::min<int64_t>(ix->opts.screen_dims, m), cnt_r.p, tmp);
 }
 
-// An index whose self-joins may take the list-pair kernels: the default
-// algorithm with no geometry asked for (a tile variant, range width or group
-// given by the caller names the accumulating kernel), and the sparse pass of
-// the screened join (whose geometry is that of the accumulating kernel
-// wherever the cost rule leaves it there).
-bool default_geometry(const apss_index* ix) {
-  const apss_opts& o = ix->opts;
+// No geometry asked for: a tile variant, range width or group given by the
+// caller, or by the environment when the index is built, names the
+// accumulating kernel.
+bool default_geometry(const apss_opts& o) {
   return o.variant < 0 && o.range_rows == 0 && o.range_group == 0 && !getenv("APSS_VARIANT") &&
          !getenv("APSS_RANGE_ROWS") && !getenv("APSS_RANGE_GROUP");
 }
 
+// An index whose self-joins may take the list-pair kernels: the default
+// algorithm and geometry, and the sparse pass of the screened join (whose
+// geometry is that of the accumulating kernel wherever the cost rule leaves it
+// there).
 bool pairs_eligible(const apss_index* ix) {
   const apss_opts& o = ix->opts;
   if (o.index_all || o.local_parts > 1 || o.remscore || o.screen_dims) return false;
   if (ix->n <= 1 || ix->n > (1 << 25)) return false;  // (a list's units are counted in 32 bits)
-  return ix->head_cut > 0 || default_geometry(ix);
+  return ix->head_cut > 0 || ix->default_geometry;
 }
 
 int32_t dense_ranks(const apss_index* ix) {
@@ -807,6 +808,7 @@ int build_screen(apss_index* ix, int32_t head, const uint32_t* cnt_r, Arena& tmp
   sx->variant = ix->variant;
   sx->range_rows = ix->range_rows;
   sx->range_group = ix->range_group;
+  sx->default_geometry = ix->default_geometry;
   sx->head_cut = head;
   sx->rows.n = ix->rows.n;
   sx->rows.nnz = ix->rows.nnz;
@@ -1105,7 +1107,7 @@ void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue
 // True when a batch of nq queries takes the few-query kernel: default
 // algorithm and geometry, and list offsets at its row bounds.
 bool takes_few(const apss_index* ix, int64_t nq) {
-  return nq <= kFewQueries && ix->opts.reserved[0] != kProbePairs && ix->parts == 1 && !ix->opts.remscore && ix->head_cut == 0 && default_geometry(ix) &&
+  return nq <= kFewQueries && ix->opts.reserved[0] != kProbePairs && ix->parts == 1 && !ix->opts.remscore && ix->head_cut == 0 && ix->default_geometry &&
          ix->toff_rows > 0 && ix->toff_rows % kFewRows == 0;
 }
 
@@ -2145,6 +2147,7 @@ int apss_build_index(int64_t n, int64_t m, const int64_t* row_ptr, const int32_t
     const int g = atoi(ev);
     if (g >= 1 && g <= kMaxRangeGroup) ix->range_group = g;
   }
+  ix->default_geometry = default_geometry(o);
   (void)hipGetDevice(&ix->device);
   if (o.screen_dims > 0 && !screen_variant_ok(ix->variant)) {
     set_error("tile variant %d is not available for the screened join", ix->variant);

@@ -275,6 +275,7 @@ struct apss_index {
   int variant = 1;          // tile variant of the join kernel
   int64_t range_rows = 0;   // corpus rows per work-item range
   int32_t range_group = 1;  // ranges per work item
+  bool default_geometry = false;  // neither the options nor the environment name one
   int32_t head_cut = 0;     // > 0: the unindexed part of every row is its components of rank < head_cut
   apss_index* screen = nullptr;  // head-cut index over the same rows (screened join), owned
   // the index's tables, and those that only the list-pair and sketch kernels

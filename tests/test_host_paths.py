@@ -229,3 +229,26 @@ for k in range(3):
     apss.release_memory()
     assert fake.fake_live() == 0
 """, before="news = ctypes.CDLL(%r, ctypes.RTLD_GLOBAL)\n" % str(lib))
+
+
+def test_the_environment_counts_when_an_index_is_built(tmp_path):
+    # an index keeps its kernels when the variables change after its build
+    fake_device.run(tmp_path, """
+import os
+q = rows(3)
+
+def kernels(ix):
+    launches()
+    apss.query(ix.handle, 3, *q, 0.5)
+    return [k for k in launches() if "k_few" in k or "k_join" in k]
+
+default = index(300)
+assert "k_few" in kernels(default)[0]
+for name, value in (("APSS_VARIANT", "0"), ("APSS_RANGE_ROWS", "4096"), ("APSS_RANGE_GROUP", "2")):
+    os.environ[name] = value
+    assert len(kernels(default)) == 1 and "k_few" in kernels(default)[0]
+    named = index(300)
+    assert "k_join" in kernels(named)[0]
+    del os.environ[name]
+    assert "k_join" in kernels(named)[0]
+""")
