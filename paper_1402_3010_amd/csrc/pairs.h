@@ -119,11 +119,13 @@ struct CountArgs {
 
 // Least sketch product of a pair that can reach t: a pair with sim >= t has a
 // product of at least t * kSkScale^2; the 1e-3 covers the rounding of that
-// many times over.
+// many times over.  At least 1, the product of rows that share a group: rows
+// without components (whose first one is not to be read) survive at no t.
 __host__ __device__ inline int32_t pair_threshold(float t) {
   const double v = (double)t * kSkScale * kSkScale - 1e-3;
   const int32_t k = (int32_t)v;
-  return (double)k < v ? k + 1 : k;
+  const int32_t up = (double)k < v ? k + 1 : k;
+  return up < 1 ? 1 : up;
 }
 
 // gid[r] from the cumulative component counts by rank (exclusive scan cum[m], total nnz)
