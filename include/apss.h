@@ -66,7 +66,7 @@ typedef struct {
                             their kernels (accumulating, list pairs, sketches) is expected to be
                             faster; a variant, range_rows or range_group given here names the
                             accumulating join kernel.  The environment variable APSS_VARIANT
-                            overrides it. */
+                            overrides it (the variables are read when an index is built). */
   int32_t head_dims;     /* densest dimensions that get per-block list offsets (0 = default) */
   int32_t range_rows;    /* corpus rows per work item of the join (rounded down to a multiple of the
                             variant's block rows; 0 = default 16384).  The environment variable
@@ -99,7 +99,7 @@ typedef struct {
   int32_t range_group;   /* corpus ranges per work item of the join (1 to 64): an item stages its
                             query tile once and visits that many consecutive ranges in turn;
                             0 = 1.  The environment variable APSS_RANGE_GROUP overrides it. */
-  int32_t reserved[4];
+  int32_t reserved[4];   /* zero (apss_default_opts); other values are for the library's own tests */
 } apss_opts;
 
 void apss_default_opts(apss_opts* opts);

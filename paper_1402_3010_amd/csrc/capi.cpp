@@ -1,6 +1,9 @@
 // C ABI of the apss library: index construction, self-join, external
 // queries.  Host code only orchestrates device work; every step of the
-// join runs in the kernels of index_build.hip, join.hip and primitives.hip.
+// join runs in the kernels of index_build.hip (index, query rows), pairs.hip
+// (list pairs, sketches, candidate count), few.hip (few queries), join.hip
+// (accumulating join), screen.hip (head screen), finish.hip and primitives.hip
+// (pairs sorted and handed over).
 #include <stdarg.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -605,15 +608,17 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   CHK(hipStreamSynchronize(s), "sample");
   const double k = (double)plan.pa.every;
   const double blocks = (double)((n + kCountRows - 1) / kCountRows);
-  const double pairs_ms = 1e3 * (k * (double)c[C_VISITS] / 1.5e12 + 2.0 * k * (double)c[C_SURVIVORS] * 0.45e-9 +
-                                 (double)ix->nshort * 1.6e-9 + (double)windows * 0.4e-9 + (ix->head_cut > 0 ? 2.8e-12 * (double)c[C_TAILVISITS] : 0.5 * blocks * (double)ix->P * (2e-9 / 110.0)));
-  const double lists_ms = 1e3 * ((double)c[C_TAILVISITS] / 1.2e12 + 0.5 * (double)n * (double)n / 1.1e12 +
-                                 (ix->head_cut > 0 ? k * (double)c[C_SURVIVORS] * 9e-9 : 0.0));
+  const double visits = (double)c[C_TAILVISITS], survivors = k * (double)c[C_SURVIVORS];
+  const double count_s = ix->head_cut > 0 ? 2.8e-12 * visits : 0.5 * blocks * (double)ix->P * (2e-9 / 110.0);
+  const double test_s = k * (double)c[C_VISITS] / 1.5e12 + (double)ix->nshort * 1.6e-9 + (double)windows * 0.4e-9;
+  const double pairs_s = test_s + 2.0 * survivors * 0.45e-9 + count_s;
+  const double lists_s = visits / 1.2e12 + 0.5 * (double)n * (double)n / 1.1e12 +
+                         (ix->head_cut > 0 ? survivors * 9e-9 : 0.0);
   // (up to one block of rows launches and waits are most of either: 0.24 ms
   // against 0.27 ms for 2,000 rows, so there only many survivors decide)
-  const bool few = k * (double)c[C_SURVIVORS] <= 64.0 * (double)n;
-  ix->pairs_ready = (n <= kCountRows && (few || ix->head_cut == 0)) ? few : pairs_ms < lists_ms;
-  ix->pair_survivors = k * (double)c[C_SURVIVORS];
+  const bool few = survivors <= 64.0 * (double)n;
+  ix->pairs_ready = (n <= kCountRows && (few || ix->head_cut == 0)) ? few : pairs_s < lists_s;
+  ix->pair_survivors = survivors;
   if (ix->opts.reserved[0] == kProbePairs) ix->pairs_ready = true;
   // Queries, per pair of a query and a row: 0.32 ps for the test and 0.49 for
   // the count at 110 indexed components a row, against 0.9 and 0.83 per list
@@ -622,14 +627,15 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   // are known when the thresholds are; the tables are kept if the kernels
   // would win halfway between t_build and 1.
   const double rows2 = (double)n * (double)n;
-  const int64_t qrows = std::min<int64_t>(n, ((n + kWideRows * qsample.every - 1) / (kWideRows * qsample.every)) * kWideRows);
+  const int64_t span = kWideRows * qsample.every;
+  const int64_t qrows = std::min<int64_t>(n, (n + span - 1) / span * kWideRows);
   double reach = 0.0;
   for (int b = kRateBins - 1; b >= 0; --b) {
     reach += (double)qc[b];
     ix->rate[b] = reach / ((double)plan.qa.nq * (double)qrows);
   }
   ix->screen_ps = 0.32 + 0.49 * (double)ix->P / (110.0 * (double)n);
-  ix->accumulate_ps = 0.9 + 0.83 * 2.0 * (double)c[C_TAILVISITS] / rows2;
+  ix->accumulate_ps = 0.9 + 0.83 * 2.0 * visits / rows2;
   ix->screen_queries = ix->head_cut == 0 && ix->opts.query_safe &&
                        (ix->screen_ps + kSurvivorPs * ix->rate[kRateBins / 2] < ix->accumulate_ps ||
                         ix->opts.reserved[0] == kProbePairs);
@@ -817,7 +823,7 @@ int build_screen(apss_index* ix, int32_t head, const uint32_t* cnt_r, Arena& tmp
   if ((rc = copy_buf(sx->mem, sx->rows.rp, ix->rows.rp, ix->n + 1, s))) return rc;
   if ((rc = copy_buf(sx->mem, sx->rows.rc, ix->rows.rc, ix->nnz, s))) return rc;
   if ((rc = copy_buf(sx->mem, sx->mw_r, ix->mw_r, ix->m, s))) return rc;
-    return build_lists(sx, cnt_r, tmp);
+  return build_lists(sx, cnt_r, tmp);
 }
 
 // Query tiles: consecutive queries, at most QT of them and, unless a single
@@ -1107,7 +1113,8 @@ void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue
 // True when a batch of nq queries takes the few-query kernel: default
 // algorithm and geometry, and list offsets at its row bounds.
 bool takes_few(const apss_index* ix, int64_t nq) {
-  return nq <= kFewQueries && ix->opts.reserved[0] != kProbePairs && ix->parts == 1 && !ix->opts.remscore && ix->head_cut == 0 && ix->default_geometry &&
+  return nq <= kFewQueries && ix->opts.reserved[0] != kProbePairs && ix->parts == 1 && !ix->opts.remscore &&
+         ix->head_cut == 0 && ix->default_geometry &&
          ix->toff_rows > 0 && ix->toff_rows % kFewRows == 0;
 }
 

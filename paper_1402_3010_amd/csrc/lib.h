@@ -378,11 +378,11 @@ void bind_plan(apss_index* ix, const QuerySet& Q, int triangle, float t, const f
                uint32_t* wg_cur_dev, JoinPlan& P);
 
 // Work queue counters of a launch: 8 queues of the accumulating join, or the
-// list-pair join's units and survivors (3).
+// list-pair join's units and survivors (2).
 constexpr int kQueueCounters = 8;
 constexpr int64_t kControlWords = C_NUM + kQueueCounters / 2 + 1;
 int reserve_control(Workspace& ws);
-// Test hook outside the ABI: apss_opts.reserved[0] of an index whose self-joins
+// For the library's tests only: apss_opts.reserved[0] of an index whose self-joins
 // take the list-pair kernels, and its queries the sketch kernels, whatever the
 // cost rules say.
 constexpr int32_t kProbePairs = 0x50414952;
@@ -396,13 +396,14 @@ constexpr double kSurvivorPs = 1200.0;
 constexpr int64_t kQueryTile = 64;  // queries a workgroup of theirs meets at a time
 // True when a self-join of the index takes the list-pair kernels.
 bool use_pairs(const apss_index* ix);
-// The list-pair self-join's kernel arguments, with 2 unit counters.
+// The list-pair self-join's kernel arguments, with its queue counters and a
+// survivor queue of qcap entries.
 void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue_dev, int64_t qcap, JoinPlan& P);
 // Survivor queue entries (3 words each) of a self-join by list pairs.
 constexpr int64_t kPairQueueMost = 64ll << 20;
 int64_t pair_queue_entries(const apss_index* ix);
-// Launch a plan's kernels (the queue counters are cleared here, the result
-// counters by the caller).
+// Launch a plan's kernels (the caller has cleared the queue counters and the
+// result counters).
 int launch_plan(JoinPlan& P, uint64_t* out_key, float* out_sim, int64_t cap, unsigned long long* counters,
                 unsigned int* qctr, hipStream_t s);
 

@@ -68,7 +68,7 @@ struct PairArgs {
   int64_t every, first;   // wide units, groups of short units and windows first, first + every, ...
                           // (of a join set from turns by its launcher)
   int32_t sstep;          // short units a wave takes at a time (at most kShortUnits)
-  unsigned int* uctr;     // [3] next wide unit, unused, queued survivors (zero at launch)
+  unsigned int* uctr;     // [2] next wide unit, queued survivors (zero at launch)
   uint32_t* queue;        // [3 * qcap] survivors to decide: two row ids and the list's rank
   int64_t qcap;
   float t;
@@ -147,8 +147,8 @@ struct PairGroups {
   int wide = 0, shorts = 0, screen = 0, decide = 0;
 };
 PairGroups pairs_resident_groups();
-// The pair tests, then the queued survivors' decisions, a.turns times.
-// Survivors past a.qcap are decided by the wave that finds them, so any
+// The pair tests, then the queued survivors' decisions, a.turns times (uctr is
+// cleared between them).  Survivors past a.qcap are decided by the wave that finds them, so any
 // capacity (0 too) gives the whole result; but one at a time and from memory,
 // some fifty times slower: hence the turns.  (a.sstep is set here.)
 hipError_t launch_pairs(PairArgs a, const PairGroups& g, hipStream_t s);

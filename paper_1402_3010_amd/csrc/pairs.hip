@@ -564,7 +564,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   const int lane = (int)(threadIdx.x & 63u);
   const int wave = uni((int)(threadIdx.x >> 6));
   if (a.counters[C_OVERFLOW]) return;  // (the call is made by the accumulating kernel)
-  const int64_t held = (int64_t)a.uctr[2] < a.qcap ? (int64_t)a.uctr[2] : a.qcap;
+  const int64_t held = (int64_t)a.uctr[1] < a.qcap ? (int64_t)a.uctr[1] : a.qcap;
   const int64_t waves = (int64_t)gridDim.x * 4;
   const int64_t even = (held + waves - 1) / waves;
   // (each wave ends with atomics on the same few counters)
@@ -613,8 +613,8 @@ struct Survivors {
     // entries per wave of the capacity
     unsigned int at = 0;
     if (lane == 0) {
-      at = __hip_atomic_load(&pa.uctr[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if ((int64_t)at < pa.qcap) at = atomicAdd(&pa.uctr[2], (unsigned int)n);
+      at = __hip_atomic_load(&pa.uctr[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if ((int64_t)at < pa.qcap) at = atomicAdd(&pa.uctr[1], (unsigned int)n);
     }
     at = (unsigned int)uni((int)at);
     const int64_t room = pa.qcap - (int64_t)at;
@@ -653,8 +653,8 @@ struct Survivors {
     if (threadIdx.x == 0) {
       unsigned int at = 0xFFFFFFFFu;
       if (!pa.sample) {
-        at = __hip_atomic_load(&pa.uctr[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        at = (int64_t)at + (int64_t)total <= pa.qcap ? atomicAdd(&pa.uctr[2], total) : 0xFFFFFFFFu;
+        at = __hip_atomic_load(&pa.uctr[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        at = (int64_t)at + (int64_t)total <= pa.qcap ? atomicAdd(&pa.uctr[1], total) : 0xFFFFFFFFu;
       }
       base = at;
     }
@@ -1156,7 +1156,7 @@ __global__ void k_present(const int64_t* __restrict__ off, const Post* __restric
   }
 }
 
-// Segment {first entry, entries} of every rank < H in each block, side by side.
+// Segment {first entry, end} of every rank < H in each block, side by side.
 __global__ void k_segments(const uint32_t* __restrict__ hoff, int32_t H, int32_t cb, int64_t nb, int64_t nblk,
                            uint2* __restrict__ seg) {
   const int64_t step = kCountRows / cb;
@@ -1716,10 +1716,11 @@ PairGroups pairs_resident_groups() {
 
 hipError_t launch_pairs(PairArgs a, const PairGroups& g, hipStream_t s) {
   if (a.ndeep <= 0) return hipSuccess;
-  if (!a.dlr || !a.rp || !a.rc || !a.sk || !a.gid || !a.fidx || !a.fsk || !a.qrp || !a.qrc || !a.qfidx || !a.qfsk || !a.dl || !a.doff || !a.wide || !a.shorts || !a.uctr ||
-      (!a.sample && (!a.out_key || !a.out_sim || a.turns < 1)) || (a.sample && (a.every < 1 || a.first)) || !a.counters || (a.qcap > 0 && !a.queue) || a.nwide > kMaxUnits ||
-      a.nshort > kMaxUnits)
+  if (!a.dlr || !a.rp || !a.rc || !a.sk || !a.gid || !a.fidx || !a.fsk || !a.qrp || !a.qrc || !a.qfidx || !a.qfsk ||
+      !a.dl || !a.doff || !a.wide || !a.shorts || !a.uctr || !a.counters || (a.qcap > 0 && !a.queue) ||
+      a.nwide > kMaxUnits || a.nshort > kMaxUnits)
     return hipErrorInvalidValue;
+  if (a.sample ? a.every < 1 || a.first != 0 : !a.out_key || !a.out_sim || a.turns < 1) return hipErrorInvalidValue;
   hipError_t e = hipSuccess;
   if (!a.sample) a.every = a.turns;
   const int64_t every = a.every, turns = a.sample ? 1 : a.turns;
@@ -1734,7 +1735,7 @@ hipError_t launch_pairs(PairArgs a, const PairGroups& g, hipStream_t s) {
   const int64_t need = std::max((steps + 15) / 16, std::min<int64_t>((steps + 3) / 4, 256));
   for (int64_t turn = 0; turn < turns; ++turn) {
     if (!a.sample) a.first = turn;
-    if (turn > 0 && (e = fill_u32(a.uctr, 0u, 3, s)) != hipSuccess) return e;
+    if (turn > 0 && (e = fill_u32(a.uctr, 0u, 2, s)) != hipSuccess) return e;
     if (wide > 0) {
       hipLaunchKernelGGL(k_pairs_wide, dim3((unsigned)(wide < g.wide ? wide : g.wide)), dim3(256), 0, s, a);
       if ((e = hipGetLastError()) != hipSuccess) return e;
