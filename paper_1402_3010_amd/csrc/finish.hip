@@ -30,9 +30,11 @@ __global__ __launch_bounds__(64 * kWaves) void k_finish(FinishArgs a) {
   const int wave = tid >> 6;
   if (blockIdx.x == 0 && tid < C_NUM) a.host[tid] = a.counters[tid];
   if (blockIdx.x == 0 && tid >= C_NUM && tid < C_NUM + 2) a.host[tid] = a.checks ? a.checks[tid - C_NUM] : 0ull;
-  const unsigned long long matches = a.counters[C_MATCHES];
+  // (three words in one wait)
+  const unsigned long long matches = a.counters[C_MATCHES], full = a.counters[C_OVERFLOW];
+  const uint32_t failed = (uint32_t)*(a.checks ? a.checks : a.counters + C_OVERFLOW);
   if (matches > (unsigned long long)kFinishPairs || matches > (unsigned long long)a.cap ||
-      matches > (unsigned long long)a.room || a.counters[C_OVERFLOW] || (a.checks && (uint32_t)a.checks[0] != 0u))
+      matches > (unsigned long long)a.room || ((uint32_t)full | failed) != 0u)
     return;
   const int n = (int)matches;
   const int own = (int)blockIdx.x * kOwn + lane;

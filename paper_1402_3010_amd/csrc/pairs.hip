@@ -563,8 +563,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   __shared__ StagedRow rows[4];
   const int lane = (int)(threadIdx.x & 63u);
   const int wave = uni((int)(threadIdx.x >> 6));
-  if (a.counters[C_OVERFLOW]) return;  // (the call is made by the accumulating kernel)
-  const int64_t held = (int64_t)a.uctr[1] < a.qcap ? (int64_t)a.uctr[1] : a.qcap;
+  const unsigned int queued = a.uctr[1];
+  if (a.query && a.counters[C_OVERFLOW]) return;  // (the call is made by the accumulating kernel)
+  const int64_t held = (int64_t)queued < a.qcap ? (int64_t)queued : a.qcap;
   const int64_t waves = (int64_t)gridDim.x * 4;
   const int64_t even = (held + waves - 1) / waves;
   // (each wave ends with atomics on the same few counters)
@@ -1009,9 +1010,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // accumulating kernel took 15 ms.  256 groups where a self-join's lists have
 // 128: no list narrows the pairs here.
 // Once the survivors have outgrown their queue the rest of the rows is left
-// out: thread 0 reads the flag with each block's sketches, and the others see
-// it behind the block's barriers (in two words in turn: a block has a barrier,
-// so nobody still reads the word that is written).
+// out: thread 0 reads the flag with each block's sketches and passes it on at
+// the block's end, when it has long arrived; all threads follow it at the end
+// of the next block, whose barriers lie between (two words in turn, so that
+// nobody still reads the one that is written).  Batches of a few steps are over
+// too soon for it (64 queries: 41 us, and 43 with the reads).
 // SAMPLE: every a.every-th workgroup only, counting the pairs that reach
 // each of kRateBins thresholds, evenly between s.t and 1.
 constexpr int kMidSteps = kMidGroups / 32;
@@ -1029,6 +1032,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   Survivors sv{qa[wave], qb[wave], qd[wave]};
   Decided dc;
   if (SAMPLE && tid < kRateBins) bins[tid] = 0u;
+  if (tid == 0) full[1] = 0u;
   // this thread's part of a step's columns: 64 groups of column tid / 4
   const int col = tid >> 2, part = tid & 3;
   i32x4 x[4];
@@ -1042,11 +1046,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   // chunk c of column r at position c ^ (r % 16) of its row
   auto at = [](int r, int c) { return r * 16 + (c ^ (r & 15)); };
   const int64_t step = (int64_t)gridDim.x * kWideRows * (SAMPLE ? a.every : 1);
+  const bool watch = !SAMPLE && s.nq - s.q0 > 512;
   int buf = 0, turn = 0;
   for (int64_t block0 = (int64_t)blockIdx.x * kWideRows * (SAMPLE ? a.every : 1); block0 < s.n;
        block0 += step, turn ^= 1) {
     unsigned long long flag = 0ull;
-    if (!SAMPLE && tid == 0)
+    if (watch && tid == 0)
       flag = __hip_atomic_load(&a.counters[C_OVERFLOW], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int64_t row0 = block0 + 64 * wave;
     const int na = s.n - row0 < 64 ? (int)(s.n - row0) : 64;  // may be <= 0
@@ -1060,7 +1065,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       for (int ks = 0; ks < kMidSteps; ++ks) fa[i][ks] = *reinterpret_cast<const i32x4*>(p + 32 * ks);
     }
     fetch(s.q0);
-    if (!SAMPLE && tid == 0) full[turn] = flag != 0ull ? 1u : 0u;
     for (int64_t b0 = s.q0; b0 < s.nq; b0 += 64, buf ^= 1) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) cols[buf][at(col, 4 * part + c)] = x[c];
@@ -1100,7 +1104,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         }
       }
     }
-    if (!SAMPLE && full[turn]) break;
+    if (watch) {
+      if (full[turn ^ 1]) break;
+      if (tid == 0) full[turn] = flag != 0ull ? 1u : 0u;
+    }
   }
   if (SAMPLE) {
     __syncthreads();
@@ -1245,7 +1252,9 @@ __global__ __launch_bounds__(64 * kCountWaves) __attribute__((amdgpu_waves_per_e
   const int wave = uni(tid >> 6);
   int64_t b, j;
   count_item(a, nchunk, &b, &j);
-  if (b >= a.nblk || a.counters[C_OVERFLOW]) return;
+  if (b >= a.nblk) return;
+  // (a batch of queries that outgrew its queue is not counted; read with the first loads)
+  const unsigned long long flag = a.triangle ? 0ull : a.counters[C_OVERFLOW];
   const int64_t row0 = b * kCountRows;
   const int64_t qbeg = j * a.chunk;
   const int64_t qend = qbeg + a.chunk < a.nq ? qbeg + a.chunk : a.nq;
@@ -1262,6 +1271,7 @@ __global__ __launch_bounds__(64 * kCountWaves) __attribute__((amdgpu_waves_per_e
   uint32_t* const sp = spare[wave];
   sp[2 * lane] = 0u;
   sp[2 * lane + 1] = 0u;
+  if (flag) return;
   __syncthreads();
 
   const uint2* const seg = a.seg + b * (int64_t)a.H;
@@ -1445,7 +1455,9 @@ __global__ __launch_bounds__(64 * kCountWaves) void k_count_pieces(CountArgs a, 
   const int wave = uni(tid >> 6);
   int64_t b, j;
   count_item(a, nchunk, &b, &j);
-  if (b >= a.nblk || a.counters[C_OVERFLOW]) return;
+  if (b >= a.nblk) return;
+  // (a batch of queries that outgrew its queue is not counted; read with the first loads)
+  const unsigned long long flag = a.triangle ? 0ull : a.counters[C_OVERFLOW];
   const int64_t row0 = b * kCountRows;
   int64_t q0 = j * a.chunk;
   const int64_t qend = q0 + a.chunk < a.nq ? q0 + a.chunk : a.nq;
@@ -1462,6 +1474,7 @@ __global__ __launch_bounds__(64 * kCountWaves) void k_count_pieces(CountArgs a, 
     s = a.rp[q0 + lane] + (a.skip ? (int64_t)a.skip[q0 + lane].cut : 0);
     len = (int)(a.rp[q0 + lane + 1] - s);
   }
+  if (flag) return;
   const int own_pieces = (len + 63) >> 6;
   int upto = own_pieces;
 #pragma unroll
