@@ -11,6 +11,7 @@
 
 #include <algorithm>
 #include <array>
+#include <cmath>
 #include <cstddef>
 #include <mutex>
 #include <new>
@@ -460,6 +461,17 @@ int64_t count_bytes(const apss_index* ix) {
          Arena::bytes<uint32_t>(blocks * std::max<int64_t>(1, (ix->m - H + 31) / 32));
 }
 
+// Queries per work item of a self-join's candidate count: about eight items per
+// compute unit, of at least a few queries per wave; where that leaves the
+// device idle kPieceRows, counted by pieces of rows (a replay of 12,000 rows of
+// mean 80: 350 us by the larger items, 269 so; 30,000 of mean 150: 1,069 us
+// and 1,241; about even at 20,000).
+int64_t count_chunk(int64_t n, int64_t blocks) {
+  const int64_t want = n * blocks / 2 / 2048;
+  const int64_t chunk = std::max<int64_t>(64, std::min<int64_t>(4096, (want + 63) / 64 * 64));
+  return n * blocks / 2 / chunk < 512 ? kPieceRows : chunk;
+}
+
 // An index without the list-pair and sketch tables: its joins and queries take
 // the accumulating kernel.
 int drop_pair_tables(apss_index* ix) {
@@ -504,7 +516,12 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   CHK(hipMemcpyAsync(&deep, total.p, sizeof(int64_t), hipMemcpyDeviceToHost, s), "deep lists");
   CHK(hipStreamSynchronize(s), "deep lists");
   int64_t longs = 0;
-  for (int64_t r = 0; r < n; ++r) longs += ix->rows.rp_host[(size_t)r + 1] - ix->rows.rp_host[(size_t)r] > kFineRow;
+  double unstaged = 0.0;  // share of the components that lie in rows whose lookups go to memory
+  for (int64_t r = 0; r < n; ++r) {
+    const int64_t len = ix->rows.rp_host[(size_t)r + 1] - ix->rows.rp_host[(size_t)r];
+    longs += len > kFineRow;
+    if (len > kStageRanks) unstaged += (double)len / (double)ix->nnz;
+  }
   bool have = false;
   int rc = reserve_pair_tables(ix, 2 * Arena::bytes<uint32_t>(deep) + Arena::bytes<int64_t>(m + 1) +
                                        Arena::bytes<uint16_t>(m) + Arena::bytes<uint8_t>(n * kSkGroups) +
@@ -558,7 +575,8 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   ix->pair_groups = pairs_resident_groups();
   // The list-pair kernels or the accumulating one, whichever should take
   // less, by their measured rates (MI355X): the accumulating kernel visits
-  // 1.2e12 list entries and filters 1.1e12 pairs of rows a second; the
+  // 1.2e12 list entries and filters 1.1e12 pairs of rows a second, beside
+  // which it takes 25 ps to enter a query's component in 1,024 rows; the
   // list-pair kernels test 1.5e12 pairs a second, take 1.6 ns per short unit
   // (a wave's), decide a survivor in 0.45 ns, and count the candidates of a
   // query in a block of 4,096 rows in 2 ns (at 120 components with lists, in
@@ -578,9 +596,10 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   // ms against 3.3 by list pairs; head 512: 6.3 against 2.6; 100,000 text
   // rows, 0.505, head 2048: 497 against 63), so 9 ns are counted.
   DBuf<unsigned long long> cnt;
-  CHK(cnt.take(tmp, C_NUM + kRateBins), "alloc");
+  constexpr int kWords = C_NUM + kRateBins + 2;  // the pairs' counters, the queries' bins, visits
+  CHK(cnt.take(tmp, kWords), "alloc");
   if (int rc = reserve_control(ws)) return rc;
-  CHK(fill_u64((uint64_t*)cnt.p, 0ull, C_NUM + kRateBins, s), "fill");
+  CHK(fill_u64((uint64_t*)cnt.p, 0ull, kWords, s), "fill");
   CHK(fill_u32(ws.qctr, 0u, kQueueCounters, s), "fill");
   JoinPlan plan;
   bind_pairs(ix, ix->t_build, ws.qctr, nullptr, 0, plan);
@@ -590,7 +609,7 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   plan.pa.sample = 1;
   plan.pa.every = std::max<int64_t>(1, units / 4096);
   CHK(launch_pairs(plan.pa, plan.pg, s), "sample");
-  CHK(launch_visits(cnt_r, ix->off.p, m, cnt.p + C_TAILVISITS, s), "sample");
+  CHK(launch_visits(cnt_r, ix->off.p, m, kCountRanks, cnt.p + C_NUM + kRateBins, s), "sample");
   // ... and for queries the survivors among about 2^24 pairs of rows
   plan.qa.sk = ix->mid.p;
   plan.qa.n = n;
@@ -602,22 +621,38 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   qsample.counters = cnt.p + C_NUM;
   qsample.every = std::max<int64_t>(1, n / kWideRows / 64);
   CHK(launch_query_sample(qsample, plan.qa, s), "sample");
-  unsigned long long c[C_NUM + kRateBins];
+  unsigned long long c[kWords];
   const unsigned long long* const qc = c + C_NUM;
   CHK(hipMemcpyAsync(c, cnt.p, sizeof(c), hipMemcpyDeviceToHost, s), "sample");
   CHK(hipStreamSynchronize(s), "sample");
   const double k = (double)plan.pa.every;
   const double blocks = (double)((n + kCountRows - 1) / kCountRows);
-  const double visits = (double)c[C_TAILVISITS], survivors = k * (double)c[C_SURVIVORS];
-  const double count_s = ix->head_cut > 0 ? 2.8e-12 * visits : 0.5 * blocks * (double)ix->P * (2e-9 / 110.0);
+  const double survivors = k * (double)c[C_SURVIVORS];
+  const double visits = (double)c[C_NUM + kRateBins], entries = (double)c[C_NUM + kRateBins + 1];
+  // What long rows cost beyond that: in the count the entries of lists past the
+  // bitmaps, by lane (4 ps, 6 by pieces), and a wave's share of the rows, one
+  // piece after another; in the decisions lookups of rows too long for LDS.
+  // Rows of mean 1,500 over a million dimensions, accumulating and list pairs:
+  // 2,000 rows 0.44 and 0.93 ms, 10,000 4.2 and 8.0, 30,000 35.5 and 59.6; of
+  // mean 500: 2,000 rows 0.19 and 0.17, 5,000 0.45 and 0.57, 12,000 1.55 and
+  // 0.86, 60,000 34.1 and 14.4.
+  const bool pieces = count_chunk(n, (int64_t)blocks) <= kPieceRows;
+  const double chain_s = pieces ? 10e-6 * (double)ix->nnz / (64.0 * (double)n) : 0.0;
+  const double long_s = (ix->head_cut > 0 ? 0.0 : entries * (pieces ? 6e-12 : 4e-12) + chain_s) +
+                        3e-9 * survivors * unstaged;
   const double test_s = k * (double)c[C_VISITS] / 1.5e12 + (double)ix->nshort * 1.6e-9 + (double)windows * 0.4e-9;
-  const double pairs_s = test_s + 2.0 * survivors * 0.45e-9 + count_s;
-  const double lists_s = visits / 1.2e12 + 0.5 * (double)n * (double)n / 1.1e12 +
-                         (ix->head_cut > 0 ? survivors * 9e-9 : 0.0);
+  const double count_s = ix->head_cut > 0 ? 2.8e-12 * visits : 0.5 * blocks * (double)ix->P * (2e-9 / 110.0);
+  const double pairs_s = test_s + 2.0 * survivors * 0.45e-9 + count_s + long_s;
+  const double stream_s = visits / 1.2e12 + 0.5 * (double)n * (double)n / 1.1e12;
+  const double stage_s = 25e-12 * (double)ix->nnz * 0.5 * (double)n / 1024.0;
+  const double lists_s =
+      ix->head_cut > 0 ? stream_s + survivors * 9e-9 : std::sqrt(stream_s * stream_s + stage_s * stage_s);
   // (up to one block of rows launches and waits are most of either: 0.24 ms
-  // against 0.27 ms for 2,000 rows, so there only many survivors decide)
+  // against 0.27 ms for 2,000 rows, so there only many survivors and long rows
+  // decide)
   const bool few = survivors <= 64.0 * (double)n;
-  ix->pairs_ready = (n <= kCountRows && (few || ix->head_cut == 0)) ? few : pairs_s < lists_s;
+  if (n <= kCountRows && ix->head_cut == 0) ix->pairs_ready = few && long_s <= lists_s + 0.15e-3;
+  else ix->pairs_ready = (n <= kCountRows && few) || pairs_s < lists_s;
   ix->pair_survivors = survivors;
   if (ix->opts.reserved[0] == kProbePairs) ix->pairs_ready = true;
   // Queries, per pair of a query and a row: 0.32 ps for the test and 0.49 for
@@ -1098,16 +1133,8 @@ void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue
   c.skip = ix->head_cut > 0 ? ix->rs.p : nullptr;
   c.nq = ix->n;
   c.triangle = 1;
-  // about eight work items per compute unit, of at least a few queries per
-  // wave; where that leaves the device idle one query per wave, counted by
-  // pieces of rows (a replay of 12,000 rows of mean 80: 350 us by the larger
-  // items, 269 so; 30,000 of mean 150: 1,069 us and 1,241; about even at 20,000)
-  const int64_t want = ix->n * ix->count_blocks / 2 / 2048;
-  c.chunk = std::max<int64_t>(64, std::min<int64_t>(4096, (want + 63) / 64 * 64));
-  if (ix->n * ix->count_blocks / 2 / c.chunk < 512) {
-    c.chunk = 16;
-    c.lds_ranks = 0;
-  }
+  c.chunk = count_chunk(ix->n, ix->count_blocks);
+  if (c.chunk <= kPieceRows) c.lds_ranks = 0;
 }
 
 // True when a batch of nq queries takes the few-query kernel: default
@@ -1216,9 +1243,9 @@ int plan_queries(apss_index* ix, Workspace& ws, const QuerySet& Q, float t, cons
   // a block's items (as many as run on an XCD at once) take the batch, so that
   // they share one block's bitmaps in its L2
   const int64_t want = Q.n >= 1024 ? std::max<int64_t>(64, Q.n / 64) : Q.n * ix->count_blocks / 1024;
-  c.chunk = std::max<int64_t>(16, std::min<int64_t>(4096, (want + 15) / 16 * 16));
+  c.chunk = std::max<int64_t>(kPieceRows, std::min<int64_t>(4096, (want + 15) / 16 * 16));
   if (c.chunk < 64) {
-    c.chunk = 16;
+    c.chunk = kPieceRows;
     c.lds_ranks = 0;
   }
   return APSS_OK;

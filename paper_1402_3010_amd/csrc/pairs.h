@@ -27,6 +27,8 @@ constexpr int kWideSpan = 16;
 constexpr int kUnitRows = 64;
 constexpr int kTinyList = 32;
 constexpr int kShortUnits = 16;
+// Longest row that the decision of a pair looks up in LDS.
+constexpr int kStageRanks = 2048;
 constexpr int64_t kMaxUnits = 0x7FFFFFFF;  // of either kind
 // The candidate count: corpus rows per block, and the densest ranks with a
 // bitmap per block (one bit per row whose indexed part holds the rank).
@@ -40,6 +42,8 @@ constexpr int kCountSpan = 516096;
 constexpr int kLdsRanks = 144;
 constexpr int kCountWords = kCountRows / 32;
 constexpr int kCountRanks = 2048;
+// queries of a work item that counts them by pieces (one per wave)
+constexpr int64_t kPieceRows = 16;
 
 struct PairArgs {
   const int64_t* rp;      // [n+1] row offsets of the rank-space rows
@@ -130,8 +134,9 @@ __host__ __device__ inline int32_t pair_threshold(float t) {
 
 // gid[r] from the cumulative component counts by rank (exclusive scan cum[m], total nnz)
 hipError_t launch_groups(const int64_t* cum, const uint32_t* cnt_r, int64_t m, int64_t nnz, uint16_t* gid, hipStream_t s);
-// *out (zeroed before) = list entries an accumulating self-join visits
-hipError_t launch_visits(const uint32_t* cnt_r, const int64_t* off, int64_t m, unsigned long long* out, hipStream_t s);
+// out[0] (zeroed before) = list entries an accumulating self-join visits, out[1] = those of ranks >= hb
+hipError_t launch_visits(const uint32_t* cnt_r, const int64_t* off, int64_t m, int64_t hb, unsigned long long* out,
+                         hipStream_t s);
 hipError_t launch_widen(const uint32_t* in, int64_t n, int64_t* out, hipStream_t s);
 // sk (may be NULL), mid and fine sketches of n rows; nfine: a zeroed counter;
 // fsk: room for every row longer than kFineRow

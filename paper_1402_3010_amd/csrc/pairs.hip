@@ -56,19 +56,23 @@ __global__ void k_groups(const int64_t* __restrict__ cum, const uint32_t* __rest
   }
 }
 
-// *out += sum over ranks of components times postings, halved: the list
-// entries an accumulating self-join visits.
-__global__ void k_visits(const uint32_t* __restrict__ cnt_r, const int64_t* __restrict__ off, int64_t m,
+// out[0] += sum over ranks of components times postings, halved: the list
+// entries an accumulating self-join visits; out[1] those of ranks >= hb.
+__global__ void k_visits(const uint32_t* __restrict__ cnt_r, const int64_t* __restrict__ off, int64_t m, int64_t hb,
                          unsigned long long* __restrict__ out) {
-  __shared__ unsigned long long sum;
-  if (threadIdx.x == 0) sum = 0ull;
+  __shared__ unsigned long long sum[2];
+  if (threadIdx.x < 2) sum[threadIdx.x] = 0ull;
   __syncthreads();
-  unsigned long long v = 0ull;
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < m; r += (int64_t)gridDim.x * blockDim.x)
-    v += (unsigned long long)cnt_r[r] * (unsigned long long)(off[r + 1] - off[r]) / 2;
-  if (v) atomicAdd(&sum, v);
+  unsigned long long v = 0ull, tail = 0ull;
+  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < m; r += (int64_t)gridDim.x * blockDim.x) {
+    const unsigned long long x = (unsigned long long)cnt_r[r] * (unsigned long long)(off[r + 1] - off[r]) / 2;
+    v += x;
+    if (r >= hb) tail += x;
+  }
+  if (v) atomicAdd(&sum[0], v);
+  if (tail) atomicAdd(&sum[1], tail);
   __syncthreads();
-  if (threadIdx.x == 0 && sum) atomicAdd(out, sum);
+  if (threadIdx.x < 2 && sum[threadIdx.x]) atomicAdd(&out[threadIdx.x], sum[threadIdx.x]);
 }
 
 __global__ void k_widen(const uint32_t* __restrict__ in, int64_t n, int64_t* __restrict__ out) {
@@ -213,7 +217,7 @@ __device__ __forceinline__ float row_lookup(const RComp* __restrict__ q, int qle
 // weights too; of longer rows (up to kStageRanks) the weights found are read
 // from memory.
 constexpr int kStageRow = 1024;
-constexpr int kStageRanks = 2 * kStageRow;
+static_assert(kStageRanks == 2 * kStageRow, "ranks, or ranks and weights");
 struct StagedRow {
   int32_t v[kStageRanks];  // ranks, then (from kStageRow on) weights' bits or more ranks
 };
@@ -1668,10 +1672,11 @@ hipError_t launch_groups(const int64_t* cum, const uint32_t* cnt_r, int64_t m, i
   return hipGetLastError();
 }
 
-hipError_t launch_visits(const uint32_t* cnt_r, const int64_t* off, int64_t m, unsigned long long* out, hipStream_t s) {
+hipError_t launch_visits(const uint32_t* cnt_r, const int64_t* off, int64_t m, int64_t hb, unsigned long long* out,
+                         hipStream_t s) {
   if (m <= 0) return hipSuccess;
   const unsigned g = grid1d(m);
-  hipLaunchKernelGGL(k_visits, dim3(g < 256 ? g : 256), dim3(256), 0, s, cnt_r, off, m, out);
+  hipLaunchKernelGGL(k_visits, dim3(g < 256 ? g : 256), dim3(256), 0, s, cnt_r, off, m, hb, out);
   return hipGetLastError();
 }
 
@@ -1826,7 +1831,8 @@ hipError_t launch_count(const CountArgs& a, hipStream_t s) {
   if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
   // a segment spans at most the ranges that meet a block
   const bool packed = kCountRows + 2 * a.rr <= 65536;
-  const bool pieces = a.chunk <= kCountWaves && a.lds_ranks == 0;
+  static_assert(kPieceRows == kCountWaves, "a query per wave");
+  const bool pieces = a.chunk <= kPieceRows && a.lds_ranks == 0;
   if (pieces && packed)
     hipLaunchKernelGGL(k_count_pieces<true>, dim3((unsigned)grid), dim3(64 * kCountWaves), 0, s, a, nchunk);
   else if (pieces)
