@@ -487,6 +487,9 @@ int drop_pair_tables(apss_index* ix) {
   return APSS_OK;
 }
 
+// About the norm that a byte code stands for (an upper bound in 1/254 steps).
+double norm_of_code(int c) { return c >= kPn8None ? 1.0 : c > 0 ? ((double)c - 0.5) / 254.0 : 0.0; }
+
 // Memory for those tables.  *have is false, and the index does without them,
 // if the device has too little.
 int reserve_pair_tables(apss_index* ix, int64_t bytes, bool* have) {
@@ -582,21 +585,13 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   // query in a block of 4,096 rows in 2 ns (at 120 components with lists, in
   // proportion to them).  Measured, accumulating and list pairs: 30 and 13 ms
   // (100,000 rows of mean 80, t = 0.5), 490 and 77 ms (500,000 of mean 120,
-  // 0.7), 21 and 4 ms (sparse pass of 200,000 of mean 150, 0.8, where 0.28 ns
-  // per posting met count the candidates).  The
-  // survivors are estimated from every k-th unit, and doubled: on rows that
-  // the sketches do not tell apart (flat weights over few dimensions) they
-  // are most pairs, and the accumulating kernel is ahead.  A join at a higher
-  // threshold than the index's has fewer.  In the sparse pass of a screened
-  // join the accumulating kernel pays for such pairs too: its bound there adds
-  // a product of the head's norms to what it has accumulated, and what passes
-  // is rescored one pair at a time.  Measured on flat, short, text and heavy
-  // rows with heads of 512 to 4096, it took 9 to 220 ns per survivor of the
-  // sketches beyond its visits (31,340 flat rows, t = 0.505, head 4096: 24.6
-  // ms against 3.3 by list pairs; head 512: 6.3 against 2.6; 100,000 text
-  // rows, 0.505, head 2048: 497 against 63), so 9 ns are counted.
+  // 0.7).  The survivors are estimated from every k-th unit, and doubled: on
+  // rows that the sketches do not tell apart (flat weights over few dimensions)
+  // they are most pairs, and the accumulating kernel is ahead.  A join at a
+  // higher threshold than the index's has fewer.
   DBuf<unsigned long long> cnt;
-  constexpr int kWords = C_NUM + kRateBins + 2;  // the pairs' counters, the queries' bins, visits
+  constexpr int kCodes = 256;
+  constexpr int kWords = C_NUM + kRateBins + 2 + kCodes;  // the pairs' counters, the queries' bins, visits, norms
   CHK(cnt.take(tmp, kWords), "alloc");
   if (int rc = reserve_control(ws)) return rc;
   CHK(fill_u64((uint64_t*)cnt.p, 0ull, kWords, s), "fill");
@@ -610,6 +605,7 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   plan.pa.every = std::max<int64_t>(1, units / 4096);
   CHK(launch_pairs(plan.pa, plan.pg, s), "sample");
   CHK(launch_visits(cnt_r, ix->off.p, m, kCountRanks, cnt.p + C_NUM + kRateBins, s), "sample");
+  if (ix->head_cut > 0) CHK(launch_norm_codes(ix->pn8.p, n, cnt.p + C_NUM + kRateBins + 2, s), "sample");
   // ... and for queries the survivors among about 2^24 pairs of rows
   plan.qa.sk = ix->mid.p;
   plan.qa.n = n;
@@ -636,23 +632,47 @@ int build_pair_lists(apss_index* ix, const uint32_t* cnt_r, Arena& tmp) {
   // 2,000 rows 0.44 and 0.93 ms, 10,000 4.2 and 8.0, 30,000 35.5 and 59.6; of
   // mean 500: 2,000 rows 0.19 and 0.17, 5,000 0.45 and 0.57, 12,000 1.55 and
   // 0.86, 60,000 34.1 and 14.4.
-  const bool pieces = count_chunk(n, (int64_t)blocks) <= kPieceRows;
-  const double chain_s = pieces ? 10e-6 * (double)ix->nnz / (64.0 * (double)n) : 0.0;
-  const double long_s = (ix->head_cut > 0 ? 0.0 : entries * (pieces ? 6e-12 : 4e-12) + chain_s) +
-                        3e-9 * survivors * unstaged;
-  const double test_s = k * (double)c[C_VISITS] / 1.5e12 + (double)ix->nshort * 1.6e-9 + (double)windows * 0.4e-9;
-  const double count_s = ix->head_cut > 0 ? 2.8e-12 * visits : 0.5 * blocks * (double)ix->P * (2e-9 / 110.0);
-  const double pairs_s = test_s + 2.0 * survivors * 0.45e-9 + count_s + long_s;
   const double stream_s = visits / 1.2e12 + 0.5 * (double)n * (double)n / 1.1e12;
-  const double stage_s = 25e-12 * (double)ix->nnz * 0.5 * (double)n / 1024.0;
-  const double lists_s =
-      ix->head_cut > 0 ? stream_s + survivors * 9e-9 : std::sqrt(stream_s * stream_s + stage_s * stage_s);
-  // (up to one block of rows launches and waits are most of either: 0.24 ms
-  // against 0.27 ms for 2,000 rows, so there only many survivors and long rows
-  // decide)
-  const bool few = survivors <= 64.0 * (double)n;
-  if (n <= kCountRows && ix->head_cut == 0) ix->pairs_ready = few && long_s <= lists_s + 0.15e-3;
-  else ix->pairs_ready = (n <= kCountRows && few) || pairs_s < lists_s;
+  const double test_s = k * (double)c[C_VISITS] / 1.5e12 + (double)ix->nshort * 1.6e-9 + (double)windows * 0.4e-9;
+  if (ix->head_cut > 0) {
+    // The sparse pass.  Its accumulating kernel adds a product of the head's
+    // norms to what it has accumulated, and what passes is rescored one pair at
+    // a time, some 4 ns each: half of the pairs that share a tail dimension and
+    // whose heads' norms alone could reach t.  Without such heads it is ahead
+    // of the list pairs where those have many survivors.  Accumulating and list
+    // pairs, measured: heads of 4,096 dimensions, 30,000 rows of mean 300 at t =
+    // 0.6 415 and 6.2 ms, 50,000 flat rows at 0.6 15.3 and 1.1; 40,000 text rows,
+    // 0.6, head 512 20 and 0.7; but heads of 64, 30,000 rows of mean 300 6.0 and
+    // 16.2, of mean 500 at 0.5 8.4 and 24; and rows of mean 1,500 and 6,000 with
+    // any head, 8,000 at 0.8 1.8 and 4.6, 4,500 at 0.8 5.1 and 532.  Over 109
+    // such pairs of corpus and head the rule is within 0.06 ms or an eighth of
+    // the better one.
+    double reach = 0.0, above = 0.0;
+    for (int lo = 0, hi = kCodes; lo < kCodes; ++lo) {  // codes lo whose products with hi and up reach t
+      while (hi > 0 && norm_of_code(lo) * norm_of_code(hi - 1) >= (double)ix->t_build)
+        above += (double)c[C_NUM + kRateBins + 2 + --hi];
+      reach += 0.5 * (double)c[C_NUM + kRateBins + 2 + lo] * above;
+    }
+    const double rows2 = 0.5 * (double)n * (double)n;
+    const double chain_s = n <= 4 * kCountRows ? 10e-6 * (double)ix->P / (64.0 * (double)n) : 0.0;
+    const double pairs_s = test_s + survivors * (0.6e-9 + 3e-9 * unstaged) + visits * 1.6e-12 + chain_s;
+    const double stage_s = 25e-12 * (double)ix->P * 0.5 * (double)n / 1024.0;
+    const double rescored = 0.5 * reach * std::min(1.0, visits / rows2);
+    ix->pairs_ready = pairs_s < std::sqrt(stream_s * stream_s + stage_s * stage_s) + rescored * 4e-9;
+  } else {
+    const bool pieces = count_chunk(n, (int64_t)blocks) <= kPieceRows;
+    const double chain_s = pieces ? 10e-6 * (double)ix->nnz / (64.0 * (double)n) : 0.0;
+    const double long_s = entries * (pieces ? 6e-12 : 4e-12) + chain_s + survivors * 3e-9 * unstaged;
+    const double count_s = 0.5 * blocks * (double)ix->P * (2e-9 / 110.0);
+    const double pairs_s = test_s + 2.0 * survivors * 0.45e-9 + count_s + long_s;
+    const double stage_s = 25e-12 * (double)ix->nnz * 0.5 * (double)n / 1024.0;
+    const double lists_s = std::sqrt(stream_s * stream_s + stage_s * stage_s);
+    // (up to one block of rows launches and waits are most of either: 0.24 ms
+    // against 0.27 ms for 2,000 rows, so there only many survivors and long rows
+    // decide)
+    const bool few = survivors <= 64.0 * (double)n;
+    ix->pairs_ready = n <= kCountRows ? few && long_s <= lists_s + 0.15e-3 : pairs_s < lists_s;
+  }
   ix->pair_survivors = survivors;
   if (ix->opts.reserved[0] == kProbePairs) ix->pairs_ready = true;
   // Queries, per pair of a query and a row: 0.32 ps for the test and 0.49 for

@@ -137,6 +137,8 @@ hipError_t launch_groups(const int64_t* cum, const uint32_t* cnt_r, int64_t m, i
 // out[0] (zeroed before) = list entries an accumulating self-join visits, out[1] = those of ranks >= hb
 hipError_t launch_visits(const uint32_t* cnt_r, const int64_t* off, int64_t m, int64_t hb, unsigned long long* out,
                          hipStream_t s);
+// hist[c] (zeroed before, 256 words) = rows whose unindexed part's norm has byte code c
+hipError_t launch_norm_codes(const uint8_t* pn8, int64_t n, unsigned long long* hist, hipStream_t s);
 hipError_t launch_widen(const uint32_t* in, int64_t n, int64_t* out, hipStream_t s);
 // sk (may be NULL), mid and fine sketches of n rows; nfine: a zeroed counter;
 // fsk: room for every row longer than kFineRow

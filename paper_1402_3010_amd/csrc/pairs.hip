@@ -75,6 +75,17 @@ __global__ void k_visits(const uint32_t* __restrict__ cnt_r, const int64_t* __re
   if (threadIdx.x < 2 && sum[threadIdx.x]) atomicAdd(&out[threadIdx.x], sum[threadIdx.x]);
 }
 
+__global__ __launch_bounds__(256) void k_norm_codes(const uint8_t* __restrict__ pn8, int64_t n,
+                                                    unsigned long long* __restrict__ hist) {
+  __shared__ unsigned int h[256];
+  h[threadIdx.x] = 0u;
+  __syncthreads();
+  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x)
+    atomicAdd(&h[pn8[r]], 1u);
+  __syncthreads();
+  if (h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], (unsigned long long)h[threadIdx.x]);
+}
+
 __global__ void k_widen(const uint32_t* __restrict__ in, int64_t n, int64_t* __restrict__ out) {
   for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
     out[k] = (int64_t)in[k];
@@ -1677,6 +1688,13 @@ hipError_t launch_visits(const uint32_t* cnt_r, const int64_t* off, int64_t m, i
   if (m <= 0) return hipSuccess;
   const unsigned g = grid1d(m);
   hipLaunchKernelGGL(k_visits, dim3(g < 256 ? g : 256), dim3(256), 0, s, cnt_r, off, m, hb, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_norm_codes(const uint8_t* pn8, int64_t n, unsigned long long* hist, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  const unsigned g = grid1d(n);
+  hipLaunchKernelGGL(k_norm_codes, dim3(g < 256 ? g : 256), dim3(256), 0, s, pn8, n, hist);
   return hipGetLastError();
 }
 

@@ -1,4 +1,5 @@
-"""Corpora of long rows over many dimensions keep the accumulating kernel: the list pairs' count and decisions are slower."""
+"""Corpora of long rows over many dimensions keep the accumulating kernel: the list pairs' count and decisions are slower,
+in self-joins and in the sparse pass of the screened join."""
 import numpy as np
 import pytest
 
@@ -31,3 +32,16 @@ def test_kernels_of_long_rows(n, mean, t, pairs):
         assert np.array_equal(x, y)
     assert sa["candidates"] == sb["candidates"]
     assert (sa["posting_visits"] < sb["posting_visits"]) == pairs
+
+
+@pytest.mark.parametrize("n,mean,t,head,pairs", [(2000, 1500, 0.8, 64, False), (2000, 1500, 0.8, 4096, False),
+                                                 (8000, 1500, 0.6, 512, False), (20000, 120, 0.6, 4096, True),
+                                                 (20000, 120, 0.5, 512, True)])
+def test_kernels_of_the_sparse_pass(n, mean, t, head, pairs):
+    V = corpus(n, mean)
+    (a, sa), (b, sb), (c, _) = [join(V, np.float32(t), screen_dims=head, pairs=p) for p in (False, True)] + [
+        join(V, np.float32(t), variant=1)]
+    for x, y, z in zip(a, b, c):
+        assert np.array_equal(x, y) and np.array_equal(x, z)
+    # (visits of the accumulating kernel are list entries, those of the list pairs fewer pairs)
+    assert (sa["posting_visits"] == sb["posting_visits"]) == pairs
