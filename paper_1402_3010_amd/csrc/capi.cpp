@@ -1088,7 +1088,8 @@ int64_t pair_queue_entries(const apss_index* ix) {
 // million pairs' room in the fixed scratch beside 0.4 of 6 million survivors,
 // took 54 ms where the accumulating kernel takes 11.3, in turns 5.2; 300,000
 // such rows, 64M entries for 150 million, 645 ms, 266 and 102.  Turns cost
-// little (150,000 rows in two 27.1 ms, in one 26.3; 16M entries 29.5).
+// little (150,000 rows in two 27.1 ms, in one 26.3, by 16M entries 29.5;
+// 1,000,000 of mean 120 at 0.7 in two 293.3, in one 291.4).
 int64_t pair_turns(const apss_index* ix, int64_t qcap) {
   return qcap > 0 ? 1 + (int64_t)((1.5 * ix->pair_survivors) / (double)qcap) : 1;
 }

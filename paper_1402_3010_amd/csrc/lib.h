@@ -400,7 +400,7 @@ bool use_pairs(const apss_index* ix);
 // survivor queue of qcap entries.
 void bind_pairs(apss_index* ix, float t, unsigned int* uctr_dev, uint32_t* queue_dev, int64_t qcap, JoinPlan& P);
 // Survivor queue entries (3 words each) of a self-join by list pairs.
-constexpr int64_t kPairQueueMost = 64ll << 20;
+constexpr int64_t kPairQueueMost = 96ll << 20;
 int64_t pair_queue_entries(const apss_index* ix);
 // Launch a plan's kernels (the caller has cleared the queue counters and the
 // result counters).

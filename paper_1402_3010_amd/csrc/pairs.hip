@@ -1457,10 +1457,10 @@ __global__ __launch_bounds__(64 * kCountWaves) __attribute__((amdgpu_waves_per_e
 // bitmaps a wave reads at some 20 ns a component.  So the rows' components
 // are cut into pieces of 64, the waves take them in turn, and the unions meet
 // in LDS; eight bitmaps are loaded at once, since few waves run.
-// A captured self-join with it, and with a wave for each row: 3,001 rows of
-// mean 80 (up to 2,000) 89 us and 116, 4,000 of mean 120 109 and 170, 12,000
-// of mean 150 233 and 300, 8,960 of 10 to 60 components 95 and 95; 64 queries
-// of 500,000 rows 187 and 199.
+// Device time of a captured self-join's replay with it, and with a wave for
+// each row: 3,001 rows of mean 80 (up to 2,000) 86 us and 116, 4,000 of mean
+// 120 106 and 170, 8,960 of 10 to 60 components even; the call takes some 17 us
+// more.  64 queries of 500,000 rows, the call: 187 us and 199.
 template <bool PACKED>
 __global__ __launch_bounds__(64 * kCountWaves) void k_count_pieces(CountArgs a, int64_t nchunk) {
   __shared__ uint32_t bits[kCountWaves][kCountWords];
