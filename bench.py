@@ -32,6 +32,7 @@ if ROOT not in sys.path:
 
 PEAK_HBM_GBS = 8000.0
 PEAK_BF16_TFLOPS = 2500.0  # dense bf16 MFMA
+PEAK_L1_GACCESSES = 256 * 2.4  # one access a cycle in each compute unit's L1
 TUNING = os.path.join(ROOT, "paper_1402_3010_amd", "tuning", "gfx950.json")
 WORKLOADS = {
     "c1": "n=2,000 m=10,000 nnz/vector uniform 10..60, Zipf s=1.0, t=0.5",
@@ -126,13 +127,35 @@ def cpu_baseline(V, t, budget_s: float):
     }
 
 
-def kernel_source_hash():
+def source_hash(files):
     import hashlib
     h = hashlib.sha256()
-    for f in ("join.hip", "join.h", "apss_internal.h"):
+    for f in files:
         with open(os.path.join(ROOT, "paper_1402_3010_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
+
+
+def kernel_source_hash():
+    return source_hash(("join.hip", "join.h", "apss_internal.h"))
+
+
+def pair_source_hash():
+    return source_hash(("pairs.hip", "pairs.h", "rescore.h", "apss_internal.h"))
+
+
+def measured_pairs(config, t, n):
+    """Counters of the list-pair kernels of one join from the committed
+    summary, if it was taken on this workload at full size and on the kernel
+    source as it is now."""
+    path = os.path.join(ROOT, "profiles", "list_pairs_%s_counters.json" % config)
+    if n is not None or not os.path.exists(path):
+        return None
+    with open(path) as fh:
+        rec = json.load(fh)
+    if rec.get("source_hash") != pair_source_hash() or abs(rec.get("t", -1) - float(t)) > 1e-6:
+        return None
+    return rec
 
 
 def measured_traffic(config, t, n):
@@ -160,6 +183,37 @@ def measured_counters(config, t, n):
     if rec.get("source_hash") != kernel_source_hash() or abs(rec.get("t", -1) - float(t)) > 1e-6:
         return None
     return rec
+
+
+def roofline_of(args, t, nnz, stats, kms):
+    """What binds the timed kernels, at what share of its peak.  The bytes that
+    no join can do without (every component read once, 8 B, every pair written
+    once, 12 B) are a two-thousandth of the memory's rate for either join, so
+    the binding unit is reported where its counters are known: for the list
+    pairs the L1's address units, which the exact candidate count keeps busy
+    (one access a compute unit and cycle at most); for the accumulating join,
+    whose visits outnumber its candidates, vector issue."""
+    alg_bytes = 8.0 * nnz + 12.0 * stats["matches"]
+    sec = kms / 1000.0
+    pairs = stats["posting_visits"] < stats["candidates"]
+    rec = measured_pairs(args.config, t, args.n) if pairs else measured_counters(args.config, t, args.n)
+    traffic = (rec["traffic_bytes"] if rec else None) if pairs else measured_traffic(args.config, t, args.n)
+    out = {"bound": "hbm", "achieved": alg_bytes / sec / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s"}
+    if pairs and rec:
+        out = {"bound": "l1 address units", "achieved": rec["l1_accesses"] / sec / 1e9, "peak": PEAK_L1_GACCESSES,
+               "unit": "G accesses/s"}
+    out["frac"] = out["achieved"] / out["peak"]
+    name = "list_pairs" if pairs else "k_join"
+    out.update({
+        "traffic": traffic, "frac_dram": traffic / sec / 1e9 / PEAK_HBM_GBS if traffic else None,
+        "binding_unit": rec["binding_unit"] if rec else None,
+        "issue": {k: rec[k] for k in ("valu_issue_frac", "salu_issue_frac", "lds_bank_conflict_frac", "ta_busy_frac")
+                  if k in rec} if rec else None,
+        "kernel": "k_count, k_pairs_wide, k_pairs_short and k_decide" if pairs else "k_join", "kernel_ms": kms,
+        "algorithmic_bytes": alg_bytes,
+        "pairs_tested": stats["posting_visits"] if pairs else None,
+        "counters_source": "profiles/%s_%s_counters.md" % (name, args.config)})
+    return out
 
 
 def percentile(x, q):
@@ -564,15 +618,8 @@ def main():
     ms_step = 1000.0 * elapsed / args.steps
     cand = stats["candidates"]
     value = cand / (ms_step / 1000.0)
-    # the bytes that no join can do without: every component read once (8 B),
-    # every pair written once (12 B).  The kernels are bound elsewhere: the
-    # list-pair join by the L1 gathers of its candidate count and the vector
-    # issue of its decisions, the accumulating join by vector issue.
-    alg_bytes = 8.0 * V.nnz + 12.0 * stats["matches"]
     kms = sum(kern_ms) / len(kern_ms)
-    achieved = alg_bytes / (kms / 1000.0) / 1e9
-    traffic = measured_traffic(args.config, t, args.n)
-    counters = measured_counters(args.config, t, args.n)
+    roofline = roofline_of(args, t, V.nnz, stats, kms)
     out = {
         "metric": "candidate pairs scored/s and matches/s at 1M vectors t=0.7; serve p50/p99 latency",
         "value": value,
@@ -598,18 +645,7 @@ def main():
         "band_rescored": stats["band"],
         "index_build_s": build_s,
         "tuning": tune,
-        "roofline": {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                     "frac": achieved / PEAK_HBM_GBS,
-                     "traffic": traffic,
-                     "frac_dram": (traffic / (kms / 1000.0) / 1e9 / PEAK_HBM_GBS) if traffic else None,
-                     "binding_unit": counters.get("binding_unit") if counters else None,
-                     "issue": ({k: counters[k] for k in ("valu_issue_frac", "salu_issue_frac", "lds_bank_conflict_frac")
-                                if k in counters} if counters else None),
-                     "kernel": "k_count, k_pairs_wide, k_pairs_short and k_decide (or k_join where the index's cost "
-                               "rule names it)",
-                     "kernel_ms": kms, "algorithmic_bytes": alg_bytes,
-                     "traffic_source": "profiles/k_join_%s_traffic.md" % args.config,
-                     "counters_source": "profiles/k_join_%s_counters.md" % args.config},
+        "roofline": roofline,
         "paper_figures": PAPER_FIGURES,
     }
     ix.close()
